@@ -141,37 +141,85 @@ static ClearArgs clear_args(char* ws, const Layout& L, int B, int N, int K) {
 }
 
 // ---------------------------------------------------------------- LM head fused with the row reduction
-// Slab height: the one that costs least for the padded row count (below).  Runs of vocabulary tiles: about one work-group per compute unit in all, so that
-// the whole grid is resident at once with the same amount of work for every work-group.  The
-// hardware hands work-group i to die i mod 8 and a work-group fills a compute unit, so the
-// (run, slab) pairs are dealt out die by die, an equal share to each: the slabs of a run then sit on one die
-// (at most two) and find the weight tiles they share in its L2, and no die is given more
-// work-groups than it has compute units (its last ones would start when the others have
-// finished: twice the time).
+// Slab height and width: see lm_plan.  The hardware hands work-group i to die i mod 8 and a work-group fills a
+// compute unit, so the work-groups are dealt out die by die, an equal share to each, and no die is given more
+// work-groups than it has compute units (its last ones would start when the others have finished: twice the time).
 struct LmPlan {
-  int bm, slabs, tiles_n, tiles_per_run, runs, parts;
+  int bm, slabs, tiles_n, launch_slabs, parts;
+  bool wide;  // sizes beyond what a buffer spans
+  LmGrid grid;  // of a full launch
 };
 constexpr int kDies = 8;
-static LmPlan lm_plan(long rows, int V) {
+constexpr int kLmBand = 7;  // slabs of a band: a die's 32 work-groups then read about as many bytes of weight as of hidden states
+static LmPlan lm_plan(long rows, int V, int H, bool sampling) {
   LmPlan p;
-  // (time ~ padded rows x cost per row of the slab height: a taller slab reuses a weight tile more,
-  // measured 1.2 PFLOP/s with 192 rows against 1.07 with 128; 64 only pays for a single small slab)
+  p.wide = H > (1 << 22) || V > (1 << 25);
+  p.tiles_n = static_cast<int>((static_cast<long>(V) + kLmBN - 1) / kLmBN);
+  // The slab height that takes the least time: units per work-group x time per unit.  Measured per unit at
+  // H = 4096, greedy form: 49-51 us with 64 rows, 61-63 with 128, 80-83 with 192, 100-104 with 256; with two slabs
+  // of 64 at most and a work-group on (nearly) every compute unit the weight's way from memory bounds it, at
+  // 71-78 us (128 rows: 69-75).  The sampling form does not fit the registers with 256.
+  static const struct { int bm; double cost; } kHeights[] = {{64, 0.60}, {128, 0.75}, {192, 1.0}, {256, 1.235}};
   double best = -1.0;
   p.bm = 64;
-  for (int bm = 64; bm <= kLmMaxBM; bm += 64) {
-    const long padded = (rows + bm - 1) / bm * bm;
-    const double cost = static_cast<double>(padded) * (bm == 192 ? 1.0 : bm == 128 ? 1.12 : 1.6);
-    if (best < 0.0 || cost <= best) { best = cost; p.bm = bm; }
+  for (const auto& h : kHeights) {
+    if (h.bm > (p.wide ? 64 : sampling ? 192 : 256)) break;
+    const long slabs = (rows + h.bm - 1) / h.bm, units = slabs * p.tiles_n;
+    const bool weight_bound = h.bm == 64 && slabs <= 2 && units >= 192;
+    const double time = static_cast<double>((units + kComputeUnits - 1) / kComputeUnits) * (weight_bound ? 0.87 : h.cost);
+    if (best < 0.0 || time < best) { best = time; p.bm = h.bm; }
   }
   p.slabs = static_cast<int>((rows + p.bm - 1) / p.bm);
-  p.tiles_n = (V + kLmBN - 1) / kLmBN;
-  int want = kComputeUnits / p.slabs;
-  if (want < 1) want = 1;
-  if (want > p.tiles_n) want = p.tiles_n;
-  p.tiles_per_run = (p.tiles_n + want - 1) / want;
-  p.runs = (p.tiles_n + p.tiles_per_run - 1) / p.tiles_per_run;
-  p.parts = p.runs;  // one partial result per (row, run)
+  // (unit numbers are 32-bit: inputs far beyond the ordinary take several launches)
+  const long most = (1L << 30) / p.tiles_n;
+  p.launch_slabs = static_cast<int>(p.slabs < most ? p.slabs : most < 1 ? 1 : most);
+  LmGrid& g = p.grid;
+  g.slabs = p.launch_slabs;
+  const int bands = (g.slabs + kLmBand - 1) / kLmBand;
+  g.band = (g.slabs + bands - 1) / bands;
+  g.tiles_n = p.tiles_n;
+  g.units = g.slabs * p.tiles_n;
+  g.width = (g.units + kComputeUnits - 1) / kComputeUnits;
+  if (g.width > p.tiles_n) g.width = p.tiles_n;
+  const int columns = (p.tiles_n + g.width - 1) / g.width;
+  g.split = g.slabs > 1 && p.tiles_n % g.width != 0;
+  g.parts = p.parts = g.split ? 2 * columns : columns;
   return p;
+}
+
+// The fused kernel over all slabs.
+template <bool SAMPLING>
+static hipError_t launch_lmhead(const LmPlan& p, const bf16_t* hidden, const bf16_t* weight, int M, int V, int H,
+                                Partial* partials, bf16_t* logits_out, float c, LmClear clear, hipStream_t stream) {
+  for (int s0 = 0; s0 < p.slabs; s0 += p.launch_slabs) {
+    LmGrid g = p.grid;
+    g.slabs = p.slabs - s0 < p.launch_slabs ? p.slabs - s0 : p.launch_slabs;
+    g.units = g.slabs * g.tiles_n;
+    const int groups = (g.units + g.width - 1) / g.width, per_die = (groups + kDies - 1) / kDies;
+    const dim3 grid(static_cast<unsigned int>(kDies * per_die)), block(kLmThreads);
+    const size_t row0 = static_cast<size_t>(s0) * p.bm;
+    const int rows = M - static_cast<int>(row0);
+    const bf16_t* h = hidden + row0 * H;
+    Partial* out = partials + row0 * p.parts;
+    bf16_t* lo = SAMPLING ? logits_out + row0 * V : nullptr;
+#define MARS_LM_LAUNCH(...)                                                                                            \
+  hipLaunchKernelGGL((lmhead_reduce_kernel<__VA_ARGS__>), grid, block, 0, stream, h, weight, rows, V, H, g, out, lo, c, clear)
+    switch (p.bm) {
+      case 64:
+        if (p.wide) MARS_LM_LAUNCH(64, SAMPLING, true); else MARS_LM_LAUNCH(64, SAMPLING);
+        break;
+      case 128: MARS_LM_LAUNCH(128, SAMPLING); break;
+      case 192: MARS_LM_LAUNCH(192, SAMPLING); break;
+      default:
+        if constexpr (!SAMPLING) MARS_LM_LAUNCH(256, false);
+        break;
+    }
+#undef MARS_LM_LAUNCH
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    clear.nwords = 0; clear.nstatus = 0;
+  }
+  return hipSuccess;
 }
 
 struct LmLayout {
@@ -179,10 +227,10 @@ struct LmLayout {
   int G;  // work-groups per request of the sampling walk
   size_t partials_off, stats_off, xslots_off, total;
 };
-static LmLayout lm_layout(int B, int N, int V, int K) {
+static LmLayout lm_layout(int B, int N, int V, int H, int K, bool sampling) {
   LmLayout L;
   const long rows = static_cast<long>(B) * N;
-  L.plan = lm_plan(rows, V);
+  L.plan = lm_plan(rows, V, H, sampling);
   L.partials_off = 0;
   L.stats_off = align_up(static_cast<size_t>(rows) * L.plan.parts * sizeof(Partial));
   L.G = choose_groups(K * B, V);
@@ -250,15 +298,6 @@ static int launch_groups(int G, int KB) {
     if (G < 1) G = 1;
   }
   return G;
-}
-
-// Zeroes words (the exchange words of the sampling walk, request status words) where no row reduction
-// runs in front of the walk to do it.
-__global__ __launch_bounds__(256) void clear_words_kernel(unsigned long long* words, long nwords, int32_t* status,
-                                                          int nstatus) {
-  const long i = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;
-  if (i < nwords) words[i] = 0ull;
-  if (status && i < nstatus) status[i] = 0;
 }
 
 static bool lm_sizes_ok(int B, int N, int V, int H, int K) {
@@ -493,7 +532,8 @@ int mars_margin_stats(const void* logits, int logits_dtype, const float* theta, 
 size_t mars_lmhead_workspace_bytes(int B, int N, int V, int H, int n_theta) {
   const int K = n_theta == 0 ? 1 : n_theta;
   if (!mars::lm_sizes_ok(B, N, V, H, K)) return 0;
-  return mars::lm_layout(B, N, V, K).total;
+  const size_t greedy = mars::lm_layout(B, N, V, H, K, false).total, sampling = mars::lm_layout(B, N, V, H, K, true).total;
+  return greedy > sampling ? greedy : sampling;
 }
 
 int mars_lmhead_verify(const void* hidden, const void* weight, int H, const int32_t* draft_tokens,
@@ -522,7 +562,7 @@ int mars_lmhead_verify(const void* hidden, const void* weight, int H, const int3
   const int given = (out_tokens != nullptr) + (out_len != nullptr) + (keep_rows != nullptr) + (keep_offsets != nullptr);
   if (given != 0 && given != 4) return MARS_ERR_ARG;
   if (!lm_sizes_ok(B, N, V, H, K)) return MARS_ERR_ARG;
-  const LmLayout L = lm_layout(B, N, V, K);
+  const LmLayout L = lm_layout(B, N, V, H, K, false);
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.total)
     return MARS_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -531,22 +571,10 @@ int mars_lmhead_verify(const void* hidden, const void* weight, int H, const int3
   Partial* partials = reinterpret_cast<Partial*>(ws + L.partials_off);
   const LmPlan& p = L.plan;
 
-  const int pairs = p.runs * p.slabs, per_die = (pairs + kDies - 1) / kDies;
-  const dim3 grid(static_cast<unsigned int>(kDies * per_die)), block(kLmThreads);
-  const bf16_t* hp = static_cast<const bf16_t*>(hidden);
-  const bf16_t* wp = static_cast<const bf16_t*>(weight);
-#define MARS_LM_LAUNCH(BM)                                                                                      \
-  hipLaunchKernelGGL((lmhead_reduce_kernel<BM, false>), grid, block, 0, stream, hp, wp, rows, V, H, p.slabs, p.tiles_n, \
-                     p.tiles_per_run, p.runs, partials, static_cast<bf16_t*>(nullptr), 0.0f)
-  if (lm_stages & MARS_STAGE_ROWS) {
-    switch (p.bm) {
-      case 64: MARS_LM_LAUNCH(64); break;
-      case 128: MARS_LM_LAUNCH(128); break;
-      default: MARS_LM_LAUNCH(192); break;
-    }
-    if (hipGetLastError() != hipSuccess) return MARS_ERR_HIP;
-  }
-#undef MARS_LM_LAUNCH
+  if ((lm_stages & MARS_STAGE_ROWS) &&
+      launch_lmhead<false>(p, static_cast<const bf16_t*>(hidden), static_cast<const bf16_t*>(weight), rows, V, H, partials,
+                           nullptr, 0.0f, LmClear{nullptr, 0, nullptr, 0}, stream) != hipSuccess)
+    return MARS_ERR_HIP;
   if (!(lm_stages & MARS_STAGE_REQUESTS)) return MARS_OK;
 
   TailArgs a;
@@ -601,7 +629,7 @@ int mars_lmhead_verify_sampling(const void* hidden, const void* weight, int H, c
   const int given = (out_tokens != nullptr) + (out_len != nullptr) + (keep_rows != nullptr) + (keep_offsets != nullptr);
   if (given != 0 && given != 4) return MARS_ERR_ARG;
   if (!lm_sizes_ok(B, N, V, H, K)) return MARS_ERR_ARG;
-  const LmLayout L = lm_layout(B, N, V, K);
+  const LmLayout L = lm_layout(B, N, V, H, K, true);
   if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.total)
     return MARS_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
@@ -613,26 +641,11 @@ int mars_lmhead_verify_sampling(const void* hidden, const void* weight, int H, c
   const float c = log2e_over_t(temperature);
 
   if (lm_stages & MARS_STAGE_ROWS) {
-    // What the streaming row reduction clears for the walk behind it, the fused kernel does not.
-    const long nwords = static_cast<long>(K) * B * (N + 2) * 2 * L.G;
-    const long nclear = nwords > static_cast<long>(K) * B ? nwords : static_cast<long>(K) * B;
-    hipLaunchKernelGGL(clear_words_kernel, dim3(static_cast<unsigned int>((nclear + 255) / 256)), dim3(256), 0, stream,
-                       xslots, nwords, request_status, K * B);
-    const int pairs = p.runs * p.slabs, per_die = (pairs + kDies - 1) / kDies;
-    const dim3 grid(static_cast<unsigned int>(kDies * per_die)), block(kLmThreads);
-    const bf16_t* hp = static_cast<const bf16_t*>(hidden);
-    const bf16_t* wp = static_cast<const bf16_t*>(weight);
-    bf16_t* lo = static_cast<bf16_t*>(logits_out);
-#define MARS_LM_LAUNCH(BM)                                                                                            \
-  hipLaunchKernelGGL((lmhead_reduce_kernel<BM, true>), grid, block, 0, stream, hp, wp, rows, V, H, p.slabs, p.tiles_n, \
-                     p.tiles_per_run, p.runs, partials, lo, c)
-    switch (p.bm) {
-      case 64: MARS_LM_LAUNCH(64); break;
-      case 128: MARS_LM_LAUNCH(128); break;
-      default: MARS_LM_LAUNCH(192); break;
-    }
-#undef MARS_LM_LAUNCH
-    if (hipGetLastError() != hipSuccess) return MARS_ERR_HIP;
+    // What the streaming row reduction clears for the walk behind it, the fused kernel does here.
+    const LmClear clear = {xslots, static_cast<long>(K) * B * (N + 2) * 2 * L.G, request_status, K * B};
+    if (launch_lmhead<true>(p, static_cast<const bf16_t*>(hidden), static_cast<const bf16_t*>(weight), rows, V, H, partials,
+                            static_cast<bf16_t*>(logits_out), c, clear, stream) != hipSuccess)
+      return MARS_ERR_HIP;
   }
   if (!(lm_stages & MARS_STAGE_REQUESTS)) return MARS_OK;
 

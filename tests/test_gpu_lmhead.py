@@ -329,3 +329,52 @@ def test_headline_shape_sampled_requests():
             node = k
         assert bonus[b] == s["id1"][b, node]
     assert alen.max() >= 2
+
+
+# Slab heights and cells: 64 rows; 128 (a single slab that streams the weight); 192 and 256 with columns two tiles wide
+# and one left over, so that cells are shared between two work-groups; the last slab and the last tile ragged.
+CELL_SHAPES = [(40, 5003), (100, 60001), (520, 33011), (1000, 32401)]
+
+
+@pytest.mark.parametrize("rows,V", CELL_SHAPES)
+@pytest.mark.parametrize("sign", ["negative", "zeros", "both"])
+@pytest.mark.parametrize("T", [0.0, 1.0])
+def test_integer_logits_with_ties_of_every_sign(rows, V, sign, T):
+    # Small integers: every logit is an exact integer of magnitude below 256, and ties are everywhere.  All
+    # logits negative, none positive with many zeros, and both signs: the order of the keys must hold
+    # on either side of zero, lowest index first among equals.
+    rng = np.random.default_rng(rows + V)
+    H = 128
+    V -= V % 8 if T else 0
+    h = (rng.random((rows, H)) < 0.3).astype(np.float32)
+    lo, hi = {"negative": (-2, 0), "zeros": (-1, 1), "both": (-2, 3)}[sign]
+    w = rng.integers(lo, hi, size=(V, H)).astype(np.float32) * (rng.random((V, 1)) < (1.0 if sign == "negative" else 0.7))
+    z = h @ w.T
+    assert np.abs(z).max() < 256 and (sign == "both" or z.max() <= 0)
+    id1 = z.argmax(axis=1)
+    z1 = z[np.arange(rows), id1]
+    rest = z.copy()
+    rest[np.arange(rows), id1] = -np.inf
+    id2 = rest.argmax(axis=1)
+    par = np.arange(-1, rows - 1, dtype=np.int32)[None]
+    tok = rng.integers(0, V, size=(1, rows)).astype(np.int32)
+    B, N = (1, rows) if rows <= M.MARS_MAX_NODES else (2, rows // 2)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)  # noqa: E731
+    hd, wd = dev(h).to(torch.bfloat16).view(B, N, H), dev(w).to(torch.bfloat16)
+    th = torch.full((B,), 0.9, device=DEV)
+    say(f"[case] lmhead integers: rows={rows} V={V} {sign} T={T}")
+    if T:
+        out, logits = M.mars_lmhead_verify_sampling(hd, wd, dev(tok.reshape(B, N)), dev(par.reshape(B, N)), th, T,
+                                                    torch.full((B, N + 1), 0.5, device=DEV))
+        torch.cuda.synchronize()
+        got = logits.view(torch.bfloat16).float().cpu().numpy().reshape(rows, V)
+        assert np.array_equal(got, z)
+        want = np.exp((z - z1[:, None]).astype(np.float64)).sum(axis=1)
+        s = M.unpack_stats(out.stats)["sum_exp"].cpu().numpy()
+        assert np.abs(s / want - 1).max() <= 1e-5
+    else:
+        out = M.mars_lmhead_verify(hd, wd, dev(tok.reshape(B, N)), dev(par.reshape(B, N)), th)
+        torch.cuda.synchronize()
+    st = {k: v.cpu().numpy() for k, v in M.unpack_stats(out.stats).items()}
+    assert np.array_equal(st["id1"], id1) and np.array_equal(st["id2"], id2)
+    assert np.array_equal(st["z1"], z1) and np.array_equal(st["z2"], rest[np.arange(rows), id2])
