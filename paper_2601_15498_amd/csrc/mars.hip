@@ -94,32 +94,31 @@ static bool sizes_ok(int B, int N, int V, int K = 1) {
   return rows <= 0x7FFFFFFFL / 64;  // rows * splits must fit the grid and int arithmetic
 }
 
-template <typename T, int EPV>
+template <typename T, int EPV, bool RAGGED>
 static hipError_t launch_row_reduce_t(const void* logits, long rows, int V, int splits, bool sampling, float c,
                                       Partial* partials, const ClearArgs& clr, hipStream_t stream) {
-  const int nvec = V / EPV;
+  const int nvec = V / EPV;  // (the most a row can have)
   const int vps = (nvec + splits - 1) / splits;
   const dim3 grid(static_cast<unsigned int>(rows * splits)), block(kRowThreads);
   if (sampling)
-    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, true>), grid, block, 0, stream, static_cast<const T*>(logits), V,
+    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, true, RAGGED>), grid, block, 0, stream, static_cast<const T*>(logits), V,
                        splits, vps, c, partials, clr);
   else
-    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, false>), grid, block, 0, stream, static_cast<const T*>(logits), V,
+    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, false, RAGGED>), grid, block, 0, stream, static_cast<const T*>(logits), V,
                        splits, vps, c, partials, clr);
   return hipGetLastError();
 }
 
-// 16-byte loads need every row to start on a 16-byte boundary; otherwise the same kernel runs
-// with one element per load.
+// 16-byte loads; rows that do not all start on a 16-byte boundary take the form that looks for the first one.
 static hipError_t launch_row_reduce(const void* logits, int dtype, long rows, int V, int splits, bool sampling,
                                     float c, Partial* partials, const ClearArgs& clr, hipStream_t stream) {
   const size_t elt = dtype == MARS_BF16 ? 2 : 4;
-  const bool wide = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && ((static_cast<size_t>(V) * elt) % 16 == 0);
+  const bool even = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && ((static_cast<size_t>(V) * elt) % 16 == 0);
   if (dtype == MARS_BF16)
-    return wide ? launch_row_reduce_t<bf16_t, 8>(logits, rows, V, splits, sampling, c, partials, clr, stream)
-                : launch_row_reduce_t<bf16_t, 1>(logits, rows, V, splits, sampling, c, partials, clr, stream);
-  return wide ? launch_row_reduce_t<float, 4>(logits, rows, V, splits, sampling, c, partials, clr, stream)
-              : launch_row_reduce_t<float, 1>(logits, rows, V, splits, sampling, c, partials, clr, stream);
+    return even ? launch_row_reduce_t<bf16_t, 8, false>(logits, rows, V, splits, sampling, c, partials, clr, stream)
+                : launch_row_reduce_t<bf16_t, 8, true>(logits, rows, V, splits, sampling, c, partials, clr, stream);
+  return even ? launch_row_reduce_t<float, 4, false>(logits, rows, V, splits, sampling, c, partials, clr, stream)
+              : launch_row_reduce_t<float, 4, true>(logits, rows, V, splits, sampling, c, partials, clr, stream);
 }
 
 static float log2e_over_t(float temperature) {
@@ -264,15 +263,15 @@ static void* static_scratch() {
 static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int draft_dtype, hipStream_t stream) {
   const int V = a.V;
   const bool dense = draft_dtype >= 0;
+  // groups of eight elements as single aligned loads: whole rows of groups, arrays on 16-byte boundaries
+  const bool vec = (V % 8 == 0) && (reinterpret_cast<uintptr_t>(a.logits) % 16 == 0) &&
+                   (!dense || reinterpret_cast<uintptr_t>(a.dprobs) % 16 == 0);
   // Slices of at most kResident groups of eight per thread stay in registers between passes.
-  const int ngroups8 = (V + 7) / 8;
+  const int ngroups8 = row_groups(V, vec);
   const int slice8 = ((ngroups8 + a.G - 1) / a.G + kWave - 1) / kWave * kWave;
   const bool resident = slice8 <= kResident * kSamplingThreads;
   const bool qbf = dense && draft_dtype == MARS_BF16;
   const void* kernel;
-  // groups of eight elements as single aligned loads: whole rows of groups, arrays on 16-byte boundaries
-  const bool vec = (V % 8 == 0) && (reinterpret_cast<uintptr_t>(a.logits) % 16 == 0) &&
-                   (!dense || reinterpret_cast<uintptr_t>(a.dprobs) % 16 == 0);
 #define MARS_PICK2(TT, QQ, VV) (resident ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, VV>) \
                                          : reinterpret_cast<const void*>(&tail_sampling_streamed_kernel<TT, QQ, VV>))
 #define MARS_PICK(TT, QQ) (vec ? MARS_PICK2(TT, QQ, true) : MARS_PICK2(TT, QQ, false))

@@ -186,37 +186,7 @@ __global__ __launch_bounds__(kGreedyThreads) void tail_greedy_kernel(TailArgs a)
 }
 
 // ---------------------------------------------------------------- sampling mode
-// Eight consecutive elements of a row, widened; out-of-range positions read as `fill`.
-template <typename T>
-__device__ __forceinline__ void load8(const T* __restrict__ row, int g, int V, bool vec_ok, float fill, float (&x)[8]);
-
-template <>
-__device__ __forceinline__ void load8<bf16_t>(const bf16_t* __restrict__ row, int g, int V, bool vec_ok, float fill,
-                                              float (&x)[8]) {
-  if (vec_ok) {
-    Vec<bf16_t, 8> v;
-    v.load(row, g);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = v.get(e);
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { const int i = g * 8 + e; x[e] = i < V ? widen(row[i]) : fill; }
-  }
-}
-template <>
-__device__ __forceinline__ void load8<float>(const float* __restrict__ row, int g, int V, bool vec_ok, float fill,
-                                             float (&x)[8]) {
-  if (vec_ok) {
-    const float4 lo = *reinterpret_cast<const float4*>(row + static_cast<size_t>(g) * 8);
-    const float4 hi = *reinterpret_cast<const float4*>(row + static_cast<size_t>(g) * 8 + 4);
-    x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w; x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { const int i = g * 8 + e; x[e] = i < V ? row[i] : fill; }
-  }
-}
-
-// Eight consecutive elements as they lie in memory (one aligned group): requested without being looked at,
+// Eight consecutive elements as they lie in memory (one group): requested without being looked at,
 // so that nothing waits for them until they are widened.
 template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {
@@ -376,28 +346,126 @@ __device__ __forceinline__ double exchange_end(const TailArgs& a, const double* 
 }
 
 // Everything a pass over a row needs to evaluate the current distribution f.
-template <typename T, typename TQ>
+//
+// A row is looked at in groups of eight elements.  VEC: the groups count from the row's start, and every one is
+// whole and aligned (V % 8 == 0, arrays on 16-byte boundaries; the host checks both).  Otherwise they count in the
+// whole array -- group c holds its elements 8c .. 8c + 7 -- so that on an aligned array every group is still one
+// aligned load, and a row begins `shift` elements into its first group and ends somewhere in its last: what lies
+// outside the row is masked where a group is used, which only the lanes with those two groups do.  (It was
+// eight loads and eight comparisons per group: on 8 trees of 26 nodes over 100 001 bf16 entries the walk took
+// 21.4 us, now 18.5.)  The array's own last group may be cut short: it is read element by element.
+template <typename T, typename TQ, bool VEC>
 struct RowView {
   const T* zrow;
   const TQ* qrow;   // nullptr = one-hot draft distribution
   bool use_q;       // false: this pass does not look at q (no rejection at this node so far), skip its loads
   int V;
-  bool vec_ok;
   float z1, c, inv_S;
   Chain ch;
+  // VEC == false: first group of the row, elements in front of the row in it, the row's last group, and the last
+  // group that lies in the array as a whole (below 0 in an array of less than eight elements), counted from the first.
+  const T* zgroup;
+  const TQ* qgroup;
+  int shift, last, whole;
+  // Of the request: the group its first row begins in, how many elements into it, how many whole groups lie between
+  // it and the array's end, and readable memory for loads from an array of less than eight elements (else nullptr).
+  const T* zreq;
+  const TQ* qreq;
+  int begin;
+  long wholes;
+  const void* instead;
+  // The request whose rows begin at element `at` of arrays of `count` elements.
+  __device__ __forceinline__ void request(const T* zarray, const TQ* qarray, size_t at, size_t count, const void* somewhere) {
+    if (VEC) {
+      zreq = zarray + at;
+      qreq = qarray ? qarray + at : nullptr;
+    } else {
+      const size_t first = at >> 3 << 3;
+      begin = static_cast<int>(at & 7);
+      wholes = static_cast<long>(count >> 3) - static_cast<long>(at >> 3);
+      zreq = zarray + first;
+      qreq = qarray ? qarray + first : nullptr;
+      instead = count < 8 ? somewhere : nullptr;
+    }
+  }
+  __device__ __forceinline__ void row(int node, bool dense) {
+    if (VEC) {
+      zrow = zreq + static_cast<size_t>(node) * V;
+      qrow = dense ? qreq + static_cast<size_t>(node) * V : nullptr;
+    } else {
+      const size_t at = static_cast<size_t>(node) * V + begin;
+      zrow = zreq + at;
+      qrow = dense ? qreq + at : nullptr;
+      shift = static_cast<int>(at & 7);
+      last = (shift + V - 1) >> 3;
+      const long left = wholes - static_cast<long>(at >> 3) - 1;
+      whole = static_cast<int>(left < last ? left : last);
+      const long first = static_cast<long>(at - shift) + min(whole, 0) * 8;  // (a row in the array's cut-short group)
+      zgroup = instead ? static_cast<const T*>(instead) : zreq + first;
+      qgroup = instead ? static_cast<const TQ*>(instead) : qreq + first;
+    }
+  }
+  __device__ __forceinline__ int element(int gi, int e) const { return VEC ? gi * 8 + e : gi * 8 + e - shift; }
+  __device__ __forceinline__ void load_raw(int gi, Raw8<T>& z) const {
+    z.load(VEC ? zrow : zgroup, VEC ? gi : min(gi, max(whole, 0)));
+  }
+  __device__ __forceinline__ void load_raw_q(int gi, Raw8<TQ>& q) const {
+    q.load(VEC ? qrow : qgroup, VEC ? gi : min(gi, max(whole, 0)));
+  }
+  // Requested here, widened where they are needed (see load).
   __device__ __forceinline__ void load(int gi, float (&z)[8], float (&q)[8]) const {
-    load8<T>(zrow, gi, V, vec_ok, neg_inf(), z);
+    Raw8<T> rz;
+    load_raw(gi, rz);
+    rz.widen_to(z);
     if (qrow && use_q) {
-      load8<TQ>(qrow, gi, V, vec_ok, 0.0f, q);
+      Raw8<TQ> rq;
+      load_raw_q(gi, rq);
+      rq.widen_to(q);
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e) q[e] = 0.0f;
     }
   }
+  template <typename E>
+  __device__ __forceinline__ void reload(const E* row, int gi, float (&x)[8]) const {
+#pragma unroll 1
+    for (int e = 0; e < 8; ++e) {
+      const float y = widen(row[min(max(element(gi, e), 0), V - 1)]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = k == e ? y : x[k];
+    }
+  }
+  // The group the array ends in, which load() has not read: element by element.
+  __device__ __forceinline__ bool cut_short() const { return !VEC && whole < last; }  // (the same for every lane)
+  __device__ __forceinline__ void complete(int gi, float (&z)[8], float (&q)[8]) const {
+    if (gi > whole) {
+      reload(zrow, gi, z);
+      if (qrow && use_q) reload(qrow, gi, q);
+    }
+  }
+  // What of a group lies outside the row: no mass (z = -inf, q = 0).
+  __device__ __forceinline__ void mask(int gi, float (&z)[8], float (&q)[8]) const {
+    if (VEC || (gi != 0 && gi < last)) return;
+    int v0 = element(gi, 0);
+    asm volatile("" : "+v"(v0));  // (the masks stay in here: worked out ahead for every group they are 250 scalar registers)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const bool in = static_cast<unsigned int>(v0 + e) < static_cast<unsigned int>(V);
+      z[e] = in ? z[e] : neg_inf();
+      q[e] = in ? q[e] : 0.0f;
+    }
+  }
+  // Both, behind the loads of a batch.
+  __device__ __forceinline__ void trim(int gi, float (&z)[8], float (&q)[8]) const {
+    if (__builtin_expect(cut_short(), 0)) complete(gi, z, q);
+    mask(gi, z, q);
+  }
   __device__ __forceinline__ float f(const float (&z)[8], const float (&q)[8], int gi, int e) const {
-    return eval_f(z[e], qrow ? q[e] : 0.0f, gi * 8 + e, z1, c, inv_S, qrow != nullptr, ch);
+    return eval_f(z[e], qrow ? q[e] : 0.0f, element(gi, e), z1, c, inv_S, qrow != nullptr, ch);
   }
 };
+// Groups a row can touch.
+__device__ __host__ __forceinline__ int row_groups(int V, bool vec) { return vec ? V / 8 : static_cast<int>((static_cast<long>(V) + 14) / 8); }
 
 // Groups whose loads a thread issues before it starts computing.  (The streamed form runs 1024 threads, so 128
 // registers each; with four groups in flight the kernel needs about 160 and spills, which on the B = 128 chain
@@ -407,8 +475,8 @@ constexpr int kPassBatch = 2;
 // This work-group's share of Z = sum_v max(0, f(v) - q_k(v)) over groups [g_begin, g_end):
 // q_k dense, or one-hot at token x.  The loads of kPassBatch groups are issued together so
 // that a pass costs about one memory round trip per batch, not one per group.
-template <typename T, typename TQ, int NT>
-__device__ __forceinline__ double residual_mass_slice(const RowView<T, TQ>& rv, int g_begin, int g_end, int x) {
+template <typename T, typename TQ, int NT, bool VEC>
+__device__ __forceinline__ double residual_mass_slice(const RowView<T, TQ, VEC>& rv, int g_begin, int g_end, int x) {
   double part = 0.0;
   for (int base = g_begin + static_cast<int>(threadIdx.x); base < g_end; base += kPassBatch * NT) {
     float z[kPassBatch][8], q[kPassBatch][8];
@@ -422,9 +490,10 @@ __device__ __forceinline__ double residual_mass_slice(const RowView<T, TQ>& rv, 
       const int gi = base + i * NT;
       if (gi < g_end) {
         float acc = 0.0f;
+        rv.trim(gi, z[i], q[i]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float qk = rv.qrow ? q[i][e] : (gi * 8 + e == x ? 1.0f : 0.0f);
+          const float qk = rv.qrow ? q[i][e] : (rv.element(gi, e) == x ? 1.0f : 0.0f);
           acc += fmaxf(rv.f(z[i], q[i], gi, e) - qk, 0.0f);
         }
         part += static_cast<double>(acc);
@@ -505,17 +574,18 @@ __device__ __forceinline__ void tile_find(const double* sh_tile, int n, int lane
 // not arrived (see exchange_begin).  A rarely taken path: one group of eight at a time, so that it adds next
 // to nothing to the registers of the walk around it; groups go to threads, and sums are formed, as in the
 // owner's resident form.  (The streamed form of the tail needs no such twin: its own pass reads memory.)
-template <typename T, typename TQ, int NT>
-__device__ __forceinline__ double resident_mass_from_memory(const RowView<T, TQ>& rv, int gb, int ge, int x) {
+template <typename T, typename TQ, int NT, bool VEC>
+__device__ __forceinline__ double resident_mass_from_memory(const RowView<T, TQ, VEC>& rv, int gb, int ge, int x) {
   double part = 0.0;
 #pragma unroll 1
   for (int gi = gb + static_cast<int>(threadIdx.x); gi < ge; gi += NT) {
     float z[8], q[8];
     rv.load(gi, z, q);
+    rv.trim(gi, z, q);
     float acc = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float qk = rv.qrow ? q[e] : (gi * 8 + e == x ? 1.0f : 0.0f);
+      const float qk = rv.qrow ? q[e] : (rv.element(gi, e) == x ? 1.0f : 0.0f);
       acc += fmaxf(rv.f(z, q, gi, e) - qk, 0.0f);
     }
     part += static_cast<double>(acc);
@@ -523,8 +593,8 @@ __device__ __forceinline__ double resident_mass_from_memory(const RowView<T, TQ>
   return part;
 }
 // Tile sums (a tile = a step of 64 groups, the steps dealt out to the waves in turn); returns their number.
-template <typename T, typename TQ, int NT, int kRes>
-__device__ __forceinline__ int resident_tiles_from_memory(const RowView<T, TQ>& rv, int gb, int ge, double* out) {
+template <typename T, typename TQ, int NT, int kRes, bool VEC>
+__device__ __forceinline__ int resident_tiles_from_memory(const RowView<T, TQ, VEC>& rv, int gb, int ge, double* out) {
   constexpr int NW = NT / kWave;
   const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
   const int nst = (ge - gb + kWave - 1) / kWave;
@@ -537,6 +607,7 @@ __device__ __forceinline__ int resident_tiles_from_memory(const RowView<T, TQ>& 
       if (gi < ge) {
         float z[8], q[8], f[8];
         rv.load(gi, z, q);
+        rv.trim(gi, z, q);
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] = rv.f(z, q, gi, e);
         gs = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
@@ -552,9 +623,7 @@ constexpr float kClosedFormMinNorm = 0.1f; // one-hot residual: Z = 1 - f(x) is 
 constexpr int kResident = 3;               // groups of eight elements a thread can keep in registers
 
 // RESIDENT: every slice is at most kResident groups per thread (decided by the host from G and V).
-// VEC: every group of eight elements is one aligned 16-byte (or 32-byte) load -- the host checks V % 8 and
-// the alignment of the arrays.  The form that checks every element against the end of the row costs some
-// eighty comparisons and as many scalar registers before the walk starts, on the critical path of every call.
+// VEC: every group of eight elements is whole and aligned (RowView).
 template <typename T, typename TQ, bool RESIDENT, bool VEC>
 __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   constexpr int NT = RESIDENT ? kSamplingThreads : kStreamingThreads;
@@ -708,8 +777,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     __syncthreads();
   }
 
-  constexpr bool vec_ok = VEC;
-  const int ngroups = (V + 7) / 8;
+  const int ngroups = row_groups(V, VEC);
   // This work-group's slice of the vocabulary, in groups of eight elements (a multiple of 64
   // groups, so that the slices are made of whole wave steps).
   const int slice = ((ngroups + G - 1) / G + kWave - 1) / kWave * kWave;
@@ -726,8 +794,10 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   int cnode = 0, plen = 0, passes = 0, nexch = 0;
   float last_norm = 0.0f;
   bool pending_norm = false;  // the last rejection's normaliser is still to come out of the final pass
-  RowView<T, TQ> rv;
-  rv.V = V; rv.vec_ok = vec_ok; rv.c = c;
+  RowView<T, TQ, VEC> rv;
+  rv.V = V; rv.c = c;
+  rv.request(static_cast<const T*>(a.logits), static_cast<const TQ*>(a.dprobs), rd * static_cast<size_t>(V),
+             static_cast<size_t>(a.Bd) * N * static_cast<size_t>(V), a.partials);
   rv.ch.tok = sh_ctok; rv.ch.inv_norm = sh_cinv; rv.ch.n = 0;
   float fc[kResident][8], qv[kResident][8];  // resident slice: current f and the draft probabilities
   bool have = false;                          // fc holds the current f of this node's slice
@@ -744,26 +814,20 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   bool rq_loaded = false;
   auto load_resident = [&]() {
     rq_loaded = rv.qrow && rv.use_q;
-    if (VEC) {
-      // No load stands under a condition, per lane or per call: a lane past the end of its slice reads the
-      // row's last group and throws it away, and when the draft probabilities are not wanted every lane reads
-      // the first 32 bytes of the logits in their place.  With a branch between two loads the compiler can no
-      // longer count what is in flight and makes each wait for the one before (three trips to memory instead
-      // of one); with a branch around them it copies what they return into the registers of the other path
-      // right away, and waits for it there.
-      const TQ* __restrict__ qsrc = rq_loaded ? rv.qrow : reinterpret_cast<const TQ*>(zall);
+    // No load stands under a condition, per lane or per call: a lane past the end of its slice reads the
+    // row's last group and throws it away, and when the draft probabilities are not wanted every lane reads
+    // 32 bytes in their place: the first ones of the logits (an array that can be cut short: of the partial results).  With a branch between two loads the compiler can no
+    // longer count what is in flight and makes each wait for the one before (three trips to memory instead
+    // of one); with a branch around them it copies what they return into the registers of the other path
+    // right away, and waits for it there.
+    const TQ* __restrict__ qsrc = rq_loaded ? (VEC ? rv.qrow : rv.qgroup)
+                                            : VEC ? reinterpret_cast<const TQ*>(zall) : reinterpret_cast<const TQ*>(a.partials + rd * a.splits);
 #pragma unroll
-      for (int i = 0; i < kResident; ++i) {
-        const int gi = min(g_begin + i * NT + tid, ngroups - 1);
-        rz[i].load(rv.zrow, gi);
-        rq[i].load(qsrc, rq_loaded ? gi : 0);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < kResident; ++i) {
-        const int gi = g_begin + i * NT + tid;
-        if (gi < g_end) rv.load(gi, fc[i], qv[i]);
-      }
+    for (int i = 0; i < kResident; ++i) {
+      int gi = min(g_begin + i * NT + tid, ngroups - 1);
+      if (!VEC) gi = min(gi, max(rv.whole, 0));
+      rz[i].load(VEC ? rv.zrow : rv.zgroup, gi);
+      rq[i].load(qsrc, rq_loaded ? gi : 0);
     }
     raw = true;
     have = false;
@@ -773,17 +837,29 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     for (int i = 0; i < kResident; ++i) {
       const int gi = g_begin + i * NT + tid;
       if (gi < g_end) {
-        if (VEC) {
-          rz[i].widen_to(fc[i]);
-          if (rq_loaded) rq[i].widen_to(qv[i]);
-        }
+        rz[i].widen_to(fc[i]);
+        if (rq_loaded) rq[i].widen_to(qv[i]);
       } else {  // nothing there: f = 0 and q = 0 contribute nothing
 #pragma unroll
         for (int e = 0; e < 8; ++e) { fc[i][e] = neg_inf(); qv[i][e] = 0.0f; }
       }
-      if (!dense || (VEC && !rq_loaded)) {
+      if (!rq_loaded) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) qv[i][e] = 0.0f;
+      }
+    }
+    if (!VEC) {
+      if (__builtin_expect(rv.cut_short(), 0)) {
+#pragma unroll
+        for (int i = 0; i < kResident; ++i) {
+          const int gi = g_begin + i * NT + tid;
+          if (gi < g_end) rv.complete(gi, fc[i], qv[i]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kResident; ++i) {
+        const int gi = g_begin + i * NT + tid;
+        if (gi < g_end) rv.mask(gi, fc[i], qv[i]);
       }
     }
   };
@@ -813,7 +889,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
           const int gi = g_begin + i * NT + tid;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const float qj = dense ? qv[i][e] : (gi * 8 + e == tj ? 1.0f : 0.0f);
+            const float qj = dense ? qv[i][e] : (rv.element(gi, e) == tj ? 1.0f : 0.0f);
             fc[i][e] = fmaxf(fc[i][e] - qj, 0.0f) * inv;
           }
         }
@@ -840,8 +916,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       }
     }
     const mars_row_stat st = sh_st[cnode];
-    rv.zrow = zall + static_cast<size_t>(cnode) * V;
-    rv.qrow = dense ? qall + static_cast<size_t>(cnode) * V : nullptr;
+    rv.row(cnode, dense);
     rv.z1 = st.z1; rv.inv_S = 1.0f / st.sum_exp;
     rv.use_q = dense && !leaf;  // a rejection pass subtracts q; nothing is rejected at a leaf
     rv.ch.n = 0;
@@ -928,7 +1003,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
             float acc = 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              const float qk = dense ? qv[i][e] : (gi * 8 + e == x ? 1.0f : 0.0f);
+              const float qk = dense ? qv[i][e] : (rv.element(gi, e) == x ? 1.0f : 0.0f);
               acc += fmaxf(fc[i][e] - qk, 0.0f);
             }
             part += static_cast<double>(acc);
@@ -939,7 +1014,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
             const int who = __ffs(static_cast<int>(missing)) - 1;
             missing &= missing - 1u;
             const int gb = min(ngroups, who * slice), ge = min(ngroups, gb + slice);
-            const double theirs = block_sum<NT>(resident_mass_from_memory<T, TQ, NT>(rv, gb, ge, x), sh_red);
+            const double theirs = block_sum<NT>(resident_mass_from_memory<T, TQ, NT, VEC>(rv, gb, ge, x), sh_red);
             exchange_fill(sh_part, who, theirs);
             __syncthreads();  // (sh_red is free again)
           }
@@ -948,7 +1023,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
           unsigned int missing = 0u;
           for (;;) {
             const int gb = min(ngroups, who * slice), ge = min(ngroups, gb + slice);
-            const double part = block_sum<NT>(residual_mass_slice<T, TQ, NT>(rv, gb, ge, x), sh_red);
+            const double part = block_sum<NT>(residual_mass_slice<T, TQ, NT, VEC>(rv, gb, ge, x), sh_red);
             if (who == g) {
               missing = exchange_begin<NT>(a, b, g, nexch++, part, sh_part, &sh_missing);
             } else {
@@ -1023,7 +1098,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
         const int who = __ffs(static_cast<int>(missing)) - 1;
         missing &= missing - 1u;
         const int gb = min(ngroups, who * slice), ge = min(ngroups, gb + slice);
-        const int nt = resident_tiles_from_memory<T, TQ, NT, kResident>(rv, gb, ge, sh_tile2);
+        const int nt = resident_tiles_from_memory<T, TQ, NT, kResident, VEC>(rv, gb, ge, sh_tile2);
         __syncthreads();
         exchange_fill(sh_part, who, tile_total(sh_tile2, nt, lane));
         __syncthreads();  // (sh_tile2 may be filled again)
@@ -1055,7 +1130,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
             const int sw = s0 + i;
             if (sw < spw) {
               const int gi = group_at(sw);
-              if (gi >= 0) { float f[8]; acc += static_cast<double>(group_sum(z[i], q[i], gi, f)); }
+              if (gi >= 0) { float f[8]; rv.trim(gi, z[i], q[i]); acc += static_cast<double>(group_sum(z[i], q[i], gi, f)); }
               if ((sw + 1) % rp == 0 || sw + 1 == spw) {
                 const double t = wave_sum(acc);
                 if (lane == 0) tiles[wave * tpw + sw / rp] = t;
@@ -1155,6 +1230,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
         if (gi >= 0) {
           float z[8], q[8];
           rv.load(gi, z, q);
+          rv.trim(gi, z, q);
           gs = group_sum(z, q, gi, f);
         } else {
 #pragma unroll
@@ -1175,7 +1251,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) if (e == my_last) fv = f[e];
         last_pos_f = lane_value(fv, hl);
-        last_pos_v = lane_value(gi, hl) * 8 + le;
+        last_pos_v = rv.element(lane_value(gi, hl), le);
       }
       if (hit != 0ull) {
         const int hl = __ffsll(static_cast<long long>(hit)) - 1;
@@ -1194,7 +1270,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
         pe = lane_value(pe, hl);
         if (pe >= 0) {
           pick_f = lane_value(pf, hl);
-          pick = lane_value(gi, hl) * 8 + pe;
+          pick = rv.element(lane_value(gi, hl), pe);
         } else {  // rounding left no step above the target inside the lane: last element with mass
           pick = last_pos_v; pick_f = last_pos_f;
           break;

@@ -350,3 +350,65 @@ def test_ten_children_per_node_with_five_nine_and_ten_rejections(dtype, dense, B
     say(f"[info] wide trees: rejections per request {rej[:8].tolist()} accept_len {ref['accept_len'][:8].tolist()}")
     assert (rej >= 20).mean() >= 0.5, "the workload no longer produces long runs of rejected siblings"
     compare(w, cdf_guard=5e-6, allow_small_norm=True)
+
+
+# ----------------------------------------------------------------------------- rows at every alignment
+def at_offset(a, k, pad):
+    """The array on the GPU, k elements into a buffer of its own with `pad` more behind it."""
+    a = np.ascontiguousarray(a)
+    flat = torch.from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a).reshape(-1)
+    buf = torch.zeros(flat.numel() + k + pad, dtype=flat.dtype, device="cuda:0")
+    buf[k:k + flat.numel()].copy_(flat)
+    return buf[k:k + flat.numel()].view(a.shape)
+
+
+@pytest.mark.parametrize("dtype,qdtype,B,N,V", [
+    ("bf16", None, 3, 7, 8191), ("f32", None, 3, 7, 8193), ("bf16", "f32", 3, 7, 24583), ("f32", "bf16", 2, 9, 24577),
+    ("f32", "f32", 2, 5, 65543), ("bf16", "bf16", 128, 3, 30003), ("f32", None, 128, 3, 30001), ("bf16", "f32", 1, 4, 61),
+    ("bf16", "f32", 3, 7, 8192), ("f32", None, 2, 9, 16384)])
+@pytest.mark.parametrize("k", [0, 1, 4, 7])
+def test_rows_and_draft_rows_at_every_alignment(dtype, qdtype, B, N, V, k):
+    # Rows of odd lengths begin at every residue of 16 bytes, the arrays themselves k and 7 - k elements behind a
+    # boundary; slices held in registers (few requests) and streamed (128 requests); batch and vector edges.
+    # Whatever the alignment, the answers are the oracle's; and what lies around the arrays is not looked at.
+    w = make_workload(f"align_{dtype}_{qdtype}_V{V}", B=B, N=N, V=V, dtype=dtype, temperature=0.8, dense_q=qdtype is not None,
+                      tree={"kind": "tree", "depth": 2, "max_children": 3}, plant_frac=0.5, seed=V + B)
+    if qdtype == "bf16":
+        w.draft_probs = f32_to_bf16_bits(w.draft_probs)
+
+    def run(v):
+        d = to_device(v)
+        z = at_offset(v.logits, k, 0)
+        q = None if v.draft_probs is None else at_offset(v.draft_probs, 7 - k, 0)
+        from paper_2601_15498_amd import binding as M
+        out = M.mars_verify(z, d["draft_tokens"], d["tree_parent"], d["theta"], v.temperature, d["uniforms"], q)
+        torch.cuda.synchronize()
+        return out
+    compare(w, label=f"{w.name}_k{k}", cdf_guard=5e-6 if V > 20000 else None, allow_small_norm=True, run=run)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [2, 3, 7, 9, 15, 17, 8199, 24589])
+def test_row_ends_hold_the_candidates(dtype, V):
+    # The two largest entries, ties among them, at the very ends of rows that begin at every residue; a row
+    # masked down to its loose ends.
+    from oracle import mars_ref
+    from paper_2601_15498_amd import binding as M
+    from tests.gpu_util import assert_stats_match
+    rng = np.random.default_rng(V)
+    z = (rng.integers(-40, 10, size=(2, 9, V)) * 0.5).astype(np.float32)
+    z[0, :, 0] = 12.0
+    z[0, :, V - 1] = 12.0
+    z[1, 0::2, V - 1] = 13.0
+    z[1, 1::2, :] = -np.inf
+    z[1, 1::2, 0] = 3.0
+    z[1, 1::2, V - 1] = 2.0
+    bits = f32_to_bf16_bits(z) if dtype == "bf16" else z
+    for k in range(8):
+        d = at_offset(bits, k, 0)
+        st = M.mars_row_stats(d, torch.full((2,), 0.9, device="cuda:0"), 1.0)
+        torch.cuda.synchronize()
+        assert_stats_match(st, mars_ref.row_stats(bits, 0.9, 1.0), True, f"ends_{dtype}_V{V}_k{k}")
+        greedy = M.mars_row_stats(d, torch.full((2,), 0.9, device="cuda:0"), 0.0)
+        torch.cuda.synchronize()
+        assert_stats_match(greedy, mars_ref.row_stats(bits, 0.9, 0.0), False, f"ends_greedy_{dtype}_V{V}_k{k}")
