@@ -9,6 +9,7 @@
 #include "../../include/mars.h"
 #include "common.h"
 #include "row_reduce.h"
+#include "margin.h"
 #include "tail.h"
 #include "lmhead.h"
 
@@ -522,9 +523,14 @@ int mars_margin_stats(const void* logits, int logits_dtype, const float* theta, 
   clr.counters = counts; clr.ncounters = ncounters;
   if (launch_row_reduce(logits, logits_dtype, rows, V, L.splits, false, 0.0f, partials, clr, stream) != hipSuccess)
     return MARS_ERR_HIP;
-  hipLaunchKernelGGL(margin_stats_kernel, dim3(static_cast<unsigned int>((rows + 15) / 16)), dim3(256), 0, stream,
-                     partials, static_cast<int>(rows), N, L.splits * kPartsPerItem, theta, indicator_scale(temperature),
-                     hs, rows_out, counts);
+  const bool local = ncounters <= kHistLocal;
+  const dim3 grid(static_cast<unsigned int>((rows + hist_rows(local) - 1) / hist_rows(local))), block(kHistThreads);
+  if (local)
+    hipLaunchKernelGGL(margin_stats_kernel<true>, grid, block, 0, stream, partials, static_cast<int>(rows), N,
+                       L.splits * kPartsPerItem, theta, indicator_scale(temperature), hs, rows_out, counts);
+  else
+    hipLaunchKernelGGL(margin_stats_kernel<false>, grid, block, 0, stream, partials, static_cast<int>(rows), N,
+                       L.splits * kPartsPerItem, theta, indicator_scale(temperature), hs, rows_out, counts);
   return hipGetLastError() == hipSuccess ? MARS_OK : MARS_ERR_HIP;
 }
 

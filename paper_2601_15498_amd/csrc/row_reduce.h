@@ -452,58 +452,4 @@ __global__ __launch_bounds__(256) void merge_stats_kernel(const Partial* __restr
                        [&](int row, const mars_row_stat& st) { stats[first + row] = st; });
 }
 
-// Distributions of the top-2 statistics over the rows (appendix histogram figure of the paper:
-// top-1 logit, logit ratio z2/z1, probability ratio p2/p1, share of negative top-1 logits).
-// A histogram over [lo, hi) with `bins` equal cells owns bins + 2 counters: below lo, the cells,
-// at or above hi.  The cell is trunc(fl(fl(x - lo) * w)), w = fl32(bins / (hi - lo)), capped.
-struct HistSpec {
-  float lo[3], hi[3], w[3];
-  int bins[3];
-};
-__device__ __forceinline__ int hist_cell(float x, float lo, float hi, float w, int bins) {
-  if (x < lo) return 0;
-  if (!(x < hi)) return bins + 1;
-  const int k = static_cast<int>(__fmul_rn(__fsub_rn(x, lo), w));
-  return min(k, bins - 1) + 1;
-}
-// counters: [bins0+2 | bins1+2 | bins2+2 | rows, z1 < 0, z1 <= 0, low margin at theta], cleared by the
-// row reduction of the same call.  Rows with z1 <= 0 have no ratio (Sec. 3.3) and skip its histogram.
-__global__ __launch_bounds__(256) void margin_stats_kernel(const Partial* __restrict__ partials, int rows, int N,
-                                                           int parts, const float* __restrict__ theta, double cind,
-                                                           HistSpec hs, mars_margin_row* __restrict__ rows_out,
-                                                           unsigned int* __restrict__ counters) {
-  const int first = blockIdx.x * 16;
-  const int n = min(16, rows - first);
-  if (n <= 0) return;
-  unsigned int* h0 = counters;
-  unsigned int* h1 = h0 + hs.bins[0] + 2;
-  unsigned int* h2 = h1 + hs.bins[1] + 2;
-  unsigned int* summary = h2 + hs.bins[2] + 2;
-  // The summary counters would take one atomic per row on a single address each: they are
-  // gathered in LDS first and leave the work-group as one atomic per counter.
-  __shared__ unsigned int sh_sum[4];
-  if (threadIdx.x < 4) sh_sum[threadIdx.x] = 0u;
-  __syncthreads();
-  const Indicator ind = {MARS_IND_LOGIT_RATIO, cind};
-  merge_rows_coop<256>(partials + static_cast<size_t>(first) * parts, n, parts, 0.0f, ind,
-                       [&](int row) { return theta[(first + row) / N]; },
-                       [&](int row, const mars_row_stat& st) {
-                         mars_margin_row m;
-                         m.z1 = st.z1; m.z2 = st.z2;
-                         m.ratio = st.z2 / st.z1;
-                         m.prob_ratio = prob_ratio(st.z1, st.z2, cind);
-                         if (rows_out) rows_out[first + row] = m;
-                         atomicAdd(&h0[hist_cell(m.z1, hs.lo[0], hs.hi[0], hs.w[0], hs.bins[0])], 1u);
-                         if (st.z1 > 0.0f) atomicAdd(&h1[hist_cell(m.ratio, hs.lo[1], hs.hi[1], hs.w[1], hs.bins[1])], 1u);
-                         atomicAdd(&h2[hist_cell(m.prob_ratio, hs.lo[2], hs.hi[2], hs.w[2], hs.bins[2])], 1u);
-                         if (st.z1 < 0.0f) atomicAdd(&sh_sum[1], 1u);
-                         if (!(st.z1 > 0.0f)) atomicAdd(&sh_sum[2], 1u);
-                         if (st.relax_ok) atomicAdd(&sh_sum[3], 1u);
-                       });
-  __syncthreads();
-  if (threadIdx.x == 0) sh_sum[0] = static_cast<unsigned int>(n);
-  __syncthreads();
-  if (threadIdx.x < 4 && sh_sum[threadIdx.x] != 0u) atomicAdd(&summary[threadIdx.x], sh_sum[threadIdx.x]);
-}
-
 }  // namespace mars

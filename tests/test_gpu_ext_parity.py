@@ -537,3 +537,12 @@ def test_strict_sampling_on_the_gpu_reproduces_the_target_distribution():
     say(f"[info] first committed token: chi2 {stat:.2f} (limit {limit:.2f}), accepted {float(out.accept_len.float().mean()):.3f}")
     assert stat < limit
     assert ((counts - B * qn) ** 2 / (B * qn)).sum() > 10 * limit
+
+
+@pytest.mark.parametrize("B,N,V,bins", [(1, 1, 3000, (5, 3, 2)), (41, 25, 3000, (40, 50, 50)), (64, 16, 2048, (40, 50, 50)),
+                                        (64, 33, 2048, (8180 - 2 - 12, 3, 3)), (33, 31, 2048, (8190, 3, 3))])
+def test_margin_stats_counted_by_one_work_group_or_several(B, N, V, bins):
+    # one row; one row more than a work-group takes; exactly what it takes; several work-groups with as many
+    # counters as fit into LDS; more than fit
+    w = make_config(4, B=B, N=N, V=V, tree={"kind": "chain"})
+    compare_margin(w, ((0.0, 40.0), (0.5, 1.0), (0.0, 1.0)), bins, label=f"margin_{B}x{N}_{bins}")
