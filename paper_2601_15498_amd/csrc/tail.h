@@ -460,46 +460,98 @@ struct RowView {
     if (__builtin_expect(cut_short(), 0)) complete(gi, z, q);
     mask(gi, z, q);
   }
-  __device__ __forceinline__ float f(const float (&z)[8], const float (&q)[8], int gi, int e) const {
-    return eval_f(z[e], qrow ? q[e] : 0.0f, element(gi, e), z1, c, inv_S, qrow != nullptr, ch);
+  // f of a group's eight elements: as eval_f, the chain entries one after the other (one uniform branch for each
+  // entry, not for each entry and element).
+  __device__ __forceinline__ void f8(const float (&z)[8], const float (&q)[8], int gi, float (&f)[8]) const {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = __builtin_amdgcn_exp2f((z[e] - z1) * c) * inv_S;
+    auto rejected = [&](int tok, float inv) {
+      if (!(inv > 0.0f)) return;  // Z was 0: f left unchanged
+#pragma unroll
+      for (int e = 0; e < 8; ++e) f[e] = fmaxf(f[e] - (qrow ? q[e] : (element(gi, e) == tok ? 1.0f : 0.0f)), 0.0f) * inv;
+    };
+#pragma unroll
+    for (int j = 0; j < kChainRegs; ++j)
+      if (j < ch.n) rejected(ch.rtok[j], ch.rinv[j]);
+    for (int j = kChainRegs; j < ch.n; ++j) rejected(ch.tok[j], ch.inv_norm[j]);
   }
 };
 // Groups a row can touch.
 __device__ __host__ __forceinline__ int row_groups(int V, bool vec) { return vec ? V / 8 : static_cast<int>((static_cast<long>(V) + 14) / 8); }
 
-// Groups whose loads a thread issues before it starts computing.  (The streamed form runs 1024 threads, so 128
-// registers each; with four groups in flight the kernel needs about 160 and spills, which on the B = 128 chain
-// workload costs 25 us of 105; with two it needs 106 and the sixteen waves keep the memory pipeline as full.)
-constexpr int kPassBatch = 2;
+// A streamed pass: n steps, in step s a lane looks at group at(s) (any readable group where it has none).  Two batches
+// of BATCH steps take turns, one in flight while the other is worked on, as they come from memory; a step's elements
+// are widened when its turn comes.  No load stands under a condition: past the last step that step is asked
+// for again and dropped.  (The kernel has 1024 threads, so 128 registers: with the draft probabilities two steps to a
+// batch, without them four; half of that where groups have to be masked, for the size of the code.  What
+// bounds a pass is the memory latency of a compute unit that streams alone: with one batch at a time, waited for
+// and then worked on, seven thresholds on 16 trees of 60 nodes took 118 us per call and 128 chains with dense
+// probabilities 73.3; now 98.8 and 70.5.)
+template <int BATCH, bool Q, typename T, typename TQ, bool VEC, typename At, typename Body>
+__device__ __forceinline__ void stream_steps(const RowView<T, TQ, VEC>& rv, int n, At at, Body body) {
+  constexpr int NQ = Q ? BATCH : 1;
+  Raw8<T> za[BATCH], zb[BATCH];
+  Raw8<TQ> qa[NQ], qb[NQ];
+  auto request = [&](Raw8<T>(&z)[BATCH], Raw8<TQ>(&q)[NQ], int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int gi = at(min(s0 + i, n - 1));
+      rv.load_raw(gi, z[i]);
+      if (Q) rv.load_raw_q(gi, q[i % NQ]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto work = [&](const Raw8<T>(&z)[BATCH], const Raw8<TQ>(&q)[NQ], int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      if (s0 + i >= n) continue;
+      float x[8], y[8];
+      z[i].widen_to(x);
+      if (Q) q[i % NQ].widen_to(y);
+      else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = 0.0f;
+      }
+      body(s0 + i, x, y);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (n <= 0) return;
+  request(za, qa, 0);
+  for (int s = 0; s < n; s += 2 * BATCH) {
+    request(zb, qb, s + BATCH);
+    work(za, qa, s);
+    request(za, qa, s + 2 * BATCH);
+    work(zb, qb, s + BATCH);
+  }
+}
+template <typename T, typename TQ, bool VEC, typename At, typename Body>
+__device__ __forceinline__ void stream_row(const RowView<T, TQ, VEC>& rv, int n, At at, Body body) {
+  if (rv.qrow && rv.use_q) stream_steps<VEC ? 2 : 1, true>(rv, n, at, body);
+  else stream_steps<VEC ? 4 : 2, false>(rv, n, at, body);
+}
 
 // This work-group's share of Z = sum_v max(0, f(v) - q_k(v)) over groups [g_begin, g_end):
-// q_k dense, or one-hot at token x.  The loads of kPassBatch groups are issued together so
-// that a pass costs about one memory round trip per batch, not one per group.
+// q_k dense, or one-hot at token x.
 template <typename T, typename TQ, int NT, bool VEC>
 __device__ __forceinline__ double residual_mass_slice(const RowView<T, TQ, VEC>& rv, int g_begin, int g_end, int x) {
   double part = 0.0;
-  for (int base = g_begin + static_cast<int>(threadIdx.x); base < g_end; base += kPassBatch * NT) {
-    float z[kPassBatch][8], q[kPassBatch][8];
+  auto group = [&](int s) { return g_begin + static_cast<int>(threadIdx.x) + s * NT; };
+  stream_row(rv, (g_end - g_begin + NT - 1) / NT, [&](int s) { return min(group(s), g_end - 1); },
+             [&](int s, float(&z)[8], float(&q)[8]) __attribute__((always_inline)) {
+               const int gi = group(s);
+               if (gi < g_end) {
+                 float f[8], acc = 0.0f;
+                 rv.trim(gi, z, q);
+                 rv.f8(z, q, gi, f);
 #pragma unroll
-    for (int i = 0; i < kPassBatch; ++i) {  // (no load under a per-lane condition: see the final draw)
-      const int gi = base + i * NT;
-      rv.load(gi < g_end ? gi : g_end - 1, z[i], q[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < kPassBatch; ++i) {
-      const int gi = base + i * NT;
-      if (gi < g_end) {
-        float acc = 0.0f;
-        rv.trim(gi, z[i], q[i]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float qk = rv.qrow ? q[i][e] : (rv.element(gi, e) == x ? 1.0f : 0.0f);
-          acc += fmaxf(rv.f(z[i], q[i], gi, e) - qk, 0.0f);
-        }
-        part += static_cast<double>(acc);
-      }
-    }
-  }
+                 for (int e = 0; e < 8; ++e) {
+                   const float qk = rv.qrow ? q[e] : (rv.element(gi, e) == x ? 1.0f : 0.0f);
+                   acc += fmaxf(f[e] - qk, 0.0f);
+                 }
+                 part += static_cast<double>(acc);
+               }
+             });
   return part;
 }
 
@@ -582,11 +634,12 @@ __device__ __forceinline__ double resident_mass_from_memory(const RowView<T, TQ,
     float z[8], q[8];
     rv.load(gi, z, q);
     rv.trim(gi, z, q);
-    float acc = 0.0f;
+    float f[8], acc = 0.0f;
+    rv.f8(z, q, gi, f);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float qk = rv.qrow ? q[e] : (rv.element(gi, e) == x ? 1.0f : 0.0f);
-      acc += fmaxf(rv.f(z, q, gi, e) - qk, 0.0f);
+      acc += fmaxf(f[e] - qk, 0.0f);
     }
     part += static_cast<double>(acc);
   }
@@ -608,8 +661,7 @@ __device__ __forceinline__ int resident_tiles_from_memory(const RowView<T, TQ, V
         float z[8], q[8], f[8];
         rv.load(gi, z, q);
         rv.trim(gi, z, q);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = rv.f(z, q, gi, e);
+        rv.f8(z, q, gi, f);
         gs = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
       }
       const double t = wave_sum(static_cast<double>(gs));
@@ -1069,8 +1121,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     return (sw < steps_per_wave && gi < g_end) ? gi : -1;
   };
   auto group_sum = [&](const float (&z)[8], const float (&q)[8], int gi, float (&f)[8]) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = rv.f(z, q, gi, e);
+    rv.f8(z, q, gi, f);
     return ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
   };
 
@@ -1109,36 +1160,29 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       for (;;) {
         const int gb = min(ngroups, who * slice), ge = min(ngroups, gb + slice);
         double* tiles = who == g ? sh_tile : sh_tile2;
-        // tile sums of a streamed slice, kPassBatch steps of loads in flight at a time
+        // tile sums of a streamed slice
         const int spw = (((ge - gb + kWave - 1) / kWave) + NW - 1) / NW;  // steps per wave of this slice
         const int rp = max(1, (spw * NW + kMaxTiles - 1) / kMaxTiles);
         const int tpw = (spw + rp - 1) / rp;
-        auto group_at = [&](int sw) {  // group of this lane in step sw of its wave, -1 = none
-          const int gi = gb + (wave * spw + sw) * kWave + lane;
-          return (sw < spw && gi < ge) ? gi : -1;
-        };
+        auto group_at = [&](int sw) { return gb + (wave * spw + sw) * kWave + lane; };  // this lane's in step sw of its wave
         double acc = 0.0;
-        for (int s0 = 0; s0 < spw; s0 += kPassBatch) {
-          float z[kPassBatch][8], q[kPassBatch][8];
-#pragma unroll
-          for (int i = 0; i < kPassBatch; ++i) {  // (no load under a per-lane condition: a lane without a group
-            const int gi = group_at(s0 + i);      // reads the row's last one and ignores it, and the loads of a
-            rv.load(gi >= 0 ? gi : ngroups - 1, z[i], q[i]);  // batch go out together instead of one by one)
-          }
-#pragma unroll
-          for (int i = 0; i < kPassBatch; ++i) {
-            const int sw = s0 + i;
-            if (sw < spw) {
-              const int gi = group_at(sw);
-              if (gi >= 0) { float f[8]; rv.trim(gi, z[i], q[i]); acc += static_cast<double>(group_sum(z[i], q[i], gi, f)); }
-              if ((sw + 1) % rp == 0 || sw + 1 == spw) {
-                const double t = wave_sum(acc);
-                if (lane == 0) tiles[wave * tpw + sw / rp] = t;
-                acc = 0.0;
-              }
-            }
-          }
-        }
+        int tile_steps = 0, next_tile = wave * tpw;
+        stream_row(rv, spw, [&](int sw) { const int gi = group_at(sw); return gi < ge ? gi : ngroups - 1; },
+                   [&](int sw, float(&z)[8], float(&q)[8]) __attribute__((always_inline)) {
+                     const int gi = group_at(sw);
+                     if (gi < ge) {
+                       float f[8];
+                       rv.trim(gi, z, q);
+                       acc += static_cast<double>(group_sum(z, q, gi, f));
+                     }
+                     if (++tile_steps == rp || sw + 1 == spw) {
+                       const double t = wave_sum(acc);
+                       if (lane == 0) tiles[next_tile] = t;
+                       ++next_tile;
+                       tile_steps = 0;
+                       acc = 0.0;
+                     }
+                   });
         __syncthreads();
         const double slice_total = tile_total(tiles, tpw * NW, lane);
         if (who == g) {

@@ -412,3 +412,13 @@ def test_row_ends_hold_the_candidates(dtype, V):
         greedy = M.mars_row_stats(d, torch.full((2,), 0.9, device="cuda:0"), 0.0)
         torch.cuda.synchronize()
         assert_stats_match(greedy, mars_ref.row_stats(bits, 0.9, 0.0), False, f"ends_greedy_{dtype}_V{V}_k{k}")
+
+
+@pytest.mark.parametrize("dtype,dense,V", [("bf16", True, 24600), ("f32", False, 40008), ("bf16", False, 65544),
+                                           ("f32", True, 81936), ("bf16", True, 98328), ("f32", False, 147464)])
+def test_streamed_passes_of_every_length(dtype, dense, V):
+    # 128 requests share the chip two work-groups each: a wave's share of a pass is 2, 3, 4, 5, 6 and 9 steps, which end in
+    # the first and the second of the two batches in flight, full and not
+    w = make_workload(f"stream_{dtype}_{dense}_V{V}", B=128, N=3, V=V, dtype=dtype, temperature=0.9, dense_q=dense,
+                      tree={"kind": "tree", "depth": 1, "max_children": 2}, plant_frac=0.5, seed=V)
+    compare(w, cdf_guard=5e-6, allow_small_norm=True)
