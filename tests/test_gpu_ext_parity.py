@@ -546,3 +546,13 @@ def test_margin_stats_counted_by_one_work_group_or_several(B, N, V, bins):
     # counters as fit into LDS; more than fit
     w = make_config(4, B=B, N=N, V=V, tree={"kind": "chain"})
     compare_margin(w, ((0.0, 40.0), (0.5, 1.0), (0.0, 1.0)), bins, label=f"margin_{B}x{N}_{bins}")
+
+
+@pytest.mark.parametrize("B,N", [(3, 1), (2, 2), (5, 9), (4, 10), (3, 11), (300, 12)])
+def test_kept_rows_of_paths_shorter_and_longer_than_are_read_ahead(B, N):
+    # every draft is the top entry of its row: whole chains of N - 1 drafts are kept, up to and beyond the eight
+    # path entries that are requested ahead of the length, in one round of requests and in several
+    w = make_config(4, B=B, N=N, V=2048, tree={"kind": "chain"}, temperature=0.0)
+    for i in range(1, N):
+        w.draft_tokens[:, i] = w.logits[:, i - 1].argmax(axis=-1)
+    compare_ex(w, label=f"kept_rows_B{B}_N{N}")
