@@ -13,11 +13,11 @@
 // 128 entries is taken inside the lane, a running pair per row is carried across the tiles of a
 // (slab, column) cell, and the two halves of a wave and the two waves that share a row meet at its end.
 //
-// What bounds it: the matrix cores and the power they draw.  6 656 rows x 4096 x 151 936: 6.14-6.24 ms =
-// 1.33-1.35 PFLOP/s (the library's product alone 1.48; 8192^3: 1.40), the clock at 1.65 GHz of 2.4 and the matrix
+// What bounds it: the matrix cores and the power they draw.  6 656 rows x 4096 x 151 936: 6.06-6.11 ms =
+// 1.36 PFLOP/s (the library's product alone 1.48; 8192^3: 1.40), the clock at 1.65 GHz of 2.4 and the matrix
 // units busy 3/4 of the time; before (192 rows at most, keys in 32-bit integers, unequal shares) 6.76-6.81 ms.
-// 960 rows, sampling form: 1 065-1 075 us (before 1 146-1 160).  60 rows: bound by the weight, 1.24 GB in 208 us =
-// 6.0 TB/s (before 217 us).
+// 960 rows, sampling form: 1 059-1 070 us (before 1 133-1 160).  60 rows: bound by the weight, 1.24 GB in 203 us =
+// 6.1 TB/s, and the per-request kernel behind it.
 #pragma once
 
 #include <type_traits>

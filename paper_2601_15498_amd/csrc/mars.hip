@@ -150,22 +150,27 @@ struct LmPlan {
   LmGrid grid;  // of a full launch
 };
 constexpr int kDies = 8;
-constexpr int kLmBand = 7;  // slabs of a band: a die's 32 work-groups then read about as many bytes of weight as of hidden states
+// Slabs of a band, at most: work-groups of a die then share weight tiles and hidden states about evenly, and few bands
+// leave few columns narrower than a work-group's share, behind which the work-groups of a band are out of step
+// with the next one's.  6 656 rows in slabs of 256: 6.26 ms with 5, 6.14 with 7 and 9, 6.08 with 13, 6.10 with 26;
+// 2 048 rows x 128 256: 1 620 us with 7 (two bands of 4), 1 576 with 13 (one of 8).
+constexpr int kLmBand = 13;
 static LmPlan lm_plan(long rows, int V, int H, bool sampling) {
   LmPlan p;
   p.wide = H > (1 << 22) || V > (1 << 25);
   p.tiles_n = static_cast<int>((static_cast<long>(V) + kLmBN - 1) / kLmBN);
   // The slab height that takes the least time: units per work-group x time per unit.  Measured per unit at
   // H = 4096, greedy form: 49-51 us with 64 rows, 61-63 with 128, 80-83 with 192, 100-104 with 256; with two slabs
-  // of 64 at most and a work-group on (nearly) every compute unit the weight's way from memory bounds it, at
-  // 71-78 us (128 rows: 69-75).  The sampling form does not fit the registers with 256.
+  // of 64 and a work-group on (nearly) every compute unit the weight's way from memory bounds it, at
+  // 78 us (128 rows, one slab: 75); with one slab both heights wait for the weight (60 rows: 215.5 us per call
+  // with 64, 218.2 with 128).  The sampling form does not fit the registers with 256.
   static const struct { int bm; double cost; } kHeights[] = {{64, 0.60}, {128, 0.75}, {192, 1.0}, {256, 1.235}};
   double best = -1.0;
   p.bm = 64;
   for (const auto& h : kHeights) {
     if (h.bm > (p.wide ? 64 : sampling ? 192 : 256)) break;
     const long slabs = (rows + h.bm - 1) / h.bm, units = slabs * p.tiles_n;
-    const bool weight_bound = h.bm == 64 && slabs <= 2 && units >= 192;
+    const bool weight_bound = h.bm == 64 && slabs == 2 && units >= 192;
     const double time = static_cast<double>((units + kComputeUnits - 1) / kComputeUnits) * (weight_bound ? 0.87 : h.cost);
     if (best < 0.0 || time < best) { best = time; p.bm = h.bm; }
   }
