@@ -272,14 +272,16 @@ static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int 
   // groups of eight elements as single aligned loads: whole rows of groups, arrays on 16-byte boundaries
   const bool vec = (V % 8 == 0) && (reinterpret_cast<uintptr_t>(a.logits) % 16 == 0) &&
                    (!dense || reinterpret_cast<uintptr_t>(a.dprobs) % 16 == 0);
-  // Slices of at most kResident groups of eight per thread stay in registers between passes.
+  // Slices of at most kMaxResident groups of eight per thread stay in registers between passes.
   const int ngroups8 = row_groups(V, vec);
   const int slice8 = ((ngroups8 + a.G - 1) / a.G + kWave - 1) / kWave * kWave;
-  const bool resident = slice8 <= kResident * kSamplingThreads;
+  const bool resident = slice8 <= kMaxResident * kSamplingThreads, two = slice8 <= 2 * kSamplingThreads;
   const bool qbf = dense && draft_dtype == MARS_BF16;
   const void* kernel;
-#define MARS_PICK2(TT, QQ, VV) (resident ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, VV>) \
-                                         : reinterpret_cast<const void*>(&tail_sampling_streamed_kernel<TT, QQ, VV>))
+#define MARS_PICK2(TT, QQ, VV)                                                                    \
+  (two        ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, 2, VV>)           \
+   : resident ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, kMaxResident, VV>) \
+              : reinterpret_cast<const void*>(&tail_sampling_streamed_kernel<TT, QQ, VV>))
 #define MARS_PICK(TT, QQ) (vec ? MARS_PICK2(TT, QQ, true) : MARS_PICK2(TT, QQ, false))
   if (logits_dtype == MARS_BF16) kernel = qbf ? MARS_PICK(bf16_t, bf16_t) : MARS_PICK(bf16_t, float);
   else kernel = qbf ? MARS_PICK(float, bf16_t) : MARS_PICK(float, float);

@@ -672,12 +672,18 @@ __device__ __forceinline__ int resident_tiles_from_memory(const RowView<T, TQ, V
 }
 
 constexpr float kClosedFormMinNorm = 0.1f; // one-hot residual: Z = 1 - f(x) is used when at least this
-constexpr int kResident = 3;               // groups of eight elements a thread can keep in registers
+constexpr int kMaxResident = 3;            // groups of eight elements a thread can keep in registers
 
-// RESIDENT: every slice is at most kResident groups per thread (decided by the host from G and V).
+// RES: every slice is at most RES groups per thread and stays in registers (decided by the host from G and V), 0: it is
+// streamed.  Two of them where they are enough -- few requests, or a small vocabulary -- carry two thirds of the
+// loads, exponentials, registers and code of three, and the walk is bound by what a wave has to issue and to fetch: one
+// tree of 60 nodes 22.6 -> 21.9 us per call, 8 trees over 100 001 entries 28.0 -> 26.5, 3 over 3 001 with dense
+// probabilities 21.2 -> 19.4.
 // VEC: every group of eight elements is whole and aligned (RowView).
-template <typename T, typename TQ, bool RESIDENT, bool VEC>
+template <typename T, typename TQ, int RES, bool VEC>
 __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
+  constexpr bool RESIDENT = RES > 0;
+  constexpr int kResident = RESIDENT ? RES : 1;
   constexpr int NT = RESIDENT ? kSamplingThreads : kStreamingThreads;
   constexpr int NW = NT / kWave;
   __shared__ int16_t sh_par[MARS_MAX_NODES];     // parent of every node
@@ -834,7 +840,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   // groups, so that the slices are made of whole wave steps).
   const int slice = ((ngroups + G - 1) / G + kWave - 1) / kWave * kWave;
   const int g_begin = min(ngroups, g * slice), g_end = min(ngroups, g_begin + slice);
-  // A slice of at most kResident groups per thread stays in registers between the passes over
+  // A slice of at most RES groups per thread stays in registers between the passes over
   // one node: f is then loaded and exponentiated once per visited node, every further
   // rejection at that node only updates it in place, and the final draw reads it where it is.
   // Thread t holds groups g_begin + i*NT + t; "step" s = i*NW + wave is 64 consecutive groups.
@@ -1340,13 +1346,13 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   }
 }
 
-template <typename T, typename TQ, bool VEC>
+template <typename T, typename TQ, int RES, bool VEC>
 __global__ __launch_bounds__(kSamplingThreads) void tail_sampling_resident_kernel(TailArgs a) {
-  tail_sampling_body<T, TQ, true, VEC>(a);
+  tail_sampling_body<T, TQ, RES, VEC>(a);
 }
 template <typename T, typename TQ, bool VEC>
 __global__ __launch_bounds__(kStreamingThreads) void tail_sampling_streamed_kernel(TailArgs a) {
-  tail_sampling_body<T, TQ, false, VEC>(a);
+  tail_sampling_body<T, TQ, 0, VEC>(a);
 }
 
 // ---------------------------------------------------------------- cache rows that stay

@@ -422,3 +422,12 @@ def test_streamed_passes_of_every_length(dtype, dense, V):
     w = make_workload(f"stream_{dtype}_{dense}_V{V}", B=128, N=3, V=V, dtype=dtype, temperature=0.9, dense_q=dense,
                       tree={"kind": "tree", "depth": 1, "max_children": 2}, plant_frac=0.5, seed=V)
     compare(w, cdf_guard=5e-6, allow_small_norm=True)
+
+
+@pytest.mark.parametrize("V", [262144, 262141, 262152, 262147, 393216, 393209, 393728])
+@pytest.mark.parametrize("dense", [False, True])
+def test_slices_of_two_and_three_groups_per_thread(V, dense):
+    # one request on 32 work-groups: slices of exactly two groups per thread, one more, exactly three, and streamed
+    w = make_workload(f"slices_V{V}_{dense}", B=1, N=4, V=V, dtype="bf16", temperature=0.9, dense_q=dense,
+                      tree={"kind": "tree", "depth": 2, "max_children": 2}, plant_frac=0.5, seed=V)
+    compare(w, cdf_guard=5e-6, allow_small_norm=True)
