@@ -269,9 +269,7 @@ static void* static_scratch() {
 static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int draft_dtype, hipStream_t stream) {
   const int V = a.V;
   const bool dense = draft_dtype >= 0;
-  // groups of eight elements as single aligned loads: whole rows of groups, arrays on 16-byte boundaries
-  const bool vec = (V % 8 == 0) && (reinterpret_cast<uintptr_t>(a.logits) % 16 == 0) &&
-                   (!dense || reinterpret_cast<uintptr_t>(a.dprobs) % 16 == 0);
+  const bool vec = whole_groups(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, dense ? a.dprobs : nullptr, a.N, V);
   // Slices of at most kMaxResident groups of eight per thread stay in registers between passes.
   const int ngroups8 = row_groups(V, vec);
   const int slice8 = ((ngroups8 + a.G - 1) / a.G + kWave - 1) / kWave * kWave;

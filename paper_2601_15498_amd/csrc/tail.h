@@ -412,6 +412,12 @@ struct RowView {
   __device__ __forceinline__ void load_raw_q(int gi, Raw8<TQ>& q) const {
     q.load(VEC ? qrow : qgroup, VEC ? gi : min(gi, max(whole, 0)));
   }
+  // What the groups of the draft probabilities are read from.  Where they are not wanted, a load that is made all the
+  // same reads group 0 of this: up to 32 bytes of the request's own logits (VEC: whole_groups() asks for that many), or
+  // `somewhere`.
+  __device__ __forceinline__ const TQ* q_source(bool wanted, const void* somewhere) const {
+    return wanted ? (VEC ? qrow : qgroup) : static_cast<const TQ*>(VEC ? static_cast<const void*>(zreq) : somewhere);
+  }
   // Requested here, widened where they are needed (see load).
   __device__ __forceinline__ void load(int gi, float (&z)[8], float (&q)[8]) const {
     Raw8<T> rz;
@@ -476,6 +482,13 @@ struct RowView {
     for (int j = kChainRegs; j < ch.n; ++j) rejected(ch.tok[j], ch.inv_norm[j]);
   }
 };
+// Whether the walk takes its VEC form (host): whole rows of groups, arrays on 16-byte boundaries, and requests with 32
+// bytes of logits at least -- one row of eight bf16 entries has 16, and where it is the array's last one the load in place of
+// draft probabilities that are not wanted (q_source) would run past the array's end.
+inline bool whole_groups(const void* logits, size_t elt, const void* dprobs, int N, int V) {
+  return V % 8 == 0 && reinterpret_cast<uintptr_t>(logits) % 16 == 0 && reinterpret_cast<uintptr_t>(dprobs) % 16 == 0 &&
+         static_cast<size_t>(N) * V * elt >= 32;
+}
 // Groups a row can touch.
 __device__ __host__ __forceinline__ int row_groups(int V, bool vec) { return vec ? V / 8 : static_cast<int>((static_cast<long>(V) + 14) / 8); }
 
@@ -874,12 +887,11 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     rq_loaded = rv.qrow && rv.use_q;
     // No load stands under a condition, per lane or per call: a lane past the end of its slice reads the
     // row's last group and throws it away, and when the draft probabilities are not wanted every lane reads
-    // 32 bytes in their place: the first ones of the logits (an array that can be cut short: of the partial results).  With a branch between two loads the compiler can no
+    // 32 bytes in their place: the first ones of the logits or of the partial results.  With a branch between two loads the compiler can no
     // longer count what is in flight and makes each wait for the one before (three trips to memory instead
     // of one); with a branch around them it copies what they return into the registers of the other path
     // right away, and waits for it there.
-    const TQ* __restrict__ qsrc = rq_loaded ? (VEC ? rv.qrow : rv.qgroup)
-                                            : VEC ? reinterpret_cast<const TQ*>(zall) : reinterpret_cast<const TQ*>(a.partials + rd * a.splits);
+    const TQ* __restrict__ qsrc = rv.q_source(rq_loaded, a.partials + rd * a.splits);
 #pragma unroll
     for (int i = 0; i < kResident; ++i) {
       int gi = min(g_begin + i * NT + tid, ngroups - 1);

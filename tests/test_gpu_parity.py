@@ -431,3 +431,15 @@ def test_slices_of_two_and_three_groups_per_thread(V, dense):
     w = make_workload(f"slices_V{V}_{dense}", B=1, N=4, V=V, dtype="bf16", temperature=0.9, dense_q=dense,
                       tree={"kind": "tree", "depth": 2, "max_children": 2}, plant_frac=0.5, seed=V)
     compare(w, cdf_guard=5e-6, allow_small_norm=True)
+
+
+@pytest.mark.parametrize("V", [2, 3, 7, 8, 16])
+@pytest.mark.parametrize("N,qdtype", [(1, None), (1, "f32"), (2, None), (2, "bf16")])
+def test_arrays_shorter_than_the_loads_of_the_walk(V, N, qdtype):
+    # Down to one row of two entries: a group of eight, or the 32 bytes read in place of draft probabilities that
+    # are not wanted (a row of eight bf16 entries has 16), is more than the whole array.
+    w = make_workload(f"short_V{V}_N{N}_{qdtype}", B=1 if V < 8 else 3, N=N, V=V, dtype="bf16", temperature=0.8,
+                      dense_q=qdtype is not None, tree={"kind": "chain"}, plant_frac=0.5, seed=V + N)
+    if qdtype == "bf16":
+        w.draft_probs = f32_to_bf16_bits(w.draft_probs)
+    compare(w, allow_small_norm=True)
