@@ -187,12 +187,17 @@ __global__ __launch_bounds__(kGreedyThreads) void tail_greedy_kernel(TailArgs a)
 
 // ---------------------------------------------------------------- sampling mode
 // Eight consecutive elements as they lie in memory (one group): requested without being looked at,
-// so that nothing waits for them until they are widened.
+// so that nothing waits for them until they are widened.  ALIGNED: on a 16-byte boundary.  Otherwise no more is known,
+// and said, than where an element may begin; the hardware takes such an address, and it is the same one load.
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {
   u32x4 v;
+  template <bool ALIGNED>
   __device__ __forceinline__ void load(const bf16_t* __restrict__ row, int g) {
-    v = *reinterpret_cast<const u32x4*>(row + static_cast<size_t>(g) * 8);
+    const bf16_t* at = row + static_cast<size_t>(g) * 8;
+    if (ALIGNED) v = *reinterpret_cast<const u32x4*>(at); else v = *reinterpret_cast<const u32x4_any*>(at);
   }
   __device__ __forceinline__ void widen_to(float (&x)[8]) const {
     x[0] = __uint_as_float(v.x << 16); x[1] = __uint_as_float(v.x & 0xFFFF0000u);
@@ -203,9 +208,16 @@ template <> struct Raw8<bf16_t> {
 };
 template <> struct Raw8<float> {
   f32x4 lo, hi;
+  template <bool ALIGNED>
   __device__ __forceinline__ void load(const float* __restrict__ row, int g) {
-    lo = *reinterpret_cast<const f32x4*>(row + static_cast<size_t>(g) * 8);
-    hi = *reinterpret_cast<const f32x4*>(row + static_cast<size_t>(g) * 8 + 4);
+    const float* at = row + static_cast<size_t>(g) * 8;
+    if (ALIGNED) {
+      lo = *reinterpret_cast<const f32x4*>(at);
+      hi = *reinterpret_cast<const f32x4*>(at + 4);
+    } else {
+      lo = *reinterpret_cast<const f32x4_any*>(at);
+      hi = *reinterpret_cast<const f32x4_any*>(at + 4);
+    }
   }
   __device__ __forceinline__ void widen_to(float (&x)[8]) const {
     x[0] = lo.x; x[1] = lo.y; x[2] = lo.z; x[3] = lo.w; x[4] = hi.x; x[5] = hi.y; x[6] = hi.z; x[7] = hi.w;
@@ -407,10 +419,10 @@ struct RowView {
   }
   __device__ __forceinline__ int element(int gi, int e) const { return VEC ? gi * 8 + e : gi * 8 + e - shift; }
   __device__ __forceinline__ void load_raw(int gi, Raw8<T>& z) const {
-    z.load(VEC ? zrow : zgroup, VEC ? gi : min(gi, max(whole, 0)));
+    z.template load<VEC>(VEC ? zrow : zgroup, VEC ? gi : min(gi, max(whole, 0)));
   }
   __device__ __forceinline__ void load_raw_q(int gi, Raw8<TQ>& q) const {
-    q.load(VEC ? qrow : qgroup, VEC ? gi : min(gi, max(whole, 0)));
+    q.template load<VEC>(VEC ? qrow : qgroup, VEC ? gi : min(gi, max(whole, 0)));
   }
   // What the groups of the draft probabilities are read from.  Where they are not wanted, a load that is made all the
   // same reads group 0 of this: up to 32 bytes of the request's own logits (VEC: whole_groups() asks for that many), or
@@ -896,8 +908,8 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     for (int i = 0; i < kResident; ++i) {
       int gi = min(g_begin + i * NT + tid, ngroups - 1);
       if (!VEC) gi = min(gi, max(rv.whole, 0));
-      rz[i].load(VEC ? rv.zrow : rv.zgroup, gi);
-      rq[i].load(qsrc, rq_loaded ? gi : 0);
+      rz[i].template load<VEC>(VEC ? rv.zrow : rv.zgroup, gi);
+      rq[i].template load<VEC>(qsrc, rq_loaded ? gi : 0);
     }
     raw = true;
     have = false;

@@ -30,5 +30,5 @@ def run_on_cpu(source, tmp_path, *sanitizers):
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 def test_the_walk_reads_rows_and_nothing_around_them(tmp_path):
-    out = run_on_cpu("walk_loads_main.hip", tmp_path, "address")
+    out = run_on_cpu("walk_loads_main.hip", tmp_path, "address", "alignment")
     assert " 0 failed" in out, out

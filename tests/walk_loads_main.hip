@@ -1,12 +1,14 @@
 // The sampling walk's view of a row (csrc/tail.h: RowView), run on the CPU: every load it makes of every group of
-// every row, from arrays that end where their allocation ends, under AddressSanitizer.  What is loaded and trimmed is
-// compared with the array, element by element.
+// every row, from arrays at every alignment that end where their allocation ends, under AddressSanitizer and with the
+// alignment of every access checked.  What is loaded and trimmed is compared with the array, element by element.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
+
+#include <sanitizer/asan_interface.h>
 
 // (the headers have this for the device alone)
 static inline __host__ float __uint_as_float(unsigned int x) { return __builtin_bit_cast(float, x); }
@@ -33,16 +35,20 @@ static float q_value(size_t i) { return static_cast<float>(i * 5 % 241 + 1) / 25
 static void put(float& x, float v) { x = v; }
 static void put(bf16_t& x, float v) { x = static_cast<bf16_t>(__builtin_bit_cast(unsigned int, v) >> 16); }
 
-// An array of n elements at the very end of an allocation of its own.
+// An array of n elements, k behind the beginning of an allocation and at its very end.
 template <typename T>
 struct Array {
   T* base;
-  size_t n;
-  Array(size_t n_, float (*value)(size_t)) : base(static_cast<T*>(std::malloc(n_ * sizeof(T)))), n(n_) {
-    for (size_t i = 0; i < n; ++i) put(base[i], value(i));
+  size_t n, k;
+  Array(size_t n_, size_t k_, float (*value)(size_t)) : base(static_cast<T*>(std::malloc((n_ + k_) * sizeof(T)))), n(n_), k(k_) {
+    for (size_t i = 0; i < n; ++i) put(base[k + i], value(i));
+    ASAN_POISON_MEMORY_REGION(base, k * sizeof(T));  // (in steps of eight bytes)
   }
-  ~Array() { std::free(base); }
-  T* data() const { return base; }
+  ~Array() {
+    ASAN_UNPOISON_MEMORY_REGION(base, k * sizeof(T));
+    std::free(base);
+  }
+  T* data() const { return base + k; }
 };
 
 static long failed = 0, cases = 0, loads = 0;
@@ -63,7 +69,7 @@ static void check(const T* z, const TQ* q, int B, int N, int V, const void* spar
         rv.row(node, q != nullptr);
         const bool dense = q != nullptr && rv.use_q;
         Raw8<TQ> r;
-        r.load(rv.q_source(false, spare), 0);
+        r.template load<VEC>(rv.q_source(false, spare), 0);
         float unused[8];
         r.widen_to(unused);
         for (float u : unused) sink = u;
@@ -90,10 +96,10 @@ static void check(const T* z, const TQ* q, int B, int N, int V, const void* spar
 }
 
 template <typename T, typename TQ>
-static void run(int B, int N, int V, bool dense) {
+static void run(int B, int N, int V, bool dense, int k) {
   const size_t n = static_cast<size_t>(B) * N * V;
-  Array<T> z(n, z_value);
-  Array<TQ> q(dense ? n : 1, q_value);
+  Array<T> z(n, k, z_value);
+  Array<TQ> q(dense ? n : 1, k == 0 ? 0 : 8 - k, q_value);
   alignas(16) static char spare[32];
   const T* zp = z.data();
   const TQ* qp = dense ? q.data() : nullptr;
@@ -108,12 +114,13 @@ int main() {
   const int sizes[][3] = {{1, 1, 2}, {1, 1, 7}, {1, 1, 8}, {1, 2, 8}, {2, 1, 9}, {3, 1, 5}, {1, 3, 16}, {2, 3, 24}, {2, 5, 13},
                           {3, 4, 61}, {2, 3, 63}, {1, 3, 65}, {2, 2, 520}, {2, 2, 1001}};
   for (const auto& s : sizes)
-    for (int dense = 0; dense < 2; ++dense) {
-      run<bf16_t, float>(s[0], s[1], s[2], dense != 0);
-      run<bf16_t, bf16_t>(s[0], s[1], s[2], dense != 0);
-      run<float, float>(s[0], s[1], s[2], dense != 0);
-      run<float, bf16_t>(s[0], s[1], s[2], dense != 0);
-    }
+    for (int dense = 0; dense < 2; ++dense)
+      for (int k = 0; k < 8; ++k) {
+        run<bf16_t, float>(s[0], s[1], s[2], dense != 0, k);
+        run<bf16_t, bf16_t>(s[0], s[1], s[2], dense != 0, k);
+        run<float, float>(s[0], s[1], s[2], dense != 0, k);
+        run<float, bf16_t>(s[0], s[1], s[2], dense != 0, k);
+      }
   std::printf("%ld cases, %ld loads, %ld failed\n", cases, loads, failed);
   return failed != 0;
 }
