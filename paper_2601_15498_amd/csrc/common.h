@@ -19,7 +19,8 @@ using bf16_t = uint16_t;
 __device__ __forceinline__ float widen(float x) { return x; }
 __device__ __forceinline__ float widen(bf16_t h) { return __uint_as_float(static_cast<uint32_t>(h) << 16); }
 
-// A 16-byte vector of EPV elements, with compile-time element access.
+// A 16-byte vector of EPV elements (or a single element when EPV == 1), with
+// compile-time element access.
 template <typename T, int EPV> struct Vec;
 
 // The logits are read exactly once per call: the streaming loads carry the non-temporal hint so
@@ -41,6 +42,13 @@ template <> struct Vec<bf16_t, 8> {
   }
 };
 
+template <> struct Vec<bf16_t, 1> {
+  bf16_t r;
+  __device__ __forceinline__ void load(const bf16_t* row, unsigned int vec) { r = __builtin_nontemporal_load(row + vec); }
+  __device__ __forceinline__ void fill_neg_inf() { r = 0xFF80u; }
+  __device__ __forceinline__ float get(int) const { return widen(r); }
+};
+
 template <> struct Vec<float, 4> {
   float4 r;
   __device__ __forceinline__ void load(const float* row, unsigned int vec) {
@@ -49,6 +57,13 @@ template <> struct Vec<float, 4> {
   }
   __device__ __forceinline__ void fill_neg_inf() { r = make_float4(neg_inf(), neg_inf(), neg_inf(), neg_inf()); }
   __device__ __forceinline__ float get(int e) const { return e == 0 ? r.x : e == 1 ? r.y : e == 2 ? r.z : r.w; }
+};
+
+template <> struct Vec<float, 1> {
+  float r;
+  __device__ __forceinline__ void load(const float* row, unsigned int vec) { r = __builtin_nontemporal_load(row + vec); }
+  __device__ __forceinline__ void fill_neg_inf() { r = neg_inf(); }
+  __device__ __forceinline__ float get(int) const { return r; }
 };
 
 // ---------------------------------------------------------------- total order (value desc, index asc)

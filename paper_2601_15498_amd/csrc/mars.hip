@@ -110,11 +110,21 @@ static hipError_t launch_row_reduce_t(const void* logits, long rows, int V, int 
   return hipGetLastError();
 }
 
-// 16-byte loads; rows that do not all start on a 16-byte boundary take the form that looks for the first one.
+// Rows off a 16-byte boundary of at most this many entries are read one element per load.  By vectors one or two of the
+// work-group's eight waves do all the work, and a wave with a handful of vectors does not find two batch maxima
+// and ranks its elements one by one.  One element per load against vectors, us, bf16: 21 rows of 13 entries with the sum of
+// exponentials 3.9 and 5.3; 960 rows of 61 entries 6.3 and 7.8, of 511 7.2 and 7.7, of 1 001 7.4 and 7.8, of 1 501 even.
+// Greedy, or fp32: 8 rows of 255 entries 3.6 and 3.9, of 511 3.8-3.9 both, longer ones gain from vectors.
+static int single_elements(int dtype, bool sampling) { return dtype == MARS_BF16 && sampling ? 1024 : 512; }
+// 16-byte loads; rows that do not all start on a 16-byte boundary take the form that looks for the first one, or, where
+// they are short, the one of single elements.
 static hipError_t launch_row_reduce(const void* logits, int dtype, long rows, int V, int splits, bool sampling,
                                     float c, Partial* partials, const ClearArgs& clr, hipStream_t stream) {
   const size_t elt = dtype == MARS_BF16 ? 2 : 4;
   const bool even = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && ((static_cast<size_t>(V) * elt) % 16 == 0);
+  if (!even && V <= single_elements(dtype, sampling))
+    return dtype == MARS_BF16 ? launch_row_reduce_t<bf16_t, 1, false>(logits, rows, V, splits, sampling, c, partials, clr, stream)
+                              : launch_row_reduce_t<float, 1, false>(logits, rows, V, splits, sampling, c, partials, clr, stream);
   if (dtype == MARS_BF16)
     return even ? launch_row_reduce_t<bf16_t, 8, false>(logits, rows, V, splits, sampling, c, partials, clr, stream)
                 : launch_row_reduce_t<bf16_t, 8, true>(logits, rows, V, splits, sampling, c, partials, clr, stream);

@@ -443,3 +443,11 @@ def test_arrays_shorter_than_the_loads_of_the_walk(V, N, qdtype):
     if qdtype == "bf16":
         w.draft_probs = f32_to_bf16_bits(w.draft_probs)
     compare(w, allow_small_norm=True)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [505, 511, 512, 513, 520, 1023, 1024, 1025, 1032])
+def test_row_ends_where_rows_get_one_element_per_load(dtype, V):
+    # rows off a 16-byte boundary are read one element per load up to 512 entries (1 024 in bf16 with the sum of
+    # exponentials), by aligned vectors and loose ends above: either side of both lines, at every alignment
+    test_row_ends_hold_the_candidates(dtype, V)
