@@ -134,7 +134,26 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
     // turn the wait for the previous batch into a wait before this one is even issued.
     __builtin_amdgcn_sched_barrier(0);
   };
-  if (nfull > 2) load_full(bufA, 0);
+  // A batch that may be cut short, requested ahead all the same: every lane loads, one past the end of the share from
+  // the share's last vector, and what such a lane has loaded is replaced when it arrives.
+  auto load_edge = [&](Vec<T, EPV>(&buf)[U], int kk) {
+    const int base = v_begin + kk * BV + tid;
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      buf[j].load(vecp, static_cast<unsigned int>(min(base + j * kRowThreads, v_end - 1)));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto trim_edge = [&](Vec<T, EPV>(&buf)[U], int kk) {
+    const int base = v_begin + kk * BV + tid;
+#pragma unroll
+    for (int j = 0; j < U; ++j)
+      if (base + j * kRowThreads >= v_end) buf[j].fill_neg_inf();
+  };
+  // (RAGGED: a share of any length, short ones too.  Their batches one behind the other behind the set-up made a few rows
+  // slower than one element per load had been, which streams: 8 rows of 50 257 bf16 entries, greedy, 4.8 us with
+  // single elements, 5.1 with vectors, 4.9 now.)
+  const bool ahead = RAGGED ? nb > 0 : nfull > 2;
+  if (ahead) { if (RAGGED) load_edge(bufA, 0); else load_full(bufA, 0); }
   // The loose elements at the row's ends, one per lane (every wave asks for them, so that no load stands under a
   // condition; the first wave of the first split looks at them).
   const int tail = RAGGED ? V - head - nvec * EPV : 0;
@@ -217,19 +236,6 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
   __shared__ int sh_done;
   if (tid == 0) sh_done = 0;
 
-  auto load_edge = [&](Vec<T, EPV>(&buf)[U], int kk) {
-    const int base = v_begin + kk * BV + tid;
-#pragma unroll
-    for (int j = 0; j < U; ++j)
-      buf[j].load(vecp, static_cast<unsigned int>(min(base + j * kRowThreads, v_end - 1)));
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  auto trim_edge = [&](Vec<T, EPV>(&buf)[U], int kk) {
-    const int base = v_begin + kk * BV + tid;
-#pragma unroll
-    for (int j = 0; j < U; ++j)
-      if (base + j * kRowThreads >= v_end) buf[j].fill_neg_inf();
-  };
   auto load_tail = [&](Vec<T, EPV>(&buf)[U], int k) {
     const int base = v_begin + k * BV + tid;
 #pragma unroll
@@ -307,11 +313,11 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
   };
 
   // Double-buffered stream over the full batches: the loads of batch k+1 are in flight while
-  // batch k is processed.  The last one to three batches (the ragged one among them) run
+  // batch k is processed.  Short shares of aligned rows run
   // through a plain loop with bounds-checked loads; keeping that part small keeps the kernel's
   // code small, which matters for the cold code every wave runs once at its end.
   int k = 0;
-  if (nfull > 2) {
+  if (ahead) {
     __syncthreads();
     gather_issue();
     for (; k + 2 < nfull; k += 2) {
@@ -321,14 +327,14 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
       process(bufB, k + 1);
     }
     // bufA holds batch k; at most two batches follow it (the last full one, the ragged one).  They are
-    // requested ahead like the others -- every lane loads, one past the end of the share from the share's last
-    // vector, and what such a lane has loaded is replaced when it arrives -- so that a wave does not end its
-    // stream on one or two trips to memory with nothing else in flight.  (The requests stand under no
+    // requested ahead like the others, so that a wave does not end its stream on one or two
+    // trips to memory with nothing else in flight.  (The requests stand under no
     // condition: where no batch follows, the last one is asked for again and not looked at.  Under a
     // condition, even one that is the same for the whole wave, the compiler no longer knows how many loads
     // are in flight and waits for all of them before batch k is processed.)
     const bool more1 = k + 1 < nb, more2 = k + 2 < nb;
     load_edge(bufB, min(k + 1, nb - 1));
+    if (RAGGED) trim_edge(bufA, k);  // (a short share: batch 0 can be the last)
     process(bufA, k);
     load_edge(bufA, min(k + 2, nb - 1));
     if (more1) { trim_edge(bufB, k + 1); process(bufB, k + 1); }
@@ -339,7 +345,7 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
     gather_issue();
   }
 #pragma unroll 1
-  for (; k < nb; ++k) {
+  for (; !RAGGED && k < nb; ++k) {
     load_tail(bufB, k);
     process(bufB, k);
   }

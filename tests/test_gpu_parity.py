@@ -451,3 +451,22 @@ def test_row_ends_where_rows_get_one_element_per_load(dtype, V):
     # rows off a 16-byte boundary are read one element per load up to 512 entries (1 024 in bf16 with the sum of
     # exponentials), by aligned vectors and loose ends above: either side of both lines, at every alignment
     test_row_ends_hold_the_candidates(dtype, V)
+
+
+@pytest.mark.parametrize("dtype,V", [(d, b * (8192 if d == "bf16" else 4096) + e) for d in ("bf16", "f32") for b in (1, 2, 3, 4, 5)
+                                     for e in (-3, 11)])
+def test_unaligned_rows_of_few_batches(dtype, V):
+    # 128 rows, one work-group each: a row is just short of one to five batches of vectors, or just longer, so that the
+    # batches requested ahead are none, one or both of those that follow the first, whole and cut short
+    from oracle import mars_ref
+    from paper_2601_15498_amd import binding as M
+    from tests.gpu_util import assert_stats_match
+    rng = np.random.default_rng(V)
+    z = (rng.integers(-4000, 1000, size=(2, 64, V)) * 2.0 ** -7).astype(np.float32)
+    z[0, np.arange(64), V - 1 - np.arange(64) % 9] = 9.0   # runners-up and ties where the last batch ends
+    z[1, np.arange(64), rng.integers(0, V, 64)] = 9.0
+    bits = f32_to_bf16_bits(z) if dtype == "bf16" else z
+    for T in (0.0, 0.7):
+        st = M.mars_row_stats(at_offset(bits, 1, 0), torch.full((2,), 0.9, device="cuda:0"), T)
+        torch.cuda.synchronize()
+        assert_stats_match(st, mars_ref.row_stats(bits, 0.9, T), T > 0, f"few_batches_{dtype}_V{V}_T{T}")
