@@ -280,14 +280,17 @@ static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int 
   const int V = a.V;
   const bool dense = draft_dtype >= 0;
   const bool vec = whole_groups(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, dense ? a.dprobs : nullptr, a.N, V);
-  // Slices of at most kMaxResident groups of eight per thread stay in registers between passes.
+  // Slices of at most kMaxResident groups of eight per thread stay in registers between passes.  One per thread in the
+  // form for rows at every alignment only (rows of up to 4 089 entries): see tail_sampling_body.
   const int ngroups8 = row_groups(V, vec);
   const int slice8 = ((ngroups8 + a.G - 1) / a.G + kWave - 1) / kWave * kWave;
   const bool resident = slice8 <= kMaxResident * kSamplingThreads, two = slice8 <= 2 * kSamplingThreads;
+  const bool one = !vec && slice8 <= kSamplingThreads;
   const bool qbf = dense && draft_dtype == MARS_BF16;
   const void* kernel;
 #define MARS_PICK2(TT, QQ, VV)                                                                    \
-  (two        ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, 2, VV>)           \
+  (one        ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, VV ? 2 : 1, VV>) \
+   : two      ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, 2, VV>)           \
    : resident ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, kMaxResident, VV>) \
               : reinterpret_cast<const void*>(&tail_sampling_streamed_kernel<TT, QQ, VV>))
 #define MARS_PICK(TT, QQ) (vec ? MARS_PICK2(TT, QQ, true) : MARS_PICK2(TT, QQ, false))

@@ -470,3 +470,10 @@ def test_unaligned_rows_of_few_batches(dtype, V):
         st = M.mars_row_stats(at_offset(bits, 1, 0), torch.full((2,), 0.9, device="cuda:0"), T)
         torch.cuda.synchronize()
         assert_stats_match(st, mars_ref.row_stats(bits, 0.9, T), T > 0, f"few_batches_{dtype}_V{V}_T{T}")
+
+
+@pytest.mark.parametrize("dtype,qdtype", [("bf16", None), ("f32", None), ("bf16", "bf16"), ("f32", "f32"), ("f32", "bf16")])
+@pytest.mark.parametrize("V,k", [(4081, 0), (4088, 1), (4089, 4), (4090, 0), (4096, 7), (4097, 0)])
+def test_slices_of_one_group_per_thread(dtype, qdtype, V, k):
+    # one work-group per request: 512 groups, one for every thread, up to 4 089 entries, a second one for some beyond
+    test_rows_and_draft_rows_at_every_alignment(dtype, qdtype, 3, 9, V, k)
