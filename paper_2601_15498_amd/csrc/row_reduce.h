@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
     // are in flight and waits for all of them before batch k is processed.)
     const bool more1 = k + 1 < nb, more2 = k + 2 < nb;
     load_edge(bufB, min(k + 1, nb - 1));
-    if (RAGGED) trim_edge(bufA, k);  // (a short share: batch 0 can be the last)
+    if (RAGGED && k >= nfull) trim_edge(bufA, k);  // (a short share: batch 0 can be the last)
     process(bufA, k);
     load_edge(bufA, min(k + 2, nb - 1));
     if (more1) { trim_edge(bufB, k + 1); process(bufB, k + 1); }
