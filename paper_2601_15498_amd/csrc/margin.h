@@ -28,6 +28,10 @@ __device__ __forceinline__ int hist_cell(float x, float lo, float hi, float w, i
 // counters: 6.4 us with 60 work-groups of 16 rows and three device-wide atomics per row, 4.7 now (most of it the launch and the rows' way from
 // memory and the way back); 5 200 rows: 75.4 -> 56.3 us per call.
 constexpr int kHistThreads = 1024, kHistLocal = 8192;
+// Clearing the counters in LDS and going over them at the end is a step per 1024 of them: with many counters for each
+// row it costs more than the atomics.  us per call, atomics against LDS: 8 106 counters, 8 rows 6.6 and 7.4, 512 rows 7.9 and 8.6,
+// 960 rows 10.1 and 10.6; 152 counters, 8 rows 6.3 and 6.4, 64 rows 7.0 and 6.5; 1 506 counters, 512 rows 8.3 and 7.8.
+static inline bool count_in_lds(long rows, long ncounters) { return ncounters <= kHistLocal && ncounters <= 8 * rows; }
 constexpr int hist_rows(bool local) { return local ? kHistThreads : kHistThreads / 16; }  // rows of a work-group
 template <bool LOCAL>
 __global__ __launch_bounds__(kHistThreads) void margin_stats_kernel(const Partial* __restrict__ partials, int rows, int N,

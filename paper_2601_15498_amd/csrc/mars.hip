@@ -541,7 +541,7 @@ int mars_margin_stats(const void* logits, int logits_dtype, const float* theta, 
   clr.counters = counts; clr.ncounters = ncounters;
   if (launch_row_reduce(logits, logits_dtype, rows, V, L.splits, false, 0.0f, partials, clr, stream) != hipSuccess)
     return MARS_ERR_HIP;
-  const bool local = ncounters <= kHistLocal;
+  const bool local = count_in_lds(rows, ncounters);
   const dim3 grid(static_cast<unsigned int>((rows + hist_rows(local) - 1) / hist_rows(local))), block(kHistThreads);
   if (local)
     hipLaunchKernelGGL(margin_stats_kernel<true>, grid, block, 0, stream, partials, static_cast<int>(rows), N,

@@ -556,3 +556,12 @@ def test_kept_rows_of_paths_shorter_and_longer_than_are_read_ahead(B, N):
     for i in range(1, N):
         w.draft_tokens[:, i] = w.logits[:, i - 1].argmax(axis=-1)
     compare_ex(w, label=f"kept_rows_B{B}_N{N}")
+
+
+@pytest.mark.parametrize("B,N,bins", [(64, 16, (8176, 3, 3)), (64, 16, (8177, 3, 3)), (1, 19, (40, 50, 52)), (1, 18, (40, 50, 52)),
+                                      (33, 31, (8176, 3, 3))])
+def test_margin_stats_either_side_of_counting_in_lds(B, N, bins):
+    # 8 192 counters (as many as fit) and one more; eight counters per row (152 for 19 rows) and more than that; the most
+    # counters with rows for a second work-group
+    w = make_config(4, B=B, N=N, V=2048, tree={"kind": "chain"})
+    compare_margin(w, ((0.0, 40.0), (0.5, 1.0), (0.0, 1.0)), bins, label=f"margin_lds_{B}x{N}_{bins}")
