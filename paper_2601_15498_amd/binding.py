@@ -115,8 +115,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# (Private names of PyTorch: where one is missing, the public way is taken.)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 # struct mars_row_stat {float z1; int32 id1; float z2; int32 id2; float sum_exp; int32 relax_ok;}  (24 bytes)

@@ -180,6 +180,23 @@ def test_binding_fails_loudly_without_the_library(monkeypatch, tmp_path):
         binding.lib()
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_without_the_private_names_of_torch(monkeypatch, missing):
+    """The stream is asked for by number through two private names of PyTorch; a build without one of
+    them gives the same number the public way."""
+    import importlib.util
+    import types
+
+    import torch
+    from paper_2601_15498_amd import binding
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=1234))
+    spec = importlib.util.spec_from_file_location("binding_without_" + missing, binding.__file__)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    assert module._stream() == 1234
+
+
 def test_source_digest_ignores_comments_and_white_space():
     """bench.py ties a hardware-counter capture to the kernel's code: rewording a comment or
     re-indenting must not change the digest, changing a token must."""
