@@ -1,6 +1,7 @@
 """Parts of the device code that are plain arithmetic and loads, compiled for the host and run on the CPU under
 sanitizers: no GPU needed, and an access out of range ends the test instead of the GPU's work."""
 import os
+import random
 import subprocess
 
 import pytest
@@ -9,11 +10,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
-def run_on_cpu(source, tmp_path, *sanitizers):
+def run_on_cpu(source, tmp_path, *sanitizers, options=(), args=()):
     exe = tmp_path / "main"
     # the host half alone (no kernel is launched); the symbol of the missing device half is any address
     cmd = [HIPCC, "-x", "hip", "--offload-host-only", "-fuse-cuid=none", "-Wl,--defsym=__hip_fatbin=main", "-O1", "-g",
-           "-std=c++17", "-w"]
+           "-std=c++17", "-w", *options]
     for s in sanitizers:
         cmd += ["-Xarch_host", "-fsanitize=" + s, "-Xarch_host", "-fno-sanitize-recover=" + s]
     build = subprocess.run(cmd + ["-o", str(exe), os.path.join(HERE, source)], capture_output=True, text=True)
@@ -22,7 +23,7 @@ def run_on_cpu(source, tmp_path, *sanitizers):
     # (another library may already be preloaded into every process; leak checking needs ptrace)
     env["ASAN_OPTIONS"] = "verify_asan_link_order=0:detect_leaks=0:abort_on_error=0"
     env["UBSAN_OPTIONS"] = "print_stacktrace=1"
-    run = subprocess.run([str(exe)], capture_output=True, text=True, env=env, timeout=600)
+    run = subprocess.run([str(exe), *map(str, args)], capture_output=True, text=True, env=env, timeout=600)
     assert run.returncode == 0, (run.stdout[-1000:], run.stderr[-3000:])
     assert "runtime error" not in run.stderr and "AddressSanitizer" not in run.stderr, run.stderr[-3000:]
     return run.stdout
@@ -32,3 +33,31 @@ def run_on_cpu(source, tmp_path, *sanitizers):
 def test_the_walk_reads_rows_and_nothing_around_them(tmp_path):
     out = run_on_cpu("walk_loads_main.hip", tmp_path, "address", "alignment")
     assert " 0 failed" in out, out
+
+
+# B, N, V, H, sampling; then what the case stands for: bands of slabs, launches, cells shared by two work-groups
+PLANS = [
+    (1, 40, 5003, 128, 0, 1, 1, 0), (1, 100, 60001, 128, 0, 1, 1, 0), (1, 520, 33011, 128, 0, 1, 1, 0),
+    (1, 1000, 32400, 128, 1, 1, 1, 1),        # shared cells in the last column of a single band
+    (2, 1000, 12001, 128, 0, 2, 1, 1), (3, 1000, 12001, 128, 0, 2, 1, 1), (3, 800, 12000, 128, 1, 2, 1, 1),
+    (8, 900, 9001, 128, 0, 3, 1, 0),
+    (16, 60, 151936, 4096, 1, 1, 1, 0), (16, 60, 151936, 4096, 0, 1, 1, 0), (256, 26, 151936, 4096, 0, 2, 1, 1),
+    (1, 1, 304, (1 << 22) + 128, 0, 1, 1, 0),   # beyond what a buffer spans
+    (1, 2, (1 << 25) + 8, 128, 1, 1, 1, 0),
+    (4096, 1024, (1 << 25) + 8, 128, 0, "-", 9, "-"),   # more units than a launch takes
+    (4096, 1024, (1 << 24) + 256, 128, 0, "-", 2, "-"), (1000, 1024, (1 << 27) + 8, 128, 1, "-", 8, "-"),
+]
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_lm_head_work_is_dealt_out_exactly_once(tmp_path):
+    rng = random.Random(7)
+    cases = list(PLANS)
+    for _ in range(300):
+        rows = int(2 ** rng.uniform(0, 14))
+        n = rng.randint(1, min(rows, 1024))
+        sampling = rng.randint(0, 1)
+        v = int(2 ** rng.uniform(3, 18.5)) // (8 if sampling else 1) * (8 if sampling else 1)
+        cases.append((max(1, rows // n), n, max(8, v), 128 * rng.randint(1, 64), sampling, "-", "-", "-"))
+    out = run_on_cpu("lm_plan_main.hip", tmp_path, options=["-no-hip-rt"], args=[x for c in cases for x in c])
+    assert f"{len(cases)} cases, 0 failed" in out, out

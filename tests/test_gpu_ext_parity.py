@@ -565,3 +565,33 @@ def test_margin_stats_either_side_of_counting_in_lds(B, N, bins):
     # counters with rows for a second work-group
     w = make_config(4, B=B, N=N, V=2048, tree={"kind": "chain"})
     compare_margin(w, ((0.0, 40.0), (0.5, 1.0), (0.0, 1.0)), bins, label=f"margin_lds_{B}x{N}_{bins}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("qdtype", [None, "f32", "bf16"])
+@pytest.mark.parametrize("V", [16384, 24576, 24584, 16001, 24001, 24603, 40003])
+def test_sums_worked_out_for_a_partner_are_the_partners_own(dtype, qdtype, V):
+    # As above, in every form of the walk.  100 requests, two work-groups each: slices of two and of three groups per thread and
+    # streamed ones, in whole groups (V a multiple of 8) and at every alignment.  With a spin limit of one poll nearly every
+    # partner is late; what has been worked out in its place must be its very sum: the outputs, normalisers and
+    # probabilities among them, are the same bits as with the default limit, and the oracle's.
+    from paper_2601_15498_amd import binding as M
+    from mars_inputs import f32_to_bf16_bits, make_workload
+    from tests.gpu_util import compare, to_device
+    w = make_workload(f"partner_{dtype}_{qdtype}_V{V}", B=100, N=8, V=V, dtype=dtype, temperature=0.8, dense_q=qdtype is not None,
+                      tree={"kind": "tree", "depth": 3, "max_children": 3}, plant_frac=0.5, seed=V)
+    if qdtype == "bf16":
+        w.draft_probs = f32_to_bf16_bits(w.draft_probs)
+    outs = []
+
+    def run(v):
+        d = to_device(v)
+        for limit in (0, 1):
+            outs.append(M.mars_verify_ex(d["logits"], d["draft_tokens"], d["tree_parent"], d["theta"], v.temperature,
+                                         d["uniforms"], d["draft_probs"], spin_limit=limit))
+        torch.cuda.synchronize()
+        return outs[1]
+    compare(w, cdf_guard=5e-6, allow_small_norm=True, run=run)
+    assert int(M.unpack_diag(outs[0].diag)["residual_passes"].sum()) > 0
+    for key in ("accept_len", "bonus_token", "accept_mask", "path_idx", "decision", "request_status", "stats", "diag"):
+        assert torch.equal(getattr(outs[0], key), getattr(outs[1], key)), key

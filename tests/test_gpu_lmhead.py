@@ -64,11 +64,11 @@ SHAPES = [
     dict(B=4, N=9, H=256, V=5000, tree={"kind": "chain"}),                                   # one slab of 64, ragged tile
     dict(B=2, N=18, H=128, V=100001, tree={"kind": "tree", "depth": 4, "max_children": 3}),  # several tiles per run
     dict(B=16, N=12, H=512, V=33000, tree={"kind": "chain"}),                                # 192 rows: one slab of 192
-    dict(B=7, N=30, H=256, V=20011, tree={"kind": "tree", "depth": 5, "max_children": 4}),   # 210 rows: slabs of 64
+    dict(B=7, N=30, H=256, V=20011, tree={"kind": "tree", "depth": 5, "max_children": 4}),   # 210 rows: two slabs of 128
     dict(B=5, N=60, H=384, V=9001, tree={"kind": "tree", "depth": 6, "max_children": 4}),    # 300 rows, H = 3 * 128
     dict(B=1, N=1, H=128, V=100, tree={"kind": "chain"}),                                    # one row, one ragged tile
     dict(B=3, N=40, H=1024, V=257, tree={"kind": "tree", "depth": 6, "max_children": 3}),    # tile of one entry
-    dict(B=9, N=43, H=256, V=4096, tree={"kind": "tree", "depth": 5, "max_children": 4}),    # 387 rows: slabs of 128 + ragged slab
+    dict(B=9, N=43, H=256, V=4096, tree={"kind": "tree", "depth": 5, "max_children": 4}),    # 387 rows: seven slabs of 64, the last one ragged
     dict(B=2, N=50, H=640, V=70001, tree={"kind": "chain"}),                                 # 100 rows: 137 runs, each from its own slab of the 10 along H
     dict(B=2, N=20, H=256, V=300007, tree={"kind": "chain"}),                                # a vocabulary of 1172 tiles, the last one ragged
 ]
@@ -331,18 +331,17 @@ def test_headline_shape_sampled_requests():
     assert alen.max() >= 2
 
 
-# Slab heights and cells: 64 rows; 128 (a single slab that streams the weight); 192 and 256 with columns two tiles wide
-# and one left over, so that cells are shared between two work-groups; the last slab and the last tile ragged.
+# Slab heights and cells: 64 rows; 128 (a single slab that streams the weight); 192 and 256 with columns two tiles wide and a
+# last one of a single tile, where a work-group goes through cells of two slabs (1 000 rows under sampling: slabs of 128 and
+# cells in the last column that two work-groups share); the last slab and the last tile ragged.
 CELL_SHAPES = [(40, 5003), (100, 60001), (520, 33011), (1000, 32401)]
 
 
-@pytest.mark.parametrize("rows,V", CELL_SHAPES)
-@pytest.mark.parametrize("sign", ["negative", "zeros", "both"])
-@pytest.mark.parametrize("T", [0.0, 1.0])
-def test_integer_logits_with_ties_of_every_sign(rows, V, sign, T):
+def check_integer_logits(B, N, V, sign, T):
     # Small integers: every logit is an exact integer of magnitude below 256, and ties are everywhere.  All
     # logits negative, none positive with many zeros, and both signs: the order of the keys must hold
     # on either side of zero, lowest index first among equals.
+    rows = B * N
     rng = np.random.default_rng(rows + V)
     H = 128
     V -= V % 8 if T else 0
@@ -356,9 +355,8 @@ def test_integer_logits_with_ties_of_every_sign(rows, V, sign, T):
     rest = z.copy()
     rest[np.arange(rows), id1] = -np.inf
     id2 = rest.argmax(axis=1)
-    par = np.arange(-1, rows - 1, dtype=np.int32)[None]
+    par = np.tile(np.arange(-1, N - 1, dtype=np.int32), (B, 1))
     tok = rng.integers(0, V, size=(1, rows)).astype(np.int32)
-    B, N = (1, rows) if rows <= M.MARS_MAX_NODES else (2, rows // 2)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)  # noqa: E731
     hd, wd = dev(h).to(torch.bfloat16).view(B, N, H), dev(w).to(torch.bfloat16)
     th = torch.full((B,), 0.9, device=DEV)
@@ -378,3 +376,56 @@ def test_integer_logits_with_ties_of_every_sign(rows, V, sign, T):
     st = {k: v.cpu().numpy() for k, v in M.unpack_stats(out.stats).items()}
     assert np.array_equal(st["id1"], id1) and np.array_equal(st["id2"], id2)
     assert np.array_equal(st["z1"], z1) and np.array_equal(st["z2"], rest[np.arange(rows), id2])
+
+
+@pytest.mark.parametrize("rows,V", CELL_SHAPES)
+@pytest.mark.parametrize("sign", ["negative", "zeros", "both"])
+@pytest.mark.parametrize("T", [0.0, 1.0])
+def test_integer_logits_with_ties_of_every_sign(rows, V, sign, T):
+    check_integer_logits(1, rows, V, sign, T)
+
+
+# Two bands of slabs, and cells at the bands' ends that two work-groups share: 16 slabs of 128, 16 of 192, and under
+# sampling 19 of 128 in bands of 10 and 9, and 16 of 192.
+@pytest.mark.parametrize("B,N,V,T", [(2, 1000, 12001, 0.0), (3, 1000, 12001, 0.0), (3, 800, 12000, 1.0), (3, 1000, 12000, 1.0)])
+@pytest.mark.parametrize("sign", ["negative", "both"])
+def test_integer_logits_over_two_bands_of_slabs(B, N, V, T, sign):
+    check_integer_logits(B, N, V, sign, T)
+
+
+@pytest.mark.parametrize("T", [0.0, 1.0])
+@pytest.mark.parametrize("N,V,H", [(1, 304, (1 << 22) + 128), (3, 1000, (1 << 22) + 128), (2, (1 << 25) + 8, 128)])
+def test_sizes_beyond_what_a_buffer_spans(N, V, H, T):
+    # the form that reads its operands and writes its logits through pointers: rows of more than 8 MiB, a vocabulary beyond
+    # 2^25.  Small integers again, with few hidden elements that are not zero, at both ends of H among them.
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N + V)
+    rng = np.random.default_rng(V)
+    at = np.unique(np.concatenate([[0, 1, H - 2, H - 1], rng.integers(0, H, 60)]))
+    h = torch.zeros((1, N, H), dtype=torch.bfloat16, device=DEV)
+    some = torch.from_numpy(rng.integers(-1, 2, size=(N, at.size)).astype(np.float32))
+    h[0][:, torch.from_numpy(at).to(DEV)] = some.to(DEV).to(torch.bfloat16)
+    w = torch.randint(-2, 3, (V, H), dtype=torch.int8, device=DEV, generator=g).to(torch.bfloat16)
+    z = (some.to(DEV) @ w[:, torch.from_numpy(at).to(DEV)].float().T).double().cpu()   # (whole numbers: exact in fp32)
+    assert z.abs().max() < 256
+    par = torch.arange(-1, N - 1, dtype=torch.int32, device=DEV)[None].contiguous()
+    tok = torch.full((1, N), 5, dtype=torch.int32, device=DEV)
+    th = torch.full((1,), 0.9, device=DEV)
+    say(f"[case] lmhead pointers: N={N} V={V} H={H} T={T}")
+    if T:
+        out, logits = M.mars_lmhead_verify_sampling(h, w, tok, par, th, T, torch.full((1, N + 1), 0.5, device=DEV))
+        torch.cuda.synchronize()
+        assert torch.equal(logits.view(torch.bfloat16)[0].cpu().double(), z)
+        s = M.unpack_stats(out.stats)["sum_exp"].cpu().double()
+        # (1e-5 as above, and half a unit in the last place for every tile a lane adds to its sum: the tiles of a column)
+        bound = 1e-5 + 2.0 ** -24 * (V / 256 / 256 + 1)
+        assert (s / (z - z.max(dim=1, keepdim=True)[0]).exp().sum(dim=1) - 1).abs().max() <= bound
+    else:
+        out = M.mars_lmhead_verify(h, w, tok, par, th)
+        torch.cuda.synchronize()
+    zn = z.numpy()
+    id1 = zn.argmax(axis=1)
+    st = {k: v.cpu().numpy() for k, v in M.unpack_stats(out.stats).items()}
+    assert np.array_equal(st["id1"], id1) and np.array_equal(st["z1"], zn.max(axis=1))
+    zn[np.arange(N), id1] = -np.inf
+    assert np.array_equal(st["id2"], zn.argmax(axis=1)) and np.array_equal(st["z2"], zn.max(axis=1))

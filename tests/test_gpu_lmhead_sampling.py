@@ -81,7 +81,7 @@ SHAPES = [
     dict(B=4, N=9, H=256, V=5000, tree={"kind": "chain"}),                                   # one slab of 64, ragged tile
     dict(B=3, N=24, H=512, V=20000, tree={"kind": "tree", "depth": 4, "max_children": 4}),   # several tiles per run
     dict(B=16, N=12, H=512, V=33000, tree={"kind": "chain"}),                                # 192 rows: one slab of 192
-    dict(B=9, N=43, H=256, V=4096, tree={"kind": "tree", "depth": 5, "max_children": 4}),    # 387 rows: slabs of 128, ragged slab
+    dict(B=9, N=43, H=256, V=4096, tree={"kind": "tree", "depth": 5, "max_children": 4}),    # 387 rows: seven slabs of 64, the last one ragged
     dict(B=1, N=1, H=128, V=104, tree={"kind": "chain"}),                                    # one row, one ragged tile
     dict(B=2, N=20, H=256, V=300008, tree={"kind": "chain"}),                                # 1172 tiles, the last one ragged
 ]

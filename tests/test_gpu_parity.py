@@ -477,3 +477,13 @@ def test_unaligned_rows_of_few_batches(dtype, V):
 def test_slices_of_one_group_per_thread(dtype, qdtype, V, k):
     # one work-group per request: 512 groups, one for every thread, up to 4 089 entries, a second one for some beyond
     test_rows_and_draft_rows_at_every_alignment(dtype, qdtype, 3, 9, V, k)
+
+
+@pytest.mark.parametrize("dtype,dense,V", [("bf16", False, 40003), ("f32", True, 65547), ("bf16", True, 98331), ("f32", False, 98331),
+                                           ("bf16", False, 147467), ("f32", True, 147467)])
+def test_streamed_passes_of_every_length_at_every_alignment(dtype, dense, V):
+    # the same in the form for rows at every alignment, whose batches are half as long: 3 to 10 steps of one group with draft
+    # probabilities, of two without
+    w = make_workload(f"stream_odd_{dtype}_{dense}_V{V}", B=128, N=3, V=V, dtype=dtype, temperature=0.9, dense_q=dense,
+                      tree={"kind": "tree", "depth": 1, "max_children": 2}, plant_frac=0.5, seed=V)
+    compare(w, cdf_guard=5e-6, allow_small_norm=True)
