@@ -318,6 +318,16 @@ static int launch_groups(int G, int KB) {
   return G;
 }
 
+static hipError_t launch_keep(int K, const int32_t* out_len, const int32_t* path, int B, int N, int32_t* keep_rows,
+                              int32_t* keep_offsets, hipStream_t stream) {
+  const dim3 grid(static_cast<unsigned int>(K)), block(kKeepThreads);
+  if (N > 1)
+    hipLaunchKernelGGL(compact_keep_kernel<kKeepAhead>, grid, block, 0, stream, out_len, path, B, N, keep_rows, keep_offsets);
+  else
+    hipLaunchKernelGGL(compact_keep_kernel<0>, grid, block, 0, stream, out_len, path, B, N, keep_rows, keep_offsets);
+  return hipGetLastError();
+}
+
 static bool lm_sizes_ok(int B, int N, int V, int H, int K) {
   return sizes_ok(B, N, V, K) && H >= kLmBK * kLmDepth && H % (kLmBK * kLmDepth) == 0 && static_cast<long>(B) * N <= (1L << 22);
 }
@@ -481,9 +491,7 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   auto finish = [&]() -> int {
     if (hipGetLastError() != hipSuccess) return MARS_ERR_HIP;
     if (!keep_rows) return MARS_OK;
-    hipLaunchKernelGGL(compact_keep_kernel, dim3(static_cast<unsigned int>(K)), dim3(kKeepThreads), 0, stream,
-                       out_len, path_idx, B, N, keep_rows, keep_offsets);
-    return hipGetLastError() == hipSuccess ? MARS_OK : MARS_ERR_HIP;
+    return launch_keep(K, out_len, path_idx, B, N, keep_rows, keep_offsets, stream) == hipSuccess ? MARS_OK : MARS_ERR_HIP;
   };
 
   if (!sampling) {
@@ -614,9 +622,7 @@ int mars_lmhead_verify(const void* hidden, const void* weight, int H, const int3
   hipLaunchKernelGGL(tail_greedy_kernel, dim3(static_cast<unsigned int>(K * B)), dim3(kGreedyThreads), 0, stream, a);
   if (hipGetLastError() != hipSuccess) return MARS_ERR_HIP;
   if (!keep_rows) return MARS_OK;
-  hipLaunchKernelGGL(compact_keep_kernel, dim3(static_cast<unsigned int>(K)), dim3(kKeepThreads), 0, stream, out_len,
-                     path_idx, B, N, keep_rows, keep_offsets);
-  return hipGetLastError() == hipSuccess ? MARS_OK : MARS_ERR_HIP;
+  return launch_keep(K, out_len, path_idx, B, N, keep_rows, keep_offsets, stream) == hipSuccess ? MARS_OK : MARS_ERR_HIP;
 }
 
 int mars_lmhead_verify_sampling(const void* hidden, const void* weight, int H, const int32_t* draft_tokens,
@@ -690,9 +696,7 @@ int mars_lmhead_verify_sampling(const void* hidden, const void* weight, int H, c
   if (launch_sampling_tail(a, MARS_BF16, dense ? draft_dtype : -1, stream) != hipSuccess) return MARS_ERR_HIP;
   if (hipGetLastError() != hipSuccess) return MARS_ERR_HIP;
   if (!keep_rows) return MARS_OK;
-  hipLaunchKernelGGL(compact_keep_kernel, dim3(static_cast<unsigned int>(K)), dim3(kKeepThreads), 0, stream, out_len,
-                     path_idx, B, N, keep_rows, keep_offsets);
-  return hipGetLastError() == hipSuccess ? MARS_OK : MARS_ERR_HIP;
+  return launch_keep(K, out_len, path_idx, B, N, keep_rows, keep_offsets, stream) == hipSuccess ? MARS_OK : MARS_ERR_HIP;
 }
 
 }  // extern "C"

@@ -1387,11 +1387,13 @@ __global__ __launch_bounds__(kStreamingThreads) void tail_sampling_streamed_kern
 // exactly these), with the exclusive prefix sums of their counts.  One work-group per set of Bd
 // requests (per threshold of a sweep); unused entries of keep_rows are -1.
 //
-// The kernel is one trip to memory: the first kKeepAhead path entries of a request go out with its length, before
+// The kernel is one trip to memory: the first AHEAD path entries of a request go out with its length, before
 // anybody knows how many of them count (read one after the other behind the length they cost a trip each: 64
-// chains of eight drafts took 33.9 us per call, now 33.0; two of six 13.8, now 12.4).
+// chains of eight drafts took 33.9 us per call, now 33.0; two of six 13.8, now 12.4).  Where nothing is accepted they cost 0.1-0.2 us
+// in vain; requests of a single node have no path to read: AHEAD = 0 (300 of them 13.2 us per call with eight, 12.8).
 constexpr int kKeepThreads = 256;
 constexpr int kKeepAhead = 8;
+template <int AHEAD>
 __global__ __launch_bounds__(kKeepThreads) void compact_keep_kernel(const int32_t* __restrict__ out_len,
                                                                     const int32_t* __restrict__ path, int Bd, int N,
                                                                     int32_t* __restrict__ keep_rows,
@@ -1410,9 +1412,9 @@ __global__ __launch_bounds__(kKeepThreads) void compact_keep_kernel(const int32_
   for (int b0 = 0; b0 < Bd; b0 += NT) {
     const int b = b0 + tid;
     const int mine = b < Bd ? len[b] : 0;
-    int ahead[kKeepAhead];
+    int ahead[AHEAD ? AHEAD : 1];
 #pragma unroll
-    for (int j = 0; j < kKeepAhead; ++j) ahead[j] = pth[static_cast<size_t>(min(b, Bd - 1)) * N + min(j, N - 1)];
+    for (int j = 0; j < AHEAD; ++j) ahead[j] = pth[static_cast<size_t>(min(b, Bd - 1)) * N + min(j, N - 1)];
     // inclusive scan inside the wave, then across the waves of the work-group
     int incl = mine;
 #pragma unroll
@@ -1429,9 +1431,9 @@ __global__ __launch_bounds__(kKeepThreads) void compact_keep_kernel(const int32_
       offs[b] = start;
       rows[start] = b * N;  // the root's row
 #pragma unroll
-      for (int j = 0; j < kKeepAhead; ++j)
+      for (int j = 0; j < AHEAD; ++j)
         if (j + 1 < mine) rows[start + j + 1] = b * N + ahead[j];
-      for (int j = kKeepAhead + 1; j < mine; ++j) rows[start + j] = b * N + pth[static_cast<size_t>(b) * N + j - 1];
+      for (int j = AHEAD + 1; j < mine; ++j) rows[start + j] = b * N + pth[static_cast<size_t>(b) * N + j - 1];
     }
     __syncthreads();
     if (tid == NT - 1) sh_carry = before + incl;

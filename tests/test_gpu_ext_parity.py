@@ -595,3 +595,9 @@ def test_sums_worked_out_for_a_partner_are_the_partners_own(dtype, qdtype, V):
     assert int(M.unpack_diag(outs[0].diag)["residual_passes"].sum()) > 0
     for key in ("accept_len", "bonus_token", "accept_mask", "path_idx", "decision", "request_status", "stats", "diag"):
         assert torch.equal(getattr(outs[0], key), getattr(outs[1], key)), key
+
+
+@pytest.mark.parametrize("B", [1, 64, 300, 512])
+def test_kept_rows_of_requests_of_a_single_node(B):
+    w = make_config(4, B=B, N=1, V=2048, tree={"kind": "chain"}, temperature=0.0)
+    compare_ex(w, label=f"kept_rows_single_B{B}")
