@@ -197,8 +197,8 @@ static LmPlan lm_plan(long rows, int V, int H, bool sampling) {
   g.width = (g.units + kComputeUnits - 1) / kComputeUnits;
   if (g.width > p.tiles_n) g.width = p.tiles_n;
   const int columns = (p.tiles_n + g.width - 1) / g.width;
-  g.split = g.slabs > 1 && p.tiles_n % g.width != 0;
-  g.parts = p.parts = g.split ? 2 * columns : columns;
+  g.split = g.slabs == 1 || p.tiles_n % g.width == 0 ? columns : bands == 1 ? columns - 1 : 0;
+  g.parts = p.parts = 2 * columns - g.split;
   return p;
 }
 

@@ -96,6 +96,7 @@ static int check(int B, int N, int V, int H, int sampling, const std::string& ba
     if ((l.cleared != 0) != (sampling && next_row == 0)) return fail("words cleared other than once", B, N, V, H, sampling);
     if (static_cast<long>(g.slabs) * g.tiles_n != g.units) return fail("units", B, N, V, H, sampling);
     const int columns = (g.tiles_n + g.width - 1) / g.width;
+    if (g.parts > (g.slabs <= g.band ? columns + 1 : 2 * columns)) return fail("empty partial results", B, N, V, H, sampling);
     if (static_cast<size_t>(rows) * g.parts * sizeof(Partial) > bytes) return fail("workspace", B, N, V, H, sampling);
     std::vector<unsigned char> written(static_cast<size_t>(g.slabs) * g.parts);
     std::vector<int> tiles(static_cast<size_t>(g.slabs) * columns);
@@ -114,12 +115,13 @@ static int check(int B, int N, int V, int H, int sampling, const std::string& ba
         // (two pieces of one cell do not overlap: one is its beginning, the other its end, and the lengths add up)
         tiles[static_cast<size_t>(c.slab) * columns + c.column] += c.n;
         unsigned char* w = &written[static_cast<size_t>(c.slab) * g.parts];
-        if (!g.split) {
+        if (c.column < g.split) {
           if (!c.begins || !c.ends) return fail("a shared cell without a place for both", B, N, V, H, sampling);
           ++w[c.column];
         } else {
-          ++w[2 * c.column + (c.begins ? 0 : 1)];
-          if (c.begins && c.ends) ++w[2 * c.column + 1];
+          w += 2 * c.column - g.split;
+          ++w[c.begins ? 0 : 1];
+          if (c.begins && c.ends) ++w[1];
           any_shared |= !(c.begins && c.ends);
         }
         unit += c.n;
