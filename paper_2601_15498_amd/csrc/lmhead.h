@@ -13,10 +13,10 @@
 // 128 entries is taken inside the lane, a running pair per row is carried across the tiles of a
 // (slab, column) cell, and the two halves of a wave and the two waves that share a row meet at its end.
 //
-// What bounds it: the matrix cores and the power they draw.  6 656 rows x 4096 x 151 936: 6.06-6.11 ms =
-// 1.36 PFLOP/s (the library's product alone 1.48; 8192^3: 1.40), the clock at 1.65 GHz of 2.4 and the matrix
-// units busy 3/4 of the time; before (192 rows at most, keys in 32-bit integers, unequal shares) 6.76-6.81 ms.
-// 960 rows, sampling form: 1 059-1 070 us (before 1 133-1 160).  60 rows: bound by the weight, 1.24 GB in 203 us =
+// What bounds it: the matrix cores, the power they draw and the data moved per product.  6 656 rows x 4096 x 151 936: 6.00-6.12 ms =
+// 1.35-1.38 PFLOP/s (the library's product alone 1.47; 8192^3: 1.38-1.40), the clock at 1.72 GHz of 2.4 and the matrix
+// units busy 3/4 of the time; before (192 rows at most, keys in 32-bit integers, unequal shares) 6.76-6.87 ms.
+// 960 rows, sampling form: 1 052-1 065 us (before 1 133-1 160).  60 rows: bound by the weight, 1.24 GB in 203-205 us =
 // 6.1 TB/s, and the per-request kernel behind it.
 #pragma once
 

@@ -173,7 +173,7 @@ static LmPlan lm_plan(long rows, int V, int H, bool sampling) {
   // H = 4096, greedy form: 49-51 us with 64 rows, 61-63 with 128, 80-83 with 192, 100-104 with 256; with two slabs
   // of 64 and a work-group on (nearly) every compute unit the weight's way from memory bounds it, at
   // 78 us (128 rows, one slab: 75); with one slab both heights wait for the weight (60 rows: 215.5 us per call
-  // with 64, 218.2 with 128).  The sampling form does not fit the registers with 256.
+  // with 64, 218.2 with 128).  The sampling form does not fit the registers with 256.  (Both forms and every H go by these figures.)
   static const struct { int bm; double cost; } kHeights[] = {{64, 0.60}, {128, 0.75}, {192, 1.0}, {256, 1.235}};
   double best = -1.0;
   p.bm = 64;

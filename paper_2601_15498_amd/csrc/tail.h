@@ -701,9 +701,9 @@ constexpr int kMaxResident = 3;            // groups of eight elements a thread 
 
 // RES: every slice is at most RES groups per thread and stays in registers (decided by the host from G and V), 0: it is
 // streamed.  Two of them where they are enough -- few requests, or a small vocabulary -- carry two thirds of the
-// loads, exponentials, registers and code of three, and the walk is bound by what a wave has to issue and to fetch: one
-// tree of 60 nodes 22.6 -> 21.9 us per call, 8 trees over 100 001 entries 28.0 -> 26.5, 3 over 3 001 with dense
-// probabilities 21.2 -> 19.4.  One where one is enough and rows begin anywhere, which with two had become slower than
+// loads, exponentials, registers and code of three, and the walk is bound by what a wave has to issue and to fetch: 8
+// trees over 100 001 entries 28.0 -> 26.5 us per call, 3 over 3 001 with dense probabilities 21.2 -> 19.4, one tree of 60 nodes
+// over 151 936 3 % at most.  One where one is enough and rows begin anywhere, which with two had become slower than
 // loads of single elements in three, the masks being the more code: one row of 255 fp32 entries 11.6 us per call with single
 // elements, 12.9 with two groups, 12.0 with one; 21 rows of 255 15.9, 16.5, 15.0; 960 rows of 13 19.5, 21.3, 19.0.
 // VEC: every group of eight elements is whole and aligned (RowView).
