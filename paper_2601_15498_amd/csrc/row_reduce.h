@@ -331,12 +331,14 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
     // trips to memory with nothing else in flight.  (The requests stand under no
     // condition: where no batch follows, the last one is asked for again and not looked at.  Under a
     // condition, even one that is the same for the whole wave, the compiler no longer knows how many loads
-    // are in flight and waits for all of them before batch k is processed.)
+    // are in flight and waits for all of them before batch k is processed.  RAGGED, where a share can be a single batch: what
+    // is asked for again is the share's last vector alone, by every lane -- 3 000 rows of 4 087 fp32 entries, greedy, 18.4 us
+    // with the batch asked for three times, 16.5 so.)
     const bool more1 = k + 1 < nb, more2 = k + 2 < nb;
-    load_edge(bufB, min(k + 1, nb - 1));
+    load_edge(bufB, RAGGED ? k + 1 : min(k + 1, nb - 1));
     if (RAGGED && k >= nfull) trim_edge(bufA, k);  // (a short share: batch 0 can be the last)
     process(bufA, k);
-    load_edge(bufA, min(k + 2, nb - 1));
+    load_edge(bufA, RAGGED ? k + 2 : min(k + 2, nb - 1));
     if (more1) { trim_edge(bufB, k + 1); process(bufB, k + 1); }
     if (more2) { trim_edge(bufA, k + 2); process(bufA, k + 2); }
     k = nb;
