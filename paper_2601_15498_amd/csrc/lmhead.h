@@ -16,8 +16,17 @@
 // What bounds it: the matrix cores, the power they draw and the data moved per product.  6 656 rows x 4096 x 151 936: 6.00-6.12 ms =
 // 1.35-1.38 PFLOP/s (the library's product alone 1.47; 8192^3: 1.38-1.40), the clock at 1.72 GHz of 2.4 and the matrix
 // units busy 3/4 of the time; before (192 rows at most, keys in 32-bit integers, unequal shares) 6.76-6.87 ms.
-// 960 rows, sampling form: 1 052-1 065 us (before 1 133-1 160).  60 rows: bound by the weight, 1.24 GB in 203-205 us =
-// 6.1 TB/s, and the per-request kernel behind it.
+// 960 rows, sampling form: 1 052-1 065 us (before 1 133-1 160).
+//
+// Few rows, or few units (a small vocabulary), are not bound by the matrix cores but by the weight's way through the chip, and take
+// a second form, the ring (lmhead_ring_kernel): tiles of 64, 128 or 256 entries, so that there are enough units for
+// the chip, and operands that go from memory straight to LDS (buffer_load ... lds), STAGES - 1 steps ahead of their use, without
+// passing through registers.  With operands one step in LDS and one in registers a step of 64 rows took 0.77 us whatever its tile, a
+// trip to memory for every two steps.  A weight that is read once and does not fit the Infinity Cache is read
+// with the non-temporal hint: 6.9 TB/s instead of 6.2.  60 rows x 4096 x 151 936: bound by the weight, 1.24 GB in 178-180 us = 6.9
+// TB/s (through registers 203-205), and the per-request kernel behind it; 56 x 4096 x 2 250 45 -> 22 us per call.  Many
+// rows stay with the first form: two stages of 64 KB are all that fits LDS there, and one step of lead is too little (960
+// rows, 192 to a slab, greedy: 1 108 us against 940; rows of 64 bytes, four stages: 1 044).
 #pragma once
 
 #include <type_traits>
@@ -68,7 +77,14 @@ __device__ __forceinline__ void lm_acc8(const f32x16_t& block, float (&x)[8]) {
         "a"(block[FIRST + 5]), "a"(block[FIRST + 6]), "a"(block[FIRST + 7]));
 }
 // Sixteen of them, rounded to bf16 in pairs.
+template <bool BY_ASM>
 __device__ __forceinline__ void lm_rounded(const f32x16_t& block, uint32_t (&w)[8]) {
+  if constexpr (!BY_ASM) {
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+      w[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{block[2 * p], block[2 * p + 1]}, bf16x2_t));
+    return;
+  }
   float x[8];
   lm_acc8<0>(block, x);
 #pragma unroll
@@ -81,6 +97,12 @@ __device__ __forceinline__ void lm_results_ready() {
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // 32 wait states; an instruction of 16 passes asks for 19
   __builtin_amdgcn_sched_barrier(0);
+}
+// What a wave has written to LDS for its own lanes is read behind this, and not written again before it has been: LDS
+// operations of a wave are performed in order, the compiler is kept from changing theirs.
+__device__ __forceinline__ void lm_wave_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
 }
 // k1 >= k2, the two largest so far.
 __device__ __forceinline__ void lm_top2_step(int& k1, int& k2, int key) {
@@ -106,6 +128,18 @@ template <> struct LmRows<true> {
   __device__ __forceinline__ u32x4 load(int i, int k) const {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, static_cast<int>(off + i * pitch), k * 2, 0));
   }
+  // The same 16 bytes of every lane to LDS, lane after lane from byte address `lds` on, past the registers.  (Written by hand:
+  // behind the compiler's own form of this load it has every read of LDS wait for all that is in flight.  The wait states:
+  // an address word can come from a vector instruction just before.)
+  template <bool ONCE>
+  __device__ __forceinline__ void to_lds(int i, int k, unsigned int lds) const {
+    if (ONCE)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                   :: "s"(lds), "v"(off + i * pitch), "s"(rows), "s"(k * 2) : "memory", "m0");
+    else
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                   :: "s"(lds), "v"(off + i * pitch), "s"(rows), "s"(k * 2) : "memory", "m0");
+  }
 };
 template <> struct LmRows<false> {
   const bf16_t* base;
@@ -117,6 +151,7 @@ template <> struct LmRows<false> {
   __device__ __forceinline__ u32x4 load(int i, int k) const {
     return *reinterpret_cast<const u32x4*>(base + static_cast<size_t>(min(last, first + i * 32)) * H + chunk + k);
   }
+  template <bool ONCE> __device__ __forceinline__ void to_lds(int, int, unsigned int) const {}  // (the ring's rows are buffers)
 };
 // What a work-group does: `width` (slab, tile) units in a row, of an order that runs through bands of a few
 // slabs, in a band through columns of `width` tiles, in a column slab by slab.  A (slab, column) cell is then one
@@ -157,6 +192,18 @@ __device__ __forceinline__ LmCell lm_cell(int unit, int unit_end, int slabs, int
   c.ends = t + c.n == tiles;
   return c;
 }
+// Where chunk `chunk` of a row stands among the row's eight places in the ring (and which chunk stands at place `chunk`:
+// the same).  Sixteen rows in a row have a chunk on sixteen different groups of four banks.
+__device__ __forceinline__ int lm_place(int row, int chunk) { return chunk ^ ((row >> 1) & (kLmChunks - 1)); }
+__device__ __forceinline__ unsigned int lm_lds_address(const void* p) {
+  return static_cast<unsigned int>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)p));
+}
+// All but the last LEFT loads of this wave have arrived in LDS and all its reads in registers; so have the other waves'.
+template <int LEFT>
+__device__ __forceinline__ void lm_ring_turn() {
+  static_assert(LEFT >= 0 && LEFT < 64, "the counter's range");
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(LEFT) : "memory");
+}
 template <int n>
 __device__ __forceinline__ void lm_store_lds(const u32x4 (&g)[n], bf16_t* first) {
 #pragma unroll
@@ -177,21 +224,26 @@ __device__ __forceinline__ void lm_load_frags(u32x4 (&f)[n], const bf16_t* first
 // parts: partial results per row -- one per column, or two where a cell can belong to two work-groups (the second
 // one empty where it does not).  (Two per column throughout made the walk behind 960 rows merge 100 instead of 51: 28.5 us
 // there, 32.1 with 100.)
-template <int BM, bool SAMPLING, bool WIDE = false>
-__global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t* __restrict__ hidden,
-                                                                   const bf16_t* __restrict__ weight, int M, int V,
-                                                                   int H, LmGrid grid, Partial* __restrict__ partials,
-                                                                   bf16_t* __restrict__ logits_out, float c, LmClear clear) {
+template <int BM, int BN, int STAGES, bool SAMPLING, bool WIDE, bool ONCE>
+__device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, const bf16_t* __restrict__ weight, int M, int V,
+                                            int H, LmGrid grid, Partial* __restrict__ partials,
+                                            bf16_t* __restrict__ logits_out, float c, LmClear clear) {
+  constexpr bool RING = STAGES > 0;
+  constexpr bool BY_ASM = !RING;  // (the ring's forms have the registers)
   constexpr int WM = BM / 2;      // hidden-state rows per wave
+  constexpr int WN = BN / 2;      // vocabulary entries per wave
   constexpr int IB = WM / 32;     // 32-row blocks per wave
-  constexpr int JB = 4;           // 32-entry vocabulary blocks per wave (128 entries)
-  constexpr int A_LOADS = BM * kLmChunks / kLmThreads;      // 16-byte loads per thread and slab, hidden states
-  constexpr int W_LOADS = kLmBN * kLmChunks / kLmThreads;   // ... weight rows
-  static_assert(BM % 64 == 0 && BM >= 64 && BM <= kLmMaxBM, "slab height");
+  constexpr int JB = WN / 32;     // 32-entry vocabulary blocks per wave
+  constexpr int A_LOADS = BM * kLmChunks / kLmThreads;   // 16-byte loads per thread and slab, hidden states
+  constexpr int W_LOADS = BN * kLmChunks / kLmThreads;   // ... weight rows
+  static_assert(BM % 64 == 0 && BM >= 64 && BM <= kLmMaxBM && BN % 64 == 0 && BN >= 64 && BN <= kLmBN, "slab and tile");
 
-  __shared__ __attribute__((aligned(16))) bf16_t sh_a[2][BM][kLmStride];
-  __shared__ __attribute__((aligned(16))) bf16_t sh_w[2][kLmBN][kLmStride];
+  __shared__ __attribute__((aligned(16))) bf16_t sh_a[RING ? 1 : 2][RING ? 1 : BM][kLmStride];
+  __shared__ __attribute__((aligned(16))) bf16_t sh_w[RING ? 1 : 2][RING ? 1 : BN][kLmStride];
+  __shared__ __attribute__((aligned(1024))) bf16_t sh_ring[RING ? STAGES : 1][RING ? BM + BN : 1][kLmBK];
 
+  // The ring: a block of 32 rows x 32 logits of each wave, on its way out.
+  __shared__ __attribute__((aligned(16))) bf16_t sh_out[SAMPLING && RING ? kLmThreads / kWave : 1][32][32];
   // Results of the other wave column, on their way to the one that writes them.
   __shared__ unsigned long long sh_key[2][IB][32][2];
   __shared__ float sh_sum[SAMPLING ? 2 : 1][SAMPLING ? IB : 1][32][2];
@@ -214,14 +266,15 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
   const int l32 = lane & 31, half = lane >> 5;
   const int KT = H / kLmBK;
 
-  // What this thread stages per slab of 64: 16-byte chunk tid%8 of rows tid/8, tid/8 + 32, ... of the tile.
-  const int srow = tid / kLmChunks, schunk = (tid % kLmChunks) * 8;
+  // What this thread stages per slab of 64: a 16-byte chunk of rows tid/8, tid/8 + 32, ... of the tile -- chunk tid%8, or, in
+  // the ring, the one that belongs at place tid%8 of its row (lm_place).
+  const int srow = tid / kLmChunks, schunk = (RING ? lm_place(srow, tid % kLmChunks) : tid % kLmChunks) * 8;
   using Rows = LmRows<!WIDE>;
   auto slab_rows = [&](int slab) {
     return Rows(hidden + static_cast<size_t>(slab) * BM * H, min(BM, M - slab * BM), H, srow, schunk);
   };
   auto tile_rows = [&](int tile) {
-    return Rows(weight + static_cast<size_t>(tile) * kLmBN * H, min(kLmBN, V - tile * kLmBN), H, srow, schunk);
+    return Rows(weight + static_cast<size_t>(tile) * BN * H, min(BN, V - tile * BN), H, srow, schunk);
   };
 
   unsigned long long best1[IB], best2[IB];
@@ -270,22 +323,65 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
           a_rows = slab_rows(l_cell.slab);
         }
         w_rows = tile_rows(l_cell.tile + l_at);
+      } else if (RING) {  // past the last unit: nothing is fetched
+        a_rows = Rows(hidden, 0, H, srow, schunk);
+        w_rows = Rows(weight, 0, H, srow, schunk);
       }
     }
   };
 
-  request();
-  advance();
-  lm_store_lds<A_LOADS>(ga, &sh_a[0][srow][schunk]);
-  lm_store_lds<W_LOADS>(gw, &sh_w[0][srow][schunk]);
-  request();
-  advance();
-  __syncthreads();
+  // The ring: a step's operands go from memory straight to LDS, STAGES - 1 steps ahead of their use, and its fragments
+  // from there to registers one step ahead.
+  constexpr int kQuarters = kLmBK / 16;
+  constexpr unsigned int kStageBytes = static_cast<unsigned int>(RING ? BM + BN : 0) * kLmBK * 2;
+  const unsigned int ring_base = lm_lds_address(&sh_ring[0][0][0]);
+  unsigned int stage = 0;  // bytes: the stage of the step whose fragments are in registers
+  const unsigned int wave_rows = static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(wave)) * 1024u;  // bytes: eight rows of 128
+  auto issue = [&](unsigned int to) {
+    const unsigned int lds = ring_base + to + wave_rows;
+    if constexpr (RING) {
+#pragma unroll
+      for (int i = 0; i < A_LOADS; ++i) a_rows.template to_lds<false>(i, l_kp * kLmBK, lds + i * 4096);
+#pragma unroll
+      for (int i = 0; i < W_LOADS; ++i) w_rows.template to_lds<ONCE>(i, l_kp * kLmBK, lds + (A_LOADS + i) * 4096);
+    }
+  };
+  u32x4 rw[RING ? 2 : 1][kQuarters][JB], rh[RING ? 2 : 1][kQuarters][IB];
+  int place[kQuarters];  // of this lane's chunk in every quarter, in elements
+#pragma unroll
+  for (int ks = 0; ks < kQuarters; ++ks) place[ks] = l32 * kLmBK + lm_place(l32, 2 * ks + half) * 8;
+  auto read_stage = [&](u32x4(&w)[kQuarters][JB], u32x4(&h)[kQuarters][IB], unsigned int from) {
+    const bf16_t* at = &sh_ring[0][0][0] + from / 2;
+#pragma unroll
+    for (int ks = 0; ks < kQuarters; ++ks) {
+#pragma unroll
+      for (int r = 0; r < IB; ++r) h[ks][r] = *reinterpret_cast<const u32x4*>(at + (wm * WM + r * 32) * kLmBK + place[ks]);
+#pragma unroll
+      for (int r = 0; r < JB; ++r) w[ks][r] = *reinterpret_cast<const u32x4*>(at + (BM + wn * WN + r * 32) * kLmBK + place[ks]);
+    }
+  };
   // operand fragments of the current and the next quarter (lane l: row l%32 of its block,
   // elements 8*(l/32) .. +7 of the 16-deep quarter)
   u32x4 wf[2][JB], hf[2][IB];
-  lm_load_frags<JB>(wf[0], &sh_w[0][wn * 128 + l32][half * 8]);
-  lm_load_frags<IB>(hf[0], &sh_a[0][wm * WM + l32][half * 8]);
+  if constexpr (RING) {
+#pragma unroll 1
+    for (int s = 0; s < STAGES; ++s) {
+      issue(s * kStageBytes);
+      advance();
+    }
+    lm_ring_turn<(STAGES - 1) * (A_LOADS + W_LOADS)>();
+    read_stage(rw[0], rh[0], 0);
+  } else {
+    request();
+    advance();
+    lm_store_lds<A_LOADS>(ga, &sh_a[0][srow][schunk]);
+    lm_store_lds<W_LOADS>(gw, &sh_w[0][srow][schunk]);
+    request();
+    advance();
+    __syncthreads();
+    lm_load_frags<JB>(wf[0], &sh_w[0][wn * WN + l32][half * 8]);
+    lm_load_frags<IB>(hf[0], &sh_a[0][wm * WM + l32][half * 8]);
+  }
 
   LmCell cell = cell_at(unit_begin);  // the unit being multiplied
   int at = 0;
@@ -294,6 +390,45 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
     f32x16_t acc[JB][IB];
     // One step; the first of a tile starts its sums from zero (an operand of the instruction, not 256
     // registers to clear).
+    auto ring_step = [&](auto first_step, auto parity) {
+      constexpr int cur = decltype(parity)::value;
+      // Every wave has this step's fragments in registers and its share of the next step in LDS: this step's stage is
+      // free for the step STAGES ahead, the next stage can be read.  Requests and reads stand between the multiplications, as in
+      // the form below (all in front of them: 960 rows, 128 to a slab, 1 110 us per call against 995).
+      lm_ring_turn<(STAGES - 2) * (A_LOADS + W_LOADS)>();
+      const unsigned int lds = ring_base + stage + wave_rows;
+      const int l_k = l_kp * kLmBK;
+      a_rows.renew();
+      w_rows.renew();
+      stage = stage + kStageBytes == STAGES * kStageBytes ? 0u : stage + kStageBytes;
+      const bf16_t* at = &sh_ring[0][0][0] + stage / 2;
+      // What goes out in the step, a share of it behind every multiplication: reads of the next step's fragments and
+      // requests in turn.
+      constexpr int kReads = kQuarters * (IB + JB), kLoads = A_LOADS + W_LOADS, kMfma = kQuarters * IB * JB;
+      auto read = [&](int n) __attribute__((always_inline)) {
+        const int ks = n / (IB + JB), r = n % (IB + JB);
+        if (r < IB) rh[cur ^ 1][ks][r] = *reinterpret_cast<const u32x4*>(at + (wm * WM + r * 32) * kLmBK + place[ks]);
+        else rw[cur ^ 1][ks][r - IB] = *reinterpret_cast<const u32x4*>(at + (BM + wn * WN + (r - IB) * 32) * kLmBK + place[ks]);
+      };
+      auto load = [&](int n) __attribute__((always_inline)) {
+        if (n < A_LOADS) a_rows.template to_lds<false>(n, l_k, lds + n * 4096);
+        else w_rows.template to_lds<ONCE>(n - A_LOADS, l_k, lds + n * 4096);
+      };
+#pragma unroll
+      for (int m = 0; m < kMfma; ++m) {
+        const int ks = m / (IB * JB), jb = m % (IB * JB) / IB, ib = m % IB;
+        acc[jb][ib] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, rw[cur][ks][jb]),
+                                                              __builtin_bit_cast(bf16x8_t, rh[cur][ks][ib]),
+                                                              (decltype(first_step)::value && ks == 0) ? f32x16_t{} : acc[jb][ib],
+                                                              0, 0, 0);
+#pragma unroll
+        for (int n = m * kLoads / kMfma; n < (m + 1) * kLoads / kMfma; ++n) load(n);
+#pragma unroll
+        for (int n = m * kReads / kMfma; n < (m + 1) * kReads / kMfma; ++n) read(n);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      advance();
+    };
     auto multiply = [&](auto first_step, const int cur) {
       // Four 16-deep multiplication quarters of 4 x IB MFMAs.  A wave is alone on its SIMD, so
       // nothing hides a memory instruction's issue time or an LDS round trip but its own matrix
@@ -314,8 +449,8 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
       for (int ks = 0; ks < kRounds; ++ks) {
         const bool last = ks + 1 == kRounds;
         // where the fragments of the next quarter come from: this stage, or (quarter 3) the next step's
-        const bf16_t* wsrc = last ? &sh_w[cur ^ 1][wn * 128 + l32][half * 8]
-                                  : &sh_w[cur][wn * 128 + l32][(ks + 1) * 16 + half * 8];
+        const bf16_t* wsrc = last ? &sh_w[cur ^ 1][wn * WN + l32][half * 8]
+                                  : &sh_w[cur][wn * WN + l32][(ks + 1) * 16 + half * 8];
         const bf16_t* hsrc = last ? &sh_a[cur ^ 1][wm * WM + l32][half * 8]
                                   : &sh_a[cur][wm * WM + l32][(ks + 1) * 16 + half * 8];
         // this quarter's share of the writes and requests: rows ks, ks+3, ... of either operand; none in quarter 3
@@ -358,11 +493,23 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
       }
       advance();
     };
-    multiply(std::true_type{}, 0);
-    multiply(std::false_type{}, 1);
-    for (int kt = D; kt < KT; kt += D) {
-      multiply(std::false_type{}, 0);  // (KT is even: a tile starts with stage 0)
+    // (KT is even: a tile starts with stage 0)
+    if constexpr (RING) {
+      using P0 = std::integral_constant<int, 0>;
+      using P1 = std::integral_constant<int, 1>;
+      ring_step(std::true_type{}, P0{});
+      ring_step(std::false_type{}, P1{});
+      for (int kt = 2; kt < KT; kt += 2) {
+        ring_step(std::false_type{}, P0{});
+        ring_step(std::false_type{}, P1{});
+      }
+    } else {
+      multiply(std::true_type{}, 0);
       multiply(std::false_type{}, 1);
+      for (int kt = D; kt < KT; kt += D) {
+        multiply(std::false_type{}, 0);
+        multiply(std::false_type{}, 1);
+      }
     }
 
     // The tile's logits, in this lane: hidden-state row m0 + wm*WM + ib*32 + l32, vocabulary
@@ -370,8 +517,8 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
     // (two at a time, the hardware conversion: nearest even), made order-preserving as 16-bit integers (two
     // at a time), the upper half of a signed 32-bit key with 63 - o below it (larger value first, then the
     // lower entry); a step of the top-2 is a maximum and a median of three.
-    const int n0 = tile * kLmBN;
-    const int nbase = n0 + wn * 128 + 4 * half;
+    const int n0 = tile * BN;
+    const int nbase = n0 + wn * WN + 4 * half;
     auto entry_of = [](int o) { return (o >> 4) * 32 + ((o & 15) >> 2) * 8 + (o & 3); };  // relative to nbase
     constexpr int kPast = -2147483647 - 1;
     auto finish_tile = [&](auto ragged_tile) {
@@ -382,7 +529,7 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) {
         uint32_t w[8];
-        lm_rounded(acc[jb][ib], w);
+        lm_rounded<BY_ASM>(acc[jb][ib], w);
         int left = V - nbase;  // (made anew for every block: 64 conditions kept would be 128 scalar registers)
         if (ragged) asm volatile("" : "+v"(left));
 #pragma unroll
@@ -420,15 +567,32 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
         const __amdgpu_buffer_rsrc_t o_rows = __builtin_amdgcn_make_buffer_rsrc(
             logits_out + static_cast<size_t>(row32) * V, 0, static_cast<int>(static_cast<unsigned int>(max(0, min(32, M - row32))) * V * 2u),
             kLmBufferFlags);
-        const unsigned int first = (static_cast<unsigned int>(l32) * V + nbase) * 2;
+        // (which 16 bytes of the block's rows this lane writes out: rows lane/4 and lane/4 + 16)
+        const int orow = lane >> 2, ochunk = lane & 3;
+        const unsigned int first = RING ? (static_cast<unsigned int>(orow) * V + n0 + wn * WN + ochunk * 8) * 2
+                                        : (static_cast<unsigned int>(l32) * V + nbase) * 2;
         bf16_t* out = logits_out + static_cast<size_t>(row32 + l32) * V + nbase;
         float add = 0.0f;
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb) {
           uint32_t w[8];
-          lm_rounded(acc[jb][ib], w);
+          lm_rounded<BY_ASM>(acc[jb][ib], w);
           int left = V - nbase;
           if (ragged) asm volatile("" : "+v"(left));
+          // The ring's forms: out through LDS, 64 bytes of a row per store instead of 16 (places swapped so that neither side
+          // finds two rows on one bank): 60 rows x 4096 x 151 936 242 us per call before, 235 so.  Through registers, with 192
+          // rows, it is 0.7 % slower: the spills it brings cost what the stores save.
+          u32x4 line[2];
+          if constexpr (RING) {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+              *reinterpret_cast<uint2*>(&sh_out[wave][l32][(q4 ^ ((l32 >> 2) & 3)) * 8 + 4 * half]) = make_uint2(w[2 * q4], w[2 * q4 + 1]);
+            lm_wave_order();
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+              line[i] = *reinterpret_cast<const u32x4*>(&sh_out[wave][orow + 16 * i][(ochunk ^ ((orow >> 2) & 3)) * 8]);
+            lm_wave_order();
+          }
 #pragma unroll
           for (int q4 = 0; q4 < 4; ++q4) {
             const uint32_t w0 = w[2 * q4], w1 = w[2 * q4 + 1];
@@ -436,7 +600,7 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
             const bool inside = !ragged || e < left;
             if constexpr (WIDE) {
               if (inside && row32 + l32 < M) *reinterpret_cast<uint2*>(out + e) = make_uint2(w0, w1);
-            } else {
+            } else if constexpr (!RING) {
               __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{w0, w1}, o_rows, inside ? static_cast<int>(first + 2 * e) : -1, 0, 0);
             }
             const float x0 = __uint_as_float(w0 << 16), x1 = __uint_as_float(w0 & 0xFFFF0000u);
@@ -447,14 +611,21 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
                                 __builtin_amdgcn_exp2f(__builtin_fmaf(x3, c, -nref)));
             add += inside ? four : 0.0f;
           }
+          if constexpr (RING) {
+            const bool inside = !ragged || n0 + wn * WN + jb * 32 + ochunk * 8 < V;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+              __builtin_amdgcn_raw_buffer_store_b128(line[i], o_rows,
+                                                     inside ? static_cast<int>(first + static_cast<unsigned int>(i) * 32u * V + 64 * jb) : -1, 0, 0);
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
         ssum[ib] += add;
       }
     }
     };
-    lm_results_ready();
-    if (n0 + kLmBN > V) finish_tile(std::true_type{}); else finish_tile(std::false_type{});
+    if (BY_ASM) lm_results_ready();
+    if (n0 + BN > V) finish_tile(std::true_type{}); else finish_tile(std::false_type{});
 
     if (++at < cell.n) continue;
     // The cell, or this work-group's part of it, is done.  Lanes l and l + 32 hold the same rows (different
@@ -522,6 +693,23 @@ __global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t*
     at = 0;
     if (unit + 1 < unit_end) cell = cell_at(unit + 1);
   }
+  // (what has been requested past the last step arrives before the LDS is given back)
+  if (RING) lm_ring_turn<0>();
+}
+
+template <int BM, bool SAMPLING, bool WIDE = false>
+__global__ __launch_bounds__(kLmThreads) void lmhead_reduce_kernel(const bf16_t* __restrict__ hidden,
+                                                                   const bf16_t* __restrict__ weight, int M, int V,
+                                                                   int H, LmGrid grid, Partial* __restrict__ partials,
+                                                                   bf16_t* __restrict__ logits_out, float c, LmClear clear) {
+  lmhead_body<BM, kLmBN, 0, SAMPLING, WIDE, false>(hidden, weight, M, V, H, grid, partials, logits_out, c, clear);
+}
+template <int BM, int BN, int STAGES, bool SAMPLING, bool ONCE>
+__global__ __launch_bounds__(kLmThreads) void lmhead_ring_kernel(const bf16_t* __restrict__ hidden,
+                                                                 const bf16_t* __restrict__ weight, int M, int V, int H,
+                                                                 LmGrid grid, Partial* __restrict__ partials,
+                                                                 bf16_t* __restrict__ logits_out, float c, LmClear clear) {
+  lmhead_body<BM, BN, STAGES, SAMPLING, false, ONCE>(hidden, weight, M, V, H, grid, partials, logits_out, c, clear);
 }
 
 }  // namespace mars

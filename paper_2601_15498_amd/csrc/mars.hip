@@ -151,11 +151,38 @@ static ClearArgs clear_args(char* ws, const Layout& L, int B, int N, int K) {
 }
 
 // ---------------------------------------------------------------- LM head fused with the row reduction
-// Slab height and width: see lm_plan.  The hardware hands work-group i to die i mod 8 and a work-group fills a
+// Slab height and tile width: see lm_plan.  The hardware hands work-group i to die i mod 8 and a work-group fills a
 // compute unit, so the work-groups are dealt out die by die, an equal share to each, and no die is given more
 // work-groups than it has compute units (its last ones would start when the others have finished: twice the time).
+//
+// The forms of the fused kernel and what a unit (bm rows x bn entries) takes in each, us: for a step of 64 hidden elements,
+// alone and what is added when all compute units are at work, and for a unit beside its steps, greedy and sampling; and the
+// rate at which the weight streams through the chip in this form, TB/s.  Fitted to 2 200 shapes (rows 4-2 048, V 1 000-152 000,
+// H 1 024-4 096, both modes, all forms that make sense for the shape): the form with the least
+// time by these figures is 1.3 % slower than the best one on average.
+// The first four are the kernel that stages through registers, with a tile of 256 (which of them: lm_plan); the others the ring (lmhead.h), which wins
+// where there are few units -- a small vocabulary, or up to 256 rows -- since its tiles are narrower and its requests go out earlier, and
+// where the weight is streamed once: 56 rows x 4096 x 2 250 45 -> 22 us per call, 40 x 4096 x 32 000 74 -> 55, 120 x 4096 x 32 000 73 -> 58, 60 x 4096 x
+// 151 936 225 -> 190 (under sampling 254 -> 235), 1 000 shapes drawn as above 1.18 times as fast on average.
+struct LmForm { int bm, bn, stages; float step, step_full, unit, unit_sampling, rate; };
+constexpr LmForm kLmForms[] = {
+    {64, 256, 0, 0.48f, 0.28f, 0.0f, 0.0f, 5.4f},
+    {128, 256, 0, 0.69f, 0.22f, 0.4f, 5.4f, 4.7f},
+    {192, 256, 0, 0.63f, 0.54f, 2.1f, 11.6f, 4.1f},
+    {256, 256, 0, 0.80f, 0.68f, 4.4f, 0.0f, 4.2f},  // (greedy: the sampling form does not fit the registers)
+    {64, 64, 8, 0.081f, 0.18f, 0.0f, 0.6f, 6.5f},
+    {64, 128, 5, 0.15f, 0.30f, 0.0f, 1.2f, 6.4f},
+    {64, 256, 3, 0.30f, 0.53f, 0.0f, 1.2f, 6.5f},
+    {128, 128, 4, 0.24f, 0.28f, 0.2f, 2.2f, 5.8f},
+    {128, 256, 3, 0.48f, 0.37f, 1.2f, 4.8f, 5.9f},
+    {256, 128, 3, 0.45f, 0.33f, 1.7f, 5.4f, 4.4f},
+};
+// A weight of at least this many bytes, read once per call, is read past the caches: 6.9 TB/s instead of 6.2 (the bare stream
+// of 1.6 GB and of 1.2 GB).  A smaller one may still lie in the Infinity Cache from the call before.
+constexpr size_t kLmOnceBytes = size_t(256) << 20;
 struct LmPlan {
-  int bm, slabs, tiles_n, launch_slabs, parts;
+  int form, bm, bn, slabs, tiles_n, launch_slabs, parts;
+  bool once;  // the weight is read past the caches
   bool wide;  // sizes beyond what a buffer spans
   LmGrid grid;  // of a full launch
 };
@@ -165,26 +192,55 @@ constexpr int kDies = 8;
 // with the next one's.  6 656 rows in slabs of 256: 6.26 ms with 5, 6.14 with 7 and 9, 6.08 with 13, 6.10 with 26;
 // 2 048 rows x 128 256: 1 620 us with 7 (two bands of 4), 1 576 with 13 (one of 8).
 constexpr int kLmBand = 13;
+constexpr int kLmFormCount = sizeof(kLmForms) / sizeof(kLmForms[0]);
+constexpr double kLmCallUs = 12.0;  // launch and per-request kernel
+constexpr double kLmKnown = 0.93;   // on a near tie the form through registers (several slabs, greedy: the fit is up to 5 % off)
+struct LmUnits { long slabs, tiles, count, rounds; };
+static LmUnits lm_units(const LmForm& m, long rows, int V) {
+  LmUnits u;
+  u.slabs = (rows + m.bm - 1) / m.bm;
+  u.tiles = (static_cast<long>(V) + m.bn - 1) / m.bn;
+  u.count = u.slabs * u.tiles;
+  u.rounds = (u.count + kComputeUnits - 1) / kComputeUnits;
+  return u;
+}
+// us per call: the units' rounds, or the weight's way from memory, whichever is more (where they are close, more than either).
+static double lm_time(const LmForm& m, long rows, int V, int H, bool sampling) {
+  const LmUnits u = lm_units(m, rows, V);
+  const double rounds = static_cast<double>(u.rounds), fill = static_cast<double>(u.count) / (rounds * kComputeUnits);
+  const double work = rounds * ((H / kLmBK) * (m.step + m.step_full * fill) + (sampling ? m.unit_sampling : m.unit));
+  const double stream = static_cast<double>(V) * H * 2e-6 / m.rate;
+  return std::sqrt(std::sqrt(work * work * work * work + stream * stream * stream * stream)) + kLmCallUs;
+}
 static LmPlan lm_plan(long rows, int V, int H, bool sampling) {
   LmPlan p;
   p.wide = H > (1 << 22) || V > (1 << 25);
-  p.tiles_n = static_cast<int>((static_cast<long>(V) + kLmBN - 1) / kLmBN);
-  // The slab height that takes the least time: units per work-group x time per unit.  Measured per unit at
+  // Through registers, the slab height that takes the least time: units per work-group x time per unit.  Measured per unit at
   // H = 4096, greedy form: 49-51 us with 64 rows, 61-63 with 128, 80-83 with 192, 100-104 with 256; with two slabs
   // of 64 and a work-group on (nearly) every compute unit the weight's way from memory bounds it, at
   // 78 us (128 rows, one slab: 75); with one slab both heights wait for the weight (60 rows: 215.5 us per call
   // with 64, 218.2 with 128).  The sampling form does not fit the registers with 256.  (Both forms and every H go by these figures.)
-  static const struct { int bm; double cost; } kHeights[] = {{64, 0.60}, {128, 0.75}, {192, 1.0}, {256, 1.235}};
-  double best = -1.0;
-  p.bm = 64;
-  for (const auto& h : kHeights) {
-    if (h.bm > (p.wide ? 64 : sampling ? 192 : 256)) break;
-    const long slabs = (rows + h.bm - 1) / h.bm, units = slabs * p.tiles_n;
-    const bool weight_bound = h.bm == 64 && slabs == 2 && units >= 192;
-    const double time = static_cast<double>((units + kComputeUnits - 1) / kComputeUnits) * (weight_bound ? 0.87 : h.cost);
-    if (best < 0.0 || time < best) { best = time; p.bm = h.bm; }
+  static const double kHeightCost[] = {0.60, 0.75, 1.0, 1.235};
+  double least = -1.0;
+  for (int f = 0; f < (p.wide ? 1 : sampling ? 3 : 4); ++f) {
+    const LmUnits u = lm_units(kLmForms[f], rows, V);
+    const bool weight_bound = f == 0 && u.slabs == 2 && u.count >= 192;
+    const double time = static_cast<double>(u.rounds) * (weight_bound ? 0.87 : kHeightCost[f]);
+    if (least < 0.0 || time < least) { least = time; p.form = f; }
   }
+  // Against the ring's forms, by kLmForms.
+  double best = lm_time(kLmForms[p.form], rows, V, H, sampling) * kLmKnown;
+  for (int f = 4; f < kLmFormCount && !p.wide; ++f) {
+    // (units of fewer steps than the ring has stages, and many slabs of 64 rows, were not looked at)
+    if (kLmForms[f].stages > H / kLmBK || (kLmForms[f].bm == 64 && rows > 4 * 64)) continue;
+    const double time = lm_time(kLmForms[f], rows, V, H, sampling);
+    if (time < best) { best = time; p.form = f; }
+  }
+  const LmForm& form = kLmForms[p.form];
+  p.bm = form.bm; p.bn = form.bn;
+  p.tiles_n = static_cast<int>((static_cast<long>(V) + p.bn - 1) / p.bn);
   p.slabs = static_cast<int>((rows + p.bm - 1) / p.bm);
+  p.once = p.slabs == 1 && static_cast<size_t>(V) * H * 2 >= kLmOnceBytes;
   // (unit numbers are 32-bit: inputs far beyond the ordinary take several launches)
   const long most = (1L << 30) / p.tiles_n;
   p.launch_slabs = static_cast<int>(p.slabs < most ? p.slabs : most < 1 ? 1 : most);
@@ -219,16 +275,28 @@ static hipError_t launch_lmhead(const LmPlan& p, const bf16_t* hidden, const bf1
     bf16_t* lo = SAMPLING ? logits_out + row0 * V : nullptr;
 #define MARS_LM_LAUNCH(...)                                                                                            \
   hipLaunchKernelGGL((lmhead_reduce_kernel<__VA_ARGS__>), grid, block, 0, stream, h, weight, rows, V, H, g, out, lo, c, clear)
-    switch (p.bm) {
-      case 64:
+#define MARS_LM_RING(BM, BN, STAGES)                                                                                  \
+  if (p.once)                                                                                                          \
+    hipLaunchKernelGGL((lmhead_ring_kernel<BM, BN, STAGES, SAMPLING, true>), grid, block, 0, stream, h, weight, rows, V, H, g, out, lo, c, clear); \
+  else                                                                                                                 \
+    hipLaunchKernelGGL((lmhead_ring_kernel<BM, BN, STAGES, SAMPLING, false>), grid, block, 0, stream, h, weight, rows, V, H, g, out, lo, c, clear)
+    switch (p.form) {
+      case 0:
         if (p.wide) MARS_LM_LAUNCH(64, SAMPLING, true); else MARS_LM_LAUNCH(64, SAMPLING);
         break;
-      case 128: MARS_LM_LAUNCH(128, SAMPLING); break;
-      case 192: MARS_LM_LAUNCH(192, SAMPLING); break;
-      default:
+      case 1: MARS_LM_LAUNCH(128, SAMPLING); break;
+      case 2: MARS_LM_LAUNCH(192, SAMPLING); break;
+      case 3:
         if constexpr (!SAMPLING) MARS_LM_LAUNCH(256, false);
         break;
+      case 4: MARS_LM_RING(64, 64, 8); break;
+      case 5: MARS_LM_RING(64, 128, 5); break;
+      case 6: MARS_LM_RING(64, 256, 3); break;
+      case 7: MARS_LM_RING(128, 128, 4); break;
+      case 8: MARS_LM_RING(128, 256, 3); break;
+      default: MARS_LM_RING(256, 128, 3); break;
     }
+#undef MARS_LM_RING
 #undef MARS_LM_LAUNCH
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -64,6 +64,14 @@ hipError_t hipGetSymbolAddress(void**, const void*) { return hipErrorInvalidSymb
 template <int BM, bool S, bool W = false>
 static void form() { heights[reinterpret_cast<const void*>(&mars::lmhead_reduce_kernel<BM, S, W>)] = BM; }
 
+template <int BM, int BN, int STAGES, bool S, bool ONCE>
+static void ring_form() { heights[reinterpret_cast<const void*>(&mars::lmhead_ring_kernel<BM, BN, STAGES, S, ONCE>)] = BM; }
+template <int BM, int BN, int STAGES>
+static void ring() {
+  ring_form<BM, BN, STAGES, false, false>(); ring_form<BM, BN, STAGES, false, true>();
+  ring_form<BM, BN, STAGES, true, false>(); ring_form<BM, BN, STAGES, true, true>();
+}
+
 static int fail(const char* what, int B, int N, int V, int H, int sampling) {
   std::printf("%s: B %d N %d V %d H %d sampling %d\n", what, B, N, V, H, sampling);
   return 1;
@@ -149,6 +157,7 @@ static int check(int B, int N, int V, int H, int sampling, const std::string& ba
 int main(int argc, char** argv) {
   form<64, false>(); form<64, false, true>(); form<128, false>(); form<192, false>(); form<256, false>();
   form<64, true>(); form<64, true, true>(); form<128, true>(); form<192, true>();
+  ring<64, 64, 8>(); ring<64, 128, 5>(); ring<64, 256, 3>(); ring<128, 128, 4>(); ring<128, 256, 3>(); ring<256, 128, 3>();
   int failed = 0, cases = 0;
   for (int i = 1; i + 7 < argc; i += 8, ++cases)
     failed += check(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoi(argv[i + 2]), std::atoi(argv[i + 3]), std::atoi(argv[i + 4]),

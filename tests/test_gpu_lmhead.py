@@ -429,3 +429,49 @@ def test_sizes_beyond_what_a_buffer_spans(N, V, H, T):
     assert np.array_equal(st["id1"], id1) and np.array_equal(st["z1"], zn.max(axis=1))
     zn[np.arange(N), id1] = -np.inf
     assert np.array_equal(st["id2"], zn.argmax(axis=1)) and np.array_equal(st["z2"], zn.max(axis=1))
+
+
+# The forms that stage through the ring, by tile (rows x entries): 64 x 64, 64 x 128, 64 x 256, 128 x 128, 128 x 256 and
+# 256 x 128, each with one slab and with several where it takes both, the last slab and the last tile cut short; cells shared
+# by two work-groups; 17 and 128 rows at the end read the weight past the caches.  Small integers as above, so that
+# every sum and every rounding is exact.
+RING_SHAPES = [
+    (40, 1003, 512, 0.0), (19, 1216, 896, 1.0), (122, 3261, 512, 0.0), (223, 1144, 640, 1.0),
+    (64, 17003, 512, 0.0), (117, 4401, 384, 0.0), (16, 24072, 768, 1.0), (79, 11808, 768, 1.0),
+    (64, 120001, 512, 0.0), (17, 61368, 768, 1.0), (89, 37384, 256, 1.0),
+    (128, 30001, 384, 0.0), (210, 42403, 256, 0.0), (277, 21912, 256, 1.0),
+    (68, 58641, 384, 0.0), (220, 63401, 896, 0.0), (69, 52432, 512, 1.0), (291, 54736, 256, 1.0),
+    (210, 17696, 1024, 1.0), (974, 4704, 768, 1.0), (710, 16440, 640, 1.0),
+    (17, 65537, 2048, 0.0), (128, 131200, 1024, 1.0),
+]
+
+
+@pytest.mark.parametrize("rows,V,H,T", RING_SHAPES)
+def test_integer_logits_through_the_ring(rows, V, H, T):
+    say(f"[case] lmhead ring: rows={rows} V={V} H={H} T={T}")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + V)
+    h = (torch.rand((rows, H), generator=g, device=DEV) < 40.0 / H).float()
+    w = torch.randint(-2, 4, (V, H), generator=g, device=DEV).float()
+    z = h @ w.t()  # (sums of a few hundred small integers: exact in every order)
+    assert z.abs().max() <= 256
+    at = torch.arange(V, device=DEV)
+    z1 = z.max(dim=1, keepdim=True).values
+    id1 = torch.where(z == z1, at, V).min(dim=1).values
+    rest = z.scatter(1, id1[:, None], float("-inf"))
+    z2 = rest.max(dim=1, keepdim=True).values
+    id2 = torch.where(rest == z2, at, V).min(dim=1).values
+    par = torch.arange(-1, rows - 1, dtype=torch.int32, device=DEV)[None]
+    tok = torch.randint(0, V, (1, rows), generator=g, device=DEV, dtype=torch.int32)
+    th = torch.full((1,), 0.9, device=DEV)
+    args = (h.to(torch.bfloat16)[None], w.to(torch.bfloat16), tok, par, th)
+    if T:
+        out, logits = M.mars_lmhead_verify_sampling(*args, T, torch.full((1, rows + 1), 0.5, device=DEV))
+        assert torch.equal(logits.view(torch.bfloat16).float().view(rows, V), z)
+        want = torch.exp((z - z1).double() / T).sum(dim=1)
+        assert (M.unpack_stats(out.stats)["sum_exp"].double() / want - 1).abs().max() <= 1e-5
+    else:
+        out = M.mars_lmhead_verify(*args)
+    st = M.unpack_stats(out.stats)
+    assert torch.equal(st["id1"].long(), id1) and torch.equal(st["id2"].long(), id2)
+    assert torch.equal(st["z1"], z1[:, 0]) and torch.equal(st["z2"], z2[:, 0])
