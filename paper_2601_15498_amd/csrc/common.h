@@ -267,21 +267,60 @@ __device__ __forceinline__ unsigned long long dpp_move(unsigned long long v) {
 // when a row has at most sixteen), and a butterfly inside the DPP row merges keys and sums.
 // Every lane of the sixteen ends with the row's result; lane 0 of them hands it to `emit`.
 // Must be called by all NT threads of the work-group (NT a multiple of 64).
-constexpr int kMergeBatch = 4;  // partial results a lane has in flight at a time (a kernel with registers to spare: 8)
+constexpr int kMergeBatch = 4;  // partial results a lane has in flight at a time, twice (a kernel with registers to spare: 8)
 // Partial results s0, s0 + 16, ... of one row (empty ones past the end, or for a row that does not exist).
-template <int BATCH>
+template <int BATCH, bool SUMS>
 __device__ __forceinline__ void load_partials(const Partial* __restrict__ partials, int row, int nrows, int parts,
                                               int s0, Partial (&q)[BATCH]) {
   const Partial* __restrict__ p = partials + static_cast<size_t>(row) * parts;
 #pragma unroll
   for (int j = 0; j < BATCH; ++j) {
     const int s = s0 + 16 * j;
+    q[j].id1 = -1; q[j].id2 = -1; q[j].s = 0.0f; q[j].z1 = neg_inf(); q[j].z2 = neg_inf(); q[j].ref = 0.0f;
     if (row < nrows && s < parts) {
-      q[j] = p[s];
-    } else {
-      q[j].id1 = -1; q[j].id2 = -1; q[j].s = 0.0f; q[j].z1 = 0.0f; q[j].z2 = 0.0f; q[j].ref = 0.0f;
+      q[j].z1 = p[s].z1; q[j].id1 = p[s].id1; q[j].z2 = p[s].z2; q[j].id2 = p[s].id2;
+      if (SUMS) { q[j].s = p[s].s; q[j].ref = p[s].ref; }
     }
   }
+}
+// What a lane has seen of a row: its two largest entries and the sum against R.
+struct LaneTop2 {
+  float z1, z2;
+  int id1, id2;   // < 0: absent (and z = -inf)
+  float R;
+  double S;
+};
+__device__ __forceinline__ void lane_clear(LaneTop2& t) {
+  t.z1 = t.z2 = neg_inf(); t.id1 = t.id2 = -1; t.R = -3.0e38f; t.S = 0.0;
+}
+// (value desc, index asc); an absent entry comes behind every other.
+__device__ __forceinline__ bool before(float x, int xi, float y, int yi) {
+  return x > y || (x == y && static_cast<unsigned int>(xi) < static_cast<unsigned int>(yi));
+}
+// Takes in partial results, values and indices as they are.  (Eighteen instructions for a pair; two insertions of 64-bit keys
+// are forty.)
+template <int BATCH, bool SUMS>
+__device__ __forceinline__ void lane_fold(const Partial (&q)[BATCH], LaneTop2& t) {
+#pragma unroll
+  for (int j = 0; j < BATCH; ++j) {
+    const bool first = before(q[j].z1, q[j].id1, t.z1, t.id1);
+    const float x = first ? q[j].z2 : q[j].z1, y = first ? t.z1 : t.z2;
+    const int xi = first ? q[j].id2 : q[j].id1, yi = first ? t.id1 : t.id2;
+    const bool second = before(x, xi, y, yi);
+    t.z2 = second ? x : y;
+    t.id2 = second ? xi : yi;
+    t.z1 = first ? q[j].z1 : t.z1;
+    t.id1 = first ? q[j].id1 : t.id1;
+  }
+  if (!SUMS) return;
+  // (references are integers: scalings by powers of two, exact)
+  float R = t.R;
+#pragma unroll
+  for (int j = 0; j < BATCH; ++j) R = q[j].s > 0.0f ? fmaxf(R, q[j].ref) : R;
+  if (R > t.R) { t.S = ldexp(t.S, static_cast<int>(fmaxf(t.R - R, -1000.0f))); t.R = R; }
+#pragma unroll
+  for (int j = 0; j < BATCH; ++j)
+    t.S += ldexp(static_cast<double>(q[j].s), static_cast<int>(fmaxf(q[j].s > 0.0f ? q[j].ref - R : 0.0f, -1000.0f)));
 }
 // One butterfly step of a merge over lanes: every lane absorbs what its partner under CTRL holds.  (All
 // lanes take part; the two sides hold disjoint sets of elements, so no key is inserted twice.)
@@ -329,7 +368,7 @@ __device__ __forceinline__ mars_row_stat merge_row_few(const Partial (&q)[kFewPa
   return finish_row(k1, k2, R, S, theta, c, ind);
 }
 
-template <int NT, int BATCH = kMergeBatch, typename ThetaAt, typename Emit>
+template <int NT, int BATCH = kMergeBatch, bool SUMS = true, typename ThetaAt, typename Emit>
 __device__ __forceinline__ void merge_rows_coop(const Partial* __restrict__ partials, int nrows, int parts,
                                                 float c, const Indicator& ind, ThetaAt theta_at, Emit emit) {
   // Few partial results per row (the row reduction leaves one per split): a thread per row, one round
@@ -344,33 +383,35 @@ __device__ __forceinline__ void merge_rows_coop(const Partial* __restrict__ part
   }
   const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;
   constexpr int kGroups = NT / 16;
-  // A lane has BATCH loads in flight at a time, and the first batch of the next pass over the
-  // rows is requested before the current pass is worked on: merging N rows costs about one memory
-  // round trip, not one per pass.
+  // A lane has two batches in flight at a time, the next one -- of this row, or of the group's next row -- requested before
+  // the current one is worked on: merging N rows costs about one memory round trip, not one per pass.  (Behind the LM head a
+  // row has up to 256 partial results, two batches of eight for a lane.  With one batch of the row in flight, and 64-bit keys
+  // inserted one by one, the greedy kernel took 10.2 us behind 60 rows of 198 and 8.8 behind 13 of 250, now 9.0 and 6.5; the
+  // sampling walk, which had two partial results in flight, 25.4 and 18.4, now 21.5 and 13.8.)
   Partial nxt[BATCH];
-  load_partials(partials, grp, nrows, parts, sub, nxt);
+  load_partials<BATCH, SUMS>(partials, grp, nrows, parts, sub, nxt);
   for (int row0 = 0; row0 < nrows; row0 += kGroups) {
     const int row = row0 + grp;
     const bool live = row < nrows;
-    unsigned long long k1 = 0, k2 = 0;
-    float R = -3.0e38f;
-    double S = 0.0;
-    Partial cur[BATCH];
+    LaneTop2 t;
+    lane_clear(t);
+    for (int s0 = 0; s0 < parts; s0 += 16 * BATCH) {
+      Partial cur[BATCH];
 #pragma unroll
-    for (int j = 0; j < BATCH; ++j) cur[j] = nxt[j];
-    load_partials(partials, row + kGroups, nrows, parts, sub, nxt);
-    fold_partials(cur, c, k1, k2, R, S);
-    for (int s0 = sub + 16 * BATCH; s0 < parts; s0 += 16 * BATCH) {
-      load_partials(partials, row, nrows, parts, s0, cur);
-      fold_partials(cur, c, k1, k2, R, S);
+      for (int j = 0; j < BATCH; ++j) cur[j] = nxt[j];
+      const bool last = s0 + 16 * BATCH >= parts;
+      load_partials<BATCH, SUMS>(partials, last ? row + kGroups : row, nrows, parts, last ? sub : s0 + 16 * BATCH + sub, nxt);
+      lane_fold<BATCH, SUMS>(cur, t);
     }
+    unsigned long long k1 = t.id1 >= 0 ? make_key(t.z1, t.id1) : 0ull;
+    unsigned long long k2 = t.id2 >= 0 ? make_key(t.z2, t.id2) : 0ull;
     // Butterfly over the sixteen lanes: at every step the two sides hold disjoint sets of
     // elements, so no key can be inserted twice.  (All lanes take part; dead rows carry nothing.)
-    merge_step<kDppXor1>(k1, k2, R, S);
-    merge_step<kDppXor2>(k1, k2, R, S);
-    merge_step<kDppHalfMirror>(k1, k2, R, S);
-    merge_step<kDppMirror>(k1, k2, R, S);
-    if (live && sub == 0) emit(row, finish_row(k1, k2, R, S, theta_at(row), c, ind));
+    merge_step<kDppXor1>(k1, k2, t.R, t.S);
+    merge_step<kDppXor2>(k1, k2, t.R, t.S);
+    merge_step<kDppHalfMirror>(k1, k2, t.R, t.S);
+    merge_step<kDppMirror>(k1, k2, t.R, t.S);
+    if (live && sub == 0) emit(row, finish_row(k1, k2, t.R, t.S, theta_at(row), c, ind));
   }
 }
 

@@ -168,8 +168,8 @@ struct LmForm { int bm, bn, stages; float step, step_full, unit, unit_sampling, 
 constexpr LmForm kLmForms[] = {
     {64, 256, 0, 0.48f, 0.28f, 0.0f, 0.0f, 5.4f},
     {128, 256, 0, 0.69f, 0.22f, 0.4f, 5.4f, 4.7f},
-    {192, 256, 0, 0.63f, 0.54f, 2.1f, 11.6f, 4.1f},
-    {256, 256, 0, 0.80f, 0.68f, 4.4f, 0.0f, 4.2f},  // (greedy: the sampling form does not fit the registers)
+    {192, 256, 0, 0.63f, 0.54f, 2.1f, 11.6f, 5.0f},
+    {256, 256, 0, 0.80f, 0.68f, 4.4f, 0.0f, 5.0f},  // (greedy: the sampling form does not fit the registers)
     {64, 64, 8, 0.081f, 0.18f, 0.0f, 0.6f, 6.5f},
     {64, 128, 5, 0.15f, 0.30f, 0.0f, 1.2f, 6.4f},
     {64, 256, 3, 0.30f, 0.53f, 0.0f, 1.2f, 6.5f},

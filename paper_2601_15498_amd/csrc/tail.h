@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kGreedyThreads) void tail_greedy_kernel(TailArgs a)
   const float theta = a.theta[b];
   // (eight loads in flight per lane: this kernel has the registers, and behind the fused LM head a
   // row has up to a few hundred partial results)
-  merge_rows_coop<NT, 8>(a.partials + rd * a.splits, N, a.splits, a.c, a.ind, [&](int) { return theta; },
+  merge_rows_coop<NT, 8, false>(a.partials + rd * a.splits, N, a.splits, a.c, a.ind, [&](int) { return theta; },
                          [&](int row, const mars_row_stat& st) {
                            a.stats_ws[rb + row] = st;
                            if (a.stats) a.stats[rb + row] = st;
@@ -831,7 +831,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
         }
       }
     } else {
-      merge_rows_coop<NT, 2>(a.partials + rd * a.splits, N, a.splits, a.c, a.ind, [&](int) { return theta; }, emit);
+      merge_rows_coop<NT, RESIDENT ? 8 : 4>(a.partials + rd * a.splits, N, a.splits, a.c, a.ind, [&](int) { return theta; }, emit);
     }
 #pragma unroll
     for (int t = 0; t < kPerThread; ++t) {

@@ -601,3 +601,21 @@ def test_sums_worked_out_for_a_partner_are_the_partners_own(dtype, qdtype, V):
 def test_kept_rows_of_requests_of_a_single_node(B):
     w = make_config(4, B=B, N=1, V=2048, tree={"kind": "chain"}, temperature=0.0)
     compare_ex(w, label=f"kept_rows_single_B{B}")
+
+
+@pytest.mark.parametrize("V", [151937, 262144])
+@pytest.mark.parametrize("T", [0.0, 0.7])
+def test_equal_maxima_over_many_partial_results(V, T):
+    # 18 and 32 partial results for a row, so that a lane of the merge folds two.  Where rows begin anywhere the first of them
+    # holds the row's last elements too: level with an entry in the middle, the lower index wins.  And a row with one entry
+    # above -inf, one with none.
+    from paper_2601_15498_amd import binding as M
+    theta = torch.tensor([0.5], device="cuda:0")
+    planted = [V - 1, 140_000, 138_000, 5]
+    cases = [(-3.0, 7.0, planted[:n], want) for n, want in ((4, (5, 138_000)), (3, (138_000, 140_000)), (2, (140_000, V - 1)))]
+    cases += [(float("-inf"), 1.0, [139_999], (139_999, 0)), (float("-inf"), 1.0, [], (0, 1))]
+    for background, top, at, want in cases:
+        z = torch.full((1, 1, V), background, device="cuda:0")
+        z[0, 0, at] = top
+        st = M.unpack_stats(M.mars_row_stats(z, theta, T))
+        assert (int(st["id1"]), int(st["id2"])) == want
