@@ -226,9 +226,8 @@ __device__ __forceinline__ int low_margin(float z1, float z2, float theta, const
 // the public statistics entry.  Moving the reference to the row maximum needs the only
 // exponential of the merge, of an argument split into its integer part (exact) and a
 // fraction in [-1/2, 1/2] (one fp32 exp2).
-__device__ __forceinline__ mars_row_stat finish_row(unsigned long long k1, unsigned long long k2, float R, double S,
-                                                    float theta, float c, const Indicator& ind) {
-  const float z1 = key_value(k1), z2 = key_value(k2);
+__device__ __forceinline__ mars_row_stat finish_values(float z1, int id1, float z2, int id2, float R, double S, float theta,
+                                                       float c, const Indicator& ind) {
   float sum_exp = 0.0f;
   if (c > 0.0f && S > 0.0) {
     // S * 2^(R - z1*c)
@@ -238,11 +237,15 @@ __device__ __forceinline__ mars_row_stat finish_row(unsigned long long k1, unsig
     sum_exp = static_cast<float>(ldexp(S * static_cast<double>(__builtin_amdgcn_exp2f(frac)), static_cast<int>(n)));
   }
   mars_row_stat st;
-  st.z1 = z1; st.id1 = key_index(k1);
-  st.z2 = z2; st.id2 = key_index(k2);
+  st.z1 = z1; st.id1 = id1;
+  st.z2 = z2; st.id2 = id2;
   st.sum_exp = sum_exp;
   st.relax_ok = low_margin(z1, z2, theta, ind);
   return st;
+}
+__device__ __forceinline__ mars_row_stat finish_row(unsigned long long k1, unsigned long long k2, float R, double S,
+                                                    float theta, float c, const Indicator& ind) {
+  return finish_values(key_value(k1), key_index(k1), key_value(k2), key_index(k2), R, S, theta, c, ind);
 }
 
 // Sum S (relative to reference R) absorbs a partial sum s taken against reference ref; both
@@ -342,30 +345,26 @@ __device__ __forceinline__ void load_partials_of_row(const Partial* __restrict__
     if (j < parts) {
       q[j] = p[j];
     } else {
-      q[j].id1 = -1; q[j].id2 = -1; q[j].s = 0.0f; q[j].z1 = 0.0f; q[j].z2 = 0.0f; q[j].ref = 0.0f;
+      q[j].id1 = -1; q[j].id2 = -1; q[j].s = 0.0f; q[j].z1 = neg_inf(); q[j].z2 = neg_inf(); q[j].ref = 0.0f;
     }
   }
 }
-template <int BATCH>
-__device__ __forceinline__ void fold_partials(const Partial (&q)[BATCH], float c, unsigned long long& k1,
-                                              unsigned long long& k2, float& R, double& S) {
-#pragma unroll
-  for (int j = 0; j < BATCH; ++j) {
-    if (q[j].id1 >= 0) top2_insert(k1, k2, make_key(q[j].z1, q[j].id1));
-    if (q[j].id2 >= 0) top2_insert(k1, k2, make_key(q[j].z2, q[j].id2));
-    if (c > 0.0f && q[j].s > 0.0f) absorb_sum(R, S, q[j].ref, static_cast<double>(q[j].s));
-  }
-}
-
 // A row with at most kFewParts partial results, merged by one thread.
 constexpr int kFewParts = 4;
-__device__ __forceinline__ mars_row_stat merge_row_few(const Partial (&q)[kFewParts], float c, const Indicator& ind,
-                                                       float theta) {
-  unsigned long long k1 = 0, k2 = 0;
-  float R = -3.0e38f;
-  double S = 0.0;
-  fold_partials(q, c, k1, k2, R, S);
-  return finish_row(k1, k2, R, S, theta, c, ind);
+// (`parts` is the same for the whole work-group: a row whose partial result is its only one -- 128 rows or more -- is not merged at all.)
+__device__ __forceinline__ mars_row_stat merge_row_few(const Partial (&q)[kFewParts], int parts, float c,
+                                                       const Indicator& ind, float theta) {
+  LaneTop2 t;
+  t.z1 = q[0].z1; t.id1 = q[0].id1; t.z2 = q[0].z2; t.id2 = q[0].id2;
+  t.R = q[0].s > 0.0f ? q[0].ref : -3.0e38f;
+  t.S = static_cast<double>(q[0].s);
+#pragma unroll
+  for (int j = 1; j < kFewParts; ++j) {
+    if (j >= parts) break;
+    const Partial one[1] = {q[j]};
+    lane_fold<1, true>(one, t);
+  }
+  return finish_values(t.z1 + 0.0f, t.id1, t.z2 + 0.0f, t.id2, t.R, t.S, theta, c, ind);  // (-0 is 0, as in a key)
 }
 
 template <int NT, int BATCH = kMergeBatch, bool SUMS = true, typename ThetaAt, typename Emit>
@@ -377,7 +376,7 @@ __device__ __forceinline__ void merge_rows_coop(const Partial* __restrict__ part
     for (int row = threadIdx.x; row < nrows; row += NT) {
       Partial q[kFewParts];
       load_partials_of_row(partials + static_cast<size_t>(row) * parts, parts, q);
-      emit(row, merge_row_few(q, c, ind, theta_at(row)));
+      emit(row, merge_row_few(q, parts, c, ind, theta_at(row)));
     }
     return;
   }
