@@ -350,8 +350,7 @@ static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int 
   const bool vec = whole_groups(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, dense ? a.dprobs : nullptr, a.N, V);
   // Slices of at most kMaxResident groups of eight per thread stay in registers between passes.  One per thread in the
   // form for rows at every alignment only (rows of up to 4 089 entries): see tail_sampling_body.
-  const int ngroups8 = row_groups(V, vec);
-  const int slice8 = ((ngroups8 + a.G - 1) / a.G + kWave - 1) / kWave * kWave;
+  const int slice8 = walk_slice(V, a.G, vec);
   const bool resident = slice8 <= kMaxResident * kSamplingThreads, two = slice8 <= 2 * kSamplingThreads;
   const bool one = !vec && slice8 <= kSamplingThreads;
   const bool qbf = dense && draft_dtype == MARS_BF16;
@@ -367,14 +366,17 @@ static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int 
 #undef MARS_PICK
 #undef MARS_PICK2
   TailArgs copy = a;
+  copy.slice = slice8;
   void* params[] = {&copy};
   // With G > 1 the work-groups of a request exchange sums.  The grid never exceeds one work-group
   // per compute unit, so on a GPU that is free to run it all of them are resident together and the
   // exchanges take a couple of microseconds; when other work keeps some of them waiting for a
   // compute unit, those that run work out the missing sums themselves (tail.h: exchange_begin) --
   // slower, same bits, and no work-group ever depends on another one being there.
-  return hipLaunchKernel(kernel, dim3(static_cast<unsigned int>(a.B) * a.G),
-                         dim3(resident ? kSamplingThreads : kStreamingThreads), params, 0, stream);
+  // (Several work-groups per request: one column of the grid each, so that neither number has to be divided for; they are at
+  // most as many as compute units.  One: the requests alone, as many as there are.)
+  const unsigned int B = static_cast<unsigned int>(a.B), G = static_cast<unsigned int>(a.G);
+  return hipLaunchKernel(kernel, G == 1 ? dim3(B) : dim3(G, B), dim3(resident ? kSamplingThreads : kStreamingThreads), params, 0, stream);
 }
 
 // Work-groups per request at launch: what the workspace was laid out for, fewer on a GPU with fewer compute units.

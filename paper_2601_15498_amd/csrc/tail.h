@@ -50,6 +50,7 @@ struct TailArgs {
   float c;               // log2(e) / T, 0 in greedy mode
   // sampling mode: G work-groups share one request and exchange partial sums
   int G;
+  int slice;                // groups of eight entries in a work-group's slice (walk_slice)
   int spin_limit;        // polls a work-group gives a partner before it works out the partner's sum itself
   unsigned long long* xslots;  // [B][N+2][G][2] tagged exchange words, cleared by the row reduction
 };
@@ -700,6 +701,10 @@ __device__ __forceinline__ int resident_tiles_from_memory(const RowView<T, TQ, V
   return nst;
 }
 
+// A work-group's slice of the vocabulary, in groups of eight elements (a multiple of 64 groups, so that the slices are made of
+// whole wave steps).  (Worked out on the host: an integer division is 25 instructions.)
+inline int walk_slice(int V, int G, bool vec) { return ((row_groups(V, vec) + G - 1) / G + kWave - 1) / kWave * kWave; }
+
 constexpr float kClosedFormMinNorm = 0.1f; // one-hot residual: Z = 1 - f(x) is used when at least this
 constexpr int kMaxResident = 3;            // groups of eight elements a thread can keep in registers
 
@@ -740,10 +745,10 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   constexpr int32_t kNoChild = 0x7FFFFFFF;
 
   const int G = a.G;
-  const int b = blockIdx.x / G, g = blockIdx.x - b * G;
+  const int b = G == 1 ? blockIdx.x : blockIdx.y, g = G == 1 ? 0 : blockIdx.x;  // (the grid: see launch_sampling_tail)
   const int N = a.N, V = a.V;
   const size_t rb = static_cast<size_t>(b) * N;
-  const int bd = b % a.Bd;  // the request whose inputs this (possibly swept) request reads
+  const int bd = a.B == a.Bd ? b : b % a.Bd;  // the request whose inputs this (possibly swept) request reads
   const size_t rd = static_cast<size_t>(bd) * N;
   const int tid = threadIdx.x;
   const int wave = tid / kWave, lane = tid % kWave;
@@ -757,6 +762,9 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   // Every work-group of the request does this for itself; they produce identical bits, and only the first
   // writes the caller's outputs.
   const int nwords = (N + kWave - 1) / kWave;
+  const int ngroups = row_groups(V, VEC);
+  const int slice = a.slice;
+  const int g_begin = min(ngroups, g * slice), g_end = min(ngroups, g_begin + slice);
   {
     constexpr int kPerThread = (MARS_MAX_NODES + NT - 1) / NT;
     const float theta = a.theta[b];
@@ -870,11 +878,6 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     __syncthreads();
   }
 
-  const int ngroups = row_groups(V, VEC);
-  // This work-group's slice of the vocabulary, in groups of eight elements (a multiple of 64
-  // groups, so that the slices are made of whole wave steps).
-  const int slice = ((ngroups + G - 1) / G + kWave - 1) / kWave * kWave;
-  const int g_begin = min(ngroups, g * slice), g_end = min(ngroups, g_begin + slice);
   // A slice of at most RES groups per thread stays in registers between the passes over
   // one node: f is then loaded and exponentiated once per visited node, every further
   // rejection at that node only updates it in place, and the final draw reads it where it is.
@@ -1247,7 +1250,9 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     }
     // Which work-group's slice holds the target?  The last one with mass if rounding leaves none.  Lane i
     // holds the total of work-group i and the prefix up to it; the grand total is the last prefix.
-    {
+    if (G == 1) {
+      total = sh_part[0];
+    } else {
       const double pg = lane < G ? sh_part[lane] : 0.0;
       const double pincl = wave_prefix_sum(pg);
       total = lane_value(pincl, kWave - 1);
