@@ -16,7 +16,8 @@
 // What bounds it: the matrix cores, the power they draw and the data moved per product.  6 656 rows x 4096 x 151 936: 6.00-6.12 ms =
 // 1.35-1.38 PFLOP/s (the library's product alone 1.47; 8192^3: 1.38-1.40), the clock at 1.72 GHz of 2.4 and the matrix
 // units busy 3/4 of the time; before (192 rows at most, keys in 32-bit integers, unequal shares) 6.76-6.87 ms.
-// 960 rows, sampling form: 1 052-1 065 us (before 1 133-1 160).
+// 960 rows, sampling form: 1 000 us per call (1 032 in the same run before the stores and what is kept between tiles took their
+// present form, below).
 //
 // Few rows, or few units (a small vocabulary), are not bound by the matrix cores but by the weight's way through the chip, and take
 // a second form, the ring (lmhead_ring_kernel): tiles of 64, 128 or 256 entries, so that there are enough units for
@@ -47,7 +48,6 @@ constexpr int kLmDepth = 2;               // steps between the request of an ope
 constexpr int kLmMaxBM = 256;             // tallest slab of hidden-state rows (its accumulators are half the register file)
 
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 // Two bf16 patterns (sign and magnitude) as two 16-bit integers in the order of the values: minus the magnitude
@@ -98,11 +98,21 @@ __device__ __forceinline__ void lm_results_ready() {
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // 32 wait states; an instruction of 16 passes asks for 19
   __builtin_amdgcn_sched_barrier(0);
 }
-// What a wave has written to LDS for its own lanes is read behind this, and not written again before it has been: LDS
-// operations of a wave are performed in order, the compiler is kept from changing theirs.
-__device__ __forceinline__ void lm_wave_order() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_wave_barrier();
+// A block of 32 rows x 32 logits on its way out.  Lane l has words 2q, 2q + 1 = entries 8q + 4 (l/32) .. + 3 of row l%32, q = 0 .. 3;
+// it leaves with 16 bytes, entries 8k .. 8k + 7, of rows l%16 and l%16 + 16, k = (l/16)%2 + 2 (l/32): 64 bytes of a row per
+// store, by exchanges of half-waves and of quarter-waves between registers.  (960 rows x 4096 x 151 936, sampling form, us per call: 8 bytes per
+// lane and 16 of a row per store 1 070, 16 and 32 1 059, so 1 054, 16 and 32 with neighbouring lanes on a row 1 063; with the non-temporal hint
+// 1 093, all in one run.)
+__device__ __forceinline__ void lm_out_lines(const uint32_t (&w)[8], u32x4 (&line)[2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {  // first and second word of a pair of entries
+    const auto even = __builtin_amdgcn_permlane32_swap(w[i], w[4 + i], false, false);     // chunk 0 | 2: entries 0-3, 4-7
+    const auto odd = __builtin_amdgcn_permlane32_swap(w[2 + i], w[6 + i], false, false);  // chunk 1 | 3
+    const auto front = __builtin_amdgcn_permlane16_swap(even[0], odd[0], false, false);
+    const auto back = __builtin_amdgcn_permlane16_swap(even[1], odd[1], false, false);
+    line[0][i] = front[0]; line[1][i] = front[1];
+    line[0][2 + i] = back[0]; line[1][2 + i] = back[1];
+  }
 }
 // k1 >= k2, the two largest so far.
 __device__ __forceinline__ void lm_top2_step(int& k1, int& k2, int key) {
@@ -242,9 +252,14 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
   __shared__ __attribute__((aligned(16))) bf16_t sh_w[RING ? 1 : 2][RING ? 1 : BN][kLmStride];
   __shared__ __attribute__((aligned(1024))) bf16_t sh_ring[RING ? STAGES : 1][RING ? BM + BN : 1][kLmBK];
 
-  // The ring: a block of 32 rows x 32 logits of each wave, on its way out.
-  __shared__ __attribute__((aligned(16))) bf16_t sh_out[SAMPLING && RING ? kLmThreads / kWave : 1][32][32];
-  // Results of the other wave column, on their way to the one that writes them.
+  // Every lane's two largest and its (reference, sum) of each of its rows, from one tile of a cell to the next.  Through registers
+  // (not in the ring, whose forms have them to spare) they stay here between tiles: in registers, twelve to
+  // eighteen of them, they were what the kernels spilled, and a spilled value comes back through the counter of the loads and
+  // stores under way, so that every tile waited for all of them -- in the sampling form for its own stores of the logits.
+  constexpr bool KEPT = !RING;
+  __shared__ __attribute__((aligned(16))) unsigned long long sh_best[KEPT ? IB : 1][KEPT ? kLmThreads : 1][2];
+  __shared__ __attribute__((aligned(8))) float sh_part[KEPT && SAMPLING ? IB : 1][KEPT && SAMPLING ? kLmThreads : 1][2];
+  // The ring: results of the other wave column, on their way to the one that writes them.
   __shared__ unsigned long long sh_key[2][IB][32][2];
   __shared__ float sh_sum[SAMPLING ? 2 : 1][SAMPLING ? IB : 1][32][2];
 
@@ -277,7 +292,7 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
     return Rows(weight + static_cast<size_t>(tile) * BN * H, min(BN, V - tile * BN), H, srow, schunk);
   };
 
-  unsigned long long best1[IB], best2[IB];
+  unsigned long long best1[IB], best2[IB];  // (KEPT: in LDS; these are not used)
   float sref[IB], ssum[IB];  // SAMPLING: reference (already times c) and sum of this lane's share of its rows
 #pragma unroll
   for (int ib = 0; ib < IB; ++ib) { best1[ib] = 0ull; best2[ib] = 0ull; sref[ib] = -1.0e30f; ssum[ib] = 0.0f; }
@@ -525,6 +540,14 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
     constexpr bool ragged = decltype(ragged_tile)::value;
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) {
+      if constexpr (KEPT) {  // (a cell's first tile: nothing yet)
+        best1[ib] = at == 0 ? 0ull : sh_best[ib][tid][0];
+        best2[ib] = at == 0 ? 0ull : sh_best[ib][tid][1];
+        if constexpr (SAMPLING) {
+          sref[ib] = at == 0 ? -1.0e30f : sh_part[ib][tid][0];
+          ssum[ib] = at == 0 ? 0.0f : sh_part[ib][tid][1];
+        }
+      }
       int k1 = kPast, k2 = kPast;
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) {
@@ -553,24 +576,25 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
       const float top = lm_key_value(k1);
       if (any) top2_insert(best1[ib], best2[ib], make_key(top, e1));
       if (!ragged || e2 < V) top2_insert(best1[ib], best2[ib], make_key(lm_key_value(k2), e2));
+      if constexpr (KEPT) { sh_best[ib][tid][0] = best1[ib]; sh_best[ib][tid][1] = best2[ib]; }
       if (SAMPLING) {
         // Second pass over the block row, now that its maximum is known: move the reference if the maximum
         // has risen above it (references are integers, so sums against different ones combine by exact
-        // powers of two), store the rounded logits -- four consecutive entries, 8 bytes, at a time; lane
-        // l + 32 holds the next four; rows past the end fall outside the buffer -- and add their exponentials.
+        // powers of two), add the exponentials of the rounded logits and store these; rows past the end fall outside the buffer.
         // (V is a multiple of 8: four entries are inside the vocabulary or outside it together.)
         const float nref = any ? fmaxf(sref[ib], __builtin_ceilf(top * c)) : sref[ib];
         ssum[ib] *= __builtin_amdgcn_exp2f(sref[ib] - nref);
         sref[ib] = nref;
-        // (32 rows are one buffer, of less than 2^32 bytes; a vocabulary beyond 2^25 takes the form with pointers)
+        // (32 rows are one buffer, of less than 2^32 bytes; a vocabulary beyond 2^25 takes the form with pointers.  The number of
+        // rows is made a scalar: a median of three is a vector instruction, and with one word of the buffer in a vector
+        // register every store becomes a loop over the lanes' buffers.)
         const int row32 = m0 + __builtin_amdgcn_readfirstlane(wm) * WM + ib * 32;
+        const int rows32 = __builtin_amdgcn_readfirstlane(max(0, min(32, M - row32)));
         const __amdgpu_buffer_rsrc_t o_rows = __builtin_amdgcn_make_buffer_rsrc(
-            logits_out + static_cast<size_t>(row32) * V, 0, static_cast<int>(static_cast<unsigned int>(max(0, min(32, M - row32))) * V * 2u),
-            kLmBufferFlags);
-        // (which 16 bytes of the block's rows this lane writes out: rows lane/4 and lane/4 + 16)
-        const int orow = lane >> 2, ochunk = lane & 3;
-        const unsigned int first = RING ? (static_cast<unsigned int>(orow) * V + n0 + wn * WN + ochunk * 8) * 2
-                                        : (static_cast<unsigned int>(l32) * V + nbase) * 2;
+            logits_out + static_cast<size_t>(row32) * V, 0, static_cast<int>(static_cast<unsigned int>(rows32) * V * 2u), kLmBufferFlags);
+        // (which 16 bytes of the block's rows this lane writes out, lm_out_lines: of rows lane%16 and lane%16 + 16)
+        const int ochunk = ((lane >> 4) & 1) + 2 * half;
+        const unsigned int first = (static_cast<unsigned int>(lane & 15) * V + n0 + wn * WN + ochunk * 8) * 2;
         bf16_t* out = logits_out + static_cast<size_t>(row32 + l32) * V + nbase;
         float add = 0.0f;
 #pragma unroll
@@ -579,20 +603,6 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
           lm_rounded<BY_ASM>(acc[jb][ib], w);
           int left = V - nbase;
           if (ragged) asm volatile("" : "+v"(left));
-          // The ring's forms: out through LDS, 64 bytes of a row per store instead of 16 (places swapped so that neither side
-          // finds two rows on one bank): 60 rows x 4096 x 151 936 242 us per call before, 235 so.  Through registers, with 192
-          // rows, it is 0.7 % slower: the spills it brings cost what the stores save.
-          u32x4 line[2];
-          if constexpr (RING) {
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-              *reinterpret_cast<uint2*>(&sh_out[wave][l32][(q4 ^ ((l32 >> 2) & 3)) * 8 + 4 * half]) = make_uint2(w[2 * q4], w[2 * q4 + 1]);
-            lm_wave_order();
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-              line[i] = *reinterpret_cast<const u32x4*>(&sh_out[wave][orow + 16 * i][(ochunk ^ ((orow >> 2) & 3)) * 8]);
-            lm_wave_order();
-          }
 #pragma unroll
           for (int q4 = 0; q4 < 4; ++q4) {
             const uint32_t w0 = w[2 * q4], w1 = w[2 * q4 + 1];
@@ -600,8 +610,6 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
             const bool inside = !ragged || e < left;
             if constexpr (WIDE) {
               if (inside && row32 + l32 < M) *reinterpret_cast<uint2*>(out + e) = make_uint2(w0, w1);
-            } else if constexpr (!RING) {
-              __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{w0, w1}, o_rows, inside ? static_cast<int>(first + 2 * e) : -1, 0, 0);
             }
             const float x0 = __uint_as_float(w0 << 16), x1 = __uint_as_float(w0 & 0xFFFF0000u);
             const float x2 = __uint_as_float(w1 << 16), x3 = __uint_as_float(w1 & 0xFFFF0000u);
@@ -611,7 +619,9 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
                                 __builtin_amdgcn_exp2f(__builtin_fmaf(x3, c, -nref)));
             add += inside ? four : 0.0f;
           }
-          if constexpr (RING) {
+          if constexpr (!WIDE) {
+            u32x4 line[2];
+            lm_out_lines(w, line);
             const bool inside = !ragged || n0 + wn * WN + jb * 32 + ochunk * 8 < V;
 #pragma unroll
             for (int i = 0; i < 2; ++i)
@@ -621,6 +631,7 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
           __builtin_amdgcn_sched_barrier(0);
         }
         ssum[ib] += add;
+        if constexpr (KEPT) { sh_part[ib][tid][0] = sref[ib]; sh_part[ib][tid][1] = ssum[ib]; }
       }
     }
     };
@@ -637,6 +648,11 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
     double rS[IB];
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) {
+      if constexpr (KEPT) {
+        best1[ib] = sh_best[ib][tid][0];
+        best2[ib] = sh_best[ib][tid][1];
+        if constexpr (SAMPLING) { sref[ib] = sh_part[ib][tid][0]; ssum[ib] = sh_part[ib][tid][1]; }
+      }
       const unsigned long long o1 = __shfl_xor(best1[ib], 32, kWave), o2 = __shfl_xor(best2[ib], 32, kWave);
       r1[ib] = best1[ib]; r2[ib] = best2[ib];
       top2_insert(r1[ib], r2[ib], o1);
@@ -651,11 +667,13 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
         if (bS > 0.0f) absorb_sum(rR[ib], rS[ib], bR, static_cast<double>(bS));
       }
       if (wn == 1 && half == 0) {
-        sh_key[wm][ib][l32][0] = r1[ib];
-        sh_key[wm][ib][l32][1] = r2[ib];
-        if (SAMPLING) {
-          sh_sum[wm][ib][l32][0] = rR[ib];
-          sh_sum[wm][ib][l32][1] = static_cast<float>(rS[ib]);
+        unsigned long long* key = KEPT ? sh_best[KEPT ? ib : 0][KEPT ? tid : 0] : sh_key[wm][ib][l32];
+        key[0] = r1[ib];
+        key[1] = r2[ib];
+        if constexpr (SAMPLING) {
+          float* sum = KEPT ? sh_part[KEPT ? ib : 0][KEPT ? tid : 0] : sh_sum[wm][ib][l32];
+          sum[0] = rR[ib];
+          sum[1] = static_cast<float>(rS[ib]);
         }
       }
       best1[ib] = 0ull; best2[ib] = 0ull; sref[ib] = -1.0e30f; ssum[ib] = 0.0f;
@@ -666,18 +684,19 @@ __device__ __forceinline__ void lmhead_body(const bf16_t* __restrict__ hidden, c
       const int row = m0 + wm * WM + ib * 32 + l32;
       if (wn == 0 && half == 0 && row < M) {
         unsigned long long k1 = r1[ib], k2 = r2[ib];
-        top2_insert(k1, k2, sh_key[wm][ib][l32][0]);
-        top2_insert(k1, k2, sh_key[wm][ib][l32][1]);
+        const unsigned long long* key = KEPT ? sh_best[KEPT ? ib : 0][KEPT ? tid + kWave : 0] : sh_key[wm][ib][l32];
+        top2_insert(k1, k2, key[0]);
+        top2_insert(k1, k2, key[1]);
         Partial out;
         out.z1 = neg_inf(); out.id1 = -1; out.z2 = neg_inf(); out.id2 = -1; out.s = 0.0f; out.ref = 0.0f;
         const Partial empty = out;
         if (k1 != 0ull) { out.z1 = key_value(k1); out.id1 = key_index(k1); }
         if (k2 != 0ull) { out.z2 = key_value(k2); out.id2 = key_index(k2); }
-        if (SAMPLING) {
+        if constexpr (SAMPLING) {
           float R = rR[ib];
           double S = rS[ib];
-          const float oS = sh_sum[wm][ib][l32][1];
-          if (oS > 0.0f) absorb_sum(R, S, sh_sum[wm][ib][l32][0], static_cast<double>(oS));
+          const float* sum = KEPT ? sh_part[KEPT ? ib : 0][KEPT ? tid + kWave : 0] : sh_sum[wm][ib][l32];
+          if (sum[1] > 0.0f) absorb_sum(R, S, sum[0], static_cast<double>(sum[1]));
           if (S > 0.0) { out.s = static_cast<float>(S); out.ref = R; }
         }
         Partial* to = partials + static_cast<size_t>(row) * grid.parts;

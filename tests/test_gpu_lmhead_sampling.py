@@ -97,6 +97,22 @@ def test_dense_draft_distribution(i):
     run_case(f"lm_sampling_dense{i}", seed=320 + i, temperature=(0.8, 1.0)[i % 2], dense_q=True, **SHAPES[i])
 
 
+# Rows and entries on both sides of what one store of the logits takes (16 rows x 32 entries), and cells of several tiles.
+STORE_EDGES = [
+    dict(B=1, N=17, H=128, V=520, tree={"kind": "chain"}),
+    dict(B=3, N=5, H=128, V=264, tree={"kind": "chain"}),
+    dict(B=1, N=31, H=256, V=3000, tree={"kind": "chain"}),
+    dict(B=3, N=11, H=256, V=40008, tree={"kind": "chain"}),
+    dict(B=9, N=23, H=128, V=70000, tree={"kind": "chain"}),   # 192 + 15 rows
+    dict(B=15, N=31, H=128, V=66048, tree={"kind": "chain"}),  # 2 x 192 + 81 rows, whole tiles
+]
+
+
+@pytest.mark.parametrize("i", range(len(STORE_EDGES)))
+def test_stored_logits_at_the_edges_of_a_store(i):
+    run_case(f"lm_sampling_store{i}", seed=340 + i, temperature=(1.0, 0.7)[i % 2], **STORE_EDGES[i])
+
+
 def test_work_groups_that_do_not_wait_for_their_partners():
     run_case("lm_sampling_nowait", seed=331, temperature=1.0, dense_q=True, spin_limit=1, **SHAPES[1])
 
