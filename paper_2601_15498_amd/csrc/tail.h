@@ -708,6 +708,23 @@ inline int walk_slice(int V, int G, bool vec) { return ((row_groups(V, vec) + G 
 constexpr float kClosedFormMinNorm = 0.1f; // one-hot residual: Z = 1 - f(x) is used when at least this
 constexpr int kMaxResident = 3;            // groups of eight elements a thread can keep in registers
 
+// Where the results go, read from the kernel's arguments again at every stage that writes some (LATE): ten addresses kept in scalar
+// registers from the first write to the last were half of what a resident walk moved to vector lanes and back (81 -> 35
+// registers).  One tree of 60 nodes x 151 936 19.19 -> 18.94 us per call, 16 trees with dense q 68.01 -> 67.65, 8 trees x
+// 100 001 26.67 -> 26.10.  The streamed walk keeps them: 128 dense chains 69.04, read again 69.21.
+// (The arguments are one TailArgs at the start of the kernel's argument segment.)
+typedef const __attribute__((address_space(4))) TailArgs* LateArgs;
+template <bool LATE>
+__device__ __forceinline__ auto out_args(const TailArgs& a) {
+  if constexpr (LATE) {
+    unsigned long long at = reinterpret_cast<unsigned long long>(__builtin_amdgcn_kernarg_segment_ptr());
+    asm volatile("" : "+s"(at));
+    return reinterpret_cast<LateArgs>(at);
+  } else {
+    return &a;
+  }
+}
+
 // RES: every slice is at most RES groups per thread and stays in registers (decided by the host from G and V), 0: it is
 // streamed.  Two of them where they are enough -- few requests, or a small vocabulary -- carry two thirds of the
 // loads, exponentials, registers and code of three, and the walk is bound by what a wave has to issue and to fetch: 8
@@ -790,6 +807,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       }
     }
     const float u_draw = tid == 0 ? ureq[N] : 0.0f;  // the uniform of the final draw
+    const auto to = out_args<RESIDENT>(a);
     // (behind the requests: the barrier has nobody wait for them)
     if (tid == 0) sh_bad = 0;
     for (int i = tid; i < N; i += NT) sh_first[i] = kNoChild;
@@ -819,17 +837,17 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
         if (bad) atomicOr(&sh_bad, bad);
         else if (i > 0) atomicMin(&sh_first[p], i);
         if (g == 0) {
-          a.mask[r] = i == 0 ? 1 : 0;
-          a.path[r] = -1;
-          if (a.dec) a.dec[r] = 0;
+          to->mask[r] = i == 0 ? 1 : 0;
+          to->path[r] = -1;
+          if (to->dec) to->dec[r] = 0;
         }
       }
     }
     auto emit = [&](int row, const mars_row_stat& st) {
       sh_st[row] = st;
       if (g == 0) {
-        a.stats_ws[rb + row] = st;
-        if (a.stats) a.stats[rb + row] = st;
+        to->stats_ws[rb + row] = st;
+        if (to->stats) to->stats[rb + row] = st;
       }
     };
     if (few) {
@@ -841,8 +859,8 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
           const mars_row_stat st = merge_row_few(pq[t], a.splits, a.c, a.ind, theta);
           sh_st[i] = st;
           if (g == 0) {
-            a.stats_ws[rb + i] = st;
-            if (a.stats) a.stats[rb + i] = st;
+            to->stats_ws[rb + i] = st;
+            if (to->stats) to->stats[rb + i] = st;
           }
         }
       }
@@ -887,6 +905,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   const float c = a.c;
   const float* u = sh_u;
 
+  const auto walk_to = out_args<RESIDENT>(a);
   int cnode = 0, plen = 0, passes = 0, nexch = 0;
   float last_norm = 0.0f;
   bool pending_norm = false;  // the last rejection's normaliser is still to come out of the final pass
@@ -1000,10 +1019,10 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       const int code0 = !leaf ? __builtin_amdgcn_readfirstlane(static_cast<int>(sh_code0[k1])) : 0;
       if (code0 != 0) {  // the first child is accepted: nothing else at this node matters
         if (tid == 0 && g == 0) {
-          a.mask[rb + k1] = 1;
-          a.path[rb + plen] = k1;
-          if (a.dec) a.dec[rb + k1] = static_cast<uint8_t>(code0);
-          if (a.out_tok) a.out_tok[rb + plen] = sh_tok[k1];
+          walk_to->mask[rb + k1] = 1;
+          walk_to->path[rb + plen] = k1;
+          if (walk_to->dec) walk_to->dec[rb + k1] = static_cast<uint8_t>(code0);
+          if (walk_to->out_tok) walk_to->out_tok[rb + plen] = sh_tok[k1];
         }
         cnode = k1;
         plen += 1;
@@ -1061,10 +1080,10 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       }
       if (code) {
         if (tid == 0 && g == 0) {
-          a.mask[rb + k] = 1;
-          a.path[rb + plen] = k;
-          if (a.dec) a.dec[rb + k] = static_cast<uint8_t>(code);
-          if (a.out_tok) a.out_tok[rb + plen] = x;
+          walk_to->mask[rb + k] = 1;
+          walk_to->path[rb + plen] = k;
+          if (walk_to->dec) walk_to->dec[rb + k] = static_cast<uint8_t>(code);
+          if (walk_to->out_tok) walk_to->out_tok[rb + plen] = x;
         }
         accepted = k;
         break;
@@ -1153,6 +1172,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   }
 
   // ---------------------------------------------------------------- inverse-CDF draw from f at cnode
+  const auto draw_to = out_args<RESIDENT>(a);
   const mars_row_stat st = sh_st[cnode];
   // Without a rejection at this node f is the plain softmax: the draft distribution is not read.
   // (A resident slice that was loaded for a rejection already holds it.)
@@ -1282,14 +1302,14 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   }
   if (pending_norm) last_norm = static_cast<float>(total);
   const double target = static_cast<double>(u[N]) * total;
-  if (g == 0 && tid == 0) a.len[b] = plen;
+  if (g == 0 && tid == 0) draw_to->len[b] = plen;
   // (The request's status was set to MARS_REQ_OK by the row reduction of this call.)
   // V_out (Alg. 1): the accepted drafts were written as they were accepted; the first work-group
   // pads behind the slot of the final token, which the work-group that draws it fills in.  (No
   // address is written by two work-groups.)
-  if (g == 0 && a.out_tok) {
-    for (int j = plen + 1 + tid; j < N; j += NT) a.out_tok[rb + j] = -1;
-    if (tid == 0) a.out_len[b] = plen + 1;
+  if (g == 0 && draw_to->out_tok) {
+    for (int j = plen + 1 + tid; j < N; j += NT) draw_to->out_tok[rb + j] = -1;
+    if (tid == 0) draw_to->out_len[b] = plen + 1;
   }
   if (g != owner) return;
 
@@ -1401,15 +1421,15 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   }
   if (pick < 0) { pick = st.id1; pick_f = 0.0f; }  // degenerate: no mass anywhere
   if (lane == 0) {
-    a.bonus[b] = pick;
-    if (a.out_tok) a.out_tok[rb + plen] = pick;
-    if (a.diag) {
+    draw_to->bonus[b] = pick;
+    if (draw_to->out_tok) draw_to->out_tok[rb + plen] = pick;
+    if (draw_to->diag) {
       mars_req_diag dg;
       dg.bonus_prob = total > 0.0 ? static_cast<float>(static_cast<double>(pick_f) / total) : 0.0f;
       dg.last_residual_norm = last_norm;
       dg.residual_passes = passes;
       dg.last_node = cnode;
-      a.diag[b] = dg;
+      draw_to->diag[b] = dg;
     }
   }
 }
