@@ -237,6 +237,12 @@ struct Chain {
   int rtok[kChainRegs];
   float rinv[kChainRegs];
 };
+// Whether the rejection that becomes entry n of a node's chain ends with a barrier even if it exchanges nothing.  Thread 0
+// writes the entries in LDS and every wave reads them when it gets there, so two orders need one: behind an entry in LDS,
+// whose readers are the tests that follow; and behind the last entry in registers, since a wave may still be testing the previous
+// node's last child with that node's entries when another one is here -- no wave gets to this node's first write to
+// LDS before all have left the previous node.  (Chains of three rejections and less, the ordinary ones, have no barrier.)
+__device__ __host__ __forceinline__ constexpr bool chain_barrier(int n) { return n + 1 >= kChainRegs; }
 
 // f(v) for the current node: softmax term, then the residual chain.
 __device__ __forceinline__ float eval_f(float z, float q, int v, float z1, float c, float inv_S, bool dense,
@@ -1095,8 +1101,8 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       //    left out (factor 1) and Z comes out of the final pass as the total of what is left.
       //  * Otherwise Z is summed over the row, every work-group of the request taking a slice.
       float inv;
-      // (a barrier behind an exchange, whose staging arrays are used again, and behind a chain entry that lives in LDS)
-      bool sync = rv.ch.n >= kChainRegs;
+      // (a barrier behind an exchange, whose staging arrays are used again, and where the chain asks for one)
+      bool sync = chain_barrier(rv.ch.n);
       if (!dense && 1.0f - fx >= kClosedFormMinNorm) {
         last_norm = 1.0f - fx;
         inv = 1.0f / last_norm;

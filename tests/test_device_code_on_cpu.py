@@ -35,6 +35,12 @@ def test_the_walk_reads_rows_and_nothing_around_them(tmp_path):
     assert " 0 failed" in out, out
 
 
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_the_walk_orders_its_residual_chain(tmp_path):
+    out = run_on_cpu("walk_order_main.hip", tmp_path)
+    assert " 0 out of order, a missing barrier shows" in out, out
+
+
 # B, N, V, H, sampling; then what the case stands for: bands of slabs, launches, cells shared by two work-groups
 PLANS = [
     (1, 40, 5003, 128, 0, 1, 1, 0), (1, 100, 60001, 128, 0, 1, 1, 0), (1, 520, 33011, 128, 0, 1, 1, 0),
