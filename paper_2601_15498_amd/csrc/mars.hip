@@ -158,17 +158,22 @@ static ClearArgs clear_args(char* ws, const Layout& L, int B, int N, int K) {
 // The forms of the fused kernel and what a unit (bm rows x bn entries) takes in each, us: for a step of 64 hidden elements,
 // alone and what is added when all compute units are at work, and for a unit beside its steps, greedy and sampling; and the
 // rate at which the weight streams through the chip in this form, TB/s.  Fitted to 2 200 shapes (rows 4-2 048, V 1 000-152 000,
-// H 1 024-4 096, both modes, all forms that make sense for the shape): the form with the least
-// time by these figures is 1.3 % slower than the best one on average.
+// H 1 024-4 096, both modes, all forms that make sense for the shape).  The figures are good to some 10 %, so the choice is judged by its
+// worst shape too: 3 381 shapes (rows 4-2 048, V 1 000-152 000, H 512-5 120, both modes; half with a weight that comes from memory, half with
+// the same weight call after call), every form timed in turn.  Against the form through registers the one chosen takes 0.882 times the time (geometric
+// mean; the best one 0.873) and is more than 2 % slower on 31 shapes, 9.5 % at worst.
 // The first four are the kernel that stages through registers, with a tile of 256 (which of them: lm_plan); the others the ring (lmhead.h), which wins
 // where there are few units -- a small vocabulary, or up to 256 rows -- since its tiles are narrower and its requests go out earlier, and
 // where the weight is streamed once: 56 rows x 4096 x 2 250 45 -> 22 us per call, 40 x 4096 x 32 000 74 -> 55, 120 x 4096 x 32 000 73 -> 58, 60 x 4096 x
-// 151 936 225 -> 190 (under sampling 254 -> 235), 1 000 shapes drawn as above 1.18 times as fast on average.
+// 151 936 214 -> 188 (under sampling 254 -> 235).
+// The sampling form of 192 rows takes 9.0 us for a unit beside its steps since its stores leave 64 bytes of a row at a time; with the 11.6 of
+// before, many rows with few hidden elements went to the ring (1 984 rows x 1024 x 64 000 320 us per call instead of 303, 1 620 x 640 x 62 816 213
+// instead of 194; 75 shapes more than 2 % slower, 18 % at worst).
 struct LmForm { int bm, bn, stages; float step, step_full, unit, unit_sampling, rate; };
 constexpr LmForm kLmForms[] = {
     {64, 256, 0, 0.48f, 0.28f, 0.0f, 0.0f, 5.4f},
     {128, 256, 0, 0.69f, 0.22f, 0.4f, 5.4f, 4.7f},
-    {192, 256, 0, 0.63f, 0.54f, 2.1f, 11.6f, 5.0f},
+    {192, 256, 0, 0.63f, 0.54f, 2.1f, 9.0f, 5.0f},
     {256, 256, 0, 0.80f, 0.68f, 4.4f, 0.0f, 5.0f},  // (greedy: the sampling form does not fit the registers)
     {64, 64, 8, 0.081f, 0.18f, 0.0f, 0.6f, 6.5f},
     {64, 128, 5, 0.15f, 0.30f, 0.0f, 1.2f, 6.4f},

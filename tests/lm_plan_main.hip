@@ -2,8 +2,9 @@
 // they are (every HIP call below stands in for the runtime and launches nothing), and what each launch's work-groups
 // would do is gone through with the kernel's own cell arithmetic (csrc/lmhead.h: lm_cell).  Every tile of every slab has
 // to belong to exactly one work-group and every partial result of every row to be written exactly once.
-// Arguments: "B N V H sampling bands launches shared" per case, the last three what the case must show ("-" = anything): bands of
-// slabs, launches, and whether a cell is shared between two work-groups.
+// Arguments: "B N V H sampling bands launches shared form" per case, the last four what the case must show ("-" = anything): bands
+// of slabs, launches, whether a cell is shared between two work-groups, and the form of the kernel that runs: rows x entries of a
+// unit, "ring" behind it where the operands go straight to LDS, and "-once" where the weight is read past the caches.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -29,6 +30,7 @@ struct Launch {
 };
 static std::vector<Launch> launches;
 static std::map<const void*, int> heights;  // the fused kernel's forms
+static std::map<const void*, std::string> names;
 static dim3 call_grid;
 
 extern "C" {
@@ -62,10 +64,18 @@ hipError_t hipGetSymbolAddress(void**, const void*) { return hipErrorInvalidSymb
 }
 
 template <int BM, bool S, bool W = false>
-static void form() { heights[reinterpret_cast<const void*>(&mars::lmhead_reduce_kernel<BM, S, W>)] = BM; }
+static void form() {
+  const void* kernel = reinterpret_cast<const void*>(&mars::lmhead_reduce_kernel<BM, S, W>);
+  heights[kernel] = BM;
+  names[kernel] = std::to_string(BM) + "x256" + (W ? "-wide" : "");
+}
 
 template <int BM, int BN, int STAGES, bool S, bool ONCE>
-static void ring_form() { heights[reinterpret_cast<const void*>(&mars::lmhead_ring_kernel<BM, BN, STAGES, S, ONCE>)] = BM; }
+static void ring_form() {
+  const void* kernel = reinterpret_cast<const void*>(&mars::lmhead_ring_kernel<BM, BN, STAGES, S, ONCE>);
+  heights[kernel] = BM;
+  names[kernel] = std::to_string(BM) + "x" + std::to_string(BN) + "ring" + (ONCE ? "-once" : "");
+}
 template <int BM, int BN, int STAGES>
 static void ring() {
   ring_form<BM, BN, STAGES, false, false>(); ring_form<BM, BN, STAGES, false, true>();
@@ -77,7 +87,8 @@ static int fail(const char* what, int B, int N, int V, int H, int sampling) {
   return 1;
 }
 
-static int check(int B, int N, int V, int H, int sampling, const std::string& bands, const std::string& many, const std::string& shared) {
+static int check(int B, int N, int V, int H, int sampling, const std::string& bands, const std::string& many, const std::string& shared,
+                 const std::string& form) {
   using namespace mars;
   launches.clear();
   char* const base = reinterpret_cast<char*>(1ul << 40);  // (nothing is read or written)
@@ -151,6 +162,8 @@ static int check(int B, int N, int V, int H, int sampling, const std::string& ba
     std::printf("%d bands, %zu launches, %sshared cells\n", nbands, launches.size(), any_shared ? "" : "no ");
     return fail("not the plan the case stands for", B, N, V, H, sampling);
   }
+  const std::string& runs = names[launches[0].kernel];
+  if (form != "-" && form != runs) return fail(("another form than " + form + " (" + runs + ")").c_str(), B, N, V, H, sampling);
   return 0;
 }
 
@@ -159,9 +172,9 @@ int main(int argc, char** argv) {
   form<64, true>(); form<64, true, true>(); form<128, true>(); form<192, true>();
   ring<64, 64, 8>(); ring<64, 128, 5>(); ring<64, 256, 3>(); ring<128, 128, 4>(); ring<128, 256, 3>(); ring<256, 128, 3>();
   int failed = 0, cases = 0;
-  for (int i = 1; i + 7 < argc; i += 8, ++cases)
+  for (int i = 1; i + 8 < argc; i += 9, ++cases)
     failed += check(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoi(argv[i + 2]), std::atoi(argv[i + 3]), std::atoi(argv[i + 4]),
-                    argv[i + 5], argv[i + 6], argv[i + 7]);
+                    argv[i + 5], argv[i + 6], argv[i + 7], argv[i + 8]);
   std::printf("%d cases, %d failed\n", cases, failed);
   return failed != 0;
 }

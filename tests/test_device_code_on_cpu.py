@@ -41,6 +41,11 @@ def test_the_walk_orders_its_residual_chain(tmp_path):
     assert " 0 out of order, a missing barrier shows" in out, out
 
 
+def check_plans(tmp_path, cases):
+    out = run_on_cpu("lm_plan_main.hip", tmp_path, options=["-no-hip-rt"], args=[x for c in cases for x in c])
+    assert f"{len(cases)} cases, 0 failed" in out, out
+
+
 # B, N, V, H, sampling; then what the case stands for: bands of slabs, launches, cells shared by two work-groups
 PLANS = [
     (1, 40, 5003, 128, 0, 1, 1, 0), (1, 100, 60001, 128, 0, 1, 1, 0), (1, 520, 33011, 128, 0, 1, 1, 0),
@@ -65,5 +70,20 @@ def test_lm_head_work_is_dealt_out_exactly_once(tmp_path):
         sampling = rng.randint(0, 1)
         v = int(2 ** rng.uniform(3, 18.5)) // (8 if sampling else 1) * (8 if sampling else 1)
         cases.append((max(1, rows // n), n, max(8, v), 128 * rng.randint(1, 64), sampling, "-", "-", "-"))
-    out = run_on_cpu("lm_plan_main.hip", tmp_path, options=["-no-hip-rt"], args=[x for c in cases for x in c])
-    assert f"{len(cases)} cases, 0 failed" in out, out
+    check_plans(tmp_path, [c + ("-",) for c in cases])
+
+
+# Sizes at which another form was measured to be slower, with a weight that lies in the cache and with one that does not: B, N,
+# V, H, sampling and the form.  Many rows under sampling with few hidden elements; and sizes that keep the form they had.
+FORMS = [
+    (32, 62, 64000, 1024, 1, "192x256"), (32, 62, 100000, 1024, 1, "192x256"), (32, 62, 128256, 1024, 1, "192x256"),
+    (32, 62, 151936, 1024, 1, "192x256"), (37, 55, 9496, 640, 1, "192x256"), (36, 45, 62816, 640, 1, "192x256"),
+    (1, 60, 12000, 4096, 0, "64x64ring"), (1, 60, 32000, 4096, 0, "64x128ring"), (2, 60, 32000, 4096, 1, "128x128ring"),
+    (1, 60, 151936, 4096, 0, "64x256ring-once"), (16, 60, 151936, 4096, 0, "192x256"), (16, 60, 151936, 4096, 1, "192x256"),
+    (256, 26, 151936, 4096, 0, "256x256"),
+]
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_lm_head_takes_the_form_that_was_measured_to_be_faster(tmp_path):
+    check_plans(tmp_path, [c[:5] + ("-", "-", "-") + c[5:] for c in FORMS])
