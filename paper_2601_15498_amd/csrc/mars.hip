@@ -159,16 +159,18 @@ static ClearArgs clear_args(char* ws, const Layout& L, int B, int N, int K) {
 // alone and what is added when all compute units are at work, and for a unit beside its steps, greedy and sampling; and the
 // rate at which the weight streams through the chip in this form, TB/s.  Fitted to 2 200 shapes (rows 4-2 048, V 1 000-152 000,
 // H 1 024-4 096, both modes, all forms that make sense for the shape).  The figures are good to some 10 %, so the choice is judged by its
-// worst shape too: 3 381 shapes (rows 4-2 048, V 1 000-152 000, H 512-5 120, both modes; half with a weight that comes from memory, half with
-// the same weight call after call), every form timed in turn.  Against the form through registers the one chosen takes 0.882 times the time (geometric
-// mean; the best one 0.873) and is more than 2 % slower on 31 shapes, 9.5 % at worst.
+// worst shape too: 4 780 shapes (rows 4-2 048, V 1 000-152 000, H 512-5 120, both modes; half with a weight that comes from memory, half with
+// the same weight call after call), every form timed in turn.  Against the form through registers the one chosen takes 0.881 times the time (geometric
+// mean; the best one 0.872) and is more than 2 % slower on 36 shapes, 8.1 % at worst.  30 of these find their weight in the cache, most with a
+// vocabulary of 32 000, which narrow tiles fill the chip with in one round: from memory they win there (60 rows x 4096 55.1 us, 63.3 with tiles
+// of 256 entries, 67.6 through registers), from the cache not always (9 rows x 4096 49.3, 43.9, 45.8), and nobody here knows which it is.
 // The first four are the kernel that stages through registers, with a tile of 256 (which of them: lm_plan); the others the ring (lmhead.h), which wins
 // where there are few units -- a small vocabulary, or up to 256 rows -- since its tiles are narrower and its requests go out earlier, and
 // where the weight is streamed once: 56 rows x 4096 x 2 250 45 -> 22 us per call, 40 x 4096 x 32 000 74 -> 55, 120 x 4096 x 32 000 73 -> 58, 60 x 4096 x
 // 151 936 214 -> 188 (under sampling 254 -> 235).
 // The sampling form of 192 rows takes 9.0 us for a unit beside its steps since its stores leave 64 bytes of a row at a time; with the 11.6 of
 // before, many rows with few hidden elements went to the ring (1 984 rows x 1024 x 64 000 320 us per call instead of 303, 1 620 x 640 x 62 816 213
-// instead of 194; 75 shapes more than 2 % slower, 18 % at worst).
+// instead of 194).  Without this and the merging (lm_plan) 103 shapes are more than 2 % slower, 18 % at worst.
 struct LmForm { int bm, bn, stages; float step, step_full, unit, unit_sampling, rate; };
 constexpr LmForm kLmForms[] = {
     {64, 256, 0, 0.48f, 0.28f, 0.0f, 0.0f, 5.4f},
@@ -199,6 +201,7 @@ constexpr int kDies = 8;
 constexpr int kLmBand = 13;
 constexpr int kLmFormCount = sizeof(kLmForms) / sizeof(kLmForms[0]);
 constexpr double kLmCallUs = 12.0;  // launch and per-request kernel
+constexpr double kLmMergeGreedy = 0.01, kLmMergeSampling = 0.02;  // for a partial result of 64 rows
 constexpr double kLmKnown = 0.93;   // on a near tie the form through registers (several slabs, greedy: the fit is up to 5 % off)
 struct LmUnits { long slabs, tiles, count, rounds; };
 static LmUnits lm_units(const LmForm& m, long rows, int V) {
@@ -217,7 +220,14 @@ static double lm_time(const LmForm& m, long rows, int V, int H, bool sampling) {
   const double stream = static_cast<double>(V) * H * 2e-6 / m.rate;
   return std::sqrt(std::sqrt(work * work * work * work + stream * stream * stream * stream)) + kLmCallUs;
 }
-static LmPlan lm_plan(long rows, int V, int H, bool sampling) {
+// us the per-request kernel takes to merge the partial results of a request's rows beyond what kLmCallUs holds: one
+// per column of tiles.  (Rows of up to 64 nodes were looked at.)
+static double lm_merge_time(const LmForm& m, long rows, int N, int V, bool sampling) {
+  const LmUnits u = lm_units(m, rows, V);
+  const long width = u.rounds < u.tiles ? u.rounds : u.tiles, columns = (u.tiles + width - 1) / width;
+  return (sampling ? kLmMergeSampling : kLmMergeGreedy) * static_cast<double>(columns) * (N < 64 ? N : 64) / 64.0;
+}
+static LmPlan lm_plan(long rows, int N, int V, int H, bool sampling) {
   LmPlan p;
   p.wide = H > (1 << 22) || V > (1 << 25);
   // Through registers, the slab height that takes the least time: units per work-group x time per unit.  Measured per unit at
@@ -233,14 +243,23 @@ static LmPlan lm_plan(long rows, int V, int H, bool sampling) {
     const double time = static_cast<double>(u.rounds) * (weight_bound ? 0.87 : kHeightCost[f]);
     if (least < 0.0 || time < least) { least = time; p.form = f; }
   }
-  // Against the ring's forms, by kLmForms.
-  double best = lm_time(kLmForms[p.form], rows, V, H, sampling) * kLmKnown;
+  // Against the ring's forms, by kLmForms; if one of them takes less, the one of them that leaves the least work to it and to the
+  // per-request kernel together.  (Tiles half as wide are twice as many partial results: 60 rows x 1024 x 32 000, whose weight
+  // stays in the cache, 22.5 us per call with tiles of 128 entries, 20.1 with 256, 20.6 through registers.  The merging counts among the
+  // ring's forms alone: counted against the form through registers as well, some shapes went back that take a quarter longer there.)
+  const double known = lm_time(kLmForms[p.form], rows, V, H, sampling) * kLmKnown;
+  double best = -1.0;
+  int ring = -1;
+  bool faster = false;
   for (int f = 4; f < kLmFormCount && !p.wide; ++f) {
     // (units of fewer steps than the ring has stages, and many slabs of 64 rows, were not looked at)
     if (kLmForms[f].stages > H / kLmBK || (kLmForms[f].bm == 64 && rows > 4 * 64)) continue;
     const double time = lm_time(kLmForms[f], rows, V, H, sampling);
-    if (time < best) { best = time; p.form = f; }
+    const double all = time + lm_merge_time(kLmForms[f], rows, N, V, sampling);
+    faster |= time < known;
+    if (ring < 0 || all < best) { best = all; ring = f; }
   }
+  if (faster) p.form = ring;
   const LmForm& form = kLmForms[p.form];
   p.bm = form.bm; p.bn = form.bn;
   p.tiles_n = static_cast<int>((static_cast<long>(V) + p.bn - 1) / p.bn);
@@ -318,7 +337,7 @@ struct LmLayout {
 static LmLayout lm_layout(int B, int N, int V, int H, int K, bool sampling) {
   LmLayout L;
   const long rows = static_cast<long>(B) * N;
-  L.plan = lm_plan(rows, V, H, sampling);
+  L.plan = lm_plan(rows, N, V, H, sampling);
   L.partials_off = 0;
   L.stats_off = align_up(static_cast<size_t>(rows) * L.plan.parts * sizeof(Partial));
   L.G = choose_groups(K * B, V);

@@ -74,10 +74,12 @@ def test_lm_head_work_is_dealt_out_exactly_once(tmp_path):
 
 
 # Sizes at which another form was measured to be slower, with a weight that lies in the cache and with one that does not: B, N,
-# V, H, sampling and the form.  Many rows under sampling with few hidden elements; and sizes that keep the form they had.
+# V, H, sampling and the form.  Many rows under sampling with few hidden elements; tiles so narrow that the merging of
+# their partial results costs more than they save; and sizes that keep the form they had.
 FORMS = [
     (32, 62, 64000, 1024, 1, "192x256"), (32, 62, 100000, 1024, 1, "192x256"), (32, 62, 128256, 1024, 1, "192x256"),
     (32, 62, 151936, 1024, 1, "192x256"), (37, 55, 9496, 640, 1, "192x256"), (36, 45, 62816, 640, 1, "192x256"),
+    (1, 60, 32000, 1024, 0, "64x256ring"), (1, 60, 32000, 1024, 1, "64x256ring"), (1, 40, 32000, 1024, 1, "64x256ring"),
     (1, 60, 12000, 4096, 0, "64x64ring"), (1, 60, 32000, 4096, 0, "64x128ring"), (2, 60, 32000, 4096, 1, "128x128ring"),
     (1, 60, 151936, 4096, 0, "64x256ring-once"), (16, 60, 151936, 4096, 0, "192x256"), (16, 60, 151936, 4096, 1, "192x256"),
     (256, 26, 151936, 4096, 0, "256x256"),
