@@ -89,3 +89,13 @@ FORMS = [
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
 def test_lm_head_takes_the_form_that_was_measured_to_be_faster(tmp_path):
     check_plans(tmp_path, [c[:5] + ("-", "-", "-") + c[5:] for c in FORMS])
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_lm_head_cases_of_the_gpu_tests_run_the_forms_they_name(tmp_path):
+    from tests.test_gpu_lmhead import RING_SHAPES
+    from tests.test_gpu_lmhead_sampling import STORE_EDGE_FORMS, STORE_EDGES
+    cases = [(1, rows, V, H, int(T > 0.0), form) for rows, V, H, T, form in RING_SHAPES]
+    assert len(STORE_EDGES) == len(STORE_EDGE_FORMS)
+    cases += [(c["B"], c["N"], c["V"], c["H"], 1, form) for c, form in zip(STORE_EDGES, STORE_EDGE_FORMS)]
+    check_plans(tmp_path, [c[:5] + ("-", "-", "-") + c[5:] for c in cases])

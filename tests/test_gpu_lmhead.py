@@ -431,24 +431,32 @@ def test_sizes_beyond_what_a_buffer_spans(N, V, H, T):
     assert np.array_equal(st["id2"], zn.argmax(axis=1)) and np.array_equal(st["z2"], zn.max(axis=1))
 
 
-# The forms that stage through the ring, by tile (rows x entries): 64 x 64, 64 x 128, 64 x 256, 128 x 128, 128 x 256 and
-# 256 x 128, each with one slab and with several where it takes both, the last slab and the last tile cut short; cells shared
-# by two work-groups; 17 and 128 rows at the end read the weight past the caches.  Small integers as above, so that
-# every sum and every rounding is exact.
+# The forms that stage through the ring, by tile (rows x entries), each greedy and under sampling, with one slab and with several,
+# the last slab and the last tile cut short; with cells shared by two work-groups; and with the weight read past the caches.
+# (Which form a call takes is a matter of measurement: that these take theirs is checked on the CPU, in
+# test_device_code_on_cpu.py.)  Small integers as above, so that every sum and every rounding is exact.
 RING_SHAPES = [
-    (40, 1003, 512, 0.0), (19, 1216, 896, 1.0), (122, 3261, 512, 0.0), (223, 1144, 640, 1.0),
-    (64, 17003, 512, 0.0), (117, 4401, 384, 0.0), (16, 24072, 768, 1.0), (79, 11808, 768, 1.0),
-    (64, 120001, 512, 0.0), (17, 61368, 768, 1.0), (89, 37384, 256, 1.0),
-    (128, 30001, 384, 0.0), (210, 42403, 256, 0.0), (277, 21912, 256, 1.0),
-    (68, 58641, 384, 0.0), (220, 63401, 896, 0.0), (69, 52432, 512, 1.0), (291, 54736, 256, 1.0),
-    (210, 17696, 1024, 1.0), (974, 4704, 768, 1.0), (710, 16440, 640, 1.0),
-    (17, 65537, 2048, 0.0), (128, 131200, 1024, 1.0),
+    (40, 1003, 512, 0.0, "64x64ring"), (19, 1216, 896, 1.0, "64x64ring"), (122, 3261, 512, 0.0, "64x64ring"),
+    (223, 1144, 640, 1.0, "64x64ring"), (2, 824, 164224, 0.0, "64x64ring-once"), (2, 976, 138368, 1.0, "64x64ring-once"),
+    (64, 17003, 512, 0.0, "64x128ring"), (117, 4401, 384, 0.0, "64x128ring"), (16, 24072, 768, 1.0, "64x128ring"),
+    (79, 11808, 768, 1.0, "64x128ring"), (17, 65537, 2048, 0.0, "64x128ring-once"), (3, 65568, 2048, 1.0, "64x128ring-once"),
+    (64, 120001, 512, 0.0, "64x256ring"), (76, 25039, 256, 0.0, "64x256ring"), (128, 30001, 384, 0.0, "64x256ring"),
+    (17, 61368, 768, 1.0, "64x256ring"), (89, 37384, 256, 1.0, "64x256ring"), (60, 151936, 4096, 0.0, "64x256ring-once"),
+    (60, 151936, 4096, 1.0, "64x256ring-once"),
+    (68, 13764, 384, 0.0, "128x128ring"), (210, 42403, 256, 0.0, "128x128ring"), (105, 16440, 1024, 1.0, "128x128ring"),
+    (277, 336, 1024, 1.0, "128x128ring"), (65, 12960, 10496, 0.0, "128x128ring-once"), (65, 14816, 9216, 1.0, "128x128ring-once"),
+    (68, 58641, 384, 0.0, "128x256ring"), (881, 4957, 1408, 0.0, "128x256ring"), (69, 52432, 512, 1.0, "128x256ring"),
+    (291, 54736, 256, 1.0, "128x256ring"), (210, 17696, 1024, 1.0, "128x256ring"), (974, 4704, 768, 1.0, "128x256ring"),
+    (710, 16440, 640, 1.0, "128x256ring"), (65, 106893, 1280, 0.0, "128x256ring-once"), (128, 131200, 1024, 1.0, "128x256ring-once"),
+    (128, 151936, 4096, 1.0, "128x256ring-once"),
+    (650, 10761, 512, 0.0, "256x128ring"), (991, 4152, 1152, 1.0, "256x128ring"), (196, 16392, 8320, 1.0, "256x128ring-once"),
+    (277, 21912, 256, 1.0, "192x256"), (220, 63401, 896, 0.0, "256x256"),  # (through registers)
 ]
 
 
-@pytest.mark.parametrize("rows,V,H,T", RING_SHAPES)
-def test_integer_logits_through_the_ring(rows, V, H, T):
-    say(f"[case] lmhead ring: rows={rows} V={V} H={H} T={T}")
+@pytest.mark.parametrize("rows,V,H,T,form", RING_SHAPES)
+def test_integer_logits_through_the_ring(rows, V, H, T, form):
+    say(f"[case] lmhead ring: rows={rows} V={V} H={H} T={T} {form}")
     g = torch.Generator(device=DEV)
     g.manual_seed(rows + V)
     h = (torch.rand((rows, H), generator=g, device=DEV) < 40.0 / H).float()

@@ -80,7 +80,7 @@ def run_case(name, seed=0, temperature=1.0, dense_q=False, pick=None, spin_limit
 SHAPES = [
     dict(B=4, N=9, H=256, V=5000, tree={"kind": "chain"}),                                   # one slab of 64, ragged tile
     dict(B=3, N=24, H=512, V=20000, tree={"kind": "tree", "depth": 4, "max_children": 4}),   # several tiles per run
-    dict(B=16, N=12, H=512, V=33000, tree={"kind": "chain"}),                                # 192 rows: one slab of 192
+    dict(B=16, N=12, H=512, V=33000, tree={"kind": "chain"}),                                # 192 rows: three slabs of 64 through the ring
     dict(B=9, N=43, H=256, V=4096, tree={"kind": "tree", "depth": 5, "max_children": 4}),    # 387 rows: seven slabs of 64, the last one ragged
     dict(B=1, N=1, H=128, V=104, tree={"kind": "chain"}),                                    # one row, one ragged tile
     dict(B=2, N=20, H=256, V=300008, tree={"kind": "chain"}),                                # 1172 tiles, the last one ragged
@@ -103,9 +103,13 @@ STORE_EDGES = [
     dict(B=3, N=5, H=128, V=264, tree={"kind": "chain"}),
     dict(B=1, N=31, H=256, V=3000, tree={"kind": "chain"}),
     dict(B=3, N=11, H=256, V=40008, tree={"kind": "chain"}),
-    dict(B=9, N=23, H=128, V=70000, tree={"kind": "chain"}),   # 192 + 15 rows
-    dict(B=15, N=31, H=128, V=66048, tree={"kind": "chain"}),  # 2 x 192 + 81 rows, whole tiles
+    dict(B=9, N=23, H=128, V=70000, tree={"kind": "chain"}),   # 128 + 79 rows
+    dict(B=15, N=31, H=128, V=66048, tree={"kind": "chain"}),  # 3 x 128 + 81 rows, whole tiles
+    dict(B=16, N=12, H=128, V=33000, tree={"kind": "chain"}),  # 192 rows: one slab of 192
+    dict(B=13, N=14, H=128, V=33008, tree={"kind": "chain"}),  # 182 rows of 192
+    dict(B=15, N=31, H=128, V=33008, tree={"kind": "chain"}),  # 2 x 192 + 81 rows, cells of two tiles
 ]
+STORE_EDGE_FORMS = ["64x256"] * 4 + ["128x256"] * 2 + ["192x256"] * 3  # (checked on the CPU, in test_device_code_on_cpu.py)
 
 
 @pytest.mark.parametrize("i", range(len(STORE_EDGES)))
