@@ -25,9 +25,11 @@
 // passing through registers.  With operands one step in LDS and one in registers a step of 64 rows took 0.77 us whatever its tile, a
 // trip to memory for every two steps.  A weight that is read once and does not fit the Infinity Cache is read
 // with the non-temporal hint: 6.9 TB/s instead of 6.2.  60 rows x 4096 x 151 936: bound by the weight, 1.24 GB in 178-180 us = 6.9
-// TB/s (through registers 203-205), and the per-request kernel behind it; 56 x 4096 x 2 250 45 -> 22 us per call.  Many
-// rows stay with the first form: two stages of 64 KB are all that fits LDS there, and one step of lead is too little (960
-// rows, 192 to a slab, greedy: 1 108 us against 940; rows of 64 bytes, four stages: 1 044).
+// TB/s (through registers 203-205), and the per-request kernel behind it; 56 x 4096 x 2 250 45 -> 22 us per call.
+// Many rows, greedy, mostly stay with the first form: with 256 x 256 two stages of 64 KB are all that fits LDS, and one step of lead
+// is too little (960 rows, 192 to a slab: 1 108 us against 940; rows of 64 bytes, four stages: 1 044).  Under sampling the first form
+// has at most 192 rows and no epilogue to spare, and where its slabs do not come out even the ring's 128 x 256 and 256 x 128 serve many rows
+// too: 512 or 1 024 x 4096 x 151 936, a third of all sizes between 257 and 2 048 rows (which: lm_plan).
 #pragma once
 
 #include <type_traits>

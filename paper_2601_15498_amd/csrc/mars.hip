@@ -165,8 +165,8 @@ static ClearArgs clear_args(char* ws, const Layout& L, int B, int N, int K) {
 // vocabulary of 32 000, which narrow tiles fill the chip with in one round: from memory they win there (60 rows x 4096 55.1 us, 63.3 with tiles
 // of 256 entries, 67.6 through registers), from the cache not always (9 rows x 4096 49.3, 43.9, 45.8), and nobody here knows which it is.
 // The first four are the kernel that stages through registers, with a tile of 256 (which of them: lm_plan); the others the ring (lmhead.h), which wins
-// where there are few units -- a small vocabulary, or up to 256 rows -- since its tiles are narrower and its requests go out earlier, and
-// where the weight is streamed once: 56 rows x 4096 x 2 250 45 -> 22 us per call, 40 x 4096 x 32 000 74 -> 55, 120 x 4096 x 32 000 73 -> 58, 60 x 4096 x
+// where there are few units -- a small vocabulary, or up to 256 rows -- since its tiles are narrower and its requests go out earlier,
+// where the weight is streamed once, and under sampling on many sizes of more rows: 56 rows x 4096 x 2 250 45 -> 22 us per call, 40 x 4096 x 32 000 74 -> 55, 120 x 4096 x 32 000 73 -> 58, 60 x 4096 x
 // 151 936 214 -> 188 (under sampling 254 -> 235).
 // The sampling form of 192 rows takes 9.0 us for a unit beside its steps since its stores leave 64 bytes of a row at a time; with the 11.6 of
 // before, many rows with few hidden elements went to the ring (1 984 rows x 1024 x 64 000 320 us per call instead of 303, 1 620 x 640 x 62 816 213
@@ -202,7 +202,9 @@ constexpr int kLmBand = 13;
 constexpr int kLmFormCount = sizeof(kLmForms) / sizeof(kLmForms[0]);
 constexpr double kLmCallUs = 12.0;  // launch and per-request kernel
 constexpr double kLmMergeGreedy = 0.01, kLmMergeSampling = 0.02;  // for a partial result of 64 rows
-constexpr double kLmKnown = 0.93;   // on a near tie the form through registers (several slabs, greedy: the fit is up to 5 % off)
+// On a near tie the form through registers: the ring has to be 7 % faster by figures good to some 10 %.  With 0.95 60 instead of 36 of 4 780 shapes
+// are more than 2 % slower than through registers, with 0.90 the mean loses 0.7 %.  (What it costs: 960 rows x 1024 x 2 256 27.9 us, 24.6 in the ring.)
+constexpr double kLmKnown = 0.93;
 struct LmUnits { long slabs, tiles, count, rounds; };
 static LmUnits lm_units(const LmForm& m, long rows, int V) {
   LmUnits u;

@@ -740,9 +740,10 @@ __device__ __forceinline__ auto out_args(const TailArgs& a) {
 // elements, 12.9 with two groups, 12.0 with one; 21 rows of 255 15.9, 16.5, 15.0; 960 rows of 13 19.5, 21.3, 19.0.
 // VEC: every group of eight elements is whole and aligned (RowView).
 // What a wave issues between two trips to memory is what the walk takes: a row with one partial result not merged, a rejected
-// first child not tested again, leaves without a look for children, no barrier behind a rejection that exchanges nothing, and in
-// the draw the prefixes of the tile sums taken once, the last element with mass looked for only where it is wanted: 2 us a
-// call, one tree of 60 nodes over 151 936 entries 20.0 -> 18.0, 16 of them 68.9 -> 67.3, 21 chains of 13 over 32 000 25.7 -> 23.7.
+// first child not tested again, leaves without a look for children, no barrier behind a node's first three rejections where they exchange nothing
+// (chain_barrier), and in the draw the prefixes of the tile sums taken once, the last element with mass looked for only where it is
+// wanted: 2 us a call, one tree of 60 nodes over 151 936 entries 20.0 -> 18.0, 21 chains of 13 over 32 000 25.7 -> 23.7 (on 16 trees with
+// dense q, which are bound by the logits, no more than two runs differ by).
 template <typename T, typename TQ, int RES, bool VEC>
 __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   constexpr bool RESIDENT = RES > 0;
