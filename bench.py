@@ -107,7 +107,7 @@ def _code_only(text: str) -> str:
     return " ".join("".join(out).split())
 
 
-def kernel_source_digest(files=("common.h", "row_reduce.h")) -> str:
+def kernel_source_digest(files=("common.h", "chunks.h", "row_reduce.h")) -> str:
     h = hashlib.sha256()
     for f in files:
         with open(os.path.join(ROOT, "paper_2601_15498_amd", "csrc", f), "r", encoding="utf-8") as fh:

@@ -11,6 +11,7 @@
 #include "row_reduce.h"
 #include "margin.h"
 #include "tail.h"
+#include "onehot.h"
 #include "lmhead.h"
 
 namespace mars {
@@ -44,7 +45,8 @@ static int choose_splits(long rows, int V) {
 
 struct Layout {
   int splits, G;
-  size_t partials_off, stats_off, xslots_off, gathered_off, total;
+  size_t partials_off, stats_off, xslots_off, gathered_off, least;
+  size_t table_off, total;
 };
 
 // Work-groups per request in the sampling tail: enough to spread a request's row passes over
@@ -73,6 +75,15 @@ static int choose_groups(int B, int V) {
   return G;
 }
 
+// The chunks of a row of V entries (elt bytes each) reduced in `splits` shares, and the bytes their sums take.
+static ChunkSpec row_chunks(int V, size_t elt, int splits) {
+  const int nvec = V / static_cast<int>(16 / elt), vps = (nvec + splits - 1) / splits;
+  return chunk_spec(splits, vps > 0 ? vps : 1);
+}
+static size_t table_bytes(long rows, const ChunkSpec& s) {
+  return static_cast<size_t>(rows) * s.items * s.slots * kChunkWaves * sizeof(float2);
+}
+
 // K = thresholds per request: the row reduction works on the B*N rows once, the per-request
 // part on K*B requests (statistics table and exchange words per (threshold, request)).
 static Layout layout(int B, int N, int V, int K = 1) {
@@ -85,7 +96,12 @@ static Layout layout(int B, int N, int V, int K = 1) {
   L.xslots_off = L.stats_off + align_up(static_cast<size_t>(K) * rows * sizeof(mars_row_stat));
   L.gathered_off = L.xslots_off +
                    align_up(static_cast<size_t>(K) * B * (N + 2) * 2 * L.G * sizeof(unsigned long long));
-  L.total = L.gathered_off + align_up(static_cast<size_t>(rows) * sizeof(float2));
+  L.least = L.gathered_off + align_up(static_cast<size_t>(rows) * sizeof(float2));
+  // The sums of the rows' chunks.  (A workspace of the least size has no room for them: the draw goes over the row.)
+  L.table_off = L.least;
+  const size_t wide = table_bytes(rows, row_chunks(V, sizeof(float), L.splits)),
+               narrow = table_bytes(rows, row_chunks(V, sizeof(bf16_t), L.splits));
+  L.total = L.table_off + align_up(wide > narrow ? wide : narrow);
   return L;
 }
 
@@ -147,6 +163,7 @@ static ClearArgs clear_args(char* ws, const Layout& L, int B, int N, int K) {
   clr.N = N; clr.B = B; clr.xwords = 2 * L.G; clr.copies = K;
   clr.counters = nullptr; clr.ncounters = 0;
   clr.par = nullptr; clr.tok = nullptr; clr.q = nullptr; clr.q_bf16 = 0; clr.gathered = nullptr;
+  clr.table = nullptr; clr.slots = 1; clr.batches = 0;
   return clr;
 }
 
@@ -369,9 +386,26 @@ static void* static_scratch() {
   return g_scratch_ptr[dev];
 }
 
+// Whether all rows begin on 16-byte boundaries.
+static bool even_rows(const void* logits, size_t elt, int V) {
+  return reinterpret_cast<uintptr_t>(logits) % 16 == 0 && static_cast<size_t>(V) * elt % 16 == 0;
+}
+static hipError_t launch_onehot_tail(const TailArgs& a, int logits_dtype, hipStream_t stream) {
+  const dim3 grid(static_cast<unsigned int>(a.B)), block(kOneHotThreads);
+  if (logits_dtype == MARS_BF16) {
+    if (!a.table) hipLaunchKernelGGL((tail_onehot_kernel<bf16_t, false, true>), grid, block, 0, stream, a);
+    else if (even_rows(a.logits, 2, a.V)) hipLaunchKernelGGL((tail_onehot_kernel<bf16_t, false, false>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((tail_onehot_kernel<bf16_t, true, false>), grid, block, 0, stream, a);
+  } else {
+    if (even_rows(a.logits, 4, a.V)) hipLaunchKernelGGL((tail_onehot_kernel<float, false, false>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((tail_onehot_kernel<float, true, false>), grid, block, 0, stream, a);
+  }
+  return hipGetLastError();
+}
 // The sampling walk: G work-groups per request (a.G), a.B requests.  draft_dtype < 0: one-hot.
 static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int draft_dtype, hipStream_t stream) {
   const int V = a.V;
+  if (draft_dtype < 0 && a.chunks.slots > 0) return launch_onehot_tail(a, logits_dtype, stream);
   const bool dense = draft_dtype >= 0;
   const bool vec = whole_groups(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, dense ? a.dprobs : nullptr, a.N, V);
   // Slices of at most kMaxResident groups of eight per thread stay in registers between passes.  One per thread in the
@@ -459,7 +493,7 @@ int mars_row_reduce(const void* logits, int logits_dtype, float temperature, int
   if (!(temperature >= 0.0f) || std::isinf(temperature)) return MARS_ERR_ARG;
   if (logits_dtype != MARS_F32 && logits_dtype != MARS_BF16) return MARS_ERR_DTYPE;
   const Layout L = layout(B, N, V);
-  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.total)
+  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.least)
     return MARS_ERR_WORKSPACE;
   Partial* partials = reinterpret_cast<Partial*>(static_cast<char*>(workspace) + L.partials_off);
   const hipError_t e = launch_row_reduce(logits, logits_dtype, static_cast<long>(B) * N, V, L.splits,
@@ -477,7 +511,7 @@ int mars_row_stats(const void* logits, int logits_dtype, const float* theta, flo
   if (!(temperature >= 0.0f) || std::isinf(temperature)) return MARS_ERR_ARG;
   if (logits_dtype != MARS_F32 && logits_dtype != MARS_BF16) return MARS_ERR_DTYPE;
   const Layout L = layout(B, N, V);
-  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.total)
+  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.least)
     return MARS_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const long rows = static_cast<long>(B) * N;
@@ -542,7 +576,7 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   const bool dense = sampling && draft_probs != nullptr;
   if (dense && draft_dtype != MARS_F32 && draft_dtype != MARS_BF16) return MARS_ERR_DTYPE;
   const Layout L = layout(B, N, V, K);
-  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.total)
+  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.least)
     return MARS_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const long rows = static_cast<long>(B) * N;
@@ -556,6 +590,15 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
     clr.q = dense ? draft_probs : nullptr;
     clr.q_bf16 = draft_dtype == MARS_BF16 ? 1 : 0;
     clr.gathered = reinterpret_cast<float2*>(ws + L.gathered_off);
+  }
+  // One-hot draft distributions: the walk that reads the sums of the rows' chunks (onehot.h), if a wave can hold the tree, a draw
+  // look through the chunks and the workspace hold their sums; else the one that goes over the row.  (It is the faster one on
+  // every such size that was timed: 1.05-1.15 times on the whole call from one tree of 60 nodes to 256 trees.)
+  const ChunkSpec chunks = row_chunks(V, logits_dtype == MARS_BF16 ? 2 : 4, L.splits);
+  if (sampling && !dense && N <= kOneHotNodes && chunks.slots > 0 && workspace_bytes >= L.total) {
+    clr.xwords = 0;  // (one work-group per request: nothing is exchanged)
+    clr.slots = chunks.slots; clr.batches = 1 << chunks.log2_batches;
+    clr.table = reinterpret_cast<float2*>(ws + L.table_off);
   }
   if (sampling && request_status) {  // the sampling tail only raises a request's status
     clr.counters = reinterpret_cast<unsigned int*>(request_status);
@@ -579,6 +622,8 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   a.xslots = clr.xslots;
   a.mask = accept_mask; a.len = accept_len; a.path = path_idx; a.bonus = bonus_token;
   a.dec = decision; a.status = request_status; a.diag = diag;
+  a.chunks = chunks; a.table = clr.table; a.two_from = L.splits;
+  if (!clr.table) a.chunks.slots = 0;
   a.B = K * B; a.Bd = B; a.N = N; a.V = V; a.splits = L.splits * kPartsPerItem; a.c = c;
   a.ind.kind = indicator; a.ind.cind = indicator_scale(temperature);
   a.out_tok = out_tokens; a.out_len = out_len;
@@ -607,7 +652,7 @@ int mars_verify_static(const void* logits, int logits_dtype, const int32_t* draf
   using namespace mars;
   const int K = options && options->n_theta != 0 ? options->n_theta : 1;
   if (!sizes_ok(B, N, V, K)) return MARS_ERR_ARG;
-  if (layout(B, N, V, K).total > static_cast<size_t>(MARS_STATIC_SCRATCH_BYTES)) return MARS_ERR_SCRATCH;
+  if (layout(B, N, V, K).least > static_cast<size_t>(MARS_STATIC_SCRATCH_BYTES)) return MARS_ERR_SCRATCH;
   void* ws = static_scratch();
   if (!ws) return MARS_ERR_HIP;
   return mars_verify_ex(logits, logits_dtype, draft_tokens, tree_parent, draft_probs, draft_dtype, theta, temperature,
@@ -634,7 +679,7 @@ int mars_margin_stats(const void* logits, int logits_dtype, const float* theta, 
   }
   if (ncounters > (1 << 20)) return MARS_ERR_ARG;
   const Layout L = layout(B, N, V);
-  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.total)
+  if (!workspace || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0 || workspace_bytes < L.least)
     return MARS_ERR_WORKSPACE;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const long rows = static_cast<long>(B) * N;
@@ -709,7 +754,7 @@ int mars_lmhead_verify(const void* hidden, const void* weight, int H, const int3
   a.theta = theta; a.u = nullptr; a.partials = partials;
   a.stats = stats;
   a.stats_ws = reinterpret_cast<mars_row_stat*>(ws + L.stats_off);
-  a.G = 1; a.spin_limit = 0; a.xslots = nullptr; a.gathered = nullptr;
+  a.G = 1; a.spin_limit = 0; a.xslots = nullptr; a.gathered = nullptr; a.table = nullptr;
   a.mask = accept_mask; a.len = accept_len; a.path = path_idx; a.bonus = bonus_token;
   a.dec = decision; a.status = request_status; a.diag = nullptr;
   a.B = K * B; a.Bd = B; a.N = N; a.V = V; a.splits = p.parts; a.c = 0.0f;
@@ -779,6 +824,10 @@ int mars_lmhead_verify_sampling(const void* hidden, const void* weight, int H, c
   a.dprobs = dense ? draft_probs : nullptr;
   a.theta = theta; a.u = uniforms; a.partials = partials;
   a.gathered = nullptr;  // the walk gathers for itself: no streaming row reduction has run
+  // A column of tiles is a chunk, its sum in one partial result or two.
+  a.chunks = chunk_spec(p.parts - (p.parts - p.grid.split) / 2, p.grid.width * p.bn / 8, 1, 0);
+  if (dense || N > kOneHotNodes || a.chunks.items > kMaxColumns) a.chunks.slots = 0;
+  a.table = nullptr; a.two_from = p.grid.split;
   a.stats = stats;
   a.stats_ws = reinterpret_cast<mars_row_stat*>(ws + L.stats_off);
   a.G = launch_groups(L.G, K * B);

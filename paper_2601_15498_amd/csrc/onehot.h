@@ -1,0 +1,511 @@
+// The sampling walk where the draft model's distribution is not kept: every draft token is a one-hot q (Eq. 1 accepts it
+// with probability f(x), a rejection takes x out of f and divides by what is left).  One work-group per request, trees
+// of at most 64 nodes.
+//
+// Nothing here goes over a row: a rejection changes one entry, so what the walk needs of a row is its largest two and its sum
+// (which the row reduction leaves), the logits of the draft tokens (gathered on the way), and for the token drawn last
+// the sums of the row's chunks (chunks.h) and the one chunk that the draw falls into, 16 384 entries as a rule.
+//
+// Every wave holds the whole tree, a node per lane, and does everything but the last step for itself, without LDS traffic
+// between waves and without a barrier: the tests of all nodes are made at once (a node's test depends on the inputs and on its
+// earlier siblings alone), and the walk is a few scalar instructions per accepted draft.
+//
+// What bounds it: three trips to memory one behind the other (the tree, the sums, the chunk: 1.4, 0.5 and 0.8 us) and the issue of
+// single waves in between, 9-12 us in all; it was a pass over the row's entries by every request's work-groups for the draw, and an exchange
+// of their sums.  This kernel alone, then the whole call, us, before and after: one tree of 60 nodes x 151 936 bf16 9.1 -> 7.5
+// and 18.5 -> 17.0; 8 trees of 26 x 100 001 12.7 -> 11 and 25.2 -> 23.1; 256 trees of 26 x 151 936 fp32 (a work-group per request read 600 KB)
+// 59 -> 15 and 656 -> 623.  With the tests, the walk and the draw in LDS and behind barriers, as in tail_sampling_body, the
+// same method took 15, 22 and 25 us.
+#pragma once
+
+#include "chunks.h"
+#include "tail.h"
+
+namespace mars {
+
+constexpr int kOneHotNodes = kWave;
+constexpr int kOneHotThreads = 512;
+constexpr int kPageEntries = 32;   // the draw looks at a chunk in pages of this many entries per thread
+constexpr int kRunChunks = 4;      // behind the fused LM head: columns per lane, at most
+constexpr int kMaxColumns = kRunChunks * kWave;
+// The sum of a chunk less a token's own term is a difference of fp32 sums.  If the token holds more than this share of what is left of the row, the
+// part of the chunk that it was summed with is summed again without it.
+constexpr double kTakenShare = 0.25;
+
+// COLUMNS: behind the fused LM head.  A chunk is a column of tiles, its sum in a row's partial results.
+template <typename T, bool RAGGED, bool COLUMNS>
+__global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_kernel(TailArgs a) {
+  constexpr int NT = kOneHotThreads, NW = NT / kWave;
+  constexpr int EPV = 16 / sizeof(T), PV = kPageEntries / EPV;  // entries of a vector, vectors per thread and page
+  static_assert(PV * NW <= kWave, "one tile per lane");
+  __shared__ mars_row_stat sh_st[kOneHotNodes];               // many partial results per row: the merged statistics
+  __shared__ unsigned long long sh_kids[NW][kOneHotNodes];    // children of every node, a copy per wave
+  __shared__ double sh_tile[2][PV * NW];                      // sums of a page's tiles: 64 vectors each
+  __shared__ double sh_piece[2][NW];                          // sums of a piece that is summed again, one per wave
+
+  const int b = blockIdx.x;
+  const int N = a.N, V = a.V;
+  const size_t rb = static_cast<size_t>(b) * N;
+  const int bd = a.B == a.Bd ? b : b % a.Bd;  // the request whose inputs this (possibly swept) request reads
+  const size_t rd = static_cast<size_t>(bd) * N;
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const T* __restrict__ zall = static_cast<const T*>(a.logits) + rd * static_cast<size_t>(V);
+  const float c = a.c;
+
+  // ---------------------------------------------------------------- the tree, a node per lane: one trip to memory
+  const bool live = lane < N;
+  const size_t rl = rd + (live ? lane : 0);
+  const int par = a.par[rl], tok = a.tok[rl];
+  const float u = a.u[static_cast<size_t>(bd) * (N + 1) + (live ? lane : N)];
+  const float u_draw = a.u[static_cast<size_t>(bd) * (N + 1) + N];
+  const float theta = a.theta[b];
+  float zx = 0.0f;
+  if (!COLUMNS) zx = a.gathered[rl].x;
+  mars_row_stat st;
+  if (a.splits <= kFewParts) {
+    Partial q[kFewParts];
+    load_partials_of_row(a.partials + rl * a.splits, a.splits, q);
+    st = merge_row_few(q, a.splits, c, a.ind, theta);
+  } else {
+    merge_rows_coop<NT, 4>(a.partials + rd * a.splits, N, a.splits, c, a.ind, [&](int) { return theta; },
+                           [&](int row, const mars_row_stat& s) { sh_st[row] = s; });
+    __syncthreads();
+    st = sh_st[live ? lane : 0];
+  }
+  if (wave == 0 && live && a.stats) a.stats[rb + lane] = st;
+  const bool bad_tree = live && (lane == 0 ? par != -1 : par < 0 || par >= lane);
+  const bool bad_token = live && lane > 0 && (tok < 0 || tok >= V);
+  if (__any(bad_tree || bad_token)) {
+    write_rejected_request<NT>(a, b, __any(bad_tree) ? MARS_REQ_BAD_TREE : MARS_REQ_BAD_TOKEN, lane_value(st.id1, 0));
+    return;
+  }
+  const bool node = live && lane > 0;  // (the root is no draft)
+  if (COLUMNS && node) zx = widen(zall[static_cast<size_t>(par) * V + tok]);  // behind the fused LM head: a second trip
+  const int p = node ? par : 0;
+  // (LDS operations of a wave are performed in order; the fences keep the compiler's order)
+  sh_kids[wave][lane] = 0ull;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  if (node) atomicOr(&sh_kids[wave][p], 1ull << lane);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const unsigned long long kids = sh_kids[wave][lane], family = sh_kids[wave][p];
+  const unsigned long long older = node ? family & ((1ull << lane) - 1ull) : 0ull;  // its earlier siblings
+  // f(x) in the parent's row before any rejection (Eq. 3), and whether x is the runner-up of a low-margin row
+  const float f0 = __builtin_amdgcn_exp2f((zx - __shfl(st.z1, p, kWave)) * c) * __shfl(1.0f / st.sum_exp, p, kWave);
+  const int second = __shfl(st.relax_ok ? st.id2 : -1, p, kWave);
+  const bool runner_up = node && tok == second;
+
+  // ---------------------------------------------------------------- decisions, walk, and the sums of the row it stops at
+  float norm = -1.0f;  // Z of this node's rejection where it had to be summed (0: f was left as it was)
+  float f;             // f(x) when the node is tested
+  int code = 0, cnode = 0, plen = 0, passes = 0, path = -1;
+  float last_norm = 0.0f;
+  unsigned long long visited = 1ull;
+  const T* __restrict__ rowp = zall;
+  int head = 0, nvec = 0, tail = 0;
+  float R = 0.0f, z1 = 0.0f;
+  unsigned long long gone = 0ull;  // nodes whose tokens are out of f at cnode
+  constexpr int kRun = COLUMNS ? kRunChunks : 1;
+  double total = 0.0, mass[kRun];
+  auto run_sum = [&]() {
+    double sum = mass[0];
+#pragma unroll
+    for (int r = 1; r < kRun; ++r) sum += mass[r];
+    return sum;
+  };
+  float2 part[kChunkWaves];        // what the lane's chunks were summed in: COLUMNS two each, else the eight waves'
+  const ChunkSpec spec = a.chunks;
+  const int nchunks = spec.items * spec.slots, per = COLUMNS ? (nchunks + kWave - 1) / kWave : 1;
+  int turn = 0;
+  auto vector_of = [&](int v) { return RAGGED && v < head ? -1 : (v - head) / EPV; };
+  // Chunk of an entry, the piece of it that the entry was summed with: a wave's vectors, or the whole column.
+  struct Place { int chunk, piece; };
+  Place at = {0, 0};                // of this node's token, if it is out of f
+  unsigned long long redone = 0ull;  // nodes whose tokens' pieces have been summed again
+  auto place_of = [&](int v) {
+    int vec = vector_of(v);
+    asm volatile("" : "+v"(vec));  // (worked out where it is wanted, not ahead for every lane)
+    Place to = {0, 0};  // (loose elements: the first wave's)
+    if (RAGGED && vec >= nvec) {
+      const int first = min(nvec, (spec.items - 1) * spec.vps);
+      to.chunk = (spec.items - 1) * spec.slots + chunk_last(spec, nvec - first);
+    } else if (!RAGGED || vec >= 0) {
+      to.chunk = chunk_of(spec, nvec, vec);
+      if (!COLUMNS) to.piece = (vec - chunk_range(spec, nvec, to.chunk).begin) / kWave % kChunkWaves;
+    }
+    return to;
+  };
+  // (far below z1 the rounding of z*c - R would show: the exponent's integer part is taken exactly)
+  auto precise = [&](float x) {
+    const float n = __builtin_rintf(x * c);
+    return __builtin_ldexpf(__builtin_amdgcn_exp2f(__builtin_fmaf(x, c, -n)), static_cast<int>(fmaxf(n - R, -1000.0f)));
+  };
+  auto scaled = [&](float s, float ref) {
+    return s > 0.0f ? ldexp(static_cast<double>(s), static_cast<int>(fmaxf(ref - R, -1000.0f))) : 0.0;
+  };
+  for (;;) {
+    // The tests of all nodes, in rounds: in round r a node takes its r-th sibling's rejection into its f.  With a one-hot q
+    // that is a division by Z = 1 - f(x), where that is not a small difference.
+    f = f0;
+    bool blocked = false;
+    for (unsigned long long m = older; __any(m != 0ull);) {
+      const int j = m != 0ull ? __ffsll(static_cast<long long>(m)) - 1 : lane;
+      const float fj = __shfl(f, j, kWave), nj = __shfl(norm, j, kWave);
+      const int tj = __shfl(tok, j, kWave);
+      const float z = nj >= 0.0f ? nj : 1.0f - fj;
+      if (m != 0ull) {
+        blocked |= nj < 0.0f && !(z >= kClosedFormMinNorm);
+        const float g = (tok == tj ? 0.0f : f) * (1.0f / z);
+        f = z > 0.0f ? g : f;
+      }
+      m &= m - 1ull;
+    }
+    code = !node ? 0 : runner_up ? MARS_DEC_RELAXED : u < fminf(1.0f, f) ? MARS_DEC_SAMPLED : 0;
+    const float z_own = norm >= 0.0f ? norm : 1.0f - f;
+    const unsigned long long taken = __ballot(code != 0 && !blocked), unknown = __ballot(blocked);
+    // The walk: the first child that is accepted.
+    cnode = 0; plen = 0; passes = 0; path = -1; last_norm = 0.0f; visited = 1ull;
+    unsigned long long here;
+    auto kids_of = [&](int n) {
+      return (static_cast<unsigned long long>(static_cast<unsigned int>(lane_value(static_cast<int>(kids >> 32), n))) << 32) |
+             static_cast<unsigned int>(lane_value(static_cast<int>(kids), n));
+    };
+    auto last_of = [](unsigned long long m) { return 63 - __clzll(static_cast<long long>(m)); };
+    for (;;) {
+      here = kids_of(cnode);
+      const unsigned long long yes = here & taken;
+      if (yes == 0ull) break;
+      const int k = __ffsll(static_cast<long long>(yes)) - 1;
+      const unsigned long long rejected = here & ((1ull << k) - 1ull);
+      passes += __popcll(rejected);
+      if (rejected != 0ull) last_norm = lane_value(z_own, last_of(rejected));
+      path = lane == plen ? k : path;
+      visited |= 1ull << k;
+      plen += 1;
+      cnode = k;
+    }
+    // All its children are rejected, or one whose Z has to be summed: then the later ones wait for it.
+    const unsigned long long wait = here & unknown;
+    const bool draw = wait == 0ull;
+    const unsigned long long out = draw ? here : here & ((wait & (0ull - wait)) - 1ull);
+    const int last = out != 0ull ? last_of(out) : 0;
+    passes += __popcll(out);
+    gone = out & __ballot(norm != 0.0f);
+    const float z_last = lane_value(z_own, last), norm_last = lane_value(norm, last);
+    const bool summed = out != 0ull && norm_last < 0.0f && !(z_last >= kClosedFormMinNorm);  // Z comes out of the sums below
+    if (out != 0ull && !summed) last_norm = z_last;
+
+    // The sums of the row's chunks against 2^R, lane l's run of them.
+    rowp = zall + static_cast<size_t>(cnode) * V;
+    head = RAGGED ? min(V, static_cast<int>((16u - (reinterpret_cast<uintptr_t>(rowp) & 15u)) % 16u / sizeof(T))) : 0;
+    nvec = (V - head) / EPV;
+    tail = RAGGED ? V - head - nvec * EPV : 0;
+    z1 = lane_value(st.z1, cnode);
+    R = __builtin_ceilf(z1 * c);  // (an integer, as the references of the sums)
+    const size_t row = rd + cnode;
+    const float2* __restrict__ table = COLUMNS ? nullptr : a.table + row * nchunks * kChunkWaves;
+    const Partial* __restrict__ columns = a.partials + row * a.splits;
+    auto first_part = [&](int i) { return i < a.two_from ? i : 2 * i - a.two_from; };
+    auto column_part = [&](int i, int n) {  // (n: 0, 1)
+      const Partial* __restrict__ q = columns + first_part(min(i, nchunks - 1)) + (i < a.two_from ? 0 : n);
+      return make_float2(i < nchunks && (n == 0 || i >= a.two_from) ? q->s : 0.0f, q->ref);
+    };
+    if (COLUMNS) {
+#pragma unroll
+      for (int r = 0; r < kRunChunks; ++r)
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+          part[2 * r + n] = r < per ? column_part(lane * per + r, n) : make_float2(0.0f, 0.0f);
+    } else {
+      const float4* __restrict__ t = reinterpret_cast<const float4*>(table + min(lane, nchunks - 1) * kChunkWaves);
+#pragma unroll
+      for (int w = 0; w < kChunkWaves; w += 2) {
+        const float4 q = t[w / 2];
+        part[w] = make_float2(lane < nchunks ? q.x : 0.0f, q.y);
+        part[w + 1] = make_float2(lane < nchunks ? q.z : 0.0f, q.w);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kRun; ++r) mass[r] = 0.0;
+    auto change = [&](int chunk, double by) {
+      const int r0 = chunk - lane * per;
+#pragma unroll
+      for (int r = 0; r < kRun; ++r) mass[r] += r < per && r == r0 ? by : 0.0;
+    };
+    // Rejected tokens leave the sums.
+    const bool mine = ((gone >> lane) & 1ull) != 0ull && f > 0.0f;  // (a token met twice is out already)
+    at = {0, 0};
+    redone = 0ull;
+    if (gone != 0ull) {
+      float2 was[2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};
+      if (mine) {
+        at = place_of(tok);
+        if (COLUMNS) { was[0] = column_part(at.chunk, 0); was[1] = column_part(at.chunk, 1); }
+        else was[0] = table[at.chunk * kChunkWaves + at.piece];
+      }
+      const float rest = 1.0f - wave_sum(mine ? f0 : 0.0f);
+      unsigned long long heavy = __ballot(mine && f0 > kTakenShare * rest);
+      while (heavy != 0ull) {
+        const int j = __ffsll(static_cast<long long>(heavy)) - 1;
+        const int chunk = lane_value(at.chunk, j), piece = lane_value(at.piece, j);
+        const unsigned long long same = __ballot(mine && at.chunk == chunk && at.piece == piece);
+        heavy &= ~same;
+        redone |= same;
+        const ChunkRange range = chunk_range(spec, nvec, chunk);
+        double sum = 0.0;
+        auto add = [&](int first, float (&e)[EPV]) {  // EPV entries from `first` on
+          for (unsigned long long m = same; m != 0ull; m &= m - 1ull) {
+            const int x = lane_value(tok, __ffsll(static_cast<long long>(m)) - 1) - first;
+#pragma unroll
+            for (int n = 0; n < EPV; ++n) e[n] = n == x ? 0.0f : e[n];
+          }
+          float s = (e[0] + e[1]) + (e[2] + e[3]);
+          if (EPV == 8) s += (e[EPV - 4] + e[EPV - 3]) + (e[EPV - 2] + e[EPV - 1]);
+          sum += static_cast<double>(s);
+        };
+        // (the piece's vectors, 64 at a time, dealt out to the waves)
+        constexpr int kStride = COLUMNS ? NT : NW * kChunkWaves * kWave;
+        const int v_first = range.begin + (COLUMNS ? wave : wave * kChunkWaves + piece) * kWave;
+        for (int v0 = v_first; v0 < range.end; v0 += kStride) {
+          Vec<T, EPV> raw;
+          const int vec = v0 + lane;
+          raw.load(rowp + head, static_cast<unsigned int>(min(vec, range.end - 1)));
+          float e[EPV];
+#pragma unroll
+          for (int n = 0; n < EPV; ++n) {
+            const float t = precise(raw.get(n));
+            e[n] = vec < range.end ? t : 0.0f;
+          }
+          add(head + vec * EPV, e);
+        }
+        if (RAGGED && piece == 0 && wave == 0) {  // loose elements, one per lane
+          const bool front = chunk == 0 && lane < head;
+          const bool back = lane >= head && lane < head + tail && chunk == place_of(V - 1).chunk;
+          const int v = front ? lane : back ? V - tail + (lane - head) : 0;
+          float e[EPV] = {};
+          const float t = precise(widen(rowp[v]));
+          e[0] = front || back ? t : 0.0f;
+          add(v, e);
+        }
+        const double ws = wave_sum(sum);
+        if (lane == 0) sh_piece[turn][wave] = ws;
+        __syncthreads();
+        const double again = wave_sum(lane < NW ? sh_piece[turn][lane] : 0.0);
+        turn ^= 1;
+        double before = scaled(lane_value(was[0].x, j), lane_value(was[0].y, j));
+        if (COLUMNS) before += scaled(lane_value(was[1].x, j), lane_value(was[1].y, j));
+        change(chunk, again - before);
+      }
+      // (the others as they were added)
+      const double term = COLUMNS ? static_cast<double>(precise(zx)) : scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(zx, c, -was[0].y)), was[0].y);
+      for (unsigned long long light = __ballot(mine) & ~redone; light != 0ull; light &= light - 1ull) {
+        const int j = __ffsll(static_cast<long long>(light)) - 1;
+        change(lane_value(at.chunk, j), -lane_value(term, j));
+      }
+    }
+    double all = 0.0;
+#pragma unroll
+    for (int r = 0; r < kRun; ++r) {
+      double m = 0.0;
+#pragma unroll
+      for (int w = 0; w < kChunkWaves / kRun; ++w) m += scaled(part[r * (kChunkWaves / kRun) + w].x, part[r * (kChunkWaves / kRun) + w].y);
+      all += m;
+      m += mass[r];
+      mass[r] = m > 1e-37 ? m : 0.0;
+    }
+    if (gone != 0ull) {
+      if (summed) {
+        total = wave_sum(run_sum());
+        all = wave_sum(all);
+        if (!(total > 0.0)) {  // nothing is left without it: f stays as it was
+          norm = lane == last ? 0.0f : norm;
+          continue;
+        }
+        double z = total / all;
+        for (unsigned long long m = gone & ~(1ull << last); m != 0ull; m &= m - 1ull)
+          z /= static_cast<double>(lane_value(z_own, __ffsll(static_cast<long long>(m)) - 1));
+        if (!draw) {
+          norm = lane == last ? static_cast<float>(z) : norm;
+          continue;
+        }
+        last_norm = static_cast<float>(z);
+      }
+    }
+    break;
+  }
+
+  // ---------------------------------------------------------------- the draw
+  const double run = run_sum(), run_incl = wave_prefix_sum(run);
+  total = lane_value(run_incl, kWave - 1);
+  const double target = static_cast<double>(u_draw) * total;
+  int chunk = -1;
+  double cum = 0.0;
+  if (total > 0.0) {
+    // The chunk the target falls into; where rounding leaves none, the last one with mass.
+    const unsigned long long hit = __ballot(run_incl > target), any = __ballot(run > 0.0);
+    const int hl = hit != 0ull ? __ffsll(static_cast<long long>(hit)) - 1 : 63 - __clzll(static_cast<long long>(any));
+    double at = run_incl - run, front = at;
+    int in_run = 0;
+    bool over = false;
+#pragma unroll
+    for (int r = 0; r < kRun; ++r) {
+      if (!over && mass[r] > 0.0) { in_run = r; front = at; over = at + mass[r] > target; }
+      at += mass[r];
+    }
+    chunk = hl * per + lane_value(in_run, hl);
+    cum = lane_value(front, hl);
+  }
+  int pick = -1;
+  float pick_z = 0.0f;
+  if (chunk >= 0) {
+    const T* __restrict__ vecp = rowp + head;
+    const ChunkRange range = chunk_range(spec, nvec, chunk);
+    // the loose elements as a vector in front of the row's first, one behind its last
+    const bool front = RAGGED && head > 0 && chunk == 0, back = RAGGED && tail > 0 && chunk == place_of(V - 1).chunk;
+    const int begin = front ? -1 : range.begin, end = back ? nvec + 1 : range.end;
+    int last_page = -1, turn = 0;
+    bool take_last = false;  // rounding has left no entry above the target: the last one with mass
+    for (int page = begin; page < end; page += PV * NT, turn ^= 1) {
+      Vec<T, EPV> raw[PV];
+      if (range.end > range.begin) {
+#pragma unroll
+        for (int m = 0; m < PV; ++m)
+          raw[m].load(vecp, static_cast<unsigned int>(min(max(page + m * NT + tid, range.begin), range.end - 1)));
+      } else {
+#pragma unroll
+        for (int m = 0; m < PV; ++m) raw[m].fill_neg_inf();
+      }
+      float e[PV][EPV];
+#pragma unroll
+      for (int m = 0; m < PV; ++m) {
+        const int vec = page + m * NT + tid;
+        const bool in = vec >= range.begin && vec < range.end;
+#pragma unroll
+        for (int n = 0; n < EPV; ++n) {
+          const float t = __builtin_amdgcn_exp2f(__builtin_fmaf(raw[m].get(n), c, -R));
+          e[m][n] = in ? t : 0.0f;
+        }
+      }
+      if (front || back) {
+#pragma unroll
+        for (int n = 0; n < EPV; ++n) {
+          const int vf = head - EPV + n, vb = head + nvec * EPV + n;
+          const float ef = vf >= 0 ? __builtin_amdgcn_exp2f(__builtin_fmaf(widen(rowp[max(vf, 0)]), c, -R)) : 0.0f;
+          const float eb = vb < V ? __builtin_amdgcn_exp2f(__builtin_fmaf(widen(rowp[min(vb, V - 1)]), c, -R)) : 0.0f;
+#pragma unroll
+          for (int m = 0; m < PV; ++m) {
+            const int vec = page + m * NT + tid;
+            if (front && vec == begin) e[m][n] = ef;
+            if (back && vec == end - 1) e[m][n] = eb;
+          }
+        }
+      }
+      for (unsigned long long m = gone; m != 0ull; m &= m - 1ull) {
+        const int x = lane_value(tok, __ffsll(static_cast<long long>(m)) - 1), vec = vector_of(x), at = vec - page;
+        if (at < 0 || at >= PV * NT || tid != at % NT) continue;
+        const int flat = at / NT * EPV + (x - head - vec * EPV);
+#pragma unroll
+        for (int i = 0; i < PV; ++i)
+#pragma unroll
+          for (int n = 0; n < EPV; ++n) e[i][n] = i * EPV + n == flat ? 0.0f : e[i][n];
+      }
+      float g[PV];
+#pragma unroll
+      for (int m = 0; m < PV; ++m) {
+        g[m] = (e[m][0] + e[m][1]) + (e[m][2] + e[m][3]);
+        if (EPV == 8) g[m] += (e[m][EPV - 4] + e[m][EPV - 3]) + (e[m][EPV - 2] + e[m][EPV - 1]);
+        const double t = wave_sum(static_cast<double>(g[m]));
+        if (lane == 0) sh_tile[turn][m * NW + wave] = t;
+      }
+      __syncthreads();
+      const double mine = lane < PV * NW ? sh_tile[turn][lane] : 0.0, incl = wave_prefix_sum(mine);
+      const unsigned long long hit = __ballot(cum + incl > target), any = __ballot(mine > 0.0);
+      if ((hit != 0ull || take_last) && any != 0ull) {
+        const int tile = hit != 0ull && !take_last ? __ffsll(static_cast<long long>(hit)) - 1 : 63 - __clzll(static_cast<long long>(any));
+        if (wave != tile % NW) return;  // one wave finishes, the one that holds the tile
+        float f[EPV], z[EPV], fs = 0.0f;
+#pragma unroll
+        for (int m = 0; m < PV; ++m)
+          if (m == tile / NW) {
+            fs = g[m];
+#pragma unroll
+            for (int n = 0; n < EPV; ++n) { f[n] = e[m][n]; z[n] = raw[m].get(n); }
+          }
+        const double lanes = wave_prefix_sum(static_cast<double>(fs)), at = cum + lane_value(incl - mine, tile);
+        const unsigned long long over = __ballot(at + lanes > target);
+        int hl = 0, pe = -1;
+        float pz = 0.0f;
+        if (over != 0ull && !take_last) {
+          hl = __ffsll(static_cast<long long>(over)) - 1;
+          double sum = at + (lanes - static_cast<double>(fs));
+#pragma unroll
+          for (int n = 0; n < EPV; ++n) {
+            sum += static_cast<double>(f[n]);
+            if (pe < 0 && sum > target) { pe = n; pz = z[n]; }
+          }
+          pe = lane_value(pe, hl);
+        }
+        if (pe < 0) {  // the last entry with mass
+          int mine_last = -1;
+#pragma unroll
+          for (int n = 0; n < EPV; ++n)
+            if (f[n] > 0.0f) { mine_last = n; pz = z[n]; }
+          hl = 63 - __clzll(static_cast<long long>(__ballot(mine_last >= 0)));
+          pe = lane_value(mine_last, hl);
+        }
+        pick = head + (page + tile / NW * NT + wave * kWave + hl) * EPV + pe;
+        pick_z = lane_value(pz, hl);
+        if (RAGGED && (pick < head || pick >= V - tail)) pick_z = widen(rowp[pick]);
+        break;
+      }
+      if (any != 0ull) last_page = page;
+      cum += lane_value(incl, kWave - 1);
+      if (page + PV * NT >= end && last_page >= 0) {
+        take_last = true;
+        page = last_page - PV * NT;
+      }
+    }
+  }
+  if (pick < 0 && wave != 0) return;
+  // ---------------------------------------------------------------- results, by one wave
+  const int last_node_top1 = lane_value(st.id1, cnode);
+  float prob = 0.0f;
+  if (pick >= 0) {  // its share of the sum; if that is most of it, in the form in which it was added there, which is off by as much
+    double term = static_cast<double>(precise(pick_z));
+    if (term > kTakenShare * total) {
+      const Place to = place_of(pick);
+      float ref = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kChunkWaves; ++w)
+        ref = w == (COLUMNS ? 2 * (chunk % per) : to.piece) ? lane_value(part[w].y, chunk / per) : ref;
+      if (!(COLUMNS && chunk >= a.two_from) &&
+          !__any(((redone >> lane) & 1ull) != 0ull && at.chunk == to.chunk && at.piece == to.piece))
+        term = scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(pick_z, c, -ref)), ref);
+    }
+    prob = static_cast<float>(term / total);
+  }
+  const int token = pick >= 0 ? pick : last_node_top1;  // (no mass anywhere)
+  const bool on_path = ((visited >> lane) & 1ull) != 0ull;
+  const int committed = __shfl(tok, lane < plen ? path : 0, kWave);
+  if (live) {
+    a.mask[rb + lane] = on_path ? 1 : 0;
+    a.path[rb + lane] = path;
+    if (a.dec) a.dec[rb + lane] = static_cast<uint8_t>(on_path ? code : 0);
+    if (a.out_tok) a.out_tok[rb + lane] = lane < plen ? committed : lane == plen ? token : -1;
+  }
+  if (lane == 0) {
+    a.bonus[b] = token;
+    a.len[b] = plen;
+    if (a.out_tok) a.out_len[b] = plen + 1;
+    if (a.diag) {
+      mars_req_diag dg;
+      dg.bonus_prob = prob;
+      dg.last_residual_norm = last_norm;
+      dg.residual_passes = passes;
+      dg.last_node = cnode;
+      a.diag[b] = dg;
+    }
+  }
+}
+
+}  // namespace mars

@@ -17,13 +17,21 @@
 // very end, to fold their eight results into the work-group's one.
 #pragma once
 
+#include "chunks.h"
 #include "common.h"
 
 namespace mars {
 
 constexpr int kRowThreads = 512;  // 8 waves per work-group (512 x 2 measured best of {128..1024} x {1,2,4,8})
 constexpr int kUnroll = 2;        // 16-byte loads per lane per batch
-constexpr float kRescaleLog2 = 24.0f;  // move the sum-exp reference when the max rises by 2^24
+// The reference of a wave's sum of exponentials.  What a term's exponent is off by grows with its distance from the
+// reference (half a unit of its last place: 5e-8 of the term at 1, 7e-7 at 16), so the largest terms should be near it; and moving it costs some
+// forty instructions.  The first batch puts it 2^kHeadLog2 above its maximum, about where the maximum of a row of
+// ordinary logits ends up, and a maximum that rises 2^kRescaleLog2 above it, a logit that stands out, moves it there.
+constexpr float kHeadLog2 = 6.0f;
+constexpr float kRescaleLog2 = 2.0f;
+constexpr int kLowLog2 = 8;
+static_assert(kRowThreads * kUnroll == kChunkVecs && kRowThreads / kWave == kChunkWaves, "a batch, its waves");
 
 // Insert the elements >= cut of one vector into the running key pair (k1 >= k2).  Only a
 // vector whose maximum reaches the cut is looked at element by element (normally one or two):
@@ -92,6 +100,10 @@ struct ClearArgs {
   const void* q;               // draft probabilities [B,N,V] or nullptr (one-hot: the pair's second half is 1)
   int q_bf16;
   float2* gathered;            // [B*N]: (logit, draft probability) of node i's token in row par[i]
+  // Sums of the shares' chunks (chunks.h) for a draw that has no need of the whole row then: [rows][splits][slots][waves] pairs
+  // (sum, reference).  nullptr: not wanted (greedy mode), or a chunk is a share, whose sum is in its partial result.
+  float2* table;
+  int slots, batches;          // chunks of a share, batches of a chunk
 };
 
 // RAGGED: rows that do not start on a 16-byte boundary (a vocabulary that is not a multiple of EPV, an array that is not
@@ -155,7 +167,7 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
   const bool ahead = RAGGED ? nb > 0 : nfull > 2;
   if (ahead) { if (RAGGED) load_edge(bufA, 0); else load_full(bufA, 0); }
   // The loose elements at the row's ends, one per lane (every wave asks for them, so that no load stands under a
-  // condition; the first wave of the first split looks at them).
+  // condition; the first wave of the first split looks at those in front, of the last one at those behind).
   const int tail = RAGGED ? V - head - nvec * EPV : 0;
   int loose_at = 0;
   float loose = 0.0f;
@@ -222,10 +234,15 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
 
   float m1 = neg_inf(), m2 = neg_inf();  // best and second-best batch maximum of this lane
   int b1 = -1, b2 = -1;                  // the (distinct) batches they belong to
-  float s = 0.0f;                        // sum of exp2(z*c - ref_c) over the lane's elements
+  float s = 0.0f;                        // sum of exp2(z*c - ref_c) over the lane's elements of the current chunk
   float ref_c = -1.0e30f;                // wave-uniform, integer-valued reference (already times c)
   float thresh = -3.0e38f;               // rescale when a lane maximum exceeds this (wave-uniform)
-  const float tau_over_c = SAMPLING ? kRescaleLog2 / c : 0.0f;
+  const float inv_c = SAMPLING ? 1.0f / c : 0.0f;
+  // Lane j holds the wave's sum over chunk j and its reference, once the stream is past it.
+  float chunk_s = 0.0f, chunk_ref = 0.0f;
+  double done = 0.0;                       // sum of the chunks behind it, against done_ref
+  float done_ref = -1.0e30f;
+  int chunk = 0, chunk_end = clr.batches;  // the current chunk, the batch behind it
 
   // Raw copy of every lane's best batch (vector j of lane t at [j][t]: conflict-free 16-byte rows).
   __shared__ Vec<T, EPV> sh_best[U][kRowThreads];
@@ -281,23 +298,27 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
       }
     }
     if (SAMPLING) {
-      if (__any(m1 > thresh)) {
+      if (__any(bm > thresh)) {
         // Rare: the wave's maximum rose more than 2^kRescaleLog2 above the reference (or this is
-        // the wave's first batch).  Move the reference up to the wave maximum, rounded up to an
-        // integer, before any term of this batch is formed: no exponent ever exceeds
-        // kRescaleLog2, and references differ by exact powers of two.
-        const float wm = wave_max(m1);
-        const float new_ref_c = __builtin_ceilf(wm * c);
+        // the wave's first batch).  Move the reference up before any term of this batch is formed: no
+        // exponent ever exceeds kRescaleLog2, and references, which are whole numbers, differ by exact powers of two.
+        const float wm = wave_max(bm);
+        const float new_ref_c = __builtin_ceilf(wm * c) + (ref_c < -0.5e30f ? kHeadLog2 : 0.0f);
         s *= __builtin_amdgcn_exp2f(ref_c - new_ref_c);
         ref_c = new_ref_c;
-        thresh = wm + tau_over_c;
+        thresh = (ref_c + kRescaleLog2) * inv_c;
       }
+      // (in pairs, then fours: as many additions as one behind the other, three roundings instead of eight)
       float bs[U];
 #pragma unroll
       for (int j = 0; j < U; ++j) {
-        bs[j] = 0.0f;
-#pragma unroll
-        for (int e = 0; e < EPV; ++e) bs[j] += __builtin_amdgcn_exp2f(__builtin_fmaf(x[j * EPV + e], c, -ref_c));
+        auto term = [&](int e) { return __builtin_amdgcn_exp2f(__builtin_fmaf(x[j * EPV + e], c, -ref_c)); };
+        if (EPV == 1) {
+          bs[j] = term(0);
+        } else {
+          bs[j] = (term(0) + term(1)) + (term(2) + term(3));
+          if (EPV == 8) bs[j] += (term(4) + term(5)) + (term(6) + term(7));
+        }
       }
       float t = bs[0];
 #pragma unroll
@@ -310,6 +331,31 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
       // of 59, six waves per SIMD instead of eight, three work-groups per compute unit instead of four.
       asm volatile("" : "+v"(s));
     }
+  };
+
+  // Behind a chunk's last batch: its sum over the wave, once in two batches or more (double: the sums are what the draw is made
+  // from).  Some sixty instructions; where no draw asks for chunks the headline workload's call takes what it took (68.6 and 68.7 us),
+  // where one does the row reduction takes 0.2-0.4 us more (60 rows x 151 936).
+  auto move_done = [&](double more) {  // (the same in all lanes: scalar registers)
+    absorb_sum(done_ref, done, ref_c, more);
+    done = lane_value(done, 0);
+    done_ref = lane_value(done_ref, 0);
+  };
+  auto end_chunk = [&]() {
+    const double ws = wave_sum(static_cast<double>(s));
+    const bool mine = tid % kWave == chunk;
+    chunk_s = mine ? static_cast<float>(ws) : chunk_s;
+    chunk_ref = mine ? ref_c : chunk_ref;
+    move_done(ws);
+    // A chunk far below the reference, which a logit that stands out has moved up: the next one begins nearer to its terms.
+    const int e = __builtin_amdgcn_frexp_exp(ws);
+    if (ws > 0.0 && e < -kLowLog2) {
+      ref_c += static_cast<float>(e) + 4.0f;
+      thresh = (ref_c + kRescaleLog2) * inv_c;
+    }
+    s = 0.0f;
+    ++chunk;
+    chunk_end += clr.batches;
   };
 
   // Double-buffered stream over the full batches: the loads of batch k+1 are in flight while
@@ -325,6 +371,7 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
       process(bufA, k);
       load_full(bufA, k + 2);
       process(bufB, k + 1);
+      if (SAMPLING && k + 2 == chunk_end) end_chunk();
     }
     // bufA holds batch k; at most two batches follow it (the last full one, the ragged one).  They are
     // requested ahead like the others, so that a wave does not end its stream on one or two
@@ -387,18 +434,31 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
     const KeyPair r = rank_all<T, EPV>(vecp, head, v_begin, v_end, nb, tid);
     k1 = r.k1; k2 = r.k2;
   }
-  if (RAGGED && wave == 0 && split == 0) {
-    const bool mine = lane < head + tail;
+  if (RAGGED && wave == 0 && (split == 0 || split == splits - 1)) {
+    const bool mine = lane < head ? split == 0 : lane < head + tail && split == splits - 1;
     // (an element below w2 cannot be among the two largest: the wave holds two that are not)
     if (mine && !(loose < w2)) top2_insert(k1, k2, make_key(loose, loose_at));
     if (SAMPLING) {
       if (__any(mine && loose > thresh)) {
-        const float wm = wave_max(mine ? fmaxf(m1, loose) : m1);
-        const float new_ref_c = __builtin_ceilf(wm * c);
+        const float wm = wave_max(mine ? loose : neg_inf());
+        const float new_ref_c = fmaxf(ref_c, __builtin_ceilf(wm * c));
         s *= __builtin_amdgcn_exp2f(ref_c - new_ref_c);
         ref_c = new_ref_c;
       }
-      s += mine ? __builtin_amdgcn_exp2f(__builtin_fmaf(loose, c, -ref_c)) : 0.0f;
+      const float t = mine ? __builtin_amdgcn_exp2f(__builtin_fmaf(loose, c, -ref_c)) : 0.0f;
+      // (the elements in front belong to the row's first chunk)
+      if (chunk > 0 && split == 0) {
+        const double front = wave_sum(lane < head ? static_cast<double>(t) : 0.0);
+        if (lane == 0) {
+          const float top = fmaxf(chunk_ref, ref_c);
+          chunk_s = chunk_s * __builtin_amdgcn_exp2f(chunk_ref - top) + static_cast<float>(front) * __builtin_amdgcn_exp2f(ref_c - top);
+          chunk_ref = top;
+        }
+        move_done(front);
+        s += lane < head ? 0.0f : t;
+      } else {
+        s += t;
+      }
     }
   }
   // Wave-level top-2 of the lanes' keys: walk the (few) lanes that hold any.
@@ -412,7 +472,20 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
     if (second != 0ull) top2_insert(K1, K2, second);
   }
   float ws = 0.0f;
-  if (SAMPLING) ws = wave_sum(s);
+  if (SAMPLING) {
+    const double rest = wave_sum(static_cast<double>(s));
+    if (clr.table) {
+      if (lane == chunk) { chunk_s = static_cast<float>(rest); chunk_ref = ref_c; }
+      if (lane < clr.slots)  // (a chunk that the row's share does not have: nothing)
+        clr.table[(static_cast<size_t>(item) * clr.slots + lane) * NW + wave] = make_float2(chunk_s, chunk_ref);
+    }
+    ws = static_cast<float>(rest);
+    if (chunk > 0) {
+      move_done(rest);
+      ws = static_cast<float>(done);
+      ref_c = done_ref;
+    }
+  }
   // The wave that is last to have its result folds the eight into the work-group's partial result; the
   // others leave at once.  (LDS operations of one wave are performed in order, so a wave that sees the
   // count complete sees every result behind it.)  The kernel behind this one then reads one partial

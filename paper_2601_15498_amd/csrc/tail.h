@@ -10,6 +10,7 @@
 // renormalisation after every rejection (Sec. 2.3) and an inverse-CDF draw at the end.
 #pragma once
 
+#include "chunks.h"
 #include "common.h"
 
 namespace mars {
@@ -53,6 +54,10 @@ struct TailArgs {
   int slice;                // groups of eight entries in a work-group's slice (walk_slice)
   int spin_limit;        // polls a work-group gives a partner before it works out the partner's sum itself
   unsigned long long* xslots;  // [B][N+2][G][2] tagged exchange words, cleared by the row reduction
+  // one-hot draft distributions: the sums of the rows' chunks (chunks.h)
+  ChunkSpec chunks;
+  const float2* table;   // [rows][chunks][kChunkWaves] pairs (sum, reference); nullptr: a chunk's sum is in its partial result,
+  int two_from;          // from this chunk on in two of them
 };
 
 // ---------------------------------------------------------------- shared by both modes

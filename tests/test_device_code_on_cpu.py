@@ -41,6 +41,12 @@ def test_the_walk_orders_its_residual_chain(tmp_path):
     assert " 0 out of order, a missing barrier shows" in out, out
 
 
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_chunks_cover_a_row_and_end_where_the_row_reduction_ends_them(tmp_path):
+    out = run_on_cpu("chunks_main.hip", tmp_path, "undefined", options=["-no-hip-rt"])
+    assert " 0 failed" in out, out
+
+
 def check_plans(tmp_path, cases):
     out = run_on_cpu("lm_plan_main.hip", tmp_path, options=["-no-hip-rt"], args=[x for c in cases for x in c])
     assert f"{len(cases)} cases, 0 failed" in out, out
