@@ -352,6 +352,7 @@ __device__ __forceinline__ void load_partials_of_row(const Partial* __restrict__
 // A row with at most kFewParts partial results, merged by one thread.
 constexpr int kFewParts = 4;
 // (`parts` is the same for the whole work-group: a row whose partial result is its only one -- 128 rows or more -- is not merged at all.)
+template <bool SUMS = true>
 __device__ __forceinline__ mars_row_stat merge_row_few(const Partial (&q)[kFewParts], int parts, float c,
                                                        const Indicator& ind, float theta) {
   LaneTop2 t;
@@ -362,9 +363,9 @@ __device__ __forceinline__ mars_row_stat merge_row_few(const Partial (&q)[kFewPa
   for (int j = 1; j < kFewParts; ++j) {
     if (j >= parts) break;
     const Partial one[1] = {q[j]};
-    lane_fold<1, true>(one, t);
+    lane_fold<1, SUMS>(one, t);
   }
-  return finish_values(t.z1 + 0.0f, t.id1, t.z2 + 0.0f, t.id2, t.R, t.S, theta, c, ind);  // (-0 is 0, as in a key)
+  return finish_values(t.z1 + 0.0f, t.id1, t.z2 + 0.0f, t.id2, t.R, t.S, theta, SUMS ? c : 0.0f, ind);  // (-0 is 0, as in a key)
 }
 
 template <int NT, int BATCH = kMergeBatch, bool SUMS = true, typename ThetaAt, typename Emit>
@@ -376,7 +377,7 @@ __device__ __forceinline__ void merge_rows_coop(const Partial* __restrict__ part
     for (int row = threadIdx.x; row < nrows; row += NT) {
       Partial q[kFewParts];
       load_partials_of_row(partials + static_cast<size_t>(row) * parts, parts, q);
-      emit(row, merge_row_few(q, parts, c, ind, theta_at(row)));
+      emit(row, merge_row_few<SUMS>(q, parts, c, ind, theta_at(row)));
     }
     return;
   }

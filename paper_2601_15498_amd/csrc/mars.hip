@@ -91,6 +91,7 @@ static Layout layout(int B, int N, int V, int K = 1) {
   const long rows = static_cast<long>(B) * N;
   L.splits = choose_splits(rows, V);
   L.partials_off = 0;
+  // (the merged statistics had a place here; kernels hold them now, and the sizes callers know stay)
   L.stats_off = align_up(static_cast<size_t>(rows) * L.splits * kPartsPerItem * sizeof(Partial));
   L.G = choose_groups(K * B, V);
   L.xslots_off = L.stats_off + align_up(static_cast<size_t>(K) * rows * sizeof(mars_row_stat));
@@ -390,6 +391,12 @@ static void* static_scratch() {
 static bool even_rows(const void* logits, size_t elt, int V) {
   return reinterpret_cast<uintptr_t>(logits) % 16 == 0 && static_cast<size_t>(V) * elt % 16 == 0;
 }
+static void launch_greedy_tail(const TailArgs& a, hipStream_t stream) {
+  const dim3 grid(static_cast<unsigned int>(a.B));
+  if (a.N > kWave) hipLaunchKernelGGL(tail_greedy_kernel, grid, dim3(kGreedyThreads), 0, stream, a);
+  else if (a.splits > kFewParts) hipLaunchKernelGGL(tail_greedy_wave_kernel<kGreedyThreads>, grid, dim3(kGreedyThreads), 0, stream, a);
+  else hipLaunchKernelGGL(tail_greedy_wave_kernel<kWave>, grid, dim3(kWave), 0, stream, a);
+}
 static hipError_t launch_onehot_tail(const TailArgs& a, int logits_dtype, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned int>(a.B)), block(kOneHotThreads);
   if (logits_dtype == MARS_BF16) {
@@ -614,7 +621,6 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   a.dprobs = dense ? draft_probs : nullptr;
   a.theta = theta; a.u = uniforms; a.partials = partials;
   a.stats = stats;
-  a.stats_ws = reinterpret_cast<mars_row_stat*>(ws + L.stats_off);
   a.gathered = reinterpret_cast<const float2*>(ws + L.gathered_off);
   a.G = sampling ? launch_groups(L.G, K * B) : 1;
   // polls (about a microsecond each) a work-group gives a partner before it works out the partner's sum itself
@@ -636,7 +642,7 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   };
 
   if (!sampling) {
-    hipLaunchKernelGGL(tail_greedy_kernel, dim3(static_cast<unsigned int>(K * B)), dim3(kGreedyThreads), 0, stream, a);
+    launch_greedy_tail(a, stream);
     return finish();
   }
   if (launch_sampling_tail(a, logits_dtype, dense ? draft_dtype : -1, stream) != hipSuccess) return MARS_ERR_HIP;
@@ -753,14 +759,13 @@ int mars_lmhead_verify(const void* hidden, const void* weight, int H, const int3
   a.logits = nullptr; a.tok = draft_tokens; a.par = tree_parent; a.dprobs = nullptr;
   a.theta = theta; a.u = nullptr; a.partials = partials;
   a.stats = stats;
-  a.stats_ws = reinterpret_cast<mars_row_stat*>(ws + L.stats_off);
   a.G = 1; a.spin_limit = 0; a.xslots = nullptr; a.gathered = nullptr; a.table = nullptr;
   a.mask = accept_mask; a.len = accept_len; a.path = path_idx; a.bonus = bonus_token;
   a.dec = decision; a.status = request_status; a.diag = nullptr;
   a.B = K * B; a.Bd = B; a.N = N; a.V = V; a.splits = p.parts; a.c = 0.0f;
   a.ind.kind = indicator; a.ind.cind = indicator_scale(0.0f);
   a.out_tok = out_tokens; a.out_len = out_len;
-  hipLaunchKernelGGL(tail_greedy_kernel, dim3(static_cast<unsigned int>(K * B)), dim3(kGreedyThreads), 0, stream, a);
+  launch_greedy_tail(a, stream);
   if (hipGetLastError() != hipSuccess) return MARS_ERR_HIP;
   if (!keep_rows) return MARS_OK;
   return launch_keep(K, out_len, path_idx, B, N, keep_rows, keep_offsets, stream) == hipSuccess ? MARS_OK : MARS_ERR_HIP;
@@ -829,7 +834,6 @@ int mars_lmhead_verify_sampling(const void* hidden, const void* weight, int H, c
   if (dense || N > kOneHotNodes || a.chunks.items > kMaxColumns) a.chunks.slots = 0;
   a.table = nullptr; a.two_from = p.grid.split;
   a.stats = stats;
-  a.stats_ws = reinterpret_cast<mars_row_stat*>(ws + L.stats_off);
   a.G = launch_groups(L.G, K * B);
   a.spin_limit = spin_limit > 0 ? spin_limit : kDefaultSpinLimit;
   a.xslots = xslots;

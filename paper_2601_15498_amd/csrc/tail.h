@@ -32,7 +32,6 @@ struct TailArgs {
   const float2* gathered;   // sampling mode: (logit, draft probability) of every node's token in its parent's row
                             // (left by the row reduction; nullptr: the walk gathers them itself)
   mars_row_stat* stats;     // optional caller's table [B*N]
-  mars_row_stat* stats_ws;  // [B*N] in the workspace: the table the tail itself reads
   uint8_t* mask;
   int32_t* len;
   int32_t* path;
@@ -86,6 +85,7 @@ __device__ void write_rejected_request(const TailArgs& a, int b, int status, int
 // requested ahead of the partial results, the merged rows go to the caller's table and, for the
 // kernel's own use, to LDS, and everything after that -- decisions, reachability, the walk back
 // along the accepted path -- reads LDS only.
+// Requests of more nodes than a wave has lanes; the others take tail_greedy_wave_kernel.
 __global__ __launch_bounds__(kGreedyThreads) void tail_greedy_kernel(TailArgs a) {
   constexpr int NT = kGreedyThreads;
   static_assert(MARS_MAX_NODES <= NT, "a thread holds the parent and the token of one node");
@@ -111,7 +111,6 @@ __global__ __launch_bounds__(kGreedyThreads) void tail_greedy_kernel(TailArgs a)
   // row has up to a few hundred partial results)
   merge_rows_coop<NT, 8, false>(a.partials + rd * a.splits, N, a.splits, a.c, a.ind, [&](int) { return theta; },
                          [&](int row, const mars_row_stat& st) {
-                           a.stats_ws[rb + row] = st;
                            if (a.stats) a.stats[rb + row] = st;
                            sh_top1[row] = st.id1;
                            sh_relax[row] = st.relax_ok ? st.id2 : -1;
@@ -186,6 +185,89 @@ __global__ __launch_bounds__(kGreedyThreads) void tail_greedy_kernel(TailArgs a)
     const int correction = sh_top1[e];  // correction after a rejection, bonus after a leaf
     a.bonus[b] = correction;
     if (a.out_tok) { a.out_tok[rb + L] = correction; a.out_len[b] = L + 1; }  // ... then this token
+    if (a.status) a.status[b] = MARS_REQ_OK;
+    if (a.diag) { mars_req_diag dg = {0.0f, 0.0f, 0, e}; a.diag[b] = dg; }
+  }
+}
+
+// The same for requests of at most 64 nodes, a node per lane of one wave: a parent's row, token and decision come by lane
+// exchanges, so that behind the trip to memory there is neither LDS traffic nor a barrier, and what a request commits leaves
+// in one store per table.  NT: one wave where a lane merges its row alone (kFewParts partial results at most); else 1024 threads
+// merge, and one wave goes on.
+// What bounds it is the trip to memory and, where there are many partial results, merging them.  us per call, the kernel above and this
+// one: 64 chains of eight drafts x 128 256 with the committed tokens 32.6 -> 30.5, 112 trees of 5 x 32 000 14.1 -> 12.7, 4 trees of 22 x 151 936
+// 14.2 -> 12.4, one tree of 60 behind the LM head 187.2 -> 186.2.
+template <int NT>
+__global__ __launch_bounds__(NT) void tail_greedy_wave_kernel(TailArgs a) {
+  constexpr bool MANY = NT > kWave;
+  __shared__ int2 sh_top[MANY ? kWave : 1];  // v(1) of the node's row, v(2) where its low-margin test holds, else -1
+  const int b = blockIdx.x;
+  const int N = a.N;
+  const size_t rb = static_cast<size_t>(b) * N;
+  const size_t rd = static_cast<size_t>(a.B == a.Bd ? b : b % a.Bd) * N;  // where the request's inputs are
+  const int lane = threadIdx.x % kWave;
+  const bool live = lane < N;
+  const size_t rl = rd + (live ? lane : 0);
+  const int par = a.par[rl], tok = a.tok[rl];
+  const float theta = a.theta[b];
+  int2 top;
+  if (!MANY) {
+    Partial q[kFewParts];
+    load_partials_of_row(a.partials + rl * a.splits, a.splits, q);
+    const mars_row_stat st = merge_row_few<false>(q, a.splits, a.c, a.ind, theta);
+    if (live && a.stats) a.stats[rb + lane] = st;
+    top = make_int2(st.id1, st.relax_ok ? st.id2 : -1);
+  } else {
+    // (eight loads in flight per lane: behind the fused LM head a row has up to a few hundred partial results)
+    merge_rows_coop<NT, 8, false>(a.partials + rd * a.splits, N, a.splits, a.c, a.ind, [&](int) { return theta; },
+                                  [&](int row, const mars_row_stat& st) {
+                                    if (a.stats) a.stats[rb + row] = st;
+                                    sh_top[row] = make_int2(st.id1, st.relax_ok ? st.id2 : -1);
+                                  });
+    __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    top = sh_top[live ? lane : 0];
+  }
+  const bool bad_tree = live && (lane == 0 ? par != -1 : par < 0 || par >= lane);
+  const bool bad_token = live && lane > 0 && (tok < 0 || tok >= a.V);
+  if (__any(bad_tree || bad_token)) {
+    write_rejected_request<kWave>(a, b, __any(bad_tree) ? MARS_REQ_BAD_TREE : MARS_REQ_BAD_TOKEN, lane_value(top.x, 0));
+    return;
+  }
+  // Local decision of every node against its parent's row (Alg. 1 if-chain).
+  const bool node = live && lane > 0;
+  const int p = node ? par : 0;
+  const int exact = __shfl(top.x, p, kWave), relaxed = __shfl(top.y, p, kWave);
+  const int code = !node ? 0 : tok == exact ? MARS_DEC_EXACT : tok == relaxed ? MARS_DEC_RELAXED : 0;
+  // Pointer jumping: an ancestor, the edges up to it and the rejections on them, a byte each (63 at most).  At the root all three
+  // are 0.
+  unsigned int up = node ? static_cast<unsigned int>(p) | 0x100u | (code == 0 ? 0x10000u : 0u) : 0u;
+  while (__any((up & 0xFFu) != 0u)) up = (up & 0xFFFF00u) + __shfl(up, static_cast<int>(up & 0xFFu), kWave);
+  // Deepest reachable node, lowest index on ties.
+  const int depth = static_cast<int>(up >> 8 & 0xFFu);
+  const float rank = live && up < 0x10000u ? static_cast<float>(depth * kWave + (kWave - 1 - lane)) : 0.0f;
+  const int best = __builtin_amdgcn_readfirstlane(static_cast<int>(wave_max(rank)));  // (the root's is 63)
+  const int e = kWave - 1 - best % kWave, L = best / kWave;
+  unsigned long long visited = 1ull;
+  int path = -1, n = e;
+  for (int d = L; d >= 1; --d) {
+    visited |= 1ull << n;
+    path = lane == d - 1 ? n : path;
+    n = lane_value(par, n);
+  }
+  const bool on_path = ((visited >> lane) & 1ull) != 0ull;
+  const int correction = lane_value(top.x, e);  // correction after a rejection, bonus after a leaf
+  const int committed = __shfl(tok, lane < L ? path : 0, kWave);
+  if (live) {
+    a.mask[rb + lane] = on_path ? 1 : 0;
+    a.path[rb + lane] = path;
+    if (a.dec) a.dec[rb + lane] = static_cast<uint8_t>(on_path ? code : 0);
+    if (a.out_tok) a.out_tok[rb + lane] = lane < L ? committed : lane == L ? correction : -1;
+  }
+  if (lane == 0) {
+    a.len[b] = L;
+    a.bonus[b] = correction;
+    if (a.out_tok) a.out_len[b] = L + 1;
     if (a.status) a.status[b] = MARS_REQ_OK;
     if (a.diag) { mars_req_diag dg = {0.0f, 0.0f, 0, e}; a.diag[b] = dg; }
   }
@@ -858,7 +940,6 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     auto emit = [&](int row, const mars_row_stat& st) {
       sh_st[row] = st;
       if (g == 0) {
-        to->stats_ws[rb + row] = st;
         if (to->stats) to->stats[rb + row] = st;
       }
     };
@@ -871,7 +952,6 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
           const mars_row_stat st = merge_row_few(pq[t], a.splits, a.c, a.ind, theta);
           sh_st[i] = st;
           if (g == 0) {
-            to->stats_ws[rb + i] = st;
             if (to->stats) to->stats[rb + i] = st;
           }
         }
