@@ -118,11 +118,14 @@ static hipError_t launch_row_reduce_t(const void* logits, long rows, int V, int 
   const int nvec = V / EPV;  // (the most a row can have)
   const int vps = (nvec + splits - 1) / splits;
   const dim3 grid(static_cast<unsigned int>(rows * splits)), block(kRowThreads);
-  if (sampling)
-    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, true, RAGGED>), grid, block, 0, stream, static_cast<const T*>(logits), V,
+  if (sampling && clr.table)
+    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, true, RAGGED, true>), grid, block, 0, stream, static_cast<const T*>(logits), V,
+                       splits, vps, c, partials, clr);
+  else if (sampling)
+    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, true, RAGGED, false>), grid, block, 0, stream, static_cast<const T*>(logits), V,
                        splits, vps, c, partials, clr);
   else
-    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, false, RAGGED>), grid, block, 0, stream, static_cast<const T*>(logits), V,
+    hipLaunchKernelGGL((row_reduce_kernel<T, EPV, false, RAGGED, false>), grid, block, 0, stream, static_cast<const T*>(logits), V,
                        splits, vps, c, partials, clr);
   return hipGetLastError();
 }

@@ -110,7 +110,9 @@ struct ClearArgs {
 // aligned).  The stream runs over the row's aligned vectors; the up to 2 (EPV - 1) elements in front of the first
 // and behind the last are one element each for the first lanes of the first wave, which takes them in at
 // the end.  (This was one element per load for the whole row: 208 rows of 100 001 bf16 entries 20.8 us, now 13.0.)
-template <typename T, int EPV, bool SAMPLING, bool RAGGED>
+// CHUNKS: the sums of the shares' chunks are wanted (clr.table).  A form of its own: with that code in it, unused, calls of 15-30 us took 2-4 % more
+// (53 chains of 5 x 38 813 bf16 with dense q 20.1 -> 20.7, 3 trees of 5 x 151 936 17.2 -> 17.8).
+template <typename T, int EPV, bool SAMPLING, bool RAGGED, bool CHUNKS>
 __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __restrict__ logits, int V, int splits,
                                                                   int vecs_per_split, float c,
                                                                   Partial* __restrict__ partials, ClearArgs clr) {
@@ -371,7 +373,7 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
       process(bufA, k);
       load_full(bufA, k + 2);
       process(bufB, k + 1);
-      if (SAMPLING && k + 2 == chunk_end) end_chunk();
+      if (CHUNKS && k + 2 == chunk_end) end_chunk();
     }
     // bufA holds batch k; at most two batches follow it (the last full one, the ragged one).  They are
     // requested ahead like the others, so that a wave does not end its stream on one or two
@@ -447,7 +449,7 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
       }
       const float t = mine ? __builtin_amdgcn_exp2f(__builtin_fmaf(loose, c, -ref_c)) : 0.0f;
       // (the elements in front belong to the row's first chunk)
-      if (chunk > 0 && split == 0) {
+      if (CHUNKS && chunk > 0 && split == 0) {
         const double front = wave_sum(lane < head ? static_cast<double>(t) : 0.0);
         if (lane == 0) {
           const float top = fmaxf(chunk_ref, ref_c);
@@ -474,13 +476,13 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
   float ws = 0.0f;
   if (SAMPLING) {
     const double rest = wave_sum(static_cast<double>(s));
-    if (clr.table) {
+    if (CHUNKS) {
       if (lane == chunk) { chunk_s = static_cast<float>(rest); chunk_ref = ref_c; }
       if (lane < clr.slots)  // (a chunk that the row's share does not have: nothing)
         clr.table[(static_cast<size_t>(item) * clr.slots + lane) * NW + wave] = make_float2(chunk_s, chunk_ref);
     }
     ws = static_cast<float>(rest);
-    if (chunk > 0) {
+    if (CHUNKS && chunk > 0) {
       move_done(rest);
       ws = static_cast<float>(done);
       ref_c = done_ref;
