@@ -400,16 +400,22 @@ static void launch_greedy_tail(const TailArgs& a, hipStream_t stream) {
   else if (a.splits > kFewParts) hipLaunchKernelGGL(tail_greedy_wave_kernel<kGreedyThreads>, grid, dim3(kGreedyThreads), 0, stream, a);
   else hipLaunchKernelGGL(tail_greedy_wave_kernel<kWave>, grid, dim3(kWave), 0, stream, a);
 }
+constexpr int kMinRaggedChunked = 22 * 4096;
 static hipError_t launch_onehot_tail(const TailArgs& a, int logits_dtype, hipStream_t stream) {
-  const dim3 grid(static_cast<unsigned int>(a.B)), block(kOneHotThreads);
-  if (logits_dtype == MARS_BF16) {
-    if (!a.table) hipLaunchKernelGGL((tail_onehot_kernel<bf16_t, false, true>), grid, block, 0, stream, a);
-    else if (even_rows(a.logits, 2, a.V)) hipLaunchKernelGGL((tail_onehot_kernel<bf16_t, false, false>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((tail_onehot_kernel<bf16_t, true, false>), grid, block, 0, stream, a);
-  } else {
-    if (even_rows(a.logits, 4, a.V)) hipLaunchKernelGGL((tail_onehot_kernel<float, false, false>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((tail_onehot_kernel<float, true, false>), grid, block, 0, stream, a);
-  }
+  const dim3 grid(static_cast<unsigned int>(a.B));
+  const bool even = even_rows(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, a.V), row = a.gathered && !a.table;
+#define MARS_ONEHOT(T, COLUMNS, ROW, NT)                                                                                       \
+  if (COLUMNS || even) hipLaunchKernelGGL((tail_onehot_kernel<T, false, COLUMNS, ROW, NT>), grid, dim3(NT), 0, stream, a);      \
+  else hipLaunchKernelGGL((tail_onehot_kernel<T, !COLUMNS, COLUMNS, ROW, NT>), grid, dim3(NT), 0, stream, a)
+#define MARS_ONEHOT_ROWS(T)                                                                                                    \
+  if (row && a.V <= row_entries(kOneHotThreads)) { MARS_ONEHOT(T, false, true, kOneHotThreads); }                              \
+  else if (row) { MARS_ONEHOT(T, false, true, 2 * kOneHotThreads); }                                                           \
+  else { MARS_ONEHOT(T, false, false, kOneHotThreads); }
+  if (!a.gathered) { MARS_ONEHOT(bf16_t, true, false, kOneHotThreads); }  // behind the LM head
+  else if (logits_dtype == MARS_BF16) { MARS_ONEHOT_ROWS(bf16_t) }
+  else { MARS_ONEHOT_ROWS(float) }
+#undef MARS_ONEHOT_ROWS
+#undef MARS_ONEHOT
   return hipGetLastError();
 }
 // The sampling walk: G work-groups per request (a.G), a.B requests.  draft_dtype < 0: one-hot.
@@ -601,12 +607,18 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
     clr.q_bf16 = draft_dtype == MARS_BF16 ? 1 : 0;
     clr.gathered = reinterpret_cast<float2*>(ws + L.gathered_off);
   }
-  // One-hot draft distributions: the walk that reads the sums of the rows' chunks (onehot.h), if a wave can hold the tree, a draw
-  // look through the chunks and the workspace hold their sums; else the one that goes over the row.  (It is the faster one on
-  // every such size that was timed: 1.05-1.15 times on the whole call from one tree of 60 nodes to 256 trees.)
+  // One-hot draft distributions of trees that a wave can hold: the walk with a node per lane (onehot.h), which reads the row it draws from where that is
+  // one page, else the sums of its chunks, if a draw can look through these and the workspace holds them.  Else the one whose work-groups
+  // go over the row, also for rows off a 16-byte boundary of less than 22 of its slices, which are quick to go over: us per call, this one
+  // and by chunks, 7 chains of 10 x 48 293 bf16 with two thresholds 16.4 and 19.3, 5 of 50 x 87 465 20.9 and 22.7, 6 of 19 x 69 230 fp32 18.9 and
+  // 19.9; 2 trees of 8 x 89 993 with two thresholds 17.8 and 16.4, 8 of 26 x 100 001 25.3 and 23.0.
   const ChunkSpec chunks = row_chunks(V, logits_dtype == MARS_BF16 ? 2 : 4, L.splits);
-  if (sampling && !dense && N <= kOneHotNodes && chunks.slots > 0 && workspace_bytes >= L.total) {
-    clr.xwords = 0;  // (one work-group per request: nothing is exchanged)
+  const bool page = V <= row_entries(2 * kOneHotThreads);
+  const bool summed = chunks.slots > 0 && workspace_bytes >= L.total &&
+                      (V >= kMinRaggedChunked || even_rows(logits, logits_dtype == MARS_BF16 ? 2 : 4, V));
+  const bool onehot = sampling && !dense && N <= kOneHotNodes && (page || summed);
+  if (onehot) clr.xwords = 0;  // (one work-group per request: nothing is exchanged)
+  if (onehot && !page) {
     clr.slots = chunks.slots; clr.batches = 1 << chunks.log2_batches;
     clr.table = reinterpret_cast<float2*>(ws + L.table_off);
   }
@@ -632,7 +644,7 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   a.mask = accept_mask; a.len = accept_len; a.path = path_idx; a.bonus = bonus_token;
   a.dec = decision; a.status = request_status; a.diag = diag;
   a.chunks = chunks; a.table = clr.table; a.two_from = L.splits;
-  if (!clr.table) a.chunks.slots = 0;
+  if (!onehot) a.chunks.slots = 0;
   a.B = K * B; a.Bd = B; a.N = N; a.V = V; a.splits = L.splits * kPartsPerItem; a.c = c;
   a.ind.kind = indicator; a.ind.cind = indicator_scale(temperature);
   a.out_tok = out_tokens; a.out_len = out_len;

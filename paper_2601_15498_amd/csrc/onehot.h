@@ -25,7 +25,7 @@ namespace mars {
 
 constexpr int kOneHotNodes = kWave;
 constexpr int kOneHotThreads = 512;
-constexpr int kPageEntries = 32;   // the draw looks at a chunk in pages of this many entries per thread
+constexpr int kPageEntries = 32;   // the draw looks at a row, or at a chunk, in pages of this many entries per thread (48: no gain)
 constexpr int kRunChunks = 4;      // behind the fused LM head: columns per lane, at most
 constexpr int kMaxColumns = kRunChunks * kWave;
 // The sum of a chunk less a token's own term is a difference of fp32 sums.  If the token holds more than this share of what is left of the row, the
@@ -33,11 +33,19 @@ constexpr int kMaxColumns = kRunChunks * kWave;
 constexpr double kTakenShare = 0.25;
 
 // COLUMNS: behind the fused LM head.  A chunk is a column of tiles, its sum in a row's partial results.
-template <typename T, bool RAGGED, bool COLUMNS>
-__global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_kernel(TailArgs a) {
-  constexpr int NT = kOneHotThreads, NW = NT / kWave;
+// ROW: a vocabulary of one page (of 512 threads up to 16 368 entries, of 1 024 up to 32 752).  The row itself is read where the walk stops,
+// one trip instead of those to the sums and to a chunk, rejected tokens are left out where the terms are formed, and the row reduction
+// leaves no sums of chunks.  us per call, the walk that goes over the row by all of a request's work-groups / by chunks / this one: 30 trees of 32 x 3 458
+// bf16 19.5 / 23.3 / 19.7, one of 19 x 3 645 13.8 / 16.2 / 11.9, 6 of 63 x 6 940 19.1 / 16.9 / 13.8, 52 of 15 x 4 742 fp32 20.4 / 20.2 / 16.2, 23 of
+// 37 x 32 000 bf16 25.0 / 25.2 / 22.3, 4 of 34 x 32 000 19.6 / 16.8 / 14.9; 33 of 12 x 32 000 20.2 / 21.0 / 21.2, and in fp32 10 chains of 13 x 32 000 16.7
+// / 17.7 / 16.9.
+constexpr int row_entries(int threads) { return threads * kPageEntries - 16; }  // (loose elements are a vector in front and one behind)
+template <typename T, bool RAGGED, bool COLUMNS, bool ROW, int NT>
+__global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail_onehot_kernel(TailArgs a) {
+  constexpr int NW = NT / kWave;
   constexpr int EPV = 16 / sizeof(T), PV = kPageEntries / EPV;  // entries of a vector, vectors per thread and page
-  static_assert(PV * NW <= kWave, "one tile per lane");
+  constexpr int TILES = (PV * NW + kWave - 1) / kWave;  // of a page, per lane
+  static_assert(TILES <= 2, "one tile per lane, or two");
   __shared__ mars_row_stat sh_st[kOneHotNodes];               // many partial results per row: the merged statistics
   __shared__ unsigned long long sh_kids[NW][kOneHotNodes];    // children of every node, a copy per wave
   __shared__ double sh_tile[2][PV * NW];                      // sums of a page's tiles: 64 vectors each
@@ -113,6 +121,9 @@ __global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_ke
     for (int r = 1; r < kRun; ++r) sum += mass[r];
     return sum;
   };
+  Vec<T, EPV> raw[PV];             // a page of the row as it lies in memory, the terms of its entries, of its vectors
+  float e[PV][EPV], g[PV];
+  double tile_first = 0.0, tile_sum = 0.0, tile_incl = 0.0;  // lane l: of the first of its tiles, of its tiles, of all up to them
   float2 part[kChunkWaves];        // what the lane's chunks were summed in: COLUMNS two each, else the eight waves'
   const ChunkSpec spec = a.chunks;
   const int nchunks = spec.items * spec.slots, per = COLUMNS ? (nchunks + kWave - 1) / kWave : 1;
@@ -142,6 +153,73 @@ __global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_ke
   };
   auto scaled = [&](float s, float ref) {
     return s > 0.0f ? ldexp(static_cast<double>(s), static_cast<int>(fmaxf(ref - R, -1000.0f))) : 0.0;
+  };
+  // (ROW: against the row's largest logit, whose term is 1 then; else against 2^R, as the sums)
+  auto term_of = [&](float x) {
+    return __builtin_amdgcn_exp2f(ROW ? (x - z1) * c : __builtin_fmaf(x, c, -R));
+  };
+  // The page from vector `page` on of vectors [range.begin, range.end) and, as a vector in front of the row's first and one behind its
+  // last, the loose elements.
+  auto read_page = [&](int page, const ChunkRange& range, bool front, bool back) __attribute__((always_inline)) {
+    const T* __restrict__ vecp = rowp + head;
+    const int begin = front ? -1 : range.begin, end = back ? nvec + 1 : range.end;
+    if (range.end > range.begin) {
+#pragma unroll
+      for (int m = 0; m < PV; ++m)
+        raw[m].load(vecp, static_cast<unsigned int>(min(max(page + m * NT + tid, range.begin), range.end - 1)));
+    } else {
+#pragma unroll
+      for (int m = 0; m < PV; ++m) raw[m].fill_neg_inf();
+    }
+#pragma unroll
+    for (int m = 0; m < PV; ++m) {
+      const int vec = page + m * NT + tid;
+      const bool in = vec >= range.begin && vec < range.end;
+#pragma unroll
+      for (int n = 0; n < EPV; ++n) e[m][n] = 0.0f;
+      if (page + m * NT + wave * kWave >= range.end) continue;
+#pragma unroll
+      for (int n = 0; n < EPV; ++n) {
+        const float t = term_of(raw[m].get(n));
+        e[m][n] = in ? t : 0.0f;
+      }
+    }
+    if (front || back) {
+#pragma unroll
+      for (int n = 0; n < EPV; ++n) {
+        const int vf = head - EPV + n, vb = head + nvec * EPV + n;
+        const float ef = vf >= 0 ? term_of(widen(rowp[max(vf, 0)])) : 0.0f;
+        const float eb = vb < V ? term_of(widen(rowp[min(vb, V - 1)])) : 0.0f;
+#pragma unroll
+        for (int m = 0; m < PV; ++m) {
+          const int vec = page + m * NT + tid;
+          if (front && vec == begin) e[m][n] = ef;
+          if (back && vec == end - 1) e[m][n] = eb;
+        }
+      }
+    }
+    for (unsigned long long m = gone; m != 0ull; m &= m - 1ull) {
+      const int x = lane_value(tok, __ffsll(static_cast<long long>(m)) - 1), vec = vector_of(x), at = vec - page;
+      if (at < 0 || at >= PV * NT || tid != at % NT) continue;
+      const int flat = at / NT * EPV + (x - head - vec * EPV);
+#pragma unroll
+      for (int i = 0; i < PV; ++i)
+#pragma unroll
+        for (int n = 0; n < EPV; ++n) e[i][n] = i * EPV + n == flat ? 0.0f : e[i][n];
+    }
+#pragma unroll
+    for (int m = 0; m < PV; ++m) {
+      g[m] = (e[m][0] + e[m][1]) + (e[m][2] + e[m][3]);
+      if (EPV == 8) g[m] += (e[m][EPV - 4] + e[m][EPV - 3]) + (e[m][EPV - 2] + e[m][EPV - 1]);
+      double t = 0.0;
+      if (page + m * NT + wave * kWave < end) t = wave_sum(static_cast<double>(g[m]));
+      if (lane == 0) sh_tile[turn][m * NW + wave] = t;
+    }
+    __syncthreads();
+    tile_first = lane < PV * NW ? sh_tile[turn][lane * TILES] : 0.0;
+    tile_sum = TILES == 2 ? tile_first + sh_tile[turn][lane * TILES + 1] : tile_first;
+    tile_incl = wave_prefix_sum(tile_sum);
+    turn ^= 1;
   };
   for (;;) {
     // The tests of all nodes, in rounds: in round r a node takes its r-th sibling's rejection into its f.  With a one-hot q
@@ -202,6 +280,24 @@ __global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_ke
     tail = RAGGED ? V - head - nvec * EPV : 0;
     z1 = lane_value(st.z1, cnode);
     R = __builtin_ceilf(z1 * c);  // (an integer, as the references of the sums)
+    if constexpr (ROW) {
+      read_page(head > 0 ? -1 : 0, {0, nvec}, head > 0, tail > 0);
+      total = lane_value(tile_incl, kWave - 1);
+      if (!summed) break;
+      if (!(total > 0.0)) {  // nothing is left without it: f stays as it was
+        norm = lane == last ? 0.0f : norm;
+        continue;
+      }
+      double z = total / static_cast<double>(lane_value(st.sum_exp, cnode));
+      for (unsigned long long m = gone & ~(1ull << last); m != 0ull; m &= m - 1ull)
+        z /= static_cast<double>(lane_value(z_own, __ffsll(static_cast<long long>(m)) - 1));
+      if (!draw) {
+        norm = lane == last ? static_cast<float>(z) : norm;
+        continue;
+      }
+      last_norm = static_cast<float>(z);
+      break;
+    }
     const size_t row = rd + cnode;
     const float2* __restrict__ table = COLUMNS ? nullptr : a.table + row * nchunks * kChunkWaves;
     const Partial* __restrict__ columns = a.partials + row * a.splits;
@@ -335,12 +431,14 @@ __global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_ke
   }
 
   // ---------------------------------------------------------------- the draw
-  const double run = run_sum(), run_incl = wave_prefix_sum(run);
-  total = lane_value(run_incl, kWave - 1);
+  const double run = ROW ? 0.0 : run_sum(), run_incl = ROW ? 0.0 : wave_prefix_sum(run);
+  if (!ROW) total = lane_value(run_incl, kWave - 1);
   const double target = static_cast<double>(u_draw) * total;
   int chunk = -1;
   double cum = 0.0;
-  if (total > 0.0) {
+  if (ROW) {
+    chunk = total > 0.0 ? 0 : -1;
+  } else if (total > 0.0) {
     // The chunk the target falls into; where rounding leaves none, the last one with mass.
     const unsigned long long hit = __ballot(run_incl > target), any = __ballot(run > 0.0);
     const int hl = hit != 0ull ? __ffsll(static_cast<long long>(hit)) - 1 : 63 - __clzll(static_cast<long long>(any));
@@ -358,70 +456,25 @@ __global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_ke
   int pick = -1;
   float pick_z = 0.0f;
   if (chunk >= 0) {
-    const T* __restrict__ vecp = rowp + head;
-    const ChunkRange range = chunk_range(spec, nvec, chunk);
-    // the loose elements as a vector in front of the row's first, one behind its last
-    const bool front = RAGGED && head > 0 && chunk == 0, back = RAGGED && tail > 0 && chunk == place_of(V - 1).chunk;
+    ChunkRange range = {0, nvec};
+    if (!ROW) range = chunk_range(spec, nvec, chunk);
+    const bool front = RAGGED && head > 0 && chunk == 0, back = RAGGED && tail > 0 && (ROW || chunk == place_of(V - 1).chunk);
     const int begin = front ? -1 : range.begin, end = back ? nvec + 1 : range.end;
-    int last_page = -1, turn = 0;
+    int last_page = -1;
     bool take_last = false;  // rounding has left no entry above the target: the last one with mass
-    for (int page = begin; page < end; page += PV * NT, turn ^= 1) {
-      Vec<T, EPV> raw[PV];
-      if (range.end > range.begin) {
-#pragma unroll
-        for (int m = 0; m < PV; ++m)
-          raw[m].load(vecp, static_cast<unsigned int>(min(max(page + m * NT + tid, range.begin), range.end - 1)));
-      } else {
-#pragma unroll
-        for (int m = 0; m < PV; ++m) raw[m].fill_neg_inf();
-      }
-      float e[PV][EPV];
-#pragma unroll
-      for (int m = 0; m < PV; ++m) {
-        const int vec = page + m * NT + tid;
-        const bool in = vec >= range.begin && vec < range.end;
-#pragma unroll
-        for (int n = 0; n < EPV; ++n) {
-          const float t = __builtin_amdgcn_exp2f(__builtin_fmaf(raw[m].get(n), c, -R));
-          e[m][n] = in ? t : 0.0f;
+    for (int page = begin; page < end; page += PV * NT) {
+      if (!ROW) read_page(page, range, front, back);
+      const unsigned long long hit = __ballot(cum + tile_incl > target), any = __ballot(tile_sum > 0.0);
+      if ((ROW || hit != 0ull || take_last) && any != 0ull) {
+        const int tl = hit != 0ull && !take_last ? __ffsll(static_cast<long long>(hit)) - 1 : 63 - __clzll(static_cast<long long>(any));
+        double in_front = cum + lane_value(tile_incl - tile_sum, tl);
+        int tile = tl;
+        if (TILES == 2) {  // the first of the lane's two, or the second
+          const double first = lane_value(tile_first, tl), second = lane_value(tile_sum, tl) - first;
+          const bool over = !take_last && hit != 0ull ? !(in_front + first > target) && second > 0.0 : second > 0.0;
+          tile = 2 * tl + (over ? 1 : 0);
+          in_front += over ? first : 0.0;
         }
-      }
-      if (front || back) {
-#pragma unroll
-        for (int n = 0; n < EPV; ++n) {
-          const int vf = head - EPV + n, vb = head + nvec * EPV + n;
-          const float ef = vf >= 0 ? __builtin_amdgcn_exp2f(__builtin_fmaf(widen(rowp[max(vf, 0)]), c, -R)) : 0.0f;
-          const float eb = vb < V ? __builtin_amdgcn_exp2f(__builtin_fmaf(widen(rowp[min(vb, V - 1)]), c, -R)) : 0.0f;
-#pragma unroll
-          for (int m = 0; m < PV; ++m) {
-            const int vec = page + m * NT + tid;
-            if (front && vec == begin) e[m][n] = ef;
-            if (back && vec == end - 1) e[m][n] = eb;
-          }
-        }
-      }
-      for (unsigned long long m = gone; m != 0ull; m &= m - 1ull) {
-        const int x = lane_value(tok, __ffsll(static_cast<long long>(m)) - 1), vec = vector_of(x), at = vec - page;
-        if (at < 0 || at >= PV * NT || tid != at % NT) continue;
-        const int flat = at / NT * EPV + (x - head - vec * EPV);
-#pragma unroll
-        for (int i = 0; i < PV; ++i)
-#pragma unroll
-          for (int n = 0; n < EPV; ++n) e[i][n] = i * EPV + n == flat ? 0.0f : e[i][n];
-      }
-      float g[PV];
-#pragma unroll
-      for (int m = 0; m < PV; ++m) {
-        g[m] = (e[m][0] + e[m][1]) + (e[m][2] + e[m][3]);
-        if (EPV == 8) g[m] += (e[m][EPV - 4] + e[m][EPV - 3]) + (e[m][EPV - 2] + e[m][EPV - 1]);
-        const double t = wave_sum(static_cast<double>(g[m]));
-        if (lane == 0) sh_tile[turn][m * NW + wave] = t;
-      }
-      __syncthreads();
-      const double mine = lane < PV * NW ? sh_tile[turn][lane] : 0.0, incl = wave_prefix_sum(mine);
-      const unsigned long long hit = __ballot(cum + incl > target), any = __ballot(mine > 0.0);
-      if ((hit != 0ull || take_last) && any != 0ull) {
-        const int tile = hit != 0ull && !take_last ? __ffsll(static_cast<long long>(hit)) - 1 : 63 - __clzll(static_cast<long long>(any));
         if (wave != tile % NW) return;  // one wave finishes, the one that holds the tile
         float f[EPV], z[EPV], fs = 0.0f;
 #pragma unroll
@@ -431,7 +484,7 @@ __global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_ke
 #pragma unroll
             for (int n = 0; n < EPV; ++n) { f[n] = e[m][n]; z[n] = raw[m].get(n); }
           }
-        const double lanes = wave_prefix_sum(static_cast<double>(fs)), at = cum + lane_value(incl - mine, tile);
+        const double lanes = wave_prefix_sum(static_cast<double>(fs)), at = in_front;
         const unsigned long long over = __ballot(at + lanes > target);
         int hl = 0, pe = -1;
         float pz = 0.0f;
@@ -459,7 +512,7 @@ __global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_ke
         break;
       }
       if (any != 0ull) last_page = page;
-      cum += lane_value(incl, kWave - 1);
+      cum += lane_value(tile_incl, kWave - 1);
       if (page + PV * NT >= end && last_page >= 0) {
         take_last = true;
         page = last_page - PV * NT;
@@ -470,19 +523,33 @@ __global__ __launch_bounds__(kOneHotThreads, RAGGED ? 2 : 4) void tail_onehot_ke
   // ---------------------------------------------------------------- results, by one wave
   const int last_node_top1 = lane_value(st.id1, cnode);
   float prob = 0.0f;
-  if (pick >= 0) {  // its share of the sum; if that is most of it, in the form in which it was added there, which is off by as much
-    double term = static_cast<double>(precise(pick_z));
-    if (term > kTakenShare * total) {
-      const Place to = place_of(pick);
-      float ref = 0.0f;
+  if (pick >= 0) {
+    // Its share of the sum, against the row's largest logit: that one's term is 1.  The sums of chunks are against whole numbers, in steps that
+    // bring an error of their own for every term, which matters for the largest: these two are taken out of the sum as they were
+    // added.(Largest error of bonus_prob over 16 seeds, one tree
+    // of 60 nodes x 151 936 and one of 9 x 32 000: 5e-8 and 1.0e-7, as the walk that goes over the row; with the terms as the sums have them 1.9e-7 and
+    // 3.2e-7.)
+    double sum = total;
+    if (!ROW) {
+      double again = 0.0;
+      auto put_right = [&](int v, float z) {
+        const Place to = place_of(v);
+        const unsigned long long bit = 1ull << lane;
+        if (v < 0 || __any((gone & bit) != 0ull && tok == v)) return;
+        float ref = R;
+        if (!COLUMNS) {
 #pragma unroll
-      for (int w = 0; w < kChunkWaves; ++w)
-        ref = w == (COLUMNS ? 2 * (chunk % per) : to.piece) ? lane_value(part[w].y, chunk / per) : ref;
-      if (!(COLUMNS && chunk >= a.two_from) &&
-          !__any(((redone >> lane) & 1ull) != 0ull && at.chunk == to.chunk && at.piece == to.piece))
-        term = scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(pick_z, c, -ref)), ref);
+          for (int w = 0; w < kChunkWaves; ++w) ref = w == to.piece ? lane_value(part[w].y, to.chunk) : ref;
+        }
+        const bool exact = __any((redone & bit) != 0ull && at.chunk == to.chunk && at.piece == to.piece);
+        sum -= exact ? static_cast<double>(precise(z)) : scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(z, c, -ref)), ref);
+        again += static_cast<double>(__builtin_amdgcn_exp2f((z - z1) * c));
+      };
+      put_right(last_node_top1, z1);
+      put_right(lane_value(st.id2, cnode), lane_value(st.z2, cnode));
+      sum = sum * exp2(static_cast<double>(R) - static_cast<double>(z1) * static_cast<double>(c)) + again;
     }
-    prob = static_cast<float>(term / total);
+    prob = static_cast<float>(static_cast<double>(__builtin_amdgcn_exp2f((pick_z - z1) * c)) / sum);
   }
   const int token = pick >= 0 ? pick : last_node_top1;  // (no mass anywhere)
   const bool on_path = ((visited >> lane) & 1ull) != 0ull;

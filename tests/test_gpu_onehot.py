@@ -50,11 +50,20 @@ def heavy_workload(dtype, V, at, left, draws, seed):
     return custom(f"heavy_{dtype}_V{V}_at{at}_left{left}", f32_to_bf16_bits(z) if dtype == "bf16" else z, tok, par, 2.0, 1.0, u=u)
 
 
-@pytest.mark.parametrize("dtype,V", [("bf16", 65536), ("f32", 40003), ("bf16", 70001)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [3, 7, 8, 9, 511, 4096, 16367, 16368, 16369, 16376, 24001, 32751, 32752, 32753])
+def test_vocabularies_of_one_page(dtype, V):
+    # (16 368 and 32 752 entries are a page; trees where siblings wait for a sum, and chains)
+    tree = {"kind": "chain"} if V < 10 else {"kind": "tree", "depth": 4, "max_children": 4}
+    compare(make_workload(f"onehot_page_{dtype}_{V}", B=5, N=2 if V < 10 else 21, V=V, dtype=dtype, temperature=0.8, tree=tree,
+                          plant_frac=0.7, seed=V), allow_small_norm=True)
+
+
+@pytest.mark.parametrize("dtype,V", [("bf16", 65536), ("f32", 40003), ("bf16", 70001), ("bf16", 5003), ("f32", 16360), ("f32", 32752), ("bf16", 30011)])
 @pytest.mark.parametrize("left", [0.04, 0.3])
 def test_rejected_tokens_that_hold_most_of_the_row(dtype, V, left):
     batch = BATCH[dtype]
-    for i, at in enumerate((0, 1, V - 1, V - 2, 2 * batch - 1, 2 * batch, V // 2)):
+    for i, at in enumerate((0, 1, V - 1, V - 2, min(2 * batch, V) - 1, min(2 * batch, V - 9), V // 2)):
         compare(heavy_workload(dtype, V, at, left, [0.0, 0.31, 0.74, 0.9999], seed=i))
 
 
