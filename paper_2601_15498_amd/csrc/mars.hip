@@ -430,17 +430,20 @@ static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int 
   const bool resident = slice8 <= kMaxResident * kSamplingThreads, two = slice8 <= 2 * kSamplingThreads;
   const bool one = !vec && slice8 <= kSamplingThreads;
   const bool qbf = dense && draft_dtype == MARS_BF16;
+  const bool lanes = a.N <= kWave;
   const void* kernel;
-#define MARS_PICK2(TT, QQ, VV)                                                                    \
-  (one        ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, VV ? 2 : 1, VV>) \
-   : two      ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, 2, VV>)           \
-   : resident ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, kMaxResident, VV>) \
-              : reinterpret_cast<const void*>(&tail_sampling_streamed_kernel<TT, QQ, VV>))
+#define MARS_PICK3(TT, QQ, VV, LL)                                                                            \
+  (one        ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, VV ? 2 : 1, VV, LL>)       \
+   : two      ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, 2, VV, LL>)                 \
+   : resident ? reinterpret_cast<const void*>(&tail_sampling_resident_kernel<TT, QQ, kMaxResident, VV, LL>)      \
+              : reinterpret_cast<const void*>(&tail_sampling_streamed_kernel<TT, QQ, VV, LL>))
+#define MARS_PICK2(TT, QQ, VV) (lanes ? MARS_PICK3(TT, QQ, VV, true) : MARS_PICK3(TT, QQ, VV, false))
 #define MARS_PICK(TT, QQ) (vec ? MARS_PICK2(TT, QQ, true) : MARS_PICK2(TT, QQ, false))
   if (logits_dtype == MARS_BF16) kernel = qbf ? MARS_PICK(bf16_t, bf16_t) : MARS_PICK(bf16_t, float);
   else kernel = qbf ? MARS_PICK(float, bf16_t) : MARS_PICK(float, float);
 #undef MARS_PICK
 #undef MARS_PICK2
+#undef MARS_PICK3
   TailArgs copy = a;
   copy.slice = slice8;
   void* params[] = {&copy};

@@ -826,12 +826,17 @@ __device__ __forceinline__ auto out_args(const TailArgs& a) {
 // loads of single elements in three, the masks being the more code: one row of 255 fp32 entries 11.6 us per call with single
 // elements, 12.9 with two groups, 12.0 with one; 21 rows of 255 15.9, 16.5, 15.0; 960 rows of 13 19.5, 21.3, 19.0.
 // VEC: every group of eight elements is whole and aligned (RowView).
+// LANES: a tree of at most 64 nodes, a node per lane of every wave: the tests of all nodes against the plain softmax, and after every rejection those of
+// the siblings that are left, are made at once, a node's children are one ballot, and there is no barrier before the first sum over the
+// vocabulary.  (Larger trees keep theirs in LDS.)  us per call, dense q, in LDS and in lanes: 18 chains of 18 x 3 804 16.2 -> 14.4, 3 of 45 x 2 427 15.9 ->
+// 13.6, 45 of 21 x 34 171 28.1 -> 26.2, 27 trees of 21 x 6 026 with seven thresholds 22.5 -> 20.8, 16 of 60 x 151 936 65.8 -> 65.2 and with seven thresholds
+// 89.1 -> 87.8; geometric mean over 58 drawn calls 1.043.
 // What a wave issues between two trips to memory is what the walk takes: a row with one partial result not merged, a rejected
 // first child not tested again, leaves without a look for children, no barrier behind a node's first three rejections where they exchange nothing
 // (chain_barrier), and in the draw the prefixes of the tile sums taken once, the last element with mass looked for only where it is
 // wanted: 2 us a call, one tree of 60 nodes over 151 936 entries 20.0 -> 18.0, 21 chains of 13 over 32 000 25.7 -> 23.7 (on 16 trees with
 // dense q, which are bound by the logits, no more than two runs differ by).
-template <typename T, typename TQ, int RES, bool VEC>
+template <typename T, typename TQ, int RES, bool VEC, bool LANES>
 __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   constexpr bool RESIDENT = RES > 0;
   constexpr int kResident = RESIDENT ? RES : 1;
@@ -876,7 +881,64 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   const int ngroups = row_groups(V, VEC);
   const int slice = a.slice;
   const int g_begin = min(ngroups, g * slice), g_end = min(ngroups, g_begin + slice);
-  {
+  // LANES, of node `lane`: parent (-2: no draft), token, uniform, draft probability, f(x) in the parent's row, decision; its own row's
+  // statistics.
+  // (In vector registers, also what is one number or one bit per node: scalar ones are what these kernels run out of.)
+  int l_par = -2, l_tok = 0, l_code = 0, l_second = 0;  // (l_second: it is the runner-up of a low-margin row)
+  float l_u = 0.0f, l_qx = 1.0f, l_f = 0.0f, u_draw = 0.0f;
+  mars_row_stat l_st = {};
+  if constexpr (LANES) {
+    const bool live = lane < N;
+    const size_t rl = rd + (live ? lane : 0);
+    const float* __restrict__ ureq = a.u + static_cast<size_t>(bd) * (N + 1);
+    const int par = a.par[rl];
+    l_tok = a.tok[rl];
+    l_u = ureq[live ? lane : 0];
+    u_draw = ureq[N];
+    const float theta = a.theta[b];
+    float zx = 0.0f;
+    if (a.gathered) {
+      const float2 zq = a.gathered[rl];
+      zx = zq.x; l_qx = zq.y;
+    }
+    if (a.splits <= kFewParts) {
+      Partial pq[kFewParts];
+      load_partials_of_row(a.partials + rl * a.splits, a.splits, pq);
+      l_st = merge_row_few(pq, a.splits, a.c, a.ind, theta);
+    } else {
+      merge_rows_coop<NT, RESIDENT ? 8 : 4>(a.partials + rd * a.splits, N, a.splits, a.c, a.ind, [&](int) { return theta; },
+                                            [&](int row, const mars_row_stat& st) { sh_st[row] = st; });
+      __syncthreads();
+      l_st = sh_st[live ? lane : 0];
+    }
+    if (g == 0 && wave == 0 && live && a.stats) a.stats[rb + lane] = l_st;
+    const bool bad_tree = live && (lane == 0 ? par != -1 : par < 0 || par >= lane);
+    const bool bad_token = live && lane > 0 && (l_tok < 0 || l_tok >= V);
+    if (__any(bad_tree || bad_token)) {
+      if (g == 0)
+        write_rejected_request<NT>(a, b, __any(bad_tree) ? MARS_REQ_BAD_TREE : MARS_REQ_BAD_TOKEN, lane_value(l_st.id1, 0));
+      return;
+    }
+    const bool node = live && lane > 0;
+    const int p = node ? par : 0;
+    if (node && !a.gathered) {  // behind the fused LM head nobody has gathered: a second trip to memory
+      const size_t at = static_cast<size_t>(p) * V + l_tok;
+      zx = widen(zall[at]);
+      if (dense) l_qx = widen(qall[at]);
+    }
+    if (!node) l_qx = 1.0f;
+    l_par = node ? par : -2;
+    mars_row_stat above = {};  // of the parent's row
+    above.z1 = __shfl(l_st.z1, p, kWave);
+    above.sum_exp = __shfl(l_st.sum_exp, p, kWave);
+    above.id2 = __shfl(l_st.relax_ok ? l_st.id2 : -1, p, kWave);
+    above.relax_ok = 1;
+    float fx;
+    l_code = first_try(above, zx, l_qx, l_tok, l_u, a.c, fx);
+    l_f = softmax_at(above, zx, a.c);
+    l_second = l_tok == above.id2 ? 1 : 0;
+    asm volatile("" : "+v"(u_draw));
+  } else {
     constexpr int kPerThread = (MARS_MAX_NODES + NT - 1) / NT;
     const float theta = a.theta[b];
     const bool few = a.splits <= kFewParts;  // one thread merges a row (else sixteen lanes do)
@@ -995,8 +1057,6 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   constexpr bool resident = RESIDENT;
   const int nsteps = (g_end - g_begin + kWave - 1) / kWave;
   const float c = a.c;
-  const float* u = sh_u;
-
   const auto walk_to = out_args<RESIDENT>(a);
   int cnode = 0, plen = 0, passes = 0, nexch = 0;
   float last_norm = 0.0f;
@@ -1104,6 +1164,154 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     applied = rv.ch.n;
   };
 
+  // Token x, f(x) = fx, is rejected at the current node; `more`: the node has further children.
+  auto reject = [&](int x, float fx, bool more) __attribute__((always_inline)) {
+    // Rejected: f <- max(0, f - q_k) / Z with Z = sum_v max(0, f(v) - q_k(v)).
+    //  * With a one-hot q_k only the entry x changes and Z = 1 - f(x); that form is used while
+    //    it is well conditioned.
+    //  * After the node's last child nothing is tested against f any more: the division is
+    //    left out (factor 1) and Z comes out of the final pass as the total of what is left.
+    //  * Otherwise Z is summed over the row, every work-group of the request taking a slice.
+    float inv;
+    // (a barrier behind an exchange, whose staging arrays are used again, and where the chain asks for one)
+    bool sync = chain_barrier(rv.ch.n);
+    if (!dense && 1.0f - fx >= kClosedFormMinNorm) {
+      last_norm = 1.0f - fx;
+      inv = 1.0f / last_norm;
+    } else if (!more) {
+      pending_norm = true;
+      inv = 1.0f;
+    } else {
+      sync = true;
+      // This work-group's slice first, then (rarely) those of partners that have not arrived.  The
+      // streamed form reads memory either way and runs one loop over "whose slice"; the resident form has
+      // its own slice in registers and a lean pass over memory for the others, kept out of the way
+      // behind the exchange (both forms are short of registers in different places).
+      if (resident) {
+        refresh_resident();
+        double part = 0.0;
+#pragma unroll
+        for (int i = 0; i < kResident; ++i) {
+          const int gi = g_begin + i * NT + tid;
+          float acc = 0.0f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float qk = dense ? qv[i][e] : (rv.element(gi, e) == x ? 1.0f : 0.0f);
+            acc += fmaxf(fc[i][e] - qk, 0.0f);
+          }
+          part += static_cast<double>(acc);
+        }
+        part = block_sum<NT>(part, sh_red);
+        unsigned int missing = exchange_begin<NT>(a, b, g, nexch++, part, sh_part, &sh_missing);
+        while (missing != 0u) {
+          const int who = __ffs(static_cast<int>(missing)) - 1;
+          missing &= missing - 1u;
+          const int gb = min(ngroups, who * slice), ge = min(ngroups, gb + slice);
+          const double theirs = block_sum<NT>(resident_mass_from_memory<T, TQ, NT, VEC>(rv, gb, ge, x), sh_red);
+          exchange_fill(sh_part, who, theirs);
+          __syncthreads();  // (sh_red is free again)
+        }
+      } else {
+        int who = g;
+        unsigned int missing = 0u;
+        for (;;) {
+          const int gb = min(ngroups, who * slice), ge = min(ngroups, gb + slice);
+          const double part = block_sum<NT>(residual_mass_slice<T, TQ, NT, VEC>(rv, gb, ge, x), sh_red);
+          if (who == g) {
+            missing = exchange_begin<NT>(a, b, g, nexch++, part, sh_part, &sh_missing);
+          } else {
+            exchange_fill(sh_part, who, part);
+            __syncthreads();  // (sh_red is free again)
+          }
+          if (missing == 0u) break;
+          who = __ffs(static_cast<int>(missing)) - 1;
+          missing &= missing - 1u;
+        }
+      }
+      const double Z = exchange_end(a, sh_part);
+      last_norm = static_cast<float>(Z);
+      inv = Z > 0.0 ? static_cast<float>(1.0 / Z) : 0.0f;  // 0: f is left as it is
+    }
+    if (tid == 0) { sh_ctok[rv.ch.n] = x; sh_cinv[rv.ch.n] = inv; }
+#pragma unroll
+    for (int j = 0; j < kChainRegs; ++j)
+      if (j == rv.ch.n) { rv.ch.rtok[j] = x; rv.ch.rinv[j] = inv; }
+    rv.ch.n += 1;
+    passes += 1;
+    if (sync) __syncthreads();
+  };
+  // Arrived at a node where the walk stops (leaf) or rejects its first child.
+  auto arrive = [&](float z1, float sum_exp, bool leaf) __attribute__((always_inline)) {
+    rv.row(cnode, dense);
+    rv.z1 = z1; rv.inv_S = 1.0f / sum_exp;
+    rv.use_q = dense && !leaf;  // a rejection pass subtracts q; nothing is rejected at a leaf
+    rv.ch.n = 0;
+    pending_norm = false;
+    have = false;
+    raw = false;
+    applied = 0;
+    // The walk stops here or rejects here: at a leaf the final draw reads this row, and a node whose first
+    // child is rejected sees a pass over it either now (further children) or in the final draw, unless a later
+    // child is accepted off a closed-form normaliser (one-hot draft: the request is then wasted, nothing
+    // waits for it).  The row's slice is requested at once, so that its trip to memory runs beside the tests
+    // that follow instead of behind them.  (Only here: a node that is merely passed through never asks for its row.)
+    if (RESIDENT) load_resident();
+  };
+
+  int l_path = -1, l_on = lane == 0 ? 1 : 0;  // LANES: the path's node `lane`, whether node `lane` is on it
+  if constexpr (LANES) {
+    for (;;) {
+      const unsigned long long kids = __ballot(l_par == cnode);
+      const bool leaf = kids == 0ull;
+      int k = leaf ? 0 : __ffsll(static_cast<long long>(kids)) - 1;
+      bool accepted = !leaf && lane_value(l_code, k) != 0;
+      if (!accepted) {
+        arrive(lane_value(l_st.z1, cnode), lane_value(l_st.sum_exp, cnode), leaf);
+        if (leaf) break;
+        unsigned long long bits = kids;
+        for (;;) {
+          bits &= bits - 1ull;
+          const int x = lane_value(l_tok, k);
+          reject(x, lane_value(l_f, k), bits != 0ull);
+          if (bits == 0ull) break;
+          // f(x) and the tests of the children that are left, as eval_f and the loop below take them
+          int jl = 0;
+          float inv = 0.0f;
+#pragma unroll
+          for (int j = 0; j < kChainRegs; ++j)
+            if (j + 1 == rv.ch.n) { inv = rv.ch.rinv[j]; jl = 1; }
+          if (jl == 0) inv = sh_cinv[rv.ch.n - 1];
+          const float left = fmaxf(l_f - (dense ? l_qx : l_tok == x ? 1.0f : 0.0f), 0.0f) * inv;
+          l_f = l_par == cnode && inv > 0.0f ? left : l_f;
+          k = __ffsll(static_cast<long long>(bits)) - 1;
+          float acc;
+          if (l_f == 0.0f) acc = 0.0f;
+          else if (l_qx <= 0.0f) acc = 1.0f;
+          else acc = fminf(1.0f, l_f / l_qx);
+          const int code = l_second != 0 ? MARS_DEC_RELAXED : l_u < acc ? MARS_DEC_SAMPLED : 0;
+          accepted = lane_value(code, k) != 0;
+          if (accepted) {
+            l_code = lane == k ? code : l_code;
+            break;
+          }
+        }
+        if (!accepted) break;
+      }
+      l_on = lane == k ? 1 : l_on;
+      l_path = lane == plen ? k : l_path;
+      cnode = k;
+      plen += 1;
+    }
+    if (g == 0 && wave == 0) {  // (the committed tokens' padding and the token drawn last: below)
+      const int committed = __shfl(l_tok, lane < plen ? l_path : 0, kWave);
+      if (lane < N) {
+        walk_to->mask[rb + lane] = static_cast<uint8_t>(l_on);
+        walk_to->path[rb + lane] = l_path;
+        if (walk_to->dec) walk_to->dec[rb + lane] = static_cast<uint8_t>(l_on != 0 && lane > 0 ? l_code : 0);
+        if (walk_to->out_tok && lane < plen) walk_to->out_tok[rb + lane] = committed;
+      }
+    }
+  } else
   for (;;) {
     const int k1 = __builtin_amdgcn_readfirstlane(sh_first[cnode]);
     const bool leaf = k1 >= N;
@@ -1122,20 +1330,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       }
     }
     const mars_row_stat st = sh_st[cnode];
-    rv.row(cnode, dense);
-    rv.z1 = st.z1; rv.inv_S = 1.0f / st.sum_exp;
-    rv.use_q = dense && !leaf;  // a rejection pass subtracts q; nothing is rejected at a leaf
-    rv.ch.n = 0;
-    pending_norm = false;
-    have = false;
-    raw = false;
-    applied = 0;
-    // The walk stops here or rejects here: at a leaf the final draw reads this row, and a node whose first
-    // child is rejected sees a pass over it either now (further children) or in the final draw, unless a later
-    // child is accepted off a closed-form normaliser (one-hot draft: the request is then wasted, nothing
-    // waits for it).  The row's slice is requested at once, so that its trip to memory runs beside the tests
-    // below instead of behind them.  (Only here: a node that is merely passed through never asks for its row.)
-    if (RESIDENT) load_resident();
+    arrive(st.z1, st.sum_exp, leaf);
     // The children of cnode as bit masks over the nodes (increasing node index = increasing bit), 64
     // nodes to a word.  Every wave forms the words for itself from the parents in LDS: no wave waits for
     // another one on the way down the tree.
@@ -1168,7 +1363,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
         if (fx == 0.0f) acc = 0.0f;
         else if (qx <= 0.0f) acc = 1.0f;
         else acc = fminf(1.0f, fx / qx);
-        if (u[k] < acc) code = MARS_DEC_SAMPLED;
+        if (sh_u[k] < acc) code = MARS_DEC_SAMPLED;
       }
       if (code) {
         if (tid == 0 && g == 0) {
@@ -1180,79 +1375,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
         accepted = k;
         break;
       }
-      // Rejected: f <- max(0, f - q_k) / Z with Z = sum_v max(0, f(v) - q_k(v)).
-      //  * With a one-hot q_k only the entry x changes and Z = 1 - f(x); that form is used while
-      //    it is well conditioned.
-      //  * After the node's last child nothing is tested against f any more: the division is
-      //    left out (factor 1) and Z comes out of the final pass as the total of what is left.
-      //  * Otherwise Z is summed over the row, every work-group of the request taking a slice.
-      float inv;
-      // (a barrier behind an exchange, whose staging arrays are used again, and where the chain asks for one)
-      bool sync = chain_barrier(rv.ch.n);
-      if (!dense && 1.0f - fx >= kClosedFormMinNorm) {
-        last_norm = 1.0f - fx;
-        inv = 1.0f / last_norm;
-      } else if (!more) {
-        pending_norm = true;
-        inv = 1.0f;
-      } else {
-        sync = true;
-        // This work-group's slice first, then (rarely) those of partners that have not arrived.  The
-        // streamed form reads memory either way and runs one loop over "whose slice"; the resident form has
-        // its own slice in registers and a lean pass over memory for the others, kept out of the way
-        // behind the exchange (both forms are short of registers in different places).
-        if (resident) {
-          refresh_resident();
-          double part = 0.0;
-#pragma unroll
-          for (int i = 0; i < kResident; ++i) {
-            const int gi = g_begin + i * NT + tid;
-            float acc = 0.0f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const float qk = dense ? qv[i][e] : (rv.element(gi, e) == x ? 1.0f : 0.0f);
-              acc += fmaxf(fc[i][e] - qk, 0.0f);
-            }
-            part += static_cast<double>(acc);
-          }
-          part = block_sum<NT>(part, sh_red);
-          unsigned int missing = exchange_begin<NT>(a, b, g, nexch++, part, sh_part, &sh_missing);
-          while (missing != 0u) {
-            const int who = __ffs(static_cast<int>(missing)) - 1;
-            missing &= missing - 1u;
-            const int gb = min(ngroups, who * slice), ge = min(ngroups, gb + slice);
-            const double theirs = block_sum<NT>(resident_mass_from_memory<T, TQ, NT, VEC>(rv, gb, ge, x), sh_red);
-            exchange_fill(sh_part, who, theirs);
-            __syncthreads();  // (sh_red is free again)
-          }
-        } else {
-          int who = g;
-          unsigned int missing = 0u;
-          for (;;) {
-            const int gb = min(ngroups, who * slice), ge = min(ngroups, gb + slice);
-            const double part = block_sum<NT>(residual_mass_slice<T, TQ, NT, VEC>(rv, gb, ge, x), sh_red);
-            if (who == g) {
-              missing = exchange_begin<NT>(a, b, g, nexch++, part, sh_part, &sh_missing);
-            } else {
-              exchange_fill(sh_part, who, part);
-              __syncthreads();  // (sh_red is free again)
-            }
-            if (missing == 0u) break;
-            who = __ffs(static_cast<int>(missing)) - 1;
-            missing &= missing - 1u;
-          }
-        }
-        const double Z = exchange_end(a, sh_part);
-        last_norm = static_cast<float>(Z);
-        inv = Z > 0.0 ? static_cast<float>(1.0 / Z) : 0.0f;  // 0: f is left as it is
-      }
-      if (tid == 0) { sh_ctok[rv.ch.n] = x; sh_cinv[rv.ch.n] = inv; }
-#pragma unroll
-      for (int j = 0; j < kChainRegs; ++j)
-        if (j == rv.ch.n) { rv.ch.rtok[j] = x; rv.ch.rinv[j] = inv; }
-      rv.ch.n += 1;
-      passes += 1;
-      if (sync) __syncthreads();
+      reject(x, fx, more);
       while (bits == 0ull && wd + 1 < nwords) bits = kids_word(++wd);
       if (bits == 0ull) break;
       k = wd * kWave + __ffsll(static_cast<long long>(bits)) - 1;
@@ -1265,7 +1388,8 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
 
   // ---------------------------------------------------------------- inverse-CDF draw from f at cnode
   const auto draw_to = out_args<RESIDENT>(a);
-  const mars_row_stat st = sh_st[cnode];
+  const int last_top1 = LANES ? lane_value(l_st.id1, cnode) : sh_st[cnode].id1;
+  const float u_last = LANES ? u_draw : sh_u[N];
   // Without a rejection at this node f is the plain softmax: the draft distribution is not read.
   // (A resident slice that was loaded for a rejection already holds it.)
   rv.use_q = dense && rv.ch.n > 0;
@@ -1368,7 +1492,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       const double pg = lane < G ? sh_part[lane] : 0.0;
       const double pincl = wave_prefix_sum(pg);
       total = lane_value(pincl, kWave - 1);
-      const double target = static_cast<double>(u[N]) * total;
+      const double target = static_cast<double>(u_last) * total;
       const unsigned long long hit = __ballot(lane < G && pincl > target);
       if (hit != 0ull) {
         owner = __ffsll(static_cast<long long>(hit)) - 1;
@@ -1393,7 +1517,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     __syncthreads();
   }
   if (pending_norm) last_norm = static_cast<float>(total);
-  const double target = static_cast<double>(u[N]) * total;
+  const double target = static_cast<double>(u_last) * total;
   if (g == 0 && tid == 0) draw_to->len[b] = plen;
   // (The request's status was set to MARS_REQ_OK by the row reduction of this call.)
   // V_out (Alg. 1): the accepted drafts were written as they were accepted; the first work-group
@@ -1511,7 +1635,7 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
     }
     if (pick < 0) { pick = last_pos_v; pick_f = last_pos_f; }
   }
-  if (pick < 0) { pick = st.id1; pick_f = 0.0f; }  // degenerate: no mass anywhere
+  if (pick < 0) { pick = last_top1; pick_f = 0.0f; }  // degenerate: no mass anywhere
   if (lane == 0) {
     draw_to->bonus[b] = pick;
     if (draw_to->out_tok) draw_to->out_tok[rb + plen] = pick;
@@ -1526,13 +1650,13 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
   }
 }
 
-template <typename T, typename TQ, int RES, bool VEC>
+template <typename T, typename TQ, int RES, bool VEC, bool LANES>
 __global__ __launch_bounds__(kSamplingThreads) void tail_sampling_resident_kernel(TailArgs a) {
-  tail_sampling_body<T, TQ, RES, VEC>(a);
+  tail_sampling_body<T, TQ, RES, VEC, LANES>(a);
 }
-template <typename T, typename TQ, bool VEC>
+template <typename T, typename TQ, bool VEC, bool LANES>
 __global__ __launch_bounds__(kStreamingThreads) void tail_sampling_streamed_kernel(TailArgs a) {
-  tail_sampling_body<T, TQ, 0, VEC>(a);
+  tail_sampling_body<T, TQ, 0, VEC, LANES>(a);
 }
 
 // ---------------------------------------------------------------- cache rows that stay
