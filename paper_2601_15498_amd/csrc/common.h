@@ -368,6 +368,33 @@ __device__ __forceinline__ mars_row_stat merge_row_few(const Partial (&q)[kFewPa
   return finish_values(t.z1 + 0.0f, t.id1, t.z2 + 0.0f, t.id2, t.R, t.S, theta, SUMS ? c : 0.0f, ind);  // (-0 is 0, as in a key)
 }
 
+// The same for the kernels that hold a node per lane, up to kLaneParts partial results: one, up to four, or up to eight are loaded and folded, by
+// a branch that is the same for all lanes.  (Five to eight merged by sixteen lanes and a barrier instead, us per call: one greedy chain of 29 x 128 256
+// 10.9 -> 10.0, five of 6 x 151 936 fp32 12.7 -> 11.1, two trees of 14 x 128 256 with dense q 17.1 -> 16.1.)
+constexpr int kLaneParts = 8;
+template <int COUNT, bool SUMS>
+__device__ __forceinline__ void lane_row_of(const Partial* __restrict__ p, int parts, LaneTop2& t) {
+  Partial q[COUNT];
+  load_partials_of_row(p, parts, q);
+  t.z1 = q[0].z1; t.id1 = q[0].id1; t.z2 = q[0].z2; t.id2 = q[0].id2;
+  t.R = q[0].s > 0.0f ? q[0].ref : -3.0e38f;
+  t.S = static_cast<double>(q[0].s);
+#pragma unroll
+  for (int j = 1; j < COUNT; ++j) {
+    if (j >= parts) break;
+    const Partial one[1] = {q[j]};
+    lane_fold<1, SUMS>(one, t);
+  }
+}
+template <bool SUMS>
+__device__ __forceinline__ mars_row_stat lane_row(const Partial* __restrict__ p, int parts, float c, const Indicator& ind, float theta) {
+  LaneTop2 t;
+  if (parts == 1) lane_row_of<1, SUMS>(p, 1, t);
+  else if (parts <= kFewParts) lane_row_of<kFewParts, SUMS>(p, parts, t);
+  else lane_row_of<kLaneParts, SUMS>(p, parts, t);
+  return finish_values(t.z1 + 0.0f, t.id1, t.z2 + 0.0f, t.id2, t.R, t.S, theta, SUMS ? c : 0.0f, ind);  // (-0 is 0, as in a key)
+}
+
 template <int NT, int BATCH = kMergeBatch, bool SUMS = true, typename ThetaAt, typename Emit>
 __device__ __forceinline__ void merge_rows_coop(const Partial* __restrict__ partials, int nrows, int parts,
                                                 float c, const Indicator& ind, ThetaAt theta_at, Emit emit) {

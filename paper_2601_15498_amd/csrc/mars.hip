@@ -397,10 +397,14 @@ static bool even_rows(const void* logits, size_t elt, int V) {
 static void launch_greedy_tail(const TailArgs& a, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned int>(a.B));
   if (a.N > kWave) hipLaunchKernelGGL(tail_greedy_kernel, grid, dim3(kGreedyThreads), 0, stream, a);
-  else if (a.splits > kFewParts) hipLaunchKernelGGL(tail_greedy_wave_kernel<kGreedyThreads>, grid, dim3(kGreedyThreads), 0, stream, a);
+  else if (a.splits > kLaneParts) hipLaunchKernelGGL(tail_greedy_wave_kernel<kGreedyThreads>, grid, dim3(kGreedyThreads), 0, stream, a);
   else hipLaunchKernelGGL(tail_greedy_wave_kernel<kWave>, grid, dim3(kWave), 0, stream, a);
 }
 constexpr int kMinRaggedChunked = 22 * 4096;
+// fp32 rows of more than half a page of 1 024 threads (128 KB): this many work-groups of the walk over the row are quicker.  us per call, the page and this: 10 chains of 13 x
+// 32 000 17.1 and 16.3, 2 trees of 24 x 32 000 15.9 and 14.8, 5 chains of 51 x 32 000 17.9 and 16.7 (seven work-groups); 7 chains of 7 x 23 588 15.3 and 15.4
+// (five); 18 trees of 7 x 16 941 with seven thresholds 17.5 and 19.9 (two).
+constexpr int kPageGroups = 6;
 static hipError_t launch_onehot_tail(const TailArgs& a, int logits_dtype, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned int>(a.B));
   const bool even = even_rows(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, a.V), row = a.gathered && !a.table;
@@ -616,8 +620,9 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   // and by chunks, 7 chains of 10 x 48 293 bf16 with two thresholds 16.4 and 19.3, 5 of 50 x 87 465 20.9 and 22.7, 6 of 19 x 69 230 fp32 18.9 and
   // 19.9; 2 trees of 8 x 89 993 with two thresholds 17.8 and 16.4, 8 of 26 x 100 001 25.3 and 23.0.
   const ChunkSpec chunks = row_chunks(V, logits_dtype == MARS_BF16 ? 2 : 4, L.splits);
-  const bool page = V <= row_entries(2 * kOneHotThreads);
-  const bool summed = chunks.slots > 0 && workspace_bytes >= L.total &&
+  const bool page = V <= row_entries(kOneHotThreads) ||
+                    (V <= row_entries(2 * kOneHotThreads) && (logits_dtype == MARS_BF16 || L.G < kPageGroups));
+  const bool summed = V > row_entries(2 * kOneHotThreads) && chunks.slots > 0 && workspace_bytes >= L.total &&
                       (V >= kMinRaggedChunked || even_rows(logits, logits_dtype == MARS_BF16 ? 2 : 4, V));
   const bool onehot = sampling && !dense && N <= kOneHotNodes && (page || summed);
   if (onehot) clr.xwords = 0;  // (one work-group per request: nothing is exchanged)

@@ -71,10 +71,8 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
   float zx = 0.0f;
   if (!COLUMNS) zx = a.gathered[rl].x;
   mars_row_stat st;
-  if (a.splits <= kFewParts) {
-    Partial q[kFewParts];
-    load_partials_of_row(a.partials + rl * a.splits, a.splits, q);
-    st = merge_row_few(q, a.splits, c, a.ind, theta);
+  if (a.splits <= kLaneParts) {
+    st = lane_row<true>(a.partials + rl * a.splits, a.splits, c, a.ind, theta);
   } else {
     merge_rows_coop<NT, 4>(a.partials + rd * a.splits, N, a.splits, c, a.ind, [&](int) { return theta; },
                            [&](int row, const mars_row_stat& s) { sh_st[row] = s; });

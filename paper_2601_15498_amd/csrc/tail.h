@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kGreedyThreads) void tail_greedy_kernel(TailArgs a)
 
 // The same for requests of at most 64 nodes, a node per lane of one wave: a parent's row, token and decision come by lane
 // exchanges, so that behind the trip to memory there is neither LDS traffic nor a barrier, and what a request commits leaves
-// in one store per table.  NT: one wave where a lane merges its row alone (kFewParts partial results at most); else 1024 threads
+// in one store per table.  NT: one wave where a lane merges its row alone (kLaneParts partial results at most); else 1024 threads
 // merge, and one wave goes on.
 // What bounds it is the trip to memory and, where there are many partial results, merging them.  us per call, the kernel above and this
 // one: 64 chains of eight drafts x 128 256 with the committed tokens 32.6 -> 30.5, 112 trees of 5 x 32 000 14.1 -> 12.7, 4 trees of 22 x 151 936
@@ -212,9 +212,7 @@ __global__ __launch_bounds__(NT) void tail_greedy_wave_kernel(TailArgs a) {
   const float theta = a.theta[b];
   int2 top;
   if (!MANY) {
-    Partial q[kFewParts];
-    load_partials_of_row(a.partials + rl * a.splits, a.splits, q);
-    const mars_row_stat st = merge_row_few<false>(q, a.splits, a.c, a.ind, theta);
+    const mars_row_stat st = lane_row<false>(a.partials + rl * a.splits, a.splits, a.c, a.ind, theta);
     if (live && a.stats) a.stats[rb + lane] = st;
     top = make_int2(st.id1, st.relax_ok ? st.id2 : -1);
   } else {
@@ -901,10 +899,8 @@ __device__ __forceinline__ void tail_sampling_body(const TailArgs& a) {
       const float2 zq = a.gathered[rl];
       zx = zq.x; l_qx = zq.y;
     }
-    if (a.splits <= kFewParts) {
-      Partial pq[kFewParts];
-      load_partials_of_row(a.partials + rl * a.splits, a.splits, pq);
-      l_st = merge_row_few(pq, a.splits, a.c, a.ind, theta);
+    if (a.splits <= kLaneParts) {
+      l_st = lane_row<true>(a.partials + rl * a.splits, a.splits, a.c, a.ind, theta);
     } else {
       merge_rows_coop<NT, RESIDENT ? 8 : 4>(a.partials + rd * a.splits, N, a.splits, a.c, a.ind, [&](int) { return theta; },
                                             [&](int row, const mars_row_stat& st) { sh_st[row] = st; });
