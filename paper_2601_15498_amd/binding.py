@@ -1,9 +1,12 @@
-"""ctypes binding of libmars.so -- argument marshalling only.
+"""Binding of libmars.so -- argument marshalling only.
 
 The functions mirror include/mars.h name for name.  Tensors are torch CUDA tensors
 (ROCm); bf16 logits may be given as ``torch.bfloat16`` or as ``torch.uint16``/``int16``
 bit patterns.  Every call enqueues on the current torch stream and returns without
 synchronising.
+
+A regular call -- plain contiguous tensors, outputs and workspace given -- goes through csrc/marshal.cpp (``_marshal.so``); anything
+else through ctypes here, with the checks that say what is wrong.
 """
 import ctypes
 import os
@@ -31,6 +34,7 @@ class VerifyOptionsStruct(ctypes.Structure):
                 ("keep_rows", ctypes.c_void_p), ("keep_offsets", ctypes.c_void_p)]
 
 _lib = None
+_native = None  # csrc/marshal.cpp, once the library is loaded
 
 
 class MarsError(RuntimeError):
@@ -39,7 +43,7 @@ class MarsError(RuntimeError):
 
 def lib():
     """Load libmars.so (built by ``paper_2601_15498_amd.build``); fails loudly when missing."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise MarsError(f"{LIB_PATH} is missing: build it with `python -m paper_2601_15498_amd.build` "
@@ -89,8 +93,21 @@ def lib():
              ctypes.c_int, ctypes.c_void_p, ctypes.c_float, ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int,
              ctypes.c_void_p] + [ctypes.c_void_p] * 8
             + [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.POINTER(VerifyOptionsStruct)])
-        _lib = L
+        try:
+            from . import _marshal
+        except ImportError as e:
+            raise MarsError(f"_marshal.so is missing or does not load ({e}): build it with "
+                            "`python -m paper_2601_15498_amd.build`") from e
+        _marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                        (L.mars_verify, L.mars_verify_ex, L.mars_margin_stats, L.mars_lmhead_verify,
+                         L.mars_lmhead_verify_sampling)))
+        _lib, _native = L, _marshal
     return _lib
+
+
+def _calls():
+    lib()
+    return _native
 
 
 def _check(rc: int):
@@ -108,9 +125,7 @@ def _dtype_code(t: torch.Tensor) -> int:
     return code
 
 
-# A call of the smallest workloads takes the GPU about 9 us and the two launches the host about 8, so what this
-# module adds to them is what a caller waits for.  Pointers go over as plain integers (the argument types are
-# declared), and the stream is asked for by number: the object torch.cuda.current_stream() builds for it costs 2.9 us.
+# (The stream is asked for by number: the object torch.cuda.current_stream() builds for it costs 2.9 us.)
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -215,6 +230,12 @@ def mars_verify(logits: torch.Tensor, draft_tokens: torch.Tensor, tree_parent: t
                 draft_probs: torch.Tensor = None, out: VerifyOutputs = None,
                 workspace: torch.Tensor = None) -> VerifyOutputs:
     """The whole verification pass; see include/mars.h for argument meaning and layout."""
+    if out is not None and workspace is not None:
+        rc = (_native or _calls()).verify(logits, draft_tokens, tree_parent, theta, temperature, uniforms, draft_probs, out,
+                                          workspace, _stream)
+        if rc is not None:
+            _check(rc)
+            return out
     B, N, V = logits.shape
     dev = logits.device
     assert logits.is_contiguous()
@@ -246,6 +267,12 @@ def mars_verify_ex(logits: torch.Tensor, draft_tokens: torch.Tensor, tree_parent
                    want_commit: bool = False, spin_limit: int = 0, stages: int = 0) -> VerifyOutputs:
     """mars_verify with options: low-margin indicator, theta[K,B] swept in one pass, committed sequence and
     kept cache rows.  See include/mars.h."""
+    if out is not None and workspace is not None:
+        rc = (_native or _calls()).verify_ex(logits, draft_tokens, tree_parent, theta, temperature, uniforms, draft_probs, out,
+                                             workspace, indicator, n_theta, spin_limit, stages, _stream)
+        if rc is not None:
+            _check(rc)
+            return out
     B, N, V = logits.shape
     dev = logits.device
     assert logits.is_contiguous()
@@ -326,6 +353,11 @@ def mars_margin_stats(logits: torch.Tensor, theta: torch.Tensor, temperature: fl
     """Top-2 statistics per row ([B*N, 4] fp32: z1, z2, z2/z1, p2/p1) and their histograms (one uint32 tensor:
     three histograms of bins+2 counters each, then rows, z1 < 0, z1 <= 0, low-margin rows).  ranges: six floats
     (lo, hi of z1, of z2/z1, of p2/p1); bins: three ints.  See include/mars.h."""
+    if counts is not None and workspace is not None and (rows_out is not None or not want_rows):
+        rc = (_native or _calls()).margin_stats(logits, theta, temperature, ranges, bins, rows_out, counts, workspace, _stream)
+        if rc is not None:
+            _check(rc)
+            return rows_out, counts
     B, N, V = logits.shape
     dev = logits.device
     assert logits.is_contiguous() and theta.dtype == torch.float32 and theta.numel() == B
@@ -353,6 +385,12 @@ def mars_lmhead_verify(hidden: torch.Tensor, weight: torch.Tensor, draft_tokens:
                        want_commit: bool = False, stages: int = 0) -> VerifyOutputs:
     """Greedy verification from the last hidden states [B,N,H] and the LM-head weight [V,H] (both bf16, or
     their bit patterns): the logits are formed, reduced and dropped inside one kernel.  See include/mars.h."""
+    if out is not None and workspace is not None:
+        rc = (_native or _calls()).lmhead_verify(hidden, weight, draft_tokens, tree_parent, theta, out, workspace, indicator,
+                                                 n_theta, stages, _stream)
+        if rc is not None:
+            _check(rc)
+            return out
     B, N, H = hidden.shape
     V = weight.shape[0]
     dev = hidden.device
@@ -392,6 +430,13 @@ def mars_lmhead_verify_sampling(hidden: torch.Tensor, weight: torch.Tensor, draf
     their bit patterns): one kernel forms the logits, writes them to ``logits_out`` [B,N,V] (bf16 bit patterns) and
     takes each row's top-2 and sum of exponentials on the way; the sampling walk follows.  Returns
     (outputs, logits_out).  See include/mars.h."""
+    if logits_out is not None and out is not None and workspace is not None:
+        rc = (_native or _calls()).lmhead_verify_sampling(hidden, weight, draft_tokens, tree_parent, theta, temperature, uniforms,
+                                                          draft_probs, logits_out, out, workspace, indicator, n_theta, spin_limit,
+                                                          stages, _stream)
+        if rc is not None:
+            _check(rc)
+            return out, logits_out
     B, N, H = hidden.shape
     V = weight.shape[0]
     dev = hidden.device

@@ -1,4 +1,5 @@
-"""Compile the HIP library (csrc/mars.hip) for gfx950 into paper_2601_15498_amd/libmars.so."""
+"""Compile the HIP library (csrc/mars.hip) for gfx950 into paper_2601_15498_amd/libmars.so, and the native part of its
+Python binding (csrc/marshal.cpp) into paper_2601_15498_amd/_marshal.so."""
 import os
 import subprocess
 import sys
@@ -6,6 +7,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "mars.hip")
 LIB = os.path.join(HERE, "libmars.so")
+MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
+MARSHAL_LIB = os.path.join(HERE, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -19,11 +22,27 @@ FLAGS = [
 ]
 
 
+def build_marshal(verbose: bool = False) -> str:
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    include = [sysconfig.get_paths()["include"]] + [p for p in include_paths() if os.path.isdir(p)]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd += ["-isystem" + p for p in include] + ["-o", MARSHAL_LIB, MARSHAL_SRC]
+    cmd += ["-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return MARSHAL_LIB
+
+
 def build(verbose: bool = False, extra=()) -> str:
     cmd = [HIPCC] + FLAGS + list(extra) + ["-o", LIB, SRC]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    build_marshal(verbose)
     return LIB
 
 
