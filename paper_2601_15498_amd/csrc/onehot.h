@@ -158,7 +158,8 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
   };
   // The page from vector `page` on of vectors [range.begin, range.end) and, as a vector in front of the row's first and one behind its
   // last, the loose elements.
-  auto read_page = [&](int page, const ChunkRange& range, bool front, bool back) __attribute__((always_inline)) {
+  // `beside` is done while the page is on its way.
+  auto read_page = [&](int page, const ChunkRange& range, bool front, bool back, auto beside) __attribute__((always_inline)) {
     const T* __restrict__ vecp = rowp + head;
     const int begin = front ? -1 : range.begin, end = back ? nvec + 1 : range.end;
     if (range.end > range.begin) {
@@ -169,6 +170,8 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
 #pragma unroll
       for (int m = 0; m < PV; ++m) raw[m].fill_neg_inf();
     }
+    __builtin_amdgcn_sched_barrier(0);
+    beside();
 #pragma unroll
     for (int m = 0; m < PV; ++m) {
       const int vec = page + m * NT + tid;
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     z1 = lane_value(st.z1, cnode);
     R = __builtin_ceilf(z1 * c);  // (an integer, as the references of the sums)
     if constexpr (ROW) {
-      read_page(head > 0 ? -1 : 0, {0, nvec}, head > 0, tail > 0);
+      read_page(head > 0 ? -1 : 0, {0, nvec}, head > 0, tail > 0, [] {});
       total = lane_value(tile_incl, kWave - 1);
       if (!summed) break;
       if (!(total > 0.0)) {  // nothing is left without it: f stays as it was
@@ -451,6 +454,34 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     chunk = hl * per + lane_value(in_run, hl);
     cum = lane_value(front, hl);
   }
+  const int last_node_top1 = lane_value(st.id1, cnode);
+  double whole = 0.0;  // the sum against the row's largest logit
+  // What a token's share is taken of (bonus_prob): the sum against the row's largest logit, whose term is 1.  The sums of chunks are against whole numbers, in steps that
+  // bring an error of their own for every term, which matters for the largest: these two are taken out of the sum as they were
+  // added.  (Largest error of bonus_prob over 16 seeds, one tree
+  // of 60 nodes x 151 936 and one of 9 x 32 000: 5e-8 and 1.0e-7, as the walk that goes over the row; with the terms as the sums have them 1.9e-7 and
+  // 3.2e-7.)
+  // (Worked out beside the trip to the chunk.  Behind it, 16 drawn calls of more than 32 752 entries took 0.6 % more, one chain of 30 x 128 256 with seven thresholds 16.2 us
+  // instead of 15.5.)
+  auto settle = [&]() __attribute__((always_inline)) {
+    double sum = total, again = 0.0;
+    auto put_right = [&](int v, float z) {
+      const Place to = place_of(v);
+      const unsigned long long bit = 1ull << lane;
+      if (v < 0 || __any((gone & bit) != 0ull && tok == v)) return;
+      float ref = R;
+      if (!COLUMNS) {
+#pragma unroll
+        for (int w = 0; w < kChunkWaves; ++w) ref = w == to.piece ? lane_value(part[w].y, to.chunk) : ref;
+      }
+      const bool exact = __any((redone & bit) != 0ull && at.chunk == to.chunk && at.piece == to.piece);
+      sum -= exact ? static_cast<double>(precise(z)) : scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(z, c, -ref)), ref);
+      again += static_cast<double>(__builtin_amdgcn_exp2f((z - z1) * c));
+    };
+    put_right(last_node_top1, z1);
+    put_right(lane_value(st.id2, cnode), lane_value(st.z2, cnode));
+    whole = sum * exp2(static_cast<double>(R) - static_cast<double>(z1) * static_cast<double>(c)) + again;
+  };
   int pick = -1;
   float pick_z = 0.0f;
   if (chunk >= 0) {
@@ -461,7 +492,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     int last_page = -1;
     bool take_last = false;  // rounding has left no entry above the target: the last one with mass
     for (int page = begin; page < end; page += PV * NT) {
-      if (!ROW) read_page(page, range, front, back);
+      if (!ROW) read_page(page, range, front, back, [&] { if (page == begin && a.diag) settle(); });
       const unsigned long long hit = __ballot(cum + tile_incl > target), any = __ballot(tile_sum > 0.0);
       if ((ROW || hit != 0ull || take_last) && any != 0ull) {
         const int tl = hit != 0ull && !take_last ? __ffsll(static_cast<long long>(hit)) - 1 : 63 - __clzll(static_cast<long long>(any));
@@ -519,34 +550,9 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
   }
   if (pick < 0 && wave != 0) return;
   // ---------------------------------------------------------------- results, by one wave
-  const int last_node_top1 = lane_value(st.id1, cnode);
   float prob = 0.0f;
   if (pick >= 0) {
-    // Its share of the sum, against the row's largest logit: that one's term is 1.  The sums of chunks are against whole numbers, in steps that
-    // bring an error of their own for every term, which matters for the largest: these two are taken out of the sum as they were
-    // added.(Largest error of bonus_prob over 16 seeds, one tree
-    // of 60 nodes x 151 936 and one of 9 x 32 000: 5e-8 and 1.0e-7, as the walk that goes over the row; with the terms as the sums have them 1.9e-7 and
-    // 3.2e-7.)
-    double sum = total;
-    if (!ROW) {
-      double again = 0.0;
-      auto put_right = [&](int v, float z) {
-        const Place to = place_of(v);
-        const unsigned long long bit = 1ull << lane;
-        if (v < 0 || __any((gone & bit) != 0ull && tok == v)) return;
-        float ref = R;
-        if (!COLUMNS) {
-#pragma unroll
-          for (int w = 0; w < kChunkWaves; ++w) ref = w == to.piece ? lane_value(part[w].y, to.chunk) : ref;
-        }
-        const bool exact = __any((redone & bit) != 0ull && at.chunk == to.chunk && at.piece == to.piece);
-        sum -= exact ? static_cast<double>(precise(z)) : scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(z, c, -ref)), ref);
-        again += static_cast<double>(__builtin_amdgcn_exp2f((z - z1) * c));
-      };
-      put_right(last_node_top1, z1);
-      put_right(lane_value(st.id2, cnode), lane_value(st.z2, cnode));
-      sum = sum * exp2(static_cast<double>(R) - static_cast<double>(z1) * static_cast<double>(c)) + again;
-    }
+    const double sum = ROW ? total : whole;
     prob = static_cast<float>(static_cast<double>(__builtin_amdgcn_exp2f((pick_z - z1) * c)) / sum);
   }
   const int token = pick >= 0 ? pick : last_node_top1;  // (no mass anywhere)
