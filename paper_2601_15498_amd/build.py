@@ -22,19 +22,19 @@ FLAGS = [
 ]
 
 
-def build_marshal(verbose: bool = False) -> str:
+def build_marshal(verbose: bool = False, out: str = MARSHAL_LIB, extra=()) -> str:
     import sysconfig
     import torch
     from torch.utils.cpp_extension import include_paths
     include = [sysconfig.get_paths()["include"]] + [p for p in include_paths() if os.path.isdir(p)]
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
-    cmd += ["-isystem" + p for p in include] + ["-o", MARSHAL_LIB, MARSHAL_SRC]
+    cmd += ["-isystem" + p for p in include] + list(extra) + ["-o", out, MARSHAL_SRC]
     cmd += ["-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
-    return MARSHAL_LIB
+    return out
 
 
 def build(verbose: bool = False, extra=()) -> str:

@@ -37,17 +37,24 @@ const Tensor& tensor(PyObject* o) {
 }
 // (data_ptr() throws where a tensor has no memory of its own)
 template <typename T> T* address(const Tensor& t) { return static_cast<T*>(t.data_ptr()); }
+void require(bool ok) { if (!ok) throw Irregular(); }
+// An attribute, held until it has been looked at: it may have been made when it was asked for (a property that returns a view of
+// a larger buffer), and then nobody else holds it.
+struct Attribute {
+  PyObject* o;
+  Attribute(PyObject* of, Field f) : o(PyObject_GetAttr(of, g_names[f])) { require(o != nullptr); }
+  ~Attribute() { Py_DECREF(o); }
+  Attribute(const Attribute&) = delete;
+  Attribute& operator=(const Attribute&) = delete;
+};
 template <typename T> T* field(PyObject* out, Field f, bool optional = false) {
-  PyObject* o = PyObject_GetAttr(out, g_names[f]);
-  if (!o) throw Irregular();
-  Py_DECREF(o);  // (the object's own reference holds it)
-  if (o == Py_None) {
-    if (!optional) throw Irregular();
+  const Attribute a(out, f);
+  if (a.o == Py_None) {
+    require(optional);
     return nullptr;
   }
-  return address<T>(tensor(o));
+  return address<T>(tensor(a.o));
 }
-void require(bool ok) { if (!ok) throw Irregular(); }
 int code(const Tensor& t) {
   const auto s = t.scalar_type();
   if (s == at::kFloat) return MARS_F32;
@@ -110,10 +117,7 @@ struct Requests {
   }
 };
 mars_verify_options options_of(PyObject* out, PyObject* indicator, int K, PyObject* spin_limit, PyObject* stages) {
-  PyObject* n = PyObject_GetAttr(out, g_names[kThetas]);
-  require(n != nullptr);
-  Py_DECREF(n);
-  require(integer(n) == K);
+  require(integer(Attribute(out, kThetas).o) == K);
   mars_verify_options o = {};
   o.indicator = integer(indicator); o.n_theta = K; o.spin_limit = integer(spin_limit); o.stages = integer(stages);
   o.out_tokens = field<int32_t>(out, kOutTokens, true); o.out_len = field<int32_t>(out, kOutLen, true);

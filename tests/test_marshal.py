@@ -2,6 +2,11 @@
 replaced by ones that write down what they are given.  A regular call hands over the same arguments either way; a call that is not
 regular in any one respect is left alone."""
 import ctypes
+import importlib.util
+import os
+import shutil
+import subprocess
+import sys
 from types import SimpleNamespace
 
 import pytest
@@ -39,6 +44,10 @@ def recorder(monkeypatch):
     names = ("mars_verify", "mars_verify_ex", "mars_margin_stats", "mars_lmhead_verify", "mars_lmhead_verify_sampling")
     stubs = {n: stub(getattr(real, n)) for n in names}
     native = M._calls()
+    if "MARSHAL_UNDER_TEST" in os.environ:   # a build of the module other than the package's
+        spec = importlib.util.spec_from_file_location("_marshal", os.environ["MARSHAL_UNDER_TEST"])
+        native = importlib.util.module_from_spec(spec)
+        monkeypatch.setattr(M, "_native", native)
     native.bind(*(ctypes.cast(stubs[n], PTR).value for n in names))
     # the general way: the same stubs behind ctypes
     general = {n: (lambda c, k: lambda *a: c(*[ctypes.cast(x, PTR) if isinstance(x, (ctypes.Array, type(ctypes.byref(ctypes.c_int()))))
@@ -121,6 +130,57 @@ def test_a_call_that_is_not_regular_is_left_alone(recorder, what):
     assert native.verify(s.logits, s.tok, s.par, s.theta, s.T, s.u, s.q, s.out, s.ws, lambda: 0) is None
     assert native.verify_ex(s.logits, s.tok, s.par, s.theta, s.T, s.u, s.q, s.out, s.ws, 0, 1, 0, 0, lambda: 0) is None
     assert native.verify(s.logits) is None and not got
+
+
+class Slot(M.VerifyOutputs):
+    """Outputs whose attributes are made when they are asked for: views of slot 1 of larger buffers that nobody else holds, and a
+    number of thresholds that is worked out."""
+
+    def __init__(self, like):
+        self.buf = {k: (torch.stack([v, v]) if isinstance(v, torch.Tensor) else v) for k, v in like.__dict__.items()}
+
+    def __getattr__(self, name):
+        if name == "buf" or name not in self.buf:
+            raise AttributeError(name)
+        v = self.buf[name]
+        return v[1] if isinstance(v, torch.Tensor) else v
+
+
+class Made(Slot):
+    accept_mask = property(lambda self: self.buf["accept_mask"][1])
+    n_theta = property(lambda self: int("1000000") - 1000000 + self.buf["n_theta"])
+
+
+@pytest.mark.parametrize("kind", [Slot, Made])
+@pytest.mark.parametrize("entry", [e for e in ENTRIES if e != "margin_stats"])
+def test_outputs_that_are_made_when_they_are_asked_for(recorder, monkeypatch, kind, entry):
+    got, native, general = recorder
+    s = inputs(commit=entry != "verify")
+    s.out = kind(s.out)
+    monkeypatch.setattr(M, "_lib", None)   # the general way is not taken
+    ENTRIES[entry](s)
+    assert len(got) == 1 and s.out.accept_mask.data_ptr() in got[0] and s.out.path_idx.data_ptr() in got[0]
+    monkeypatch.setattr(M, "_lib", general)
+    monkeypatch.setattr(M, "_native", SimpleNamespace(**{e: lambda *a: None for e in ENTRIES}))
+    ENTRIES[entry](s)
+    assert len(got) == 2 and got[0] == got[1]
+
+
+def test_no_object_is_looked_at_once_it_has_been_given_back(tmp_path):
+    # the calls above with the module built under AddressSanitizer, in a process of its own
+    if shutil.which("g++") is None:
+        pytest.skip("needs g++")
+    from paper_2601_15498_amd import build
+    lib = str(tmp_path / "_marshal.so")
+    build.build_marshal(out=lib, extra=["-O1", "-g", "-fsanitize=address"])
+    asan = subprocess.run(["g++", "-print-file-name=libasan.so"], capture_output=True, text=True).stdout.strip()
+    env = dict(os.environ, MARSHAL_UNDER_TEST=lib, LD_PRELOAD=" ".join([asan, os.environ.get("LD_PRELOAD", "")]).strip(), PYTHONMALLOC="malloc",
+               ASAN_OPTIONS="verify_asan_link_order=0:detect_leaks=0:allocator_may_return_null=1")
+    run = subprocess.run([sys.executable, "-m", "pytest", "-x", "-q", "-s", "-p", "no:cacheprovider", os.path.abspath(__file__),
+                          "-k", "made_when_they_are_asked_for or either_way"], capture_output=True, text=True, env=env, timeout=600,
+                         cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    said = (run.stdout + run.stderr)
+    assert run.returncode == 0 and "AddressSanitizer" not in said, said[:2000]
 
 
 def test_errors_come_from_the_general_way():
