@@ -6,10 +6,11 @@ bit patterns.  Every call enqueues on the current torch stream and returns witho
 synchronising.
 
 A regular call -- plain contiguous tensors, outputs and workspace given -- goes through csrc/marshal.cpp (``_marshal.so``); anything
-else through ctypes here, with the checks that say what is wrong.
+else through ctypes here, with the checks that say what is wrong, and so does every call where that module does not load.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -93,16 +94,28 @@ def lib():
              ctypes.c_int, ctypes.c_void_p, ctypes.c_float, ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int,
              ctypes.c_void_p] + [ctypes.c_void_p] * 8
             + [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.POINTER(VerifyOptionsStruct)])
-        try:
-            from . import _marshal
-        except ImportError as e:
-            raise MarsError(f"_marshal.so is missing or does not load ({e}): build it with "
-                            "`python -m paper_2601_15498_amd.build`") from e
-        _marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
-                        (L.mars_verify, L.mars_verify_ex, L.mars_margin_stats, L.mars_lmhead_verify,
-                         L.mars_lmhead_verify_sampling)))
-        _lib, _native = L, _marshal
+        _native = _load_native(L)   # (before _lib: whoever sees the library has the calls)
+        _lib = L
     return _lib
+
+
+class _NoNative:
+    """In place of csrc/marshal.cpp: no call is a regular one."""
+    verify = verify_ex = margin_stats = lmhead_verify = lmhead_verify_sampling = staticmethod(lambda *args: None)
+
+
+def _load_native(L):
+    try:
+        from . import _marshal
+        if _marshal.torch_version != torch.__version__:
+            raise ImportError(f"built with PyTorch {_marshal.torch_version}, not {torch.__version__}")
+    except ImportError as e:
+        warnings.warn(f"_marshal.so is missing or does not load ({e}): calls go through ctypes, which costs some 4 us each; "
+                      "build it with `python -m paper_2601_15498_amd.build`", RuntimeWarning, stacklevel=3)
+        return _NoNative
+    _marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                    (L.mars_verify, L.mars_verify_ex, L.mars_margin_stats, L.mars_lmhead_verify, L.mars_lmhead_verify_sampling)))
+    return _marshal
 
 
 def _calls():

@@ -294,5 +294,11 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, g_method
 PyMODINIT_FUNC PyInit__marshal() {
   for (int i = 0; i < kFields; ++i)
     if (!(g_names[i] = PyUnicode_InternFromString(kNames[i]))) return nullptr;
-  return PyModule_Create(&g_module);
+  PyObject* m = PyModule_Create(&g_module);
+  // (what it was built against: the binding looks at no tensor through another version's layout)
+  if (m && PyModule_AddStringConstant(m, "torch_version", MARS_TORCH_VERSION) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
 }

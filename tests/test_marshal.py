@@ -2,6 +2,7 @@
 replaced by ones that write down what they are given.  A regular call hands over the same arguments either way; a call that is not
 regular in any one respect is left alone."""
 import ctypes
+import dis
 import importlib.util
 import os
 import shutil
@@ -181,6 +182,31 @@ def test_no_object_is_looked_at_once_it_has_been_given_back(tmp_path):
                          cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
     said = (run.stdout + run.stderr)
     assert run.returncode == 0 and "AddressSanitizer" not in said, said[:2000]
+
+
+@pytest.mark.parametrize("why", ["missing", "another PyTorch"])
+def test_without_the_native_module_calls_go_through_ctypes(recorder, monkeypatch, why):
+    got, native, general = recorder
+    if why == "missing":
+        monkeypatch.setitem(sys.modules, "paper_2601_15498_amd._marshal", None)   # its import fails
+        monkeypatch.delattr("paper_2601_15498_amd._marshal", raising=False)
+    else:
+        monkeypatch.setattr(native, "torch_version", "0.4.1")
+    monkeypatch.setattr(M, "_lib", None)
+    monkeypatch.setattr(M, "_native", None)
+    with pytest.warns(RuntimeWarning, match="through ctypes"):
+        assert M.mars_version() > 0
+    monkeypatch.setattr(M, "_lib", general)
+    s = inputs()
+    for entry in ENTRIES:
+        ENTRIES[entry](s)
+    assert len(got) == len(ENTRIES)
+
+
+def test_the_calls_are_there_before_the_library_is():
+    # (another thread's first call may come between the two)
+    order = [i.argval for i in dis.get_instructions(M.lib) if i.opname == "STORE_GLOBAL"]
+    assert order == ["_native", "_lib"]
 
 
 def test_errors_come_from_the_general_way():
