@@ -3,8 +3,7 @@
 // chunks instead of the whole row.
 //
 // A row is `items` shares of `vps` 16-byte vectors.  A share is streamed in batches of kChunkVecs vectors; `batches` of them
-// are a chunk, the last chunk takes what is left: the batches behind the stream's main loop, and the share's ragged end.  Behind the
-// fused LM head a share is a column of tiles and its only chunk.  (A row's loose elements, in front of its first aligned vector and
+// are a chunk, the last chunk takes what is left: the batches behind the stream's main loop, and the share's ragged end.  (A row's loose elements, in front of its first aligned vector and
 // behind its last, belong to its first and its last chunk.)
 #pragma once
 

@@ -407,16 +407,15 @@ constexpr int kMinRaggedChunked = 22 * 4096;
 constexpr int kPageGroups = 6;
 static hipError_t launch_onehot_tail(const TailArgs& a, int logits_dtype, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned int>(a.B));
-  const bool even = even_rows(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, a.V), row = a.gathered && !a.table;
-#define MARS_ONEHOT(T, COLUMNS, ROW, NT)                                                                                       \
-  if (COLUMNS || even) hipLaunchKernelGGL((tail_onehot_kernel<T, false, COLUMNS, ROW, NT>), grid, dim3(NT), 0, stream, a);      \
-  else hipLaunchKernelGGL((tail_onehot_kernel<T, !COLUMNS, COLUMNS, ROW, NT>), grid, dim3(NT), 0, stream, a)
+  const bool even = even_rows(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, a.V), row = !a.table;
+#define MARS_ONEHOT(T, ROW, NT)                                                                                                \
+  if (even) hipLaunchKernelGGL((tail_onehot_kernel<T, false, ROW, NT>), grid, dim3(NT), 0, stream, a);                          \
+  else hipLaunchKernelGGL((tail_onehot_kernel<T, true, ROW, NT>), grid, dim3(NT), 0, stream, a)
 #define MARS_ONEHOT_ROWS(T)                                                                                                    \
-  if (row && a.V <= row_entries(kOneHotThreads)) { MARS_ONEHOT(T, false, true, kOneHotThreads); }                              \
-  else if (row) { MARS_ONEHOT(T, false, true, 2 * kOneHotThreads); }                                                           \
-  else { MARS_ONEHOT(T, false, false, kOneHotThreads); }
-  if (!a.gathered) { MARS_ONEHOT(bf16_t, true, false, kOneHotThreads); }  // behind the LM head
-  else if (logits_dtype == MARS_BF16) { MARS_ONEHOT_ROWS(bf16_t) }
+  if (row && a.V <= row_entries(kOneHotThreads)) { MARS_ONEHOT(T, true, kOneHotThreads); }                              \
+  else if (row) { MARS_ONEHOT(T, true, 2 * kOneHotThreads); }                                                           \
+  else { MARS_ONEHOT(T, false, kOneHotThreads); }
+  if (logits_dtype == MARS_BF16) { MARS_ONEHOT_ROWS(bf16_t) }
   else { MARS_ONEHOT_ROWS(float) }
 #undef MARS_ONEHOT_ROWS
 #undef MARS_ONEHOT
@@ -425,7 +424,7 @@ static hipError_t launch_onehot_tail(const TailArgs& a, int logits_dtype, hipStr
 // The sampling walk: G work-groups per request (a.G), a.B requests.  draft_dtype < 0: one-hot.
 static hipError_t launch_sampling_tail(const TailArgs& a, int logits_dtype, int draft_dtype, hipStream_t stream) {
   const int V = a.V;
-  if (draft_dtype < 0 && a.chunks.slots > 0) return launch_onehot_tail(a, logits_dtype, stream);
+  if (a.onehot) return launch_onehot_tail(a, logits_dtype, stream);
   const bool dense = draft_dtype >= 0;
   const bool vec = whole_groups(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, dense ? a.dprobs : nullptr, a.N, V);
   // Slices of at most kMaxResident groups of eight per thread stay in registers between passes.  One per thread in the
@@ -651,8 +650,8 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   a.xslots = clr.xslots;
   a.mask = accept_mask; a.len = accept_len; a.path = path_idx; a.bonus = bonus_token;
   a.dec = decision; a.status = request_status; a.diag = diag;
-  a.chunks = chunks; a.table = clr.table; a.two_from = L.splits;
-  if (!onehot) a.chunks.slots = 0;
+  a.chunks = chunks; a.table = clr.table;
+  a.onehot = onehot;
   a.B = K * B; a.Bd = B; a.N = N; a.V = V; a.splits = L.splits * kPartsPerItem; a.c = c;
   a.ind.kind = indicator; a.ind.cind = indicator_scale(temperature);
   a.out_tok = out_tokens; a.out_len = out_len;
@@ -779,7 +778,7 @@ int mars_lmhead_verify(const void* hidden, const void* weight, int H, const int3
   if (!(lm_stages & MARS_STAGE_REQUESTS)) return MARS_OK;
 
   TailArgs a;
-  a.logits = nullptr; a.tok = draft_tokens; a.par = tree_parent; a.dprobs = nullptr;
+  a.logits = nullptr; a.tok = draft_tokens; a.par = tree_parent; a.dprobs = nullptr; a.onehot = false;
   a.theta = theta; a.u = nullptr; a.partials = partials;
   a.stats = stats;
   a.G = 1; a.spin_limit = 0; a.xslots = nullptr; a.gathered = nullptr; a.table = nullptr;
@@ -852,10 +851,10 @@ int mars_lmhead_verify_sampling(const void* hidden, const void* weight, int H, c
   a.dprobs = dense ? draft_probs : nullptr;
   a.theta = theta; a.u = uniforms; a.partials = partials;
   a.gathered = nullptr;  // the walk gathers for itself: no streaming row reduction has run
-  // A column of tiles is a chunk, its sum in one partial result or two.
-  a.chunks = chunk_spec(p.parts - (p.parts - p.grid.split) / 2, p.grid.width * p.bn / 8, 1, 0);
-  if (dense || N > kOneHotNodes || a.chunks.items > kMaxColumns) a.chunks.slots = 0;
-  a.table = nullptr; a.two_from = p.grid.split;
+  // (The sums that the fused kernel leaves, one per column of tiles, are fp32 sums of fp32 sums, for the row statistics; a draw is made from sums in 64 bits, so
+  // it goes over the row.)
+  a.chunks = {}; a.table = nullptr;
+  a.onehot = !dense && N <= kOneHotNodes && V <= row_entries(2 * kOneHotThreads);
   a.stats = stats;
   a.G = launch_groups(L.G, K * B);
   a.spin_limit = spin_limit > 0 ? spin_limit : kDefaultSpinLimit;

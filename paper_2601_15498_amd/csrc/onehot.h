@@ -26,13 +26,10 @@ namespace mars {
 constexpr int kOneHotNodes = kWave;
 constexpr int kOneHotThreads = 512;
 constexpr int kPageEntries = 32;   // the draw looks at a row, or at a chunk, in pages of this many entries per thread (48: no gain)
-constexpr int kRunChunks = 4;      // behind the fused LM head: columns per lane, at most
-constexpr int kMaxColumns = kRunChunks * kWave;
 // The sum of a chunk less a token's own term is a difference of fp32 sums.  If the token holds more than this share of what is left of the row, the
 // part of the chunk that it was summed with is summed again without it.
 constexpr double kTakenShare = 0.25;
 
-// COLUMNS: behind the fused LM head.  A chunk is a column of tiles, its sum in a row's partial results.
 // ROW: a vocabulary of one page (of 512 threads up to 16 368 entries, of 1 024 up to 32 752).  The row itself is read where the walk stops,
 // one trip instead of those to the sums and to a chunk, rejected tokens are left out where the terms are formed, and the row reduction
 // leaves no sums of chunks.  us per call, the walk that goes over the row by all of a request's work-groups / by chunks / this one: 30 trees of 32 x 3 458
@@ -40,7 +37,7 @@ constexpr double kTakenShare = 0.25;
 // 37 x 32 000 bf16 25.0 / 25.2 / 22.3, 4 of 34 x 32 000 19.6 / 16.8 / 14.9; 33 of 12 x 32 000 20.2 / 21.0 / 21.2, and in fp32 10 chains of 13 x 32 000 16.7
 // / 17.7 / 16.9.
 constexpr int row_entries(int threads) { return threads * kPageEntries - 16; }  // (loose elements are a vector in front and one behind)
-template <typename T, bool RAGGED, bool COLUMNS, bool ROW, int NT>
+template <typename T, bool RAGGED, bool ROW, int NT>
 __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail_onehot_kernel(TailArgs a) {
   constexpr int NW = NT / kWave;
   constexpr int EPV = 16 / sizeof(T), PV = kPageEntries / EPV;  // entries of a vector, vectors per thread and page
@@ -69,7 +66,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
   const float u_draw = a.u[static_cast<size_t>(bd) * (N + 1) + N];
   const float theta = a.theta[b];
   float zx = 0.0f;
-  if (!COLUMNS) zx = a.gathered[rl].x;
+  if (!ROW || a.gathered) zx = a.gathered[rl].x;
   mars_row_stat st;
   if (a.splits <= kLaneParts) {
     st = lane_row<true>(a.partials + rl * a.splits, a.splits, c, a.ind, theta);
@@ -87,7 +84,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     return;
   }
   const bool node = live && lane > 0;  // (the root is no draft)
-  if (COLUMNS && node) zx = widen(zall[static_cast<size_t>(par) * V + tok]);  // behind the fused LM head: a second trip
+  if (ROW && !a.gathered && node) zx = widen(zall[static_cast<size_t>(par) * V + tok]);  // behind the fused LM head: a second trip
   const int p = node ? par : 0;
   // (LDS operations of a wave are performed in order; the fences keep the compiler's order)
   sh_kids[wave][lane] = 0ull;
@@ -111,23 +108,16 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
   int head = 0, nvec = 0, tail = 0;
   float R = 0.0f, z1 = 0.0f;
   unsigned long long gone = 0ull;  // nodes whose tokens are out of f at cnode
-  constexpr int kRun = COLUMNS ? kRunChunks : 1;
-  double total = 0.0, mass[kRun];
-  auto run_sum = [&]() {
-    double sum = mass[0];
-#pragma unroll
-    for (int r = 1; r < kRun; ++r) sum += mass[r];
-    return sum;
-  };
+  double total = 0.0, mass = 0.0;  // (mass: lane l's of chunk l)
   Vec<T, EPV> raw[PV];             // a page of the row as it lies in memory, the terms of its entries, of its vectors
   float e[PV][EPV], g[PV];
   double tile_first = 0.0, tile_sum = 0.0, tile_incl = 0.0;  // lane l: of the first of its tiles, of its tiles, of all up to them
-  float2 part[kChunkWaves];        // what the lane's chunks were summed in: COLUMNS two each, else the eight waves'
+  float2 part[kChunkWaves];        // what the lane's chunk was summed in: the eight waves'
   const ChunkSpec spec = a.chunks;
-  const int nchunks = spec.items * spec.slots, per = COLUMNS ? (nchunks + kWave - 1) / kWave : 1;
+  const int nchunks = spec.items * spec.slots;
   int turn = 0;
   auto vector_of = [&](int v) { return RAGGED && v < head ? -1 : (v - head) / EPV; };
-  // Chunk of an entry, the piece of it that the entry was summed with: a wave's vectors, or the whole column.
+  // Chunk of an entry, the piece of it that the entry was summed with: a wave's vectors.
   struct Place { int chunk, piece; };
   Place at = {0, 0};                // of this node's token, if it is out of f
   unsigned long long redone = 0ull;  // nodes whose tokens' pieces have been summed again
@@ -140,7 +130,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
       to.chunk = (spec.items - 1) * spec.slots + chunk_last(spec, nvec - first);
     } else if (!RAGGED || vec >= 0) {
       to.chunk = chunk_of(spec, nvec, vec);
-      if (!COLUMNS) to.piece = (vec - chunk_range(spec, nvec, to.chunk).begin) / kWave % kChunkWaves;
+      to.piece = (vec - chunk_range(spec, nvec, to.chunk).begin) / kWave % kChunkWaves;
     }
     return to;
   };
@@ -274,7 +264,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     const bool summed = out != 0ull && norm_last < 0.0f && !(z_last >= kClosedFormMinNorm);  // Z comes out of the sums below
     if (out != 0ull && !summed) last_norm = z_last;
 
-    // The sums of the row's chunks against 2^R, lane l's run of them.
+    // The sums of the row's chunks against 2^R, lane l's of chunk l.
     rowp = zall + static_cast<size_t>(cnode) * V;
     head = RAGGED ? min(V, static_cast<int>((16u - (reinterpret_cast<uintptr_t>(rowp) & 15u)) % 16u / sizeof(T))) : 0;
     nvec = (V - head) / EPV;
@@ -300,45 +290,25 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
       break;
     }
     const size_t row = rd + cnode;
-    const float2* __restrict__ table = COLUMNS ? nullptr : a.table + row * nchunks * kChunkWaves;
-    const Partial* __restrict__ columns = a.partials + row * a.splits;
-    auto first_part = [&](int i) { return i < a.two_from ? i : 2 * i - a.two_from; };
-    auto column_part = [&](int i, int n) {  // (n: 0, 1)
-      const Partial* __restrict__ q = columns + first_part(min(i, nchunks - 1)) + (i < a.two_from ? 0 : n);
-      return make_float2(i < nchunks && (n == 0 || i >= a.two_from) ? q->s : 0.0f, q->ref);
-    };
-    if (COLUMNS) {
+    const float2* __restrict__ table = a.table + row * nchunks * kChunkWaves;
+    const float4* __restrict__ t = reinterpret_cast<const float4*>(table + min(lane, nchunks - 1) * kChunkWaves);
 #pragma unroll
-      for (int r = 0; r < kRunChunks; ++r)
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-          part[2 * r + n] = r < per ? column_part(lane * per + r, n) : make_float2(0.0f, 0.0f);
-    } else {
-      const float4* __restrict__ t = reinterpret_cast<const float4*>(table + min(lane, nchunks - 1) * kChunkWaves);
-#pragma unroll
-      for (int w = 0; w < kChunkWaves; w += 2) {
-        const float4 q = t[w / 2];
-        part[w] = make_float2(lane < nchunks ? q.x : 0.0f, q.y);
-        part[w + 1] = make_float2(lane < nchunks ? q.z : 0.0f, q.w);
-      }
+    for (int w = 0; w < kChunkWaves; w += 2) {
+      const float4 q = t[w / 2];
+      part[w] = make_float2(lane < nchunks ? q.x : 0.0f, q.y);
+      part[w + 1] = make_float2(lane < nchunks ? q.z : 0.0f, q.w);
     }
-#pragma unroll
-    for (int r = 0; r < kRun; ++r) mass[r] = 0.0;
-    auto change = [&](int chunk, double by) {
-      const int r0 = chunk - lane * per;
-#pragma unroll
-      for (int r = 0; r < kRun; ++r) mass[r] += r < per && r == r0 ? by : 0.0;
-    };
+    mass = 0.0;
+    auto change = [&](int chunk, double by) { mass += lane == chunk ? by : 0.0; };
     // Rejected tokens leave the sums.
     const bool mine = ((gone >> lane) & 1ull) != 0ull && f > 0.0f;  // (a token met twice is out already)
     at = {0, 0};
     redone = 0ull;
     if (gone != 0ull) {
-      float2 was[2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};
+      float2 was = {0.0f, 0.0f};
       if (mine) {
         at = place_of(tok);
-        if (COLUMNS) { was[0] = column_part(at.chunk, 0); was[1] = column_part(at.chunk, 1); }
-        else was[0] = table[at.chunk * kChunkWaves + at.piece];
+        was = table[at.chunk * kChunkWaves + at.piece];
       }
       const float rest = 1.0f - wave_sum(mine ? f0 : 0.0f);
       unsigned long long heavy = __ballot(mine && f0 > kTakenShare * rest);
@@ -361,8 +331,8 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
           sum += static_cast<double>(s);
         };
         // (the piece's vectors, 64 at a time, dealt out to the waves)
-        constexpr int kStride = COLUMNS ? NT : NW * kChunkWaves * kWave;
-        const int v_first = range.begin + (COLUMNS ? wave : wave * kChunkWaves + piece) * kWave;
+        constexpr int kStride = NW * kChunkWaves * kWave;
+        const int v_first = range.begin + (wave * kChunkWaves + piece) * kWave;
         for (int v0 = v_first; v0 < range.end; v0 += kStride) {
           Vec<T, EPV> raw;
           const int vec = v0 + lane;
@@ -389,12 +359,10 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
         __syncthreads();
         const double again = wave_sum(lane < NW ? sh_piece[turn][lane] : 0.0);
         turn ^= 1;
-        double before = scaled(lane_value(was[0].x, j), lane_value(was[0].y, j));
-        if (COLUMNS) before += scaled(lane_value(was[1].x, j), lane_value(was[1].y, j));
-        change(chunk, again - before);
+        change(chunk, again - scaled(lane_value(was.x, j), lane_value(was.y, j)));
       }
       // (the others as they were added)
-      const double term = COLUMNS ? static_cast<double>(precise(zx)) : scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(zx, c, -was[0].y)), was[0].y);
+      const double term = scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(zx, c, -was.y)), was.y);
       for (unsigned long long light = __ballot(mine) & ~redone; light != 0ull; light &= light - 1ull) {
         const int j = __ffsll(static_cast<long long>(light)) - 1;
         change(lane_value(at.chunk, j), -lane_value(term, j));
@@ -402,17 +370,12 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     }
     double all = 0.0;
 #pragma unroll
-    for (int r = 0; r < kRun; ++r) {
-      double m = 0.0;
-#pragma unroll
-      for (int w = 0; w < kChunkWaves / kRun; ++w) m += scaled(part[r * (kChunkWaves / kRun) + w].x, part[r * (kChunkWaves / kRun) + w].y);
-      all += m;
-      m += mass[r];
-      mass[r] = m > 1e-37 ? m : 0.0;
-    }
+    for (int w = 0; w < kChunkWaves; ++w) all += scaled(part[w].x, part[w].y);
+    mass += all;
+    mass = mass > 1e-37 ? mass : 0.0;
     if (gone != 0ull) {
       if (summed) {
-        total = wave_sum(run_sum());
+        total = wave_sum(mass);
         all = wave_sum(all);
         if (!(total > 0.0)) {  // nothing is left without it: f stays as it was
           norm = lane == last ? 0.0f : norm;
@@ -432,8 +395,8 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
   }
 
   // ---------------------------------------------------------------- the draw
-  const double run = ROW ? 0.0 : run_sum(), run_incl = ROW ? 0.0 : wave_prefix_sum(run);
-  if (!ROW) total = lane_value(run_incl, kWave - 1);
+  const double incl = ROW ? 0.0 : wave_prefix_sum(mass);
+  if (!ROW) total = lane_value(incl, kWave - 1);
   const double target = static_cast<double>(u_draw) * total;
   int chunk = -1;
   double cum = 0.0;
@@ -441,18 +404,9 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     chunk = total > 0.0 ? 0 : -1;
   } else if (total > 0.0) {
     // The chunk the target falls into; where rounding leaves none, the last one with mass.
-    const unsigned long long hit = __ballot(run_incl > target), any = __ballot(run > 0.0);
-    const int hl = hit != 0ull ? __ffsll(static_cast<long long>(hit)) - 1 : 63 - __clzll(static_cast<long long>(any));
-    double at = run_incl - run, front = at;
-    int in_run = 0;
-    bool over = false;
-#pragma unroll
-    for (int r = 0; r < kRun; ++r) {
-      if (!over && mass[r] > 0.0) { in_run = r; front = at; over = at + mass[r] > target; }
-      at += mass[r];
-    }
-    chunk = hl * per + lane_value(in_run, hl);
-    cum = lane_value(front, hl);
+    const unsigned long long hit = __ballot(incl > target), any = __ballot(mass > 0.0);
+    chunk = hit != 0ull ? __ffsll(static_cast<long long>(hit)) - 1 : 63 - __clzll(static_cast<long long>(any));
+    cum = lane_value(incl - mass, chunk);
   }
   const int last_node_top1 = lane_value(st.id1, cnode);
   double whole = 0.0;  // the sum against the row's largest logit
@@ -470,10 +424,8 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
       const unsigned long long bit = 1ull << lane;
       if (v < 0 || __any((gone & bit) != 0ull && tok == v)) return;
       float ref = R;
-      if (!COLUMNS) {
 #pragma unroll
-        for (int w = 0; w < kChunkWaves; ++w) ref = w == to.piece ? lane_value(part[w].y, to.chunk) : ref;
-      }
+      for (int w = 0; w < kChunkWaves; ++w) ref = w == to.piece ? lane_value(part[w].y, to.chunk) : ref;
       const bool exact = __any((redone & bit) != 0ull && at.chunk == to.chunk && at.piece == to.piece);
       sum -= exact ? static_cast<double>(precise(z)) : scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(z, c, -ref)), ref);
       again += static_cast<double>(__builtin_amdgcn_exp2f((z - z1) * c));

@@ -53,10 +53,10 @@ struct TailArgs {
   int slice;                // groups of eight entries in a work-group's slice (walk_slice)
   int spin_limit;        // polls a work-group gives a partner before it works out the partner's sum itself
   unsigned long long* xslots;  // [B][N+2][G][2] tagged exchange words, cleared by the row reduction
-  // one-hot draft distributions: the sums of the rows' chunks (chunks.h)
+  // one-hot draft distributions: whether the walk of onehot.h is taken; the sums of the rows' chunks (chunks.h), nullptr: it reads the row
+  bool onehot;
   ChunkSpec chunks;
-  const float2* table;   // [rows][chunks][kChunkWaves] pairs (sum, reference); nullptr: a chunk's sum is in its partial result,
-  int two_from;          // from this chunk on in two of them
+  const float2* table;   // [rows][chunks][kChunkWaves] pairs (sum, reference)
 };
 
 // ---------------------------------------------------------------- shared by both modes

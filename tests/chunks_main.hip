@@ -27,12 +27,12 @@ static std::vector<int> chunk_ends(int nv, int batches) {
   return ends;
 }
 
-static void check(const ChunkSpec& s, int nvec, bool streamed) {
+static void check(const ChunkSpec& s, int nvec) {
   ++rows;
   int at = 0;
   for (int item = 0; item < s.items; ++item) {
     const int begin = item * static_cast<long>(s.vps) < nvec ? item * s.vps : nvec, end = nvec - begin < s.vps ? nvec : begin + s.vps;
-    const std::vector<int> ends = streamed ? chunk_ends(end - begin, 1 << s.log2_batches) : std::vector<int>{end - begin};
+    const std::vector<int> ends = chunk_ends(end - begin, 1 << s.log2_batches);
     if (static_cast<int>(ends.size()) > s.slots) fail("too many", s, nvec, item * s.slots);
     for (int j = 0; j < s.slots; ++j) {
       const int i = item * s.slots + j;
@@ -56,19 +56,12 @@ int main() {
         if (nvec < 1) continue;
         const ChunkSpec s = chunk_spec(items, (nvec + items - 1) / items);
         if (s.slots < 1 || s.items * s.slots > kMaxChunks || s.slots > kMaxSlots) { fail("count", s, nvec, -1); continue; }
-        check(s, nvec, true);
-        if (nvec > 1) check(s, nvec - 1, true);
+        check(s, nvec);
+        if (nvec > 1) check(s, nvec - 1);
       }
   if (chunk_spec(65, 100).slots != 0) fail("accepted", chunk_spec(65, 100), 6500, -1);
-  // columns of tiles behind the LM head: a chunk each, of any width
-  for (int tiles : {1, 3, 63, 97, 256, 594})
-    for (int width = 1; width <= tiles; width += 1 + width / 3)
-      for (int bn : {64, 128, 256}) {
-        const int nvec = tiles * bn / 8 - 1;
-        check(chunk_spec((tiles + width - 1) / width, width * bn / 8, 1, 0), nvec, false);
-      }
   // far along a long row
-  check(chunk_spec(64, (1 << 28) / 64 + 5, 10, 15), 1 << 28, true);
+  check(chunk_spec(64, (1 << 28) / 64 + 5, 10, 15), 1 << 28);
   std::printf("%ld rows, %ld failed\n", rows, failed);
   return failed != 0;
 }

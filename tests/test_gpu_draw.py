@@ -1,0 +1,97 @@
+"""How far the boundaries of the final draw lie from those in 64 bits: uniforms a known distance to either side of one, and which
+token comes out.  The sums a draw is made from may be formed in several ways; none may be further off than going over
+the row, which forms every term in fp32 and every sum in 64 bits."""
+import math
+
+import pytest
+import torch
+
+from paper_2601_15498_amd import binding as M
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+FARTHEST = 1e-7
+# The rms of an error over some hundred rows, each with one largest term whose rounding counts most, is itself uncertain: two
+# draws of the rows differ by up to a quarter, so that two equally exact ways stay below this.
+AS_EXACT = 1.35
+
+
+def boundaries(z, T, gone):
+    """Cumulative sums of the softmax of the rows z less the tokens `gone`, in 64 bits, with the fp32 factor log2(e)/T."""
+    c = float(torch.tensor(1.4426950408889634 / float(torch.tensor(T, dtype=torch.float32)), dtype=torch.float32))
+    x = z.double()
+    f = torch.exp2((x - x.max(dim=1, keepdim=True).values) * c)
+    f.scatter_(1, gone, 0.0)
+    s = torch.cumsum(f, 1)
+    return s / s[:, -1:]
+
+
+def rms_error(draw, cdf, rounds=100):
+    """Root mean square distance between the boundaries of `draw` (uniforms [B] -> tokens [B]) and those of cdf [B,V]: at distance d
+    a draw falls on the wrong side with P(error > d), and E[error^2] = 2 int d P(|error| > d) dd."""
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    at, wrong = [], []
+    for _ in range(rounds):
+        t = torch.rand(cdf.shape[0], 1, generator=gen, device=DEV, dtype=torch.float64) * 0.19 + 0.06  # (uniforms 2^-26 apart at most)
+        k = torch.searchsorted(cdf, t).clamp(max=cdf.shape[1] - 2)
+        edge = cdf.gather(1, k)
+        off = (torch.rand(t.shape, generator=gen, device=DEV, dtype=torch.float64) * 2 - 1) ** 3 * FARTHEST
+        u = (edge - off).float()
+        d = edge - u.double()
+        token = draw(u[:, 0].contiguous()).long()[:, None]
+        ok = edge < 0.9
+        at.append(d.abs()[ok])
+        wrong.append(torch.where(d > 0, token > k, token <= k)[ok])
+    at, wrong = torch.cat(at), torch.cat(wrong)
+    ends = [FARTHEST * (i / 24) ** 2 for i in range(25)]
+    return math.sqrt(sum(4 * (a + b) / 2 * (b - a) * wrong[(at >= a) & (at < b)].double().mean().nan_to_num().item()
+                         for a, b in zip(ends, ends[1:])))
+
+
+def requests(B, rejected, z, seed):
+    """Trees of a root with `rejected` children, whose uniforms reject them, drawn from the root's row (none that holds more than
+    0.6 of it)."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    par = torch.tensor([-1] + [0] * rejected, dtype=torch.int32, device=DEV).repeat(B, 1).contiguous()
+    tok = torch.zeros(B, 1 + rejected, dtype=torch.int32, device=DEV)
+    gone = torch.empty(B, 0, dtype=torch.long, device=DEV)
+    if rejected:
+        p = torch.softmax(z.float(), 1)
+        gone = torch.multinomial(torch.where(p > 0.6, 0.0, p), rejected, generator=gen)
+        tok[:, 1:] = gone.int()
+    return par, tok, gone, torch.full((B,), 2.0, device=DEV), torch.full((B, 2 + rejected), 1 - 2.0 ** -24, device=DEV)
+
+
+def over_the_row(z, par, tok, theta, u, T):
+    """mars_verify of the least workspace: no room for sums of chunks."""
+    B, N, V = z.shape
+    ws = torch.empty(M.mars_workspace_bytes(B, N, V) - 256, dtype=torch.uint8, device=DEV)
+    out = M.VerifyOutputs(B, N, DEV)
+
+    def draw(last):
+        u[:, N] = last
+        return M.mars_verify(z, tok, par, theta, T, u, None, out, ws).bonus_token
+    return draw
+
+
+@pytest.mark.parametrize("B,V,rejected", [(256, 40000, 0), (160, 128256, 0), (80, 60000, 2), (256, 32000, 0), (200, 16000, 2)])
+def test_behind_the_lm_head(B, V, rejected):
+    gen = torch.Generator(device=DEV).manual_seed(V)
+    N, H, T = 1 + rejected, 128, 1.0
+    h = torch.randn(B, N, H, generator=gen, device=DEV).bfloat16()
+    w = (torch.randn(V, H, generator=gen, device=DEV) * (3 / math.sqrt(H))).bfloat16()
+    z = torch.empty(B, N, V, dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(M.mars_lmhead_workspace_bytes(B, N, V, H), dtype=torch.uint8, device=DEV)
+    out = M.VerifyOutputs(B, N, DEV)
+    par, tok, _, theta, u = requests(B, 0, None, 0) if not rejected else requests(B, rejected, torch.ones(B, V, device=DEV), 0)
+
+    def draw(last):
+        u[:, N] = last
+        M.mars_lmhead_verify_sampling(h, w, tok, par, theta, T, u, None, z, out, ws)
+        return out.bonus_token
+    draw(0.5)
+    par, tok, gone, theta, u = requests(B, rejected, z[:, 0], V)
+    cdf = boundaries(z[:, 0], T, gone)
+    mine, row = rms_error(draw, cdf), rms_error(over_the_row(z.clone(), par, tok, theta, u, T), cdf)
+    print(f"[ok?] {B} x {V}, {rejected} rejected: {mine:.1e}, over the row {row:.1e}", flush=True)
+    assert mine <= AS_EXACT * row
