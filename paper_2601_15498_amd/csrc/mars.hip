@@ -46,7 +46,7 @@ static int choose_splits(long rows, int V) {
 struct Layout {
   int splits, G;
   size_t partials_off, stats_off, xslots_off, gathered_off, least;
-  size_t table_off, total;
+  size_t table_off, low_off, total;
 };
 
 // Work-groups per request in the sampling tail: enough to spread a request's row passes over
@@ -98,11 +98,16 @@ static Layout layout(int B, int N, int V, int K = 1) {
   L.gathered_off = L.xslots_off +
                    align_up(static_cast<size_t>(K) * B * (N + 2) * 2 * L.G * sizeof(unsigned long long));
   L.least = L.gathered_off + align_up(static_cast<size_t>(rows) * sizeof(float2));
-  // The sums of the rows' chunks.  (A workspace of the least size has no room for them: the draw goes over the row.)
+  // The sums of the rows' chunks, and what their rounding has left over, half the bytes: where the statistics had their place and the exchange words, which
+  // that walk does not need, have theirs, if it is large enough.  (A workspace of the least size has no room for the sums: the draw
+  // goes over the row.)
   L.table_off = L.least;
   const size_t wide = table_bytes(rows, row_chunks(V, sizeof(float), L.splits)),
                narrow = table_bytes(rows, row_chunks(V, sizeof(bf16_t), L.splits));
-  L.total = L.table_off + align_up(wide > narrow ? wide : narrow);
+  const size_t table = align_up(wide > narrow ? wide : narrow), low = align_up(table / 2);
+  const bool behind = low > L.gathered_off - L.stats_off;
+  L.low_off = behind ? L.table_off + table : L.stats_off;
+  L.total = L.table_off + table + (behind ? low : 0);
   return L;
 }
 
@@ -167,7 +172,7 @@ static ClearArgs clear_args(char* ws, const Layout& L, int B, int N, int K) {
   clr.N = N; clr.B = B; clr.xwords = 2 * L.G; clr.copies = K;
   clr.counters = nullptr; clr.ncounters = 0;
   clr.par = nullptr; clr.tok = nullptr; clr.q = nullptr; clr.q_bf16 = 0; clr.gathered = nullptr;
-  clr.table = nullptr; clr.slots = 1; clr.batches = 0;
+  clr.table = nullptr; clr.table_low = nullptr; clr.slots = 1; clr.batches = 0;
   return clr;
 }
 
@@ -628,6 +633,7 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   if (onehot && !page) {
     clr.slots = chunks.slots; clr.batches = 1 << chunks.log2_batches;
     clr.table = reinterpret_cast<float2*>(ws + L.table_off);
+    clr.table_low = reinterpret_cast<float*>(ws + L.low_off);
   }
   if (sampling && request_status) {  // the sampling tail only raises a request's status
     clr.counters = reinterpret_cast<unsigned int*>(request_status);
@@ -650,7 +656,7 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   a.xslots = clr.xslots;
   a.mask = accept_mask; a.len = accept_len; a.path = path_idx; a.bonus = bonus_token;
   a.dec = decision; a.status = request_status; a.diag = diag;
-  a.chunks = chunks; a.table = clr.table;
+  a.chunks = chunks; a.table = clr.table; a.table_low = clr.table_low;
   a.onehot = onehot;
   a.B = K * B; a.Bd = B; a.N = N; a.V = V; a.splits = L.splits * kPartsPerItem; a.c = c;
   a.ind.kind = indicator; a.ind.cind = indicator_scale(temperature);

@@ -113,6 +113,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
   float e[PV][EPV], g[PV];
   double tile_first = 0.0, tile_sum = 0.0, tile_incl = 0.0;  // lane l: of the first of its tiles, of its tiles, of all up to them
   float2 part[kChunkWaves];        // what the lane's chunk was summed in: the eight waves'
+  float low[kChunkWaves];          // and what the rounding of these has left over
   const ChunkSpec spec = a.chunks;
   const int nchunks = spec.items * spec.slots;
   int turn = 0;
@@ -139,9 +140,10 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     const float n = __builtin_rintf(x * c);
     return __builtin_ldexpf(__builtin_amdgcn_exp2f(__builtin_fmaf(x, c, -n)), static_cast<int>(fmaxf(n - R, -1000.0f)));
   };
-  auto scaled = [&](float s, float ref) {
-    return s > 0.0f ? ldexp(static_cast<double>(s), static_cast<int>(fmaxf(ref - R, -1000.0f))) : 0.0;
+  auto scaled = [&](double s, float ref) {
+    return s > 0.0 ? ldexp(s, static_cast<int>(fmaxf(ref - R, -1000.0f))) : 0.0;
   };
+  auto sum_of = [](float high, float left) { return static_cast<double>(high) + static_cast<double>(left); };
   // (ROW: against the row's largest logit, whose term is 1 then; else against 2^R, as the sums)
   auto term_of = [&](float x) {
     return __builtin_amdgcn_exp2f(ROW ? (x - z1) * c : __builtin_fmaf(x, c, -R));
@@ -289,14 +291,24 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
       last_norm = static_cast<float>(z);
       break;
     }
-    const size_t row = rd + cnode;
-    const float2* __restrict__ table = a.table + row * nchunks * kChunkWaves;
-    const float4* __restrict__ t = reinterpret_cast<const float4*>(table + min(lane, nchunks - 1) * kChunkWaves);
+    const size_t first = (rd + cnode) * nchunks * kChunkWaves;
+    const float2* __restrict__ table = a.table + first;
+    const float* __restrict__ table_low = a.table_low + first;
+    const int mine_at = min(lane, nchunks - 1) * kChunkWaves;
+    const float4* __restrict__ t = reinterpret_cast<const float4*>(table + mine_at);
+    const float4* __restrict__ tl = reinterpret_cast<const float4*>(table_low + mine_at);
 #pragma unroll
     for (int w = 0; w < kChunkWaves; w += 2) {
       const float4 q = t[w / 2];
-      part[w] = make_float2(lane < nchunks ? q.x : 0.0f, q.y);
-      part[w + 1] = make_float2(lane < nchunks ? q.z : 0.0f, q.w);
+      part[w] = make_float2(q.x, q.y);
+      part[w + 1] = make_float2(q.z, q.w);
+    }
+#pragma unroll
+    for (int w = 0; w < kChunkWaves; w += 4) {
+      const float4 q = tl[w / 4];
+      const float r[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int n = 0; n < 4; ++n) low[w + n] = r[n];
     }
     mass = 0.0;
     auto change = [&](int chunk, double by) { mass += lane == chunk ? by : 0.0; };
@@ -306,9 +318,11 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     redone = 0ull;
     if (gone != 0ull) {
       float2 was = {0.0f, 0.0f};
+      float was_low = 0.0f;
       if (mine) {
         at = place_of(tok);
         was = table[at.chunk * kChunkWaves + at.piece];
+        was_low = table_low[at.chunk * kChunkWaves + at.piece];
       }
       const float rest = 1.0f - wave_sum(mine ? f0 : 0.0f);
       unsigned long long heavy = __ballot(mine && f0 > kTakenShare * rest);
@@ -359,7 +373,7 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
         __syncthreads();
         const double again = wave_sum(lane < NW ? sh_piece[turn][lane] : 0.0);
         turn ^= 1;
-        change(chunk, again - scaled(lane_value(was.x, j), lane_value(was.y, j)));
+        change(chunk, again - scaled(lane_value(sum_of(was.x, was_low), j), lane_value(was.y, j)));
       }
       // (the others as they were added)
       const double term = scaled(__builtin_amdgcn_exp2f(__builtin_fmaf(zx, c, -was.y)), was.y);
@@ -370,7 +384,8 @@ __global__ __launch_bounds__(NT, NT > 512 ? 4 : RAGGED || ROW ? 2 : 4) void tail
     }
     double all = 0.0;
 #pragma unroll
-    for (int w = 0; w < kChunkWaves; ++w) all += scaled(part[w].x, part[w].y);
+    for (int w = 0; w < kChunkWaves; ++w) all += scaled(sum_of(part[w].x, low[w]), part[w].y);
+    all = lane < nchunks ? all : 0.0;
     mass += all;
     mass = mass > 1e-37 ? mass : 0.0;
     if (gone != 0ull) {

@@ -17,6 +17,8 @@
 // very end, to fold their eight results into the work-group's one.
 #pragma once
 
+#include <type_traits>
+
 #include "chunks.h"
 #include "common.h"
 
@@ -26,9 +28,10 @@ constexpr int kRowThreads = 512;  // 8 waves per work-group (512 x 2 measured be
 constexpr int kUnroll = 2;        // 16-byte loads per lane per batch
 // The reference of a wave's sum of exponentials.  What a term's exponent is off by grows with its distance from the
 // reference (half a unit of its last place: 5e-8 of the term at 1, 7e-7 at 16), so the largest terms should be near it; and moving it costs some
-// forty instructions.  The first batch puts it 2^kHeadLog2 above its maximum, about where the maximum of a row of
-// ordinary logits ends up, and a maximum that rises 2^kRescaleLog2 above it, a logit that stands out, moves it there.
-constexpr float kHeadLog2 = 6.0f;
+// forty instructions.  The first batch puts it 2^kHeadLog2 above its maximum, which rows of ordinary logits seldom pass by more than
+// 2^kRescaleLog2; a maximum that rises further above the reference, a logit that stands out, moves it there.  (2^6 above: the terms
+// of flat rows, 2^10 and more below it, are off by twice as much.)
+constexpr float kHeadLog2 = 2.0f;
 constexpr float kRescaleLog2 = 2.0f;
 constexpr int kLowLog2 = 8;
 static_assert(kRowThreads * kUnroll == kChunkVecs && kRowThreads / kWave == kChunkWaves, "a batch, its waves");
@@ -101,8 +104,9 @@ struct ClearArgs {
   int q_bf16;
   float2* gathered;            // [B*N]: (logit, draft probability) of node i's token in row par[i]
   // Sums of the shares' chunks (chunks.h) for a draw that has no need of the whole row then: [rows][splits][slots][waves] pairs
-  // (sum, reference).  nullptr: not wanted (greedy mode), or a chunk is a share, whose sum is in its partial result.
+  // (sum, reference), and what the rounding of the sums has left over.  nullptr: not wanted.
   float2* table;
+  float* table_low;
   int slots, batches;          // chunks of a share, batches of a chunk
 };
 
@@ -112,6 +116,8 @@ struct ClearArgs {
 // the end.  (This was one element per load for the whole row: 208 rows of 100 001 bf16 entries 20.8 us, now 13.0.)
 // CHUNKS: the sums of the shares' chunks are wanted (clr.table).  A form of its own: with that code in it, unused, calls of 15-30 us took 2-4 % more
 // (53 chains of 5 x 38 813 bf16 with dense q 20.1 -> 20.7, 3 trees of 5 x 151 936 17.2 -> 17.8).
+// (The unaligned bf16 form takes 65 registers then, three work-groups share a compute unit instead of four.  Held to 64 it puts by three values over the
+// stream: 208 rows x 100 001 14.2 us instead of 13.4, 1 664 rows 66 instead of 58.)
 template <typename T, int EPV, bool SAMPLING, bool RAGGED, bool CHUNKS>
 __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __restrict__ logits, int V, int splits,
                                                                   int vecs_per_split, float c,
@@ -236,12 +242,15 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
 
   float m1 = neg_inf(), m2 = neg_inf();  // best and second-best batch maximum of this lane
   int b1 = -1, b2 = -1;                  // the (distinct) batches they belong to
-  float s = 0.0f;                        // sum of exp2(z*c - ref_c) over the lane's elements of the current chunk
+  // Sum of exp2(z*c - ref_c) over the lane's elements of the current chunk.  The sums of chunks decide which token is drawn: from the sums
+  // of eight terms on they are formed in double, as by a walk that goes over the row.
+  std::conditional_t<CHUNKS, double, float> s = 0.0f;
   float ref_c = -1.0e30f;                // wave-uniform, integer-valued reference (already times c)
   float thresh = -3.0e38f;               // rescale when a lane maximum exceeds this (wave-uniform)
   const float inv_c = SAMPLING ? 1.0f / c : 0.0f;
   // Lane j holds the wave's sum over chunk j and its reference, once the stream is past it.
-  float chunk_s = 0.0f, chunk_ref = 0.0f;
+  double chunk_s = 0.0;
+  float chunk_ref = 0.0f;
   double done = 0.0;                       // sum of the chunks behind it, against done_ref
   float done_ref = -1.0e30f;
   int chunk = 0, chunk_end = clr.batches;  // the current chunk, the batch behind it
@@ -310,22 +319,30 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
         ref_c = new_ref_c;
         thresh = (ref_c + kRescaleLog2) * inv_c;
       }
-      // (in pairs, then fours: as many additions as one behind the other, three roundings instead of eight)
-      float bs[U];
+      // (in pairs, then fours: as many additions as one behind the other, three roundings instead of eight; CHUNKS: eights, and these in
+      // double)
+      auto term = [&](int i) { return __builtin_amdgcn_exp2f(__builtin_fmaf(x[i], c, -ref_c)); };
+      auto four = [&](int i) { return (term(i) + term(i + 1)) + (term(i + 2) + term(i + 3)); };
+      if constexpr (EPV == 1) {
+        float t = term(0);
 #pragma unroll
-      for (int j = 0; j < U; ++j) {
-        auto term = [&](int e) { return __builtin_amdgcn_exp2f(__builtin_fmaf(x[j * EPV + e], c, -ref_c)); };
-        if (EPV == 1) {
-          bs[j] = term(0);
-        } else {
-          bs[j] = (term(0) + term(1)) + (term(2) + term(3));
-          if (EPV == 8) bs[j] += (term(4) + term(5)) + (term(6) + term(7));
+        for (int j = 1; j < U; ++j) t += term(j);
+        s += t;
+      } else if constexpr (CHUNKS) {
+#pragma unroll
+        for (int i = 0; i < NE; i += 8) s += static_cast<double>(four(i) + four(i + 4));
+      } else {
+        float bs[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          bs[j] = four(j * EPV);
+          if (EPV == 8) bs[j] += four(j * EPV + 4);
         }
-      }
-      float t = bs[0];
+        float t = bs[0];
 #pragma unroll
-      for (int j = 1; j < U; ++j) t += bs[j];
-      s += t;
+        for (int j = 1; j < U; ++j) t += bs[j];
+        s += t;
+      }
       // The batch's terms are summed here and now.  Left to itself the compiler sinks this block behind
       // the next batch's wait, widening and maxima (the scheduling barriers order instructions, not the
       // passes that move computations towards their uses): a wave then sits out its wait with this work
@@ -335,9 +352,9 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
     }
   };
 
-  // Behind a chunk's last batch: its sum over the wave, once in two batches or more (double: the sums are what the draw is made
-  // from).  Some sixty instructions; where no draw asks for chunks the headline workload's call takes what it took (68.6 and 68.7 us),
-  // where one does the row reduction takes 0.2-0.4 us more (60 rows x 151 936; 6 656 rows of fp32 608 us instead of 588, for a walk of 16 us instead of 68).
+  // Behind a chunk's last batch: its sum over the wave, once in two batches or more.  Some sixty instructions; where no draw asks for chunks the headline
+  // workload's call takes what it took (68.6 and 68.7 us), where one does the row reduction takes 0.2-0.5 us more (60 rows x 151 936; 6 656 rows of fp32
+  // 617 us instead of 588, for a walk of 12 us instead of 68; what the sums are rounded by, stored as well, is 11 of them).
   auto move_done = [&](double more) {  // (the same in all lanes: scalar registers)
     absorb_sum(done_ref, done, ref_c, more);
     done = lane_value(done, 0);
@@ -346,7 +363,7 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
   auto end_chunk = [&]() {
     const double ws = wave_sum(static_cast<double>(s));
     const bool mine = tid % kWave == chunk;
-    chunk_s = mine ? static_cast<float>(ws) : chunk_s;
+    chunk_s = mine ? ws : chunk_s;
     chunk_ref = mine ? ref_c : chunk_ref;
     move_done(ws);
     // A chunk far below the reference, which a logit that stands out has moved up: the next one begins nearer to its terms.
@@ -453,7 +470,7 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
         const double front = wave_sum(lane < head ? static_cast<double>(t) : 0.0);
         if (lane == 0) {
           const float top = fmaxf(chunk_ref, ref_c);
-          chunk_s = chunk_s * __builtin_amdgcn_exp2f(chunk_ref - top) + static_cast<float>(front) * __builtin_amdgcn_exp2f(ref_c - top);
+          chunk_s = chunk_s * __builtin_amdgcn_exp2f(chunk_ref - top) + front * __builtin_amdgcn_exp2f(ref_c - top);
           chunk_ref = top;
         }
         move_done(front);
@@ -477,9 +494,13 @@ __global__ __launch_bounds__(kRowThreads) void row_reduce_kernel(const T* __rest
   if (SAMPLING) {
     const double rest = wave_sum(static_cast<double>(s));
     if (CHUNKS) {
-      if (lane == chunk) { chunk_s = static_cast<float>(rest); chunk_ref = ref_c; }
-      if (lane < clr.slots)  // (a chunk that the row's share does not have: nothing)
-        clr.table[(static_cast<size_t>(item) * clr.slots + lane) * NW + wave] = make_float2(chunk_s, chunk_ref);
+      if (lane == chunk) { chunk_s = rest; chunk_ref = ref_c; }
+      if (lane < clr.slots) {  // (a chunk that the row's share does not have: nothing)
+        const size_t to = (static_cast<size_t>(item) * clr.slots + lane) * NW + wave;
+        const float high = static_cast<float>(chunk_s);
+        clr.table[to] = make_float2(high, chunk_ref);
+        clr.table_low[to] = static_cast<float>(chunk_s - static_cast<double>(high));
+      }
     }
     ws = static_cast<float>(rest);
     if (CHUNKS && chunk > 0) {

@@ -57,6 +57,7 @@ struct TailArgs {
   bool onehot;
   ChunkSpec chunks;
   const float2* table;   // [rows][chunks][kChunkWaves] pairs (sum, reference)
+  const float* table_low;  // what the sums lack
 };
 
 // ---------------------------------------------------------------- shared by both modes

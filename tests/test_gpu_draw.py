@@ -95,3 +95,39 @@ def test_behind_the_lm_head(B, V, rejected):
     mine, row = rms_error(draw, cdf), rms_error(over_the_row(z.clone(), par, tok, theta, u, T), cdf)
     print(f"[ok?] {B} x {V}, {rejected} rejected: {mine:.1e}, over the row {row:.1e}", flush=True)
     assert mine <= AS_EXACT * row
+
+
+def rows_of(B, V, dtype, sigma, standing_out, seed):
+    """B rows of N(0, sigma^2), `standing_out` entries of each about as large as the row's largest."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    z = torch.randn(B, V, generator=gen, device=DEV) * sigma
+    for _ in range(standing_out):
+        at = torch.randint(V, (B, 1), generator=gen, device=DEV)
+        z.scatter_(1, at, sigma * (4 + 2 * torch.rand(B, 1, generator=gen, device=DEV)))
+    return z.to(dtype)
+
+
+BF16, F32 = torch.bfloat16, torch.float32
+
+
+@pytest.mark.parametrize("dtype,B,V,sigma,standing_out,rejected", [
+    (BF16, 256, 40960, 1.0, 0, 0), (F32, 256, 40960, 1.0, 0, 0), (BF16, 200, 65536, 2.0, 0, 0), (BF16, 160, 128256, 3.0, 6, 0),
+    (F32, 96, 151936, 3.0, 0, 0), (BF16, 160, 100001, 1.0, 0, 0), (F32, 128, 98331, 2.0, 2, 0), (BF16, 80, 128256, 2.0, 4, 2),
+    (F32, 64, 98331, 2.0, 4, 2), (BF16, 2, 151936, 1.0, 0, 0)])
+def test_by_chunks(dtype, B, V, sigma, standing_out, rejected):
+    N, T = 1 + rejected, 1.0
+    z0 = rows_of(B, V, dtype, sigma, standing_out, V)
+    par, tok, gone, theta, u = requests(B, rejected, z0, V)
+    z = z0[:, None].expand(B, N, V).contiguous()
+    cdf = boundaries(z0, T, gone)
+    ws = torch.empty(M.mars_workspace_bytes(B, N, V), dtype=torch.uint8, device=DEV)
+    out = M.VerifyOutputs(B, N, DEV)
+
+    def draw(last):
+        u[:, N] = last
+        return M.mars_verify(z, tok, par, theta, T, u, None, out, ws).bonus_token
+    rounds = 100 if B > 50 else 4000
+    mine = rms_error(draw, cdf, rounds)
+    row = rms_error(over_the_row(z, par, tok, theta, u, T), cdf, rounds)
+    print(f"[ok?] {dtype} {B} x {V}, sigma {sigma}, {standing_out} standing out, {rejected} rejected: {mine:.1e}, over the row {row:.1e}", flush=True)
+    assert mine <= AS_EXACT * row
