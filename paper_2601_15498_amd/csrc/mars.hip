@@ -405,11 +405,6 @@ static void launch_greedy_tail(const TailArgs& a, hipStream_t stream) {
   else if (a.splits > kLaneParts) hipLaunchKernelGGL(tail_greedy_wave_kernel<kGreedyThreads>, grid, dim3(kGreedyThreads), 0, stream, a);
   else hipLaunchKernelGGL(tail_greedy_wave_kernel<kWave>, grid, dim3(kWave), 0, stream, a);
 }
-constexpr int kMinRaggedChunked = 22 * 4096;
-// fp32 rows of more than half a page of 1 024 threads (128 KB): this many work-groups of the walk over the row are quicker.  us per call, the page and this: 10 chains of 13 x
-// 32 000 17.1 and 16.3, 2 trees of 24 x 32 000 15.9 and 14.8, 5 chains of 51 x 32 000 17.9 and 16.7 (seven work-groups); 7 chains of 7 x 23 588 15.3 and 15.4
-// (five); 18 trees of 7 x 16 941 with seven thresholds 17.5 and 19.9 (two).
-constexpr int kPageGroups = 6;
 static hipError_t launch_onehot_tail(const TailArgs& a, int logits_dtype, hipStream_t stream) {
   const dim3 grid(static_cast<unsigned int>(a.B));
   const bool even = even_rows(a.logits, logits_dtype == MARS_BF16 ? 2 : 4, a.V), row = !a.table;
@@ -473,6 +468,36 @@ static int launch_groups(int G, int KB) {
     if (G < 1) G = 1;
   }
   return G;
+}
+
+// How the walk of one-hot draft distributions goes: of trees that a wave can hold with a node per lane (onehot.h), reading the row it draws
+// from where that is one page, or the sums of the row's chunks; else by work-groups that go over the row (tail.h).
+// The lines were measured with 1-250 requests of 6, 12, 26 and 60 nodes (us per call of tail.h / onehot.h):
+//  * A page: bf16 always (33 x 12 nodes x 20 000 entries 17.2 / 16.0, 10 x 60 x 32 000 23.6 / 21.6; the median is 0.95 times the time, and
+//    43 requests of 26 or 60 nodes are the worst, 1.05). fp32 rows of 20 000 entries and more (80 KB) are read as quickly by three or more work-groups: 4 x 12
+//    x 28 000 14.2 / 15.6, 64 x 6 x 24 008 18.9 / 19.5; by two 100 x 6 x 28 000 26.6 / 23.7, 170 x 12 x 24 008 48 / 44; below 20 000 entries 1 x 60 x 16 377 16.1 /
+//    14.1, 16 x 26 x 12 000 18.2 / 15.5.
+//  * By chunks: where a work-group's slice of the row does not fit its registers.  (What is kept there is read once, and the chunks
+//    cost the row reduction and the walk a table.)  64 x 6 x 49 152 (slices of 12 288 entries) 20.0 / 21.6, 85 x 6 x 49 152 (16 384) 24.4 / 22.5; 25 x 6 x
+//    120 000 (12 000) 21.8 / 23.5, 32 x 6 x 120 000 (15 000) 24.8 / 23.7; one tree of 60 x 151 936 18.9 / 21.2, 128 x 6 x 151 936 fp32 96 / 84.
+//  * Rows of bf16 off a 16-byte boundary, which a draw by chunks is longest at: slices of 30 000 entries.  85 x 6 x 74 001 (24 667) 31.0 / 34.4, 64 x 6
+//    x 69 231 (17 308) 26.0 / 27.7; 128 x 6 x 65 537 (32 769) 35.6 / 33.3, 64 x 26 x 128 257 (32 065) 87 / 84.
+//  * Few rows with more partial results than a lane merges, which every work-group would merge: by chunks.  One chain of 6 x 151 936 16.2 / 15.1, x 100 001
+//    16.4 / 15.7; of 12 even.
+enum OneHotForm { kOverTheRow, kByPage, kByChunks };
+constexpr int kWidePageF32 = 20000;     // entries
+constexpr int kWidePageGroups = 3;
+constexpr int kMinRaggedSlice = 30000 / 8;  // groups of eight
+static OneHotForm onehot_form(const void* logits, int dtype, int N, int V, int requests, const Layout& L, const ChunkSpec& chunks, size_t workspace_bytes) {
+  if (N > kOneHotNodes) return kOverTheRow;
+  const size_t elt = dtype == MARS_BF16 ? 2 : 4;
+  if (V <= row_entries(2 * kOneHotThreads))
+    return dtype == MARS_BF16 || V < kWidePageF32 || L.G < kWidePageGroups ? kByPage : kOverTheRow;
+  if (chunks.slots == 0 || workspace_bytes < L.total) return kOverTheRow;
+  const int slice = walk_slice(V, launch_groups(L.G, requests), whole_groups(logits, elt, nullptr, N, V));
+  const bool streamed = slice > kMaxResident * kSamplingThreads;
+  const bool quick = dtype == MARS_F32 || even_rows(logits, elt, V) || slice >= kMinRaggedSlice;
+  return L.splits > kLaneParts || (streamed && quick) ? kByChunks : kOverTheRow;
 }
 
 static hipError_t launch_keep(int K, const int32_t* out_len, const int32_t* path, int B, int N, int32_t* keep_rows,
@@ -618,19 +643,12 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
     clr.q_bf16 = draft_dtype == MARS_BF16 ? 1 : 0;
     clr.gathered = reinterpret_cast<float2*>(ws + L.gathered_off);
   }
-  // One-hot draft distributions of trees that a wave can hold: the walk with a node per lane (onehot.h), which reads the row it draws from where that is
-  // one page, else the sums of its chunks, if a draw can look through these and the workspace holds them.  Else the one whose work-groups
-  // go over the row, also for rows off a 16-byte boundary of less than 22 of its slices, which are quick to go over: us per call, this one
-  // and by chunks, 7 chains of 10 x 48 293 bf16 with two thresholds 16.4 and 19.3, 5 of 50 x 87 465 20.9 and 22.7, 6 of 19 x 69 230 fp32 18.9 and
-  // 19.9; 2 trees of 8 x 89 993 with two thresholds 17.8 and 16.4, 8 of 26 x 100 001 25.3 and 23.0.
   const ChunkSpec chunks = row_chunks(V, logits_dtype == MARS_BF16 ? 2 : 4, L.splits);
-  const bool page = V <= row_entries(kOneHotThreads) ||
-                    (V <= row_entries(2 * kOneHotThreads) && (logits_dtype == MARS_BF16 || L.G < kPageGroups));
-  const bool summed = V > row_entries(2 * kOneHotThreads) && chunks.slots > 0 && workspace_bytes >= L.total &&
-                      (V >= kMinRaggedChunked || even_rows(logits, logits_dtype == MARS_BF16 ? 2 : 4, V));
-  const bool onehot = sampling && !dense && N <= kOneHotNodes && (page || summed);
+  const OneHotForm form =
+      sampling && !dense ? onehot_form(logits, logits_dtype, N, V, K * B, L, chunks, workspace_bytes) : kOverTheRow;
+  const bool onehot = form != kOverTheRow;
   if (onehot) clr.xwords = 0;  // (one work-group per request: nothing is exchanged)
-  if (onehot && !page) {
+  if (form == kByChunks) {
     clr.slots = chunks.slots; clr.batches = 1 << chunks.log2_batches;
     clr.table = reinterpret_cast<float2*>(ws + L.table_off);
     clr.table_low = reinterpret_cast<float*>(ws + L.low_off);

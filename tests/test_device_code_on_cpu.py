@@ -47,6 +47,40 @@ def test_chunks_cover_a_row_and_end_where_the_row_reduction_ends_them(tmp_path):
     assert " 0 failed" in out, out
 
 
+OVER_THE_ROW, BY_CHUNKS, BY_PAGE, BY_WIDE_PAGE = "tail_sampling", "chunks", "page", "wide page"
+
+
+def dispatch_case(B, N, V, dtype, form, offset=0, K=1, workspace="full"):
+    """Arguments of dispatch_main.hip: a call of one-hot draft distributions, logits from `offset` entries behind a 16-byte boundary on,
+    that takes `form`, or, if that is the beginning of a kernel's name, that one."""
+    even = "false" if offset == 0 and V % (8 if dtype == "bf16" else 4) == 0 else "true"
+    T = "bf16" if dtype == "bf16" else "float"
+    rows = f"row_reduce_kernel<{T}, {8 if dtype == 'bf16' else 4}, true, {even}, "
+    kernels = {BY_CHUNKS: f"{rows}true>|tail_onehot_kernel<{T}, {even}, false, 512>", BY_PAGE: f"row_reduce_kernel<|tail_onehot_kernel<{T}, {even}, true, 512>",
+               BY_WIDE_PAGE: f"{rows}false>|tail_onehot_kernel<{T}, {even}, true, 1024>"}.get(form, f"row_reduce_kernel<|{form}")
+    return B, N, V, dtype, offset, K, "onehot", workspace, kernels
+
+
+def check_dispatch(tmp_path, cases):
+    out = run_on_cpu("dispatch_main.hip", tmp_path, options=["-no-hip-rt"], args=[x for c in cases for x in c])
+    assert f"{len(cases)} cases, 0 failed" in out, out
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_one_hot_draft_distributions_take_the_quicker_walk(tmp_path):
+    # both sides of every line that mars.hip draws (onehot_form)
+    cases = [dispatch_case(*c) for c in [
+        (64, 6, 49152, "bf16", OVER_THE_ROW), (85, 6, 49152, "bf16", BY_CHUNKS), (25, 6, 120000, "bf16", OVER_THE_ROW), (32, 6, 120000, "f32", BY_CHUNKS),
+        (1, 60, 151936, "bf16", OVER_THE_ROW), (256, 26, 151936, "f32", BY_CHUNKS), (16, 26, 128256, "bf16", OVER_THE_ROW), (32, 26, 128256, "bf16", BY_CHUNKS),
+        (8, 26, 100001, "bf16", OVER_THE_ROW), (85, 6, 74001, "bf16", OVER_THE_ROW), (128, 6, 65537, "bf16", BY_CHUNKS), (42, 6, 100001, "f32", BY_CHUNKS),
+        (1, 6, 151936, "bf16", BY_CHUNKS), (1, 6, 100001, "bf16", BY_CHUNKS), (3, 6, 151936, "bf16", OVER_THE_ROW), (256, 65, 40000, "bf16", OVER_THE_ROW),
+        (33, 12, 32000, "bf16", BY_WIDE_PAGE), (1, 12, 16369, "bf16", BY_WIDE_PAGE), (1, 12, 16368, "f32", BY_PAGE), (1, 12, 7, "bf16", BY_PAGE),
+        (4, 12, 28000, "f32", OVER_THE_ROW), (86, 12, 28000, "f32", BY_WIDE_PAGE), (85, 12, 28000, "f32", OVER_THE_ROW), (4, 12, 19999, "f32", BY_WIDE_PAGE)]]
+    cases += [dispatch_case(256, 26, 151936, "f32", OVER_THE_ROW, workspace="least"), dispatch_case(7, 6, 49152, "bf16", OVER_THE_ROW, K=7),
+              dispatch_case(16, 6, 49152, "bf16", BY_CHUNKS, K=7), dispatch_case(64, 6, 65536, "bf16", OVER_THE_ROW, offset=1)]
+    check_dispatch(tmp_path, cases)
+
+
 def check_plans(tmp_path, cases):
     out = run_on_cpu("lm_plan_main.hip", tmp_path, options=["-no-hip-rt"], args=[x for c in cases for x in c])
     assert f"{len(cases)} cases, 0 failed" in out, out
