@@ -81,6 +81,18 @@ def test_one_hot_draft_distributions_take_the_quicker_walk(tmp_path):
     check_dispatch(tmp_path, cases)
 
 
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_the_gpu_tests_of_one_hot_draft_distributions_run_the_forms_they_name(tmp_path):
+    from tests import test_gpu_draw as draw, test_gpu_onehot_forms as forms
+    cases = [dispatch_case(*c, BY_CHUNKS) for c in forms.HEAVY_BY_CHUNKS + forms.SHARES_BY_CHUNKS + forms.BEYOND_A_PAGE]
+    cases += [dispatch_case(*c, BY_WIDE_PAGE) for c in forms.WIDE_PAGES]
+    cases += [dispatch_case(*c, workspace="least") for c in forms.OVER_THE_ROW]
+    for dtype, B, V, _, _, rejected in draw.BY_CHUNKS:
+        call = B, 1 + rejected, V, "bf16" if dtype == draw.BF16 else "f32"
+        cases += [dispatch_case(*call, BY_CHUNKS), dispatch_case(*call, OVER_THE_ROW, workspace="least")]
+    check_dispatch(tmp_path, cases)
+
+
 def check_plans(tmp_path, cases):
     out = run_on_cpu("lm_plan_main.hip", tmp_path, options=["-no-hip-rt"], args=[x for c in cases for x in c])
     assert f"{len(cases)} cases, 0 failed" in out, out

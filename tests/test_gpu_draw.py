@@ -110,10 +110,13 @@ def rows_of(B, V, dtype, sigma, standing_out, seed):
 BF16, F32 = torch.bfloat16, torch.float32
 
 
-@pytest.mark.parametrize("dtype,B,V,sigma,standing_out,rejected", [
+BY_CHUNKS = [
     (BF16, 256, 40960, 1.0, 0, 0), (F32, 256, 40960, 1.0, 0, 0), (BF16, 200, 65536, 2.0, 0, 0), (BF16, 160, 128256, 3.0, 6, 0),
     (F32, 96, 151936, 3.0, 0, 0), (BF16, 160, 100001, 1.0, 0, 0), (F32, 128, 98331, 2.0, 2, 0), (BF16, 80, 128256, 2.0, 4, 2),
-    (F32, 64, 98331, 2.0, 4, 2), (BF16, 2, 151936, 1.0, 0, 0)])
+    (F32, 64, 98331, 2.0, 4, 2), (BF16, 2, 151936, 1.0, 0, 0)]
+
+
+@pytest.mark.parametrize("dtype,B,V,sigma,standing_out,rejected", BY_CHUNKS)
 def test_by_chunks(dtype, B, V, sigma, standing_out, rejected):
     N, T = 1 + rejected, 1.0
     z0 = rows_of(B, V, dtype, sigma, standing_out, V)

@@ -606,8 +606,8 @@ def test_kept_rows_of_requests_of_a_single_node(B):
 @pytest.mark.parametrize("V", [151937, 262144])
 @pytest.mark.parametrize("T", [0.0, 0.7])
 def test_equal_maxima_over_many_partial_results(V, T):
-    # 18 and 32 partial results for a row, so that a lane of the merge folds two.  Where rows begin anywhere the first of them
-    # holds the row's last elements too: level with an entry in the middle, the lower index wins.  And a row with one entry
+    # 18 and 32 partial results for a row, so that a lane of the merge folds two.  Where rows begin anywhere the last of them
+    # holds the loose elements at the row's end: level with an entry in the middle, the lower index wins.  And a row with one entry
     # above -inf, one with none.
     from paper_2601_15498_amd import binding as M
     theta = torch.tensor([0.5], device="cuda:0")

@@ -1,7 +1,10 @@
 """The sampling walk of one-hot draft distributions (csrc/onehot.h) at the sizes where it can go wrong: trees at the edge of what
 it holds, shares of a row around whole batches and chunks, rejected tokens that hold most of a row's mass at every kind of place
 in it, draws at both ends of the distribution, and a workspace without room for the sums of the chunks.  Against the oracle, to
-the bar of the other parity tests."""
+the bar of the other parity tests.
+
+Which walk a call takes depends on the number of requests, too (mars.hip: onehot_form): with the few that most tests here have, rows longer than a page are
+gone over by several work-groups.  test_gpu_onehot_forms.py has each walk at sizes that are held to it."""
 import numpy as np
 import pytest
 import torch

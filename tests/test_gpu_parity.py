@@ -418,7 +418,8 @@ def test_row_ends_hold_the_candidates(dtype, V):
                                            ("f32", True, 81936), ("bf16", True, 98328), ("f32", False, 147464)])
 def test_streamed_passes_of_every_length(dtype, dense, V):
     # 128 requests share the chip two work-groups each: a wave's share of a pass is 2, 3, 4, 5, 6 and 9 steps, which end in
-    # the first and the second of the two batches in flight, full and not
+    # the first and the second of the two batches in flight, full and not.  (Without dense q these calls draw by sums of chunks; the
+    # walk over the row without dense q is in test_gpu_onehot_forms.py.)
     w = make_workload(f"stream_{dtype}_{dense}_V{V}", B=128, N=3, V=V, dtype=dtype, temperature=0.9, dense_q=dense,
                       tree={"kind": "tree", "depth": 1, "max_children": 2}, plant_frac=0.5, seed=V)
     compare(w, cdf_guard=5e-6, allow_small_norm=True)
@@ -428,6 +429,7 @@ def test_streamed_passes_of_every_length(dtype, dense, V):
 @pytest.mark.parametrize("dense", [False, True])
 def test_slices_of_two_and_three_groups_per_thread(V, dense):
     # one request on 32 work-groups: slices of exactly two groups per thread, one more, exactly three, and streamed
+    # (without dense q: see above)
     w = make_workload(f"slices_V{V}_{dense}", B=1, N=4, V=V, dtype="bf16", temperature=0.9, dense_q=dense,
                       tree={"kind": "tree", "depth": 2, "max_children": 2}, plant_frac=0.5, seed=V)
     compare(w, cdf_guard=5e-6, allow_small_norm=True)

@@ -118,7 +118,7 @@ IRREGULAR = {
     "no tensor": ("logits", lambda t: t.float().numpy()),
     "a temperature of another kind": ("T", lambda t: "0.7"),
     "an output that is not there": ("out", lambda o: SimpleNamespace(**{**o.__dict__, "path_idx": None})),
-    "no memory": ("logits", lambda t: torch.zeros(B, N, V, device="meta", dtype=t.dtype).as_subclass(Sub)),
+    "no memory": ("theta", lambda t: t.to_sparse()),   # (mars_verify: found where its address is asked for)
 }
 
 
