@@ -129,6 +129,10 @@ const char* mars_status_string(int status);
  * Bytes of device workspace mars_verify / mars_row_stats need for these sizes
  * (0 if an argument is out of range).  The workspace must be 256-byte aligned.
  * Its contents are scratch: undefined before and after a call.
+ * (Calls accept less, down to what is needed without the sums that some draws of one-hot draft distributions are made
+ * from: 0.3 MB of 1.2 for 16 requests of 60 nodes over 151 936 entries, 0.5 of 6.9 for 256 of 26.  Those draws
+ * go over the row then, which differs in the last bits of the sums and, for the latter in fp32, takes 648 us
+ * instead of 633.)
  */
 size_t mars_workspace_bytes(int B, int N, int V);
 
@@ -233,7 +237,8 @@ int mars_verify(const void* logits, int logits_dtype,
  *                 it; MARS_STAGE_ROWS = the row reduction only (it also clears what the second part
  *                 accumulates into and, in sampling mode, gathers the logit and draft probability of
  *                 every node's token for it); MARS_STAGE_REQUESTS = the per-request part only, on a
- *                 workspace that the first part of a mars_verify_ex call with the same arguments has
+ *                 workspace that the first part of a mars_verify_ex call with the same arguments, workspace_bytes
+ *                 among them (which walk a request takes can depend on any of them), has
  *                 filled (mars_row_reduce does not: it knows no tree).  Splitting a pass lets a caller
  *                 that overlaps passes on several streams put its own events between the parts: the
  *                 per-request part of a sampling-mode pass holds up to one work-group per compute unit
@@ -289,17 +294,18 @@ int mars_verify_ex(const void* logits, int logits_dtype,
 /*
  * mars_verify_ex for callers that cannot allocate or bring a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation.  The partial results of the row
- * reduction, the merged statistics and the exchange words of the sampling-mode walk live in a
+ * reduction and what else the walk needs live in a
  * device array of MARS_STATIC_SCRATCH_BYTES that is part of the library's code object: every GPU the
  * library runs on holds its own copy from load until the process ends.  The call allocates
  * nothing, frees nothing and calls no routine that does; on its first use on a GPU it looks up the
  * array's device address (once per GPU, with that GPU current) and keeps it.
  *
  * Arguments, outputs and errors as for mars_verify_ex (options may be NULL), without workspace and
- * workspace_bytes.  Sizes whose mars_workspace_bytes_ex(B,N,V,n_theta) exceeds
- * MARS_STATIC_SCRATCH_BYTES are rejected with MARS_ERR_SCRATCH and nothing is enqueued (the
- * headline shape, 16 requests of 60 nodes over 151 936 entries, needs 0.7 MB; 256 requests of 26
- * nodes 1.4 MB).  The kernels are launched on hip_stream, which must belong to the current GPU.
+ * workspace_bytes.  Sizes for which a workspace of MARS_STATIC_SCRATCH_BYTES would be too small are rejected with
+ * MARS_ERR_SCRATCH and nothing is enqueued (the headline shape, 16 requests of 60 nodes over 151 936
+ * entries, needs 0.3 MB; 256 requests of 26 nodes 0.5 MB).  Where the array does not hold all of
+ * mars_workspace_bytes_ex(B,N,V,n_theta) (256 requests of 60 nodes: 15.9 MB), draws of one-hot draft
+ * distributions go over the row (see there).  The kernels are launched on hip_stream, which must belong to the current GPU.
  * All calls on one GPU share that GPU's array: it keeps the previous call's contents (whatever has
  * to start at zero is cleared by the call's own first kernel), and calls that overlap on one GPU --
  * on different streams, or a graph replay beside an eager call -- race on it and give undefined

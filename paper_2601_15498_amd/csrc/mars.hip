@@ -473,13 +473,14 @@ static int launch_groups(int G, int KB) {
 // How the walk of one-hot draft distributions goes: of trees that a wave can hold with a node per lane (onehot.h), reading the row it draws
 // from where that is one page, or the sums of the row's chunks; else by work-groups that go over the row (tail.h).
 // The lines were measured with 1-250 requests of 6, 12, 26 and 60 nodes (us per call of tail.h / onehot.h):
-//  * A page: bf16 always (33 x 12 nodes x 20 000 entries 17.2 / 16.0, 10 x 60 x 32 000 23.6 / 21.6; the median is 0.95 times the time, and
-//    43 requests of 26 or 60 nodes are the worst, 1.05). fp32 rows of 20 000 entries and more (80 KB) are read as quickly by three or more work-groups: 4 x 12
+//  * A page: bf16 always (33 x 12 nodes x 20 000 entries 17.2 / 16.0, 10 x 60 x 32 000 23.6 / 21.6; the median is 0.95 times the time, the
+//    worst of 220 shapes 20 x 60 x 20 001, 1.12). fp32 rows of 20 000 entries and more (80 KB) are read as quickly by three or more work-groups: 4 x 12
 //    x 28 000 14.2 / 15.6, 64 x 6 x 24 008 18.9 / 19.5; by two 100 x 6 x 28 000 26.6 / 23.7, 170 x 12 x 24 008 48 / 44; below 20 000 entries 1 x 60 x 16 377 16.1 /
 //    14.1, 16 x 26 x 12 000 18.2 / 15.5.
 //  * By chunks: where a work-group's slice of the row does not fit its registers.  (What is kept there is read once, and the chunks
 //    cost the row reduction and the walk a table.)  64 x 6 x 49 152 (slices of 12 288 entries) 20.0 / 21.6, 85 x 6 x 49 152 (16 384) 24.4 / 22.5; 25 x 6 x
-//    120 000 (12 000) 21.8 / 23.5, 32 x 6 x 120 000 (15 000) 24.8 / 23.7; one tree of 60 x 151 936 18.9 / 21.2, 128 x 6 x 151 936 fp32 96 / 84.
+//    120 000 (12 000) 21.8 / 23.5, 32 x 6 x 120 000 (15 000) 24.8 / 23.7; 128 x 6 x 151 936 fp32 96 / 84.  One tree of 60 x 151 936: fp32 3 % slower by
+//    chunks, bf16 even over twelve inputs (18.0 / 17.7 on one, 18.9 / 21.2 where rejected tokens held much of their rows).
 //  * Rows of bf16 off a 16-byte boundary, which a draw by chunks is longest at: slices of 30 000 entries.  85 x 6 x 74 001 (24 667) 31.0 / 34.4, 64 x 6
 //    x 69 231 (17 308) 26.0 / 27.7; 128 x 6 x 65 537 (32 769) 35.6 / 33.3, 64 x 26 x 128 257 (32 065) 87 / 84.
 //  * Few rows with more partial results than a lane merges, which every work-group would merge: by chunks.  One chain of 6 x 151 936 16.2 / 15.1, x 100 001

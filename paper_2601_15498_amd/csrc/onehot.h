@@ -12,10 +12,10 @@
 //
 // What bounds it: three trips to memory one behind the other (the tree, the sums, the chunk: 1.4, 0.5 and 0.8 us) and the issue of
 // single waves in between, 9-12 us in all; it was a pass over the row's entries by every request's work-groups for the draw, and an exchange
-// of their sums.  This kernel alone, then the whole call, us, before and after: one tree of 60 nodes x 151 936 bf16 9.1 -> 7.5
-// and 18.5 -> 17.0; 8 trees of 26 x 100 001 12.7 -> 11 and 25.2 -> 23.1; 256 trees of 26 x 151 936 fp32 (a work-group per request read 600 KB)
-// 59 -> 15 and 656 -> 623.  With the tests, the walk and the draw in LDS and behind barriers, as in tail_sampling_body, the
-// same method took 15, 22 and 25 us.
+// of their sums.  That pass is quick while a request has so many work-groups that each keeps its slice in registers, so these calls stay with it
+// (mars.hip: onehot_form).  us, that walk and this one: 256 trees of 26 x 151 936 fp32 (a work-group per request read 600 KB) 59 -> 14-17 for the
+// kernel alone, 648 -> 633 for the call; 64 chains of 6 x 151 936 bf16 38 -> 34, 128 of 7 66 -> 58.  With the tests, the walk and the draw in LDS and
+// behind barriers, as in tail_sampling_body, the same method took 25 us on the first.
 #pragma once
 
 #include "chunks.h"
