@@ -482,22 +482,24 @@ static int launch_groups(int G, int KB) {
 //    120 000 (12 000) 21.8 / 23.5, 32 x 6 x 120 000 (15 000) 24.8 / 23.7; 128 x 6 x 151 936 fp32 96 / 84.  One tree of 60 x 151 936: fp32 3 % slower by
 //    chunks, bf16 even over twelve inputs (18.0 / 17.7 on one, 18.9 / 21.2 where rejected tokens held much of their rows).
 //  * Rows of bf16 off a 16-byte boundary, which a draw by chunks is longest at: slices of 30 000 entries.  85 x 6 x 74 001 (24 667) 31.0 / 34.4, 64 x 6
-//    x 69 231 (17 308) 26.0 / 27.7; 128 x 6 x 65 537 (32 769) 35.6 / 33.3, 64 x 26 x 128 257 (32 065) 87 / 84.
+//    x 69 231 (17 308) 26.0 / 27.7; 128 x 6 x 65 537 (32 769) 35.6 / 33.3, 64 x 26 x 128 257 (32 065) 87 / 84.  Of 12 288 as the others where four thresholds and
+//    more share the row reduction's sums: 5 x 60 x 100 001 with seven 33.1 / 29.0, 12 x 26 x 69 231 32 / 28; with two even.
 //  * Few rows with more partial results than a lane merges, which every work-group would merge: by chunks.  One chain of 6 x 151 936 16.2 / 15.1, x 100 001
 //    16.4 / 15.7; of 12 even.
 enum OneHotForm { kOverTheRow, kByPage, kByChunks };
 constexpr int kWidePageF32 = 20000;     // entries
 constexpr int kWidePageGroups = 3;
 constexpr int kMinRaggedSlice = 30000 / 8;  // groups of eight
-static OneHotForm onehot_form(const void* logits, int dtype, int N, int V, int requests, const Layout& L, const ChunkSpec& chunks, size_t workspace_bytes) {
+constexpr int kSharingThetas = 4;
+static OneHotForm onehot_form(const void* logits, int dtype, int B, int N, int V, int K, const Layout& L, const ChunkSpec& chunks, size_t workspace_bytes) {
   if (N > kOneHotNodes) return kOverTheRow;
   const size_t elt = dtype == MARS_BF16 ? 2 : 4;
   if (V <= row_entries(2 * kOneHotThreads))
     return dtype == MARS_BF16 || V < kWidePageF32 || L.G < kWidePageGroups ? kByPage : kOverTheRow;
   if (chunks.slots == 0 || workspace_bytes < L.total) return kOverTheRow;
-  const int slice = walk_slice(V, launch_groups(L.G, requests), whole_groups(logits, elt, nullptr, N, V));
+  const int slice = walk_slice(V, launch_groups(L.G, K * B), whole_groups(logits, elt, nullptr, N, V));
   const bool streamed = slice > kMaxResident * kSamplingThreads;
-  const bool quick = dtype == MARS_F32 || even_rows(logits, elt, V) || slice >= kMinRaggedSlice;
+  const bool quick = dtype == MARS_F32 || even_rows(logits, elt, V) || slice >= kMinRaggedSlice || K >= kSharingThetas;
   return L.splits > kLaneParts || (streamed && quick) ? kByChunks : kOverTheRow;
 }
 
@@ -646,7 +648,7 @@ int mars_verify_ex(const void* logits, int logits_dtype, const int32_t* draft_to
   }
   const ChunkSpec chunks = row_chunks(V, logits_dtype == MARS_BF16 ? 2 : 4, L.splits);
   const OneHotForm form =
-      sampling && !dense ? onehot_form(logits, logits_dtype, N, V, K * B, L, chunks, workspace_bytes) : kOverTheRow;
+      sampling && !dense ? onehot_form(logits, logits_dtype, B, N, V, K, L, chunks, workspace_bytes) : kOverTheRow;
   const bool onehot = form != kOverTheRow;
   if (onehot) clr.xwords = 0;  // (one work-group per request: nothing is exchanged)
   if (form == kByChunks) {

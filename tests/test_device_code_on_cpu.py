@@ -77,7 +77,8 @@ def test_one_hot_draft_distributions_take_the_quicker_walk(tmp_path):
         (33, 12, 32000, "bf16", BY_WIDE_PAGE), (1, 12, 16369, "bf16", BY_WIDE_PAGE), (1, 12, 16368, "f32", BY_PAGE), (1, 12, 7, "bf16", BY_PAGE),
         (4, 12, 28000, "f32", OVER_THE_ROW), (86, 12, 28000, "f32", BY_WIDE_PAGE), (85, 12, 28000, "f32", OVER_THE_ROW), (4, 12, 19999, "f32", BY_WIDE_PAGE)]]
     cases += [dispatch_case(256, 26, 151936, "f32", OVER_THE_ROW, workspace="least"), dispatch_case(7, 6, 49152, "bf16", OVER_THE_ROW, K=7),
-              dispatch_case(16, 6, 49152, "bf16", BY_CHUNKS, K=7), dispatch_case(64, 6, 65536, "bf16", OVER_THE_ROW, offset=1)]
+              dispatch_case(16, 6, 49152, "bf16", BY_CHUNKS, K=7), dispatch_case(5, 26, 100001, "bf16", BY_CHUNKS, K=7),
+              dispatch_case(12, 26, 100001, "bf16", BY_CHUNKS, K=4), dispatch_case(16, 26, 100001, "bf16", OVER_THE_ROW, K=3), dispatch_case(64, 6, 65536, "bf16", OVER_THE_ROW, offset=1)]
     check_dispatch(tmp_path, cases)
 
 
@@ -85,6 +86,7 @@ def test_one_hot_draft_distributions_take_the_quicker_walk(tmp_path):
 def test_the_gpu_tests_of_one_hot_draft_distributions_run_the_forms_they_name(tmp_path):
     from tests import test_gpu_draw as draw, test_gpu_onehot_forms as forms
     cases = [dispatch_case(*c, BY_CHUNKS) for c in forms.HEAVY_BY_CHUNKS + forms.SHARES_BY_CHUNKS + forms.BEYOND_A_PAGE]
+    cases += [dispatch_case(*c, BY_CHUNKS, K=7) for c in forms.SWEEPS_BY_CHUNKS]
     cases += [dispatch_case(*c, BY_WIDE_PAGE) for c in forms.WIDE_PAGES]
     cases += [dispatch_case(*c, workspace="least") for c in forms.OVER_THE_ROW]
     for dtype, B, V, _, _, rejected in draw.BY_CHUNKS:

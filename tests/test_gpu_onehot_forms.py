@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from mars_inputs import f32_to_bf16_bits, make_workload
-from tests.gpu_util import compare, to_device
+from tests.gpu_util import compare, compare_ex, to_device
 from tests.test_gpu_parity import custom
 
 pytestmark = pytest.mark.gpu
@@ -18,6 +18,7 @@ HEAVY_BY_CHUNKS = [(128, 4, 100001, "bf16"), (128, 4, 98331, "f32"), (128, 4, 65
 SHARES_BY_CHUNKS = [(130, 2, V, dtype) for dtype, sizes in (("bf16", (40960, 65539, 155656, 172032, 311297)), ("f32", (32771, 77832, 86016, 155649)))
                     for V in sizes]
 BEYOND_A_PAGE = [(100, 5, 32760, "f32"), (100, 5, 32760, "bf16"), (250, 3, 32753, "bf16"), (100, 5, 32753, "f32")]
+SWEEPS_BY_CHUNKS = [(12, 20, 100001, "bf16"), (12, 20, 65536, "f32"), (12, 12, 69231, "bf16")]   # seven thresholds
 WIDE_PAGES = [(100, 5, V, "f32") for V in (20000, 24577, 32749, 32751, 32752)] + [(100, 5, 16377, "f32"), (3, 20, 32751, "bf16"), (3, 20, 32752, "bf16")]
 # with a workspace of the least size; the walk's kernel
 OVER_THE_ROW = [(128, 3, 40008, "f32", "tail_sampling_streamed_kernel<float, float, true, true>"),
@@ -72,6 +73,14 @@ def test_rejected_tokens_that_hold_most_of_the_row(B, N, V, dtype):
 @pytest.mark.parametrize("B,N,V,dtype", SHARES_BY_CHUNKS + BEYOND_A_PAGE)
 def test_shares_around_whole_batches(B, N, V, dtype):
     compare(make_workload(f"chunks_{dtype}_{V}", B=B, N=N, V=V, dtype=dtype, temperature=0.9, tree={"kind": "chain"}, plant_frac=0.5, seed=V))
+
+
+@pytest.mark.parametrize("B,N,V,dtype", SWEEPS_BY_CHUNKS)
+def test_sweep_by_chunks(B, N, V, dtype):
+    thetas = (0.84, 0.86, 0.88, 0.90, 0.92, 0.94, 0.96)
+    w = make_workload(f"sweep_{dtype}_{V}", B=B, N=N, V=V, dtype=dtype, temperature=0.9, tree={"kind": "tree", "depth": 4, "max_children": 3},
+                      plant_frac=0.6, seed=V, sweep_thetas=thetas)
+    compare_ex(w, thetas=np.tile(np.array(thetas, np.float32)[:, None], (1, B)), allow_small_norm=True)
 
 
 @pytest.mark.parametrize("B,N,V,dtype", WIDE_PAGES)
